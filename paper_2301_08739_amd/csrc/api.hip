@@ -1,5 +1,5 @@
 // extern "C" entry points: argument checks, workspace carving and launch order.  No kernel lives
-// here; see flatten.hip, rows.hip, layer_generic.hip, layer_mfma.hip.
+// here; see flatten.hip, rows.hip, layer_generic.hip, layer_mfma.hip, layer_f32.hip.
 #include "common.h"
 #include "pack_weights.h"
 #include <atomic>
@@ -156,23 +156,28 @@ size_t ff_group_attention_workspace_bytes(int64_t n, int G, const ff_layer_weigh
     const size_t p = align_up(layer_mfma_packed_bytes(w), 256);
     if (p > b) b = p;
   }
+  if (dtype == FF_F32 && layer_f32_supported(w, G)) {
+    const size_t p = align_up(layer_f32_packed_bytes(w), 256);
+    if (p > b) b = p;
+  }
   return b;
 }
 
 }  // extern "C"
 
 namespace {
-// Does this call run on the fused matrix-core kernel?
+// Does this call run on a fused matrix-core kernel (layer_mfma.hip, layer_f32.hip)?
 bool takes_fused_path(const ff_layer_weights* w, int G, int dtype, uint32_t flags) {
-  return is_16bit(dtype) && !(flags & FF_FLAG_FORCE_GENERIC) && layer_mfma_supported(w, G);
+  if (flags & FF_FLAG_FORCE_GENERIC) return false;
+  return is_16bit(dtype) ? layer_mfma_supported(w, G) : layer_f32_supported(w, G);
 }
 
-// ff_group_attention plus the two internal options of the fused kernel that ff_fwa_block uses to hand
+// ff_group_attention plus the internal options of the fused kernels that ff_fwa_block uses to hand
 // features from layer to layer in sorted order (see layer_mfma_launch); they need the fused path.
 int group_attention(const void* feats, void* out, int64_t n, const int32_t* perm,
                     const int32_t* group_offsets, const int32_t* num_groups, int32_t max_groups,
                     const ff_layer_weights* w, int G, int dtype, uint32_t flags, void* workspace,
-                    size_t workspace_bytes, const int32_t* out_index, int in_sorted, void* stream) {
+                    size_t workspace_bytes, const int32_t* out_index, int in_sorted, const void* packed_f32, void* stream) {
   int st = check_weights(w, dtype);
   if (st != FF_OK) return st;
   if (n < 0 || n > 0x7fffffffLL || max_groups < 0 || G < 1) return FF_ERR_ARG;
@@ -193,6 +198,18 @@ int group_attention(const void* feats, void* out, int64_t n, const int32_t* perm
                                       (hipStream_t)stream);
   if (takes_fused_path(w, G, dtype, flags)) {
     if (n == 0 || max_groups == 0) return FF_OK;
+    if (dtype == FF_F32) {
+      if (!packed_f32) {
+        if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < layer_f32_packed_bytes(w))
+          return FF_ERR_WORKSPACE;
+        st = layer_f32_pack(w, workspace, (hipStream_t)stream);
+        if (st != FF_OK) return st;
+        packed_f32 = workspace;
+      }
+      const LayerF32 call{feats, out, (int)n, perm, group_offsets, num_groups, max_groups, w, G, drop, packed_f32,
+                          out_index, in_sorted};
+      return layer_f32_launch(call, (hipStream_t)stream);
+    }
     const void* packed = w->packed;
     if (!packed) {
       if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < layer_mfma_packed_bytes(w))
@@ -226,7 +243,7 @@ int ff_group_attention(const void* feats, void* out, int64_t n, const int32_t* p
                        const ff_layer_weights* w, int G, int dtype, uint32_t flags,
                        void* workspace, size_t workspace_bytes, void* stream) {
   return group_attention(feats, out, n, perm, group_offsets, num_groups, max_groups, w, G, dtype, flags, workspace,
-                         workspace_bytes, nullptr, 0, stream);
+                         workspace_bytes, nullptr, 0, nullptr, stream);
 }
 
 int ff_group_attention_path(const ff_layer_weights* w, int G, int dtype, uint32_t flags) {
@@ -234,7 +251,7 @@ int ff_group_attention_path(const ff_layer_weights* w, int G, int dtype, uint32_
   if (st != FF_OK) return st;
   if (G < 1) return FF_ERR_ARG;
   if (G > 1024) return FF_ERR_UNSUPPORTED;
-  return takes_fused_path(w, G, dtype, flags) ? FF_PATH_FUSED : FF_PATH_PLAIN;
+  return is_16bit(dtype) && takes_fused_path(w, G, dtype, flags) ? FF_PATH_FUSED : FF_PATH_PLAIN;
 }
 
 int ff_gather(const void* src, void* dst, const int32_t* perm, int64_t n, int C, int dtype, void* stream) {
@@ -308,11 +325,13 @@ static int make_block_plan(int64_t n, const ff_geom* g, const FlattenZ* z, int G
   // One batched packing launch for the whole stack when every layer has the same packable shape
   // and the caller did not pre-pack.
   p->packed_stride = 0;
-  if (is_16bit(dtype) && layer_mfma_supported(&layers[0], G)) {
+  if (takes_fused_path(&layers[0], G, dtype, 0)) {
     bool same = true;
     for (int l = 0; l < num_layers; ++l)
-      same = same && layers[l].F == layers[0].F && layers[l].heads == layers[0].heads && !layers[l].packed;
-    if (same) p->packed_stride = align_up(layer_mfma_packed_bytes(&layers[0]), 256);
+      same = same && layers[l].F == layers[0].F && layers[l].heads == layers[0].heads &&
+             (dtype == FF_F32 || !layers[l].packed);
+    if (same)
+      p->packed_stride = align_up(dtype == FF_F32 ? layer_f32_packed_bytes(&layers[0]) : layer_mfma_packed_bytes(&layers[0]), 256);
   }
   p->off_packed = off; off += p->packed_stride * num_layers;
   p->total = off;
@@ -354,11 +373,16 @@ static int fwa_block(const int32_t* coords, int64_t n, const ff_geom* g, const F
     // take them all; otherwise by a launch of their own.
     PackJob job;
     const bool ride = p.packed_stride && n > 0 && num_layers <= kPackBatch;
-    if (ride) make_pack_job(layers, num_layers, ws + p.off_packed, p.packed_stride, dtype == FF_F16, &job);
+    if (ride) make_pack_job(layers, num_layers, ws + p.off_packed, p.packed_stride,
+                                 dtype == FF_F32 ? kPackF32 : dtype == FF_F16 ? kPackF16 : kPackBf16, &job);
     st = flatten_launch_z(coords, n, g, z, p.sorts, axis, shift, G, drop, perm, p.chain ? inv : nullptr, goff, ng, nullptr,
                           ws + p.off_flat, p.flat_bytes, ride ? &job : nullptr, (hipStream_t)stream);
     if (st != FF_OK) return st;
-    if (p.packed_stride && n > 0 && !ride) {
+    if (p.packed_stride && n > 0 && !ride && dtype == FF_F32) {
+      for (int l = 0; l < num_layers && st == FF_OK; ++l)
+        st = layer_f32_pack(&layers[l], ws + p.off_packed + (size_t)l * p.packed_stride, (hipStream_t)stream);
+      if (st != FF_OK) return st;
+    } else if (p.packed_stride && n > 0 && !ride) {
       st = dtype == FF_F16
                ? layer_mfma_pack_f16(layers, num_layers, ws + p.off_packed, p.packed_stride, (hipStream_t)stream)
                : layer_mfma_pack(layers, num_layers, ws + p.off_packed, p.packed_stride, (hipStream_t)stream);
@@ -371,14 +395,15 @@ static int fwa_block(const int32_t* coords, int64_t n, const ff_geom* g, const F
     const int s = l % 4;
     void* dst = (l == num_layers - 1) ? feats_out : bufs[l & 1];
     ff_layer_weights wl = layers[l];
-    if (p.packed_stride) wl.packed = ws + p.off_packed + (size_t)l * p.packed_stride;
+    const void* packed_l = p.packed_stride ? ws + p.off_packed + (size_t)l * p.packed_stride : nullptr;
+    if (packed_l && dtype != FF_F32) wl.packed = packed_l;
     const bool last = l == num_layers - 1;
     const int32_t* next_inv = p.chain && !last ? (const int32_t*)(ws + p.off_inv + ((l + 1) % 4) * perm_stride) : nullptr;
     const int in_sorted = p.chain && l > 0 ? (g->num_frames == 1 ? 2 : 1) : 0;
     st = group_attention(cur, dst, n, (const int32_t*)(ws + p.off_perm + s * perm_stride),
                          (const int32_t*)(ws + p.off_goff + s * goff_stride), (const int32_t*)(ws + p.off_ng) + s,
                          (int32_t)p.max_groups, &wl, G, dtype, drop ? FF_FLAG_TAIL_DROP : 0u, ws + p.off_layer,
-                         p.layer_bytes, next_inv, in_sorted, stream);
+                         p.layer_bytes, next_inv, in_sorted, dtype == FF_F32 ? packed_l : nullptr, stream);
     if (st != FF_OK) return st;
     cur = dst;
   }

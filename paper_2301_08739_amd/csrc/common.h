@@ -135,4 +135,23 @@ int layer_mfma_launch_f16(const void* feats, void* out, int64_t n, const int32_t
                           bool out_f32, bool drop, const void* packed, int variant, const int32_t* out_index,
                           int in_sorted, hipStream_t stream);
 
+// Fused float32 layer (layer_f32.hip)
+struct LayerF32 {
+  const void* feats;
+  void* out;
+  int n;
+  const int32_t *perm, *group_offsets, *num_groups;
+  int32_t max_groups;
+  const ff_layer_weights* w;
+  int G;
+  bool drop;
+  const void* packed;        // split weights (layer_f32_pack)
+  const int32_t* out_index;  // as for layer_mfma_launch
+  int in_sorted;             // 0, or non-zero: row p of feats is the pillar at sorted position p
+};
+bool layer_f32_supported(const ff_layer_weights* w, int G);
+size_t layer_f32_packed_bytes(const ff_layer_weights* w);
+int layer_f32_pack(const ff_layer_weights* w, void* packed, hipStream_t stream);
+int layer_f32_launch(const LayerF32& c, hipStream_t stream);
+
 }  // namespace ff

@@ -176,7 +176,8 @@ __device__ __forceinline__ void pack_tail(const PackJob& pack, int id) {
   const int blk = id - layer * pack.blocks;
   if (layer >= pack.layers) return;
   layer += pack.first;
-  if (pack.half) pack_weights_block<true>(pack.pb, layer, blk, pack.C, pack.F, pack.total_frags);
+  if (pack.mode == kPackF32) pack_weights_f32_block(pack.pb, layer, blk, pack.C, pack.F, pack.total_frags);
+  else if (pack.mode == kPackF16) pack_weights_block<true>(pack.pb, layer, blk, pack.C, pack.F, pack.total_frags);
   else pack_weights_block<false>(pack.pb, layer, blk, pack.C, pack.F, pack.total_frags);
 }
 

@@ -3,8 +3,8 @@
 //   F'  = F  + MHSA(LN1(F)),   F'' = F' + FFN(LN2(F'))
 //
 // This is the exact-arithmetic path: storage type T (float or bf16), every product, sum,
-// exponential and erf in fp32 on the vector ALUs.  It serves dtype FF_F32 and any shape the
-// MFMA kernels do not cover.  Three kernels, intermediates in the caller's workspace:
+// exponential and erf in fp32 on the vector ALUs.  It serves any shape the fused kernels
+// (layer_mfma.hip, layer_f32.hip) do not cover, and FF_FLAG_FORCE_GENERIC.  Three kernels, intermediates in the caller's workspace:
 //   k_ln_qkv    rows of the sorted order: gather, LN1, packed QKV projection   -> qkv [n, 3C] f32
 //               (weights staged through LDS from 8192 rows on)
 //   k_attention one workgroup per (group, head): softmax(Q K^T / sqrt(d)) V     -> o   [n, C]  f32

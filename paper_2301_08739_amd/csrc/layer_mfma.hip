@@ -1030,7 +1030,7 @@ int FF_LAYER_SYM(layer_mfma_pack)(const ff_layer_weights* w, int count, void* pa
   for (int l0 = 0; l0 < count; l0 += kPackBatch) {
     const int nl = count - l0 < kPackBatch ? count - l0 : kPackBatch;
     PackJob job;
-    make_pack_job(w + l0, nl, (char*)packed + (size_t)l0 * stride_bytes, stride_bytes, kHalf, &job);
+    make_pack_job(w + l0, nl, (char*)packed + (size_t)l0 * stride_bytes, stride_bytes, kHalf ? kPackF16 : kPackBf16, &job);
     hipLaunchKernelGGL(k_pack_weights, dim3((unsigned)job.blocks, (unsigned)nl), dim3(256), 0, stream, job.pb, job.C,
                        job.F, job.total_frags);
   }

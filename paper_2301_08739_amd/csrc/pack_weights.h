@@ -14,6 +14,7 @@ namespace ff {
 // The six row blocks of a unit (Q a=0,1; K a=0,1; V a=0,1 numbered 0..5) come in this order:
 __device__ constexpr int kQkvOrder[6] = {2, 3, 4, 5, 0, 1};
 constexpr int kPackBatch = 16;
+constexpr int kPackBf16 = 0, kPackF16 = 1, kPackF32 = 2;
 struct PackBatch {  // up to 16 layers of identical shape packed by one launch
   const uint16_t *w_qkv[kPackBatch], *w_o[kPackBatch], *w1[kPackBatch], *w2[kPackBatch];
   const uint16_t *b_qkv[kPackBatch], *b_o[kPackBatch];
@@ -23,20 +24,28 @@ struct PackBatch {  // up to 16 layers of identical shape packed by one launch
 // What a launch needs to know to pack `layers` layers: `blocks` workgroups of 256 threads per layer.
 struct PackJob {
   PackBatch pb;
-  int layers, C, F, total_frags, blocks, half;  // half: IEEE half elements instead of bfloat16
+  int layers, C, F, total_frags, blocks;
+  int mode;                                     // kPackBf16, kPackF16 or kPackF32
   int first;                                    // a launch packs layers first .. first + layers - 1 of the batch
 };
 
 inline int pack_frag_count(int C, int F) { return (C / 32) * (6 * (C / 32) + C / 16) + (F / 32) * (2 * (C / 32) + C / 16); }
 
+inline int pack_frag_count_f32(int C, int F) { return (4 * C * C + 2 * C * F) / 512; }
+
 // Layers w[0..count) (count <= kPackBatch) to packed + l * stride_bytes.
-inline void make_pack_job(const ff_layer_weights* w, int count, void* packed, size_t stride_bytes, bool half,
+inline void make_pack_job(const ff_layer_weights* w, int count, void* packed, size_t stride_bytes, int mode,
                           PackJob* job) {
   job->first = 0;
-  job->layers = count; job->C = w->C; job->F = w->F; job->half = half ? 1 : 0;
-  job->total_frags = pack_frag_count(w->C, w->F);
-  // one thread per 16 bytes of a fragment, eight per folded bias element, one per other small parameter
-  job->blocks = (job->total_frags * 64 + 8 * w->C + 6 * w->C + w->F + 255) / 256;
+  job->layers = count; job->C = w->C; job->F = w->F; job->mode = mode;
+  if (mode == kPackF32) {  // one thread per lane of a fragment
+    job->total_frags = pack_frag_count_f32(w->C, w->F);
+    job->blocks = (job->total_frags * 64 + 255) / 256;
+  } else {
+    job->total_frags = pack_frag_count(w->C, w->F);
+    // one thread per 16 bytes of a fragment, eight per folded bias element, one per other small parameter
+    job->blocks = (job->total_frags * 64 + 8 * w->C + 6 * w->C + w->F + 255) / 256;
+  }
   for (int l = 0; l < kPackBatch; ++l) {
     const ff_layer_weights* wl = &w[l < count ? l : 0];
     job->pb.w_qkv[l] = (const uint16_t*)wl->w_qkv; job->pb.w_o[l] = (const uint16_t*)wl->w_o;
@@ -171,6 +180,50 @@ __device__ __forceinline__ void pack_weights_block(const PackBatch& pb, int laye
     }
   }
   out[(size_t)frag * 64 + lane] = make_uint4(u[0], u[1], u[2], u[3]);
+}
+
+// ---- the same for the float32 kernel (layer_f32.hip) ----------------------------------------------------------------
+// Stream order: for every slice s of 32 features (one wavefront of the kernel): Q rows 32 s .. 32 s + 31 (C / 16
+// fragments), K rows, V rows, W_o rows, the slice's W1 row tiles (tiles (F / C) s .. of 32 hidden units), W2 rows
+// (F / 16 fragments).  A fragment is 32 output features x 16 inputs as three bfloat16 parts of 1 KB, hi, mid, lo; lane
+// (h, m) = 32 h + m owns 16 bytes of each: row m and eight inputs.  Q, K, V multiply the LayerNorm output in its natural
+// order: inputs 16 k + 8 h + 0..7.  The other matrices multiply operands that were accumulators: inputs 16 k + 4 h + 0..3
+// and 16 k + 8 + 4 h + 0..3.
+__device__ __forceinline__ void pack_weights_f32_block(const PackBatch& pb, int layer, int block, int C, int F,
+                                                       int total_frags) {
+  const int t = block * 256 + (int)threadIdx.x;
+  const int frag = t >> 6, lane = t & 63, m = lane & 31, h = lane >> 5;
+  if (frag >= total_frags) return;
+  const int KS = C / 16, HT = F / C, slice_fr = (4 + HT) * KS + F / 16;
+  const int s = frag / slice_fr, r = frag % slice_fr;
+  const float* src;
+  bool natural = false;
+  if (r < 3 * KS) {
+    src = reinterpret_cast<const float*>(pb.w_qkv[layer]) + (size_t)(r / KS * C + 32 * s + m) * C + 16 * (r % KS);
+    natural = true;
+  } else if (r < 4 * KS) {
+    src = reinterpret_cast<const float*>(pb.w_o[layer]) + (size_t)(32 * s + m) * C + 16 * (r - 3 * KS);
+  } else if (r < (4 + HT) * KS) {
+    const int r1 = r - 4 * KS;
+    src = reinterpret_cast<const float*>(pb.w1[layer]) + (size_t)(32 * (s * HT + r1 / KS) + m) * C + 16 * (r1 % KS);
+  } else {
+    src = reinterpret_cast<const float*>(pb.w2[layer]) + (size_t)(32 * s + m) * F + 16 * (r - (4 + HT) * KS);
+  }
+  const float4 v0 = *reinterpret_cast<const float4*>(src + (natural ? 8 : 4) * h);
+  const float4 v1 = *reinterpret_cast<const float4*>(src + (natural ? 8 * h + 4 : 8 + 4 * h));
+  float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+  for (int part = 0; part < 3; ++part) {
+    uint32_t u[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint16_t a = f32_to_bf16(v[2 * j]), b = f32_to_bf16(v[2 * j + 1]);
+      v[2 * j] -= bf16_to_f32(a);
+      v[2 * j + 1] -= bf16_to_f32(b);
+      u[j] = (uint32_t)a | ((uint32_t)b << 16);
+    }
+    pb.out[layer][(size_t)(frag * 3 + part) * 64 + lane] = make_uint4(u[0], u[1], u[2], u[3]);
+  }
 }
 
 }  // namespace ff

@@ -1,0 +1,48 @@
+"""The fused float32 layer: every block count of rows, ragged groups, both workgroup shapes for small groups, dropped
+tails and positional embedding, against the oracle and no further from it than the plain kernels."""
+import numpy as np
+import pytest
+import torch
+
+import ffsynth
+import oracle
+import paper_2301_08739_amd as ff
+from gpu_util import DEV, geoms, gpu_flatten, to_dev_feats, to_host
+
+pytestmark = pytest.mark.gpu
+
+HEADS = {64: 4, 128: 8, 256: 8}
+
+
+@pytest.mark.parametrize("C,G,n", [(64, 1, 70), (64, 32, 1003), (64, 33, 1003), (64, 96, 1003), (64, 97, 1003),
+                                   (128, 31, 1003), (128, 32, 17003), (128, 64, 1024), (128, 64, 1003), (128, 65, 1003),
+                                   (128, 128, 1003), (256, 20, 1003), (256, 64, 1003), (256, 65, 500)])
+def test_fused_fp32_layer(cfg, C, G, n):
+    c = cfg(2, 1)
+    coords = np.ascontiguousarray(c["coords"][:n])
+    rng = np.random.default_rng(C + G)
+    feats = (0.3 + rng.standard_normal((n, C))).astype(np.float32)
+    pe = (0.5 * rng.standard_normal((n, C))).astype(np.float32)
+    p = ffsynth.layer_params(C, 2 * C, HEADS[C], seed=91)
+    g, _ = geoms(c)
+    perm, off, ng, _, dev = gpu_flatten(coords, g, 1, 1, G, want_keys=False)
+    dperm, doff, dng, _ = ff.ff_flatten(torch.from_numpy(coords).to(DEV), g, 1, 1, G, ff.FF_TAIL_DROP)
+    lw = ff.LayerWeights(p, ff.FF_F32, DEV)
+    x, e = to_dev_feats(feats, ff.FF_F32), to_dev_feats(pe, ff.FF_F32)
+    mg = -(-n // G) + 1
+
+    def run(flags, lists=dev, embed=None):
+        return to_host(ff.ff_group_attention(x, lists[0], lists[1], lists[2], mg, lw, G, ff.FF_F32, flags, pos_embed=embed))
+
+    want = oracle.layer(feats, perm, off, p)
+    err = np.abs(run(0) - want)
+    plain = np.abs(run(ff.FF_FLAG_FORCE_GENERIC) - want)
+    print(f"fp32 C={C} G={G} n={n}: fused max {err.max():.2e} mean {err.mean():.2e}, plain max {plain.max():.2e} "
+          f"mean {plain.mean():.2e}", flush=True)
+    assert err.max() <= 1e-4 and err.mean() <= 1.1 * plain.mean()
+    err = np.abs(run(0, embed=e) - oracle.layer(feats, perm, off, p, pos_embed=pe)).max()
+    assert err <= 1e-4, err
+    got = run(ff.FF_FLAG_TAIL_DROP, (dperm, doff, dng))
+    tail = perm[n - n % G:]                                  # the short last group skips the layer
+    assert np.array_equal(got[tail], feats[tail])
+    assert n % G == n or np.abs(np.delete(got - want, tail, axis=0)).max() <= 1e-4
