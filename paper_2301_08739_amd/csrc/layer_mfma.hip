@@ -202,9 +202,10 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   // with three or four, the hidden units are still unrolled completely (their chunk numbers and ring slots become
   // constants) and the head-dim units in pairs (the ring of four slots repeats every two units)
   constexpr int FFN_UNROLL = C <= 128 && MINW >= 3 ? 16 : FULL_UNROLL;
-  constexpr int ATT_UNROLL = C <= 128 && MINW >= 3 ? 2 : FULL_UNROLL;
-  constexpr bool LEAN = ((NW + 3) / 4 >= 3 && MINW <= 2 && C >= 256) || MINW >= 4;  // C = 256 with three wavefronts on a SIMD
-                                                                              // (168 registers each), C = 128 with four (128)
+  constexpr int ATT_UNROLL = C <= 128 && MINW >= 3 ? (NKB > 4 && MINW >= 4 ? 1 : 2) : FULL_UNROLL;  // (1: no scratch)
+  // Few registers per wavefront: C = 256 with three wavefronts on a SIMD (168 each), any with four (128), C = 128 with
+  // three and a positional embedding.
+  constexpr bool LEAN = ((NW + 3) / 4 >= 3 && MINW <= 2 && C >= 256) || MINW >= 4 || (PE && C == 128 && MINW >= 3);
   constexpr int PF = LEAN ? 4 : kWindow;
   using LP = LdsPlan<C, F, NVB, WPG, NW, MINW>;
   constexpr int NCHUNK = LP::NCHUNK, RING = LP::RING;
@@ -699,9 +700,9 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
     constexpr int NA = DH / 16;   // 16-blocks of head dims per head
     // The (head, pillar-block) instances are independent; they go through the softmax in
     // lockstep stages so that the long per-instance dependency chains interleave.  HJ heads are
-    // staged jointly, limited by the registers the score tiles take.
+    // staged jointly, limited by the registers the score tiles take (168 of them with three wavefronts on a SIMD).
     constexpr int VJ = NVB * NKB <= 16 ? NVB : (16 / NKB >= 1 ? 16 / NKB : 1);
-    constexpr int HJ = (NH * VJ * NKB <= 16 && MINW < 4) ? NH : 1;
+    constexpr int HJ = (NH * VJ * NKB <= (MINW == 3 ? 8 : 16) && MINW < 4) ? NH : 1;
     static_assert(NVB % VJ == 0, "pillar blocks per stage");
 #pragma unroll
     for (int v0 = 0; v0 < NVB; v0 += VJ)
@@ -915,6 +916,10 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
     // The way the rows came in: through the wavefront's LDS share (free again since the attention
     // ended), so that a store instruction writes four complete rows instead of 32 bytes of sixteen.
     u32x4* stg = reinterpret_cast<u32x4*>(kvx) + wu * (NVB * 256);
+    // (six and more key blocks in a lean mapping: the lane is counted again instead of keeping what follows from it through the
+    // kernel, which is what would go to scratch)
+    const int ln = LEAN && NKB > 5 ? (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) : lane;
+    const int i = ln & 15, q = ln >> 4, lr = ln / LPR, piece32 = ln % LPR, ph = piece32 >> 4;
 #pragma unroll
     for (int p = 0; p < PH; ++p) {
 #pragma unroll
@@ -984,9 +989,10 @@ int launch_cfg(const void* feats, void* out, const void* pos_embed, const int32_
     return launch_status();
   };
   if (pos_embed) {
-    // Three mappings have no registers left for the second operand set (they would spill, which no
-    // shipped mapping may): they are not built with a positional embedding.
-    constexpr bool kFits = !(C == 128 && NVB == 2 && WPG == 1) && !(C == 256 && NW == 10) && !(C == 128 && NW == 12);
+    // These mappings have no registers left for the second operand set (they would spill, which no shipped
+    // mapping may): they are not built with a positional embedding.
+    constexpr bool kFits = !(C == 128 && NVB == 2 && WPG == 1) && !(C == 256 && NW >= 10) && !(C == 128 && WPG == 4 && NW == 12) &&
+                           !(C == 128 && WPG == 8 && MINW == 4);
     if constexpr (kFits) {
       if (out_f32) return go(k_layer_mfma<C, DH, F, NVB, WPG, NW, MINW, true, true>, 3);
       return go(k_layer_mfma<C, DH, F, NVB, WPG, NW, MINW, false, true>, 2);
@@ -1048,36 +1054,72 @@ int FF_LAYER_SYM(layer_mfma_launch)(const void* feats, void* out, int64_t n, con
   return launch_cfg<C, DH, F, NVB, WPG, NW, MINW>(feats, out, w->pos_embed, perm, group_offsets, num_groups, max_groups, pk, \
                                                   w->ln_eps, out_f32, (int)n, G, drop ? 1 : 0, out_index, in_sorted, stream)
   const int shape = shape_id(w);
+  // A launch runs in rounds of one workgroup per compute unit (a workgroup's LDS leaves room for no second one, except
+  // in mapping 8).  A workgroup of more wavefronts does more per round, because the wavefronts of a SIMD hide each
+  // other's stalls and read the staged weights together, but its round takes longer: the mapping with the smaller
+  // product of rounds and measured time of a round wins.  A mapping whose wavefronts cover G with fewer padding slots
+  // does less work.
+  auto rounds = [&](int per_wg) { return ceil_div(ceil_div((int64_t)max_groups, per_wg), kComputeUnits); };
+  const bool pe = w->pos_embed != nullptr;
   // (pillar blocks per wave, waves per group, waves per workgroup, min waves per SIMD)
   if (shape == 1) {
     if (variant == 0) {
-      // G <= 64: two, three or four groups per workgroup (8, 12, 16 wavefronts; one workgroup per compute unit).
-      // More wavefronts on a SIMD hide more of each other's stalls, but a round (one workgroup per compute
-      // unit) takes longer and the attention loop is no longer unrolled completely: 16.4, 23.2 and 28.8 us a
-      // round at this shape.  Many rounds: four groups lead (60,000 groups: 1.76, 1.61, 1.56 ms); few: the
-      // number of rounds decides (measured, in us: 938 groups 33 / 44 / 30, 1407: 49 / 48 / 56, 1875: 65 / 69 /
-      // 60, 2344: 81 / 89 / 81, 3750: 128 / 120 / 115, 7500: 256 / 228 / 219, 15,000: 477 / 419 / 390).
-      auto rounds = [&](int per_wg) { return ceil_div(ceil_div((int64_t)max_groups, per_wg), kComputeUnits); };
-      const int64_t c2 = rounds(2) * 164, c4 = rounds(4) * 288;
-      // (the three-group mapping has no registers for a positional embedding)
-      const int64_t c3 = w->pos_embed ? INT64_MAX : rounds(3) * 232;
-      variant = G <= 32 ? 10 : G > 64 ? 9 : (c2 <= c3 && c2 <= c4) ? 7 : c3 <= c4 ? 11 : 12;
+      if (G <= 32) {
+        // four or eight groups per workgroup: 14 and 24.5 us a round (941 groups 15.8 / 23.3 us, 2002: 32 / 29, 2602:
+        // 44 / 47, 3403: 55 / 48)
+        variant = rounds(4) * 140 <= rounds(8) * 245 ? 10 : 15;
+      } else if (G <= 64) {
+        // Two, three or four groups per workgroup (8, 12, 16 wavefronts): 16.4, 23.2 and 28.8 us a round.  Many rounds:
+        // four groups lead (60,000 groups: 1.76, 1.61, 1.56 ms); few: the number of rounds decides (measured, in us:
+        // 938 groups 33 / 44 / 30, 1407: 49 / 48 / 56, 1875: 65 / 69 / 60, 2344: 81 / 89 / 81, 3750: 128 / 120 / 115,
+        // 7500: 256 / 228 / 219, 15,000: 477 / 419 / 390).
+        const int64_t c2 = rounds(2) * 164, c4 = rounds(4) * 288;
+        // (the three-group mapping has no registers for a positional embedding)
+        const int64_t c3 = pe ? INT64_MAX : rounds(3) * 232;
+        variant = (c2 <= c3 && c2 <= c4) ? 7 : c3 <= c4 ? 11 : 12;
+      } else if (G <= 80) {
+        // Five wavefronts per group.  Up to one group per compute unit: one group per workgroup, 17.2 us (eight
+        // wavefronts 20.6); beyond: two (G = 69, 466 groups: 32 us one group, 23 two, 38 with eight wavefronts per
+        // group; 3407: 211, 146, 242; rounds of 16 and 21.5 us, so one group never wins from two rounds on).
+        variant = rounds(1) == 1 ? 3 : 13;
+      } else if (G <= 96) {
+        // Six wavefronts per group, two groups (G = 90, 466 groups: 38 -> 25 us; 3410: 246 -> 161); one round of one
+        // group is still shorter with mapping 9 (201 groups: 19.3 against 22.6).
+        variant = rounds(1) == 1 ? 9 : 14;
+      } else {
+        // Two workgroups on a compute unit at 128 registers (G = 128, 627 groups: 53 -> 48 us, 3414: 242 -> 210; 201
+        // groups, one per compute unit: 18.1 against 21.6); no registers for a positional embedding.
+        variant = rounds(1) == 1 || pe ? 9 : 8;
+      }
     }
     switch (variant) {
       case 1: if (G <= 32) FF_GO(128, 16, 256, 2, 1, 4, 2); break;
       case 2: if (G <= 64) FF_GO(128, 16, 256, 2, 2, 4, 1); break;  // 512 registers
+      case 3: if (G <= 80) FF_GO(128, 16, 256, 1, 5, 5, 2); break;
       case 4: if (G <= 128) FF_GO(128, 16, 256, 2, 4, 4, 1); break;
       case 6: if (G <= 64) FF_GO(128, 16, 256, 1, 4, 4, 2); break;
       case 7: if (G <= 64) FF_GO(128, 16, 256, 1, 4, 8, 2); break;
+      case 8: if (G <= 128) FF_GO(128, 16, 256, 1, 8, 8, 4); break;   // two workgroups per compute unit
       case 9: if (G <= 128) FF_GO(128, 16, 256, 1, 8, 8, 2); break;
       case 10: if (G <= 32) FF_GO(128, 16, 256, 1, 2, 8, 2); break;
       case 11: if (G <= 64) FF_GO(128, 16, 256, 1, 4, 12, 3); break;  // three groups, three waves per SIMD
       case 12: if (G <= 64) FF_GO(128, 16, 256, 1, 4, 16, 4); break;  // four groups, four waves per SIMD
+      case 13: if (G <= 80) FF_GO(128, 16, 256, 1, 5, 10, 3); break;  // two groups
+      case 14: if (G <= 96) FF_GO(128, 16, 256, 1, 6, 12, 3); break;  // two groups, three waves per SIMD
+      case 15: if (G <= 32) FF_GO(128, 16, 256, 1, 2, 16, 4); break;  // eight groups, four waves per SIMD
       default: break;
     }
   } else if (shape == 2) {
-    // with a positional embedding the ten-wave mapping has no registers to spare: one group per workgroup instead
-    if (variant == 0) variant = G <= 32 ? 1 : G <= 64 ? 2 : G <= 80 ? (w->pos_embed ? 6 : 3) : 4;
+    if (variant == 0) {
+      // A round is bound by LDS reads of the weights (1 MB per wavefront).  G <= 64: two or three groups per workgroup,
+      // 42 and 56 us a round (626 groups: 84 / 56 us, 942: 85 / 111, 1302: 126 / 112, 3407: 297 / 288).  G <= 96: two
+      // groups of six wavefronts against one of eight (201 groups 44 us one group, 55 two; 466: 91 / 60; 3410: 614 /
+      // 422).  With a positional embedding the ten- and twelve-wave mappings have no registers to spare.
+      if (G <= 32) variant = 1;
+      else if (G <= 64) variant = !pe && rounds(3) * 56 < rounds(2) * 42 ? 8 : 2;
+      else if (G <= 80) variant = pe ? 6 : 3;
+      else variant = G <= 96 && !pe && rounds(1) > 1 ? 7 : 4;
+    }
     switch (variant) {
       case 1: if (G <= 32) FF_GO(256, 32, 512, 1, 2, 8, 2); break;
       case 2: if (G <= 64) FF_GO(256, 32, 512, 1, 4, 8, 2); break;
@@ -1085,14 +1127,30 @@ int FF_LAYER_SYM(layer_mfma_launch)(const void* feats, void* out, int64_t n, con
       case 4: if (G <= 128) FF_GO(256, 32, 512, 1, 8, 8, 2); break;
       case 5: if (G <= 64) FF_GO(256, 32, 512, 2, 2, 4, 1); break;
       case 6: if (G <= 80) FF_GO(256, 32, 512, 1, 5, 5, 1); break;
+      case 7: if (G <= 96) FF_GO(256, 32, 512, 1, 6, 12, 2); break;  // lean, two groups
+      case 8: if (G <= 64) FF_GO(256, 32, 512, 1, 4, 12, 2); break;  // lean, three groups
       default: break;
     }
   } else if (shape == 3) {  // the narrow layer (64 features, 4 heads): the whole 64 KB weight stream stays in the ring
-    if (variant == 0) variant = G <= 32 ? 1 : G <= 64 ? 2 : 4;
+    if (variant == 0) {
+      // G <= 32: four or eight groups per workgroup (1301 groups 14.8 / 13.2 us, 2602: 21.9 / 23.5, 9009: 63 / 56);
+      // G <= 64: two or four (466 groups 12.1 / 13.5, 942: 16.6 / 14.4, 1302: 23.7 / 26.0, 3407: 54 / 51); G <= 80 and
+      // <= 96: two of five or six wavefronts against one of eight (466 groups 18.8 -> 12.5 and 19.6 -> 13.7, 3400: 121
+      // -> 75 and 125 -> 84); above: one or two (466: 18.9 / 16.7, 627: 27.4 / 30.1, 3414: 123 / 104).
+      if (G <= 32) variant = rounds(4) * 70 <= rounds(8) * 118 ? 1 : 3;
+      else if (G <= 64) variant = rounds(2) * 79 <= rounds(4) * 129 ? 2 : 8;
+      else if (G <= 96) variant = rounds(1) == 1 ? 4 : G <= 80 ? 5 : 6;
+      else variant = rounds(1) * 90 <= rounds(2) * 148 ? 4 : 7;
+    }
     switch (variant) {
       case 1: if (G <= 32) FF_GO(64, 16, 128, 1, 2, 8, 2); break;
       case 2: if (G <= 64) FF_GO(64, 16, 128, 1, 4, 8, 2); break;
+      case 3: if (G <= 32) FF_GO(64, 16, 128, 1, 2, 16, 4); break;   // eight groups
       case 4: if (G <= 128) FF_GO(64, 16, 128, 1, 8, 8, 2); break;
+      case 5: if (G <= 80) FF_GO(64, 16, 128, 1, 5, 10, 3); break;   // two groups
+      case 6: if (G <= 96) FF_GO(64, 16, 128, 1, 6, 12, 3); break;   // two groups
+      case 7: if (G <= 128) FF_GO(64, 16, 128, 1, 8, 16, 4); break;  // two groups
+      case 8: if (G <= 64) FF_GO(64, 16, 128, 1, 4, 16, 4); break;   // four groups
       default: break;
     }
   }
