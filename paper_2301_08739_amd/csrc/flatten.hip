@@ -14,7 +14,7 @@
 //     holds in the order the pass reads them.  Key generation writes the rows of the first pass
 //     (plain stores) and zeroes the others; each pass adds, for every word it places, one to the
 //     row of the tile the word lands in for the next pass.  Nothing has to be cleared beforehand.
-//   * Small clouds (at most 128 tiles of 1024 words: launch and latency bound): digits of up to 10
+//   * Small clouds (at most 128 tiles of 1024 words over all sorts: launch and latency bound): digits of up to 10
 //     bits, and a pass reads the whole table of its pass itself (column sums = global digit
 //     starts, rows of earlier tiles = its own offsets): key generation + one launch per pass.
 //   * Larger clouds (bandwidth bound): per-word atomics would dominate, so passes after the first
@@ -33,7 +33,11 @@ namespace ff {
 namespace {
 
 constexpr int kMaxSorts = 4;
-constexpr int kSmallKpt = 4, kSmallMaxTiles = 128;  // small clouds: tiles of 1024 words
+// Small clouds: tiles of 1024 words.  The line counts the tiles of all sorts of a call, because every workgroup of a
+// pass reads the tables of its sort: with four sorts and four layers behind them (C = 128, us, small path against
+// scanned tables) 30,000 words 93.5 / 95.3, 40,000 122 / 115, 80,000 216 / 202, 130,000 283 / 256; one sort of 80,000
+// words 37 / 39, of 120,000 46 / 48.
+constexpr int kSmallKpt = 4, kSmallMaxTiles = 128;
 constexpr int kLargeKpt = 16;                       // larger clouds: tiles of 4096 words
 // In between, the tables are scanned by their own kernel as for larger clouds, but tiles of 4096 words
 // would leave most compute units without a workgroup.  Tiles of 1024 words up to 256 K words, of 2048
@@ -42,12 +46,15 @@ constexpr int kLargeKpt = 16;                       // larger clouds: tiles of 4
 constexpr int kMidKptA = 4, kMidMaxTilesA = 256;
 constexpr int kMidKptB = 8, kMidMaxTilesB = 768;
 constexpr int kScanThreads = 1024;
-constexpr int kScanStrip = 64;  // digits per workgroup of the column scan (narrower strips were no faster)
-// Above 1024 tiles (4 M words) a thread of the 64-digit strip would own more rows than it keeps in
-// registers; strips of 16 digits give four times the workgroups and keep every thread within 64 rows
-// up to 4096 tiles.
-constexpr int kScanNarrow = 16;
-constexpr int kScanWideTiles = 1024;
+// Shape of the column scan: digits per workgroup (its 1024 threads cut the rows into 1024 / digits runs) and rows a
+// thread keeps in registers between its two sweeps.  It is a chain of latencies, so what counts is few rows per thread:
+// 64 digits and 16 rows up to 256 tiles, 16 digits and 16 rows up to 1024, 16 digits and 64 rows up to 4096.  Before,
+// 64 rows everywhere and 64 digits up to 1024 tiles: sorts of 240,000 / 480,000 / 960,000 / 3.84 M words took 52 / 59 /
+// 69 / 115 us, now 49 / 51 / 63 / 110.
+constexpr int kScanWide = 64, kScanNarrow = 16;
+constexpr int kScanFewRows = 16, kScanManyRows = 64;
+constexpr int kScanWideTiles = kScanThreads / kScanWide * kScanFewRows;
+constexpr int kScanFewRowsTiles = kScanThreads / kScanNarrow * kScanFewRows;
 
 struct KeyParams {
   int32_t B, win_x, win_y, win_z;       // win_z = 1 and stride = 3 for bird's-eye-view pillars
@@ -251,12 +258,12 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_counts(const uint64_t* __
 
 // ---- exclusive prefixes of a pass's table over the tiles, and the per-digit totals ------------------
 // One workgroup per W digits (a strip of the table, W * 4 bytes of every row).  The rows are cut into
-// 1024 / W runs, W lanes take one run.  Up to 64 rows per run are loaded at once and stay in registers
-// between the two sweeps.
-template <int RB, int W>
+// 1024 / W runs, W lanes take one run.  Up to ROWS rows per run are loaded at once and stay in
+// registers between the two sweeps.
+template <int RB, int W, int ROWS>
 __global__ __launch_bounds__(kScanThreads) void k_scan_cols(uint32_t* __restrict__ counts, uint32_t* __restrict__ totals,
                                                              int pass, int P, int64_t tiles) {
-  constexpr int BINS = 1 << RB, RUNS = kScanThreads / W, ROWS = 64;
+  constexpr int BINS = 1 << RB, RUNS = kScanThreads / W;
   __shared__ uint32_t part[RUNS][W];
   const int s = blockIdx.y, dl = threadIdx.x % W, c = threadIdx.x / W;
   const int d = blockIdx.x * W + dl;
@@ -386,6 +393,7 @@ __global__ __launch_bounds__(kSortThreads) void k_pass(const uint64_t* __restric
           v[u][0] = cnt_tab[(size_t)t * BINS + tid];
         }
       }
+      __builtin_amdgcn_sched_barrier(0);  // all 32 in flight before the first is added
 #pragma unroll
       for (int u = 0; u < 32; ++u)
 #pragma unroll
@@ -689,9 +697,9 @@ __global__ __launch_bounds__(256) void k_finalize(const uint64_t* __restrict__ s
 
 // Pass plan for keys of `key_bits` bits: digit width and number of passes.
 struct PassPlan { bool small; int kpt, rb, passes; int64_t tiles; };
-inline PassPlan pass_plan(int64_t n, int key_bits) {
+inline PassPlan pass_plan(int64_t n, int key_bits, int sorts) {
   PassPlan pp;
-  pp.small = ceil_div(n > 0 ? n : 1, (int64_t)kSortThreads * kSmallKpt) <= kSmallMaxTiles;
+  pp.small = ceil_div(n > 0 ? n : 1, (int64_t)kSortThreads * kSmallKpt) * sorts <= kSmallMaxTiles;
   pp.kpt = pp.small ? kSmallKpt
          : ceil_div(n, (int64_t)kSortThreads * kMidKptA) <= kMidMaxTilesA ? kMidKptA
          : ceil_div(n, (int64_t)kSortThreads * kMidKptB) <= kMidMaxTilesB ? kMidKptB : kLargeKpt;
@@ -711,7 +719,7 @@ struct Layout {
 void make_layout(int64_t n, int S, int num_frames, int max_key_bits, Layout* L) {
   size_t count_words = 0, total_words = 0;
   for (int kb = 0; kb <= max_key_bits; ++kb) {
-    const PassPlan pp = pass_plan(n, kb);
+    const PassPlan pp = pass_plan(n, kb, S);
     const size_t pc = pp.passes > 0 ? pp.passes : 1;  // key generation always fills one table
     const size_t cw = (size_t)S * pc * (size_t)pp.tiles * ((size_t)1 << pp.rb);
     const size_t tw = (size_t)S * pc * ((size_t)1 << pp.rb);
@@ -859,7 +867,7 @@ static int flatten_launch_impl(const int32_t* coords, const PointCells* pts, int
   int cur = 0;
   bool outputs_done = false;
   if (n > 0) {
-    const PassPlan pp = pass_plan(n, max_key_bits);
+    const PassPlan pp = pass_plan(n, max_key_bits, num_sorts);
     const int P = pp.passes > 0 ? pp.passes : 1;  // zero key bits: the words are generated in order
     // The last pass can write the outputs itself when its digit contains the whole frame field.
     bool fuse = pp.passes > 0;
@@ -892,12 +900,13 @@ static int flatten_launch_impl(const int32_t* coords, const PointCells* pts, int
           if (pass > 0)                                                                                              \
             hipLaunchKernelGGL((k_tile_counts<RB, KPT>), grid, block, 0, stream, buf[cur], n, bt, pass, P, pp.tiles, \
                                counts);                                                                              \
-          if (pp.tiles > kScanWideTiles)                                                                             \
-            hipLaunchKernelGGL((k_scan_cols<RB, kScanNarrow>), dim3((1u << RB) / kScanNarrow, (unsigned)num_sorts),  \
-                               dim3(kScanThreads), 0, stream, counts, totals, pass, P, pp.tiles);                   \
-          else                                                                                                       \
-            hipLaunchKernelGGL((k_scan_cols<RB, kScanStrip>), dim3((1u << RB) / kScanStrip, (unsigned)num_sorts),    \
-                               dim3(kScanThreads), 0, stream, counts, totals, pass, P, pp.tiles);                   \
+          auto scan = [&](auto kern, int digits) {                                                                   \
+            hipLaunchKernelGGL(kern, dim3((1u << RB) / digits, (unsigned)num_sorts), dim3(kScanThreads), 0, stream,  \
+                               counts, totals, pass, P, pp.tiles);                                                   \
+          };                                                                                                         \
+          if (pp.tiles <= kScanWideTiles) scan(k_scan_cols<RB, kScanWide, kScanFewRows>, kScanWide);                 \
+          else if (pp.tiles <= kScanFewRowsTiles) scan(k_scan_cols<RB, kScanNarrow, kScanFewRows>, kScanNarrow);     \
+          else scan(k_scan_cols<RB, kScanNarrow, kScanManyRows>, kScanNarrow);                                       \
         }                                                                                                            \
         if (fuse && pass == pp.passes - 1)                                                                           \
           hipLaunchKernelGGL((k_pass<RB, KPT, true, SCANNED>), pass == 0 ? grid_pack : grid, block, 0, stream,      \

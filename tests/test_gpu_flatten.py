@@ -207,3 +207,17 @@ def test_coordinate_check_and_safety_outside_the_geometry():
         assert np.array_equal(np.sort(perm.cpu().numpy()), np.arange(5000))
         k = int(ng.item())
         assert 0 < k <= 5000 // 16 + 3 and int(goff[k].item()) == 5000
+
+
+@pytest.mark.parametrize("sorts,n", [(4, 32768), (4, 32769), (3, 43008), (3, 43009), (2, 65536), (2, 65537), (4, 131073)])
+def test_batched_sorts_where_the_path_changes(sorts, n):
+    """The tiles of all sorts of a call decide whether a pass adds the digit tables up itself: both sides of the line,
+    against single sorts, which still take the other path at these sizes."""
+    coords = _rand_coords(n, 3, 300, 200, seed=n)
+    g = ff.Geometry(3, 300, 200, 13, 9)
+    pairs = [(0, 0), (1, 0), (0, 1), (1, 1)][:sorts]
+    ct = torch.from_numpy(coords).to("cuda")
+    for (axis, shift), (perm, goff, ng) in zip(pairs, ff.ff_flatten_batch(ct, g, pairs, 50)):
+        wperm, woff, wng, _, _ = gpu_flatten(coords, g, axis, shift, 50, want_keys=False)
+        assert int(ng.item()) == wng
+        assert np.array_equal(perm.cpu().numpy(), wperm) and np.array_equal(goff.cpu().numpy()[:wng + 1], woff)
