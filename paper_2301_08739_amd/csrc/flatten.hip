@@ -14,7 +14,7 @@
 //     holds in the order the pass reads them.  Key generation writes the rows of the first pass
 //     (plain stores) and zeroes the others; each pass adds, for every word it places, one to the
 //     row of the tile the word lands in for the next pass.  Nothing has to be cleared beforehand.
-//   * Small clouds (at most 128 tiles of 1024 words over all sorts: launch and latency bound): digits of up to 10
+//   * Small clouds (at most 128 tiles of 1024 words, see kSmallMaxTiles: launch and latency bound): digits of up to 10
 //     bits, and a pass reads the whole table of its pass itself (column sums = global digit
 //     starts, rows of earlier tiles = its own offsets): key generation + one launch per pass.
 //   * Larger clouds (bandwidth bound): per-word atomics would dominate, so passes after the first
@@ -33,10 +33,11 @@ namespace ff {
 namespace {
 
 constexpr int kMaxSorts = 4;
-// Small clouds: tiles of 1024 words.  The line counts the tiles of all sorts of a call, because every workgroup of a
-// pass reads the tables of its sort: with four sorts and four layers behind them (C = 128, us, small path against
-// scanned tables) 30,000 words 93.5 / 95.3, 40,000 122 / 115, 80,000 216 / 202, 130,000 283 / 256; one sort of 80,000
-// words 37 / 39, of 120,000 46 / 48.
+// Small clouds: tiles of 1024 words, up to 128 of them.  Inside a block the tiles of all its sorts count, because every
+// workgroup of a pass reads the tables of its sort: with four sorts and four layers behind them (C = 128, us, small path
+// against scanned tables) 30,000 words 93.5 / 95.3, 40,000 122 / 115, 80,000 216 / 202, 130,000 283 / 256.  A batch of
+// sorts by itself is bound by its launches, of which the scanned path has twice as many (50,000 words in two frames, four
+// sorts: 66 / 79), so it counts like a single sort (80,000 words 37 / 39, 120,000 46 / 48).
 constexpr int kSmallKpt = 4, kSmallMaxTiles = 128;
 constexpr int kLargeKpt = 16;                       // larger clouds: tiles of 4096 words
 // In between, the tables are scanned by their own kernel as for larger clouds, but tiles of 4096 words
@@ -697,6 +698,7 @@ __global__ __launch_bounds__(256) void k_finalize(const uint64_t* __restrict__ s
 
 // Pass plan for keys of `key_bits` bits: digit width and number of passes.
 struct PassPlan { bool small; int kpt, rb, passes; int64_t tiles; };
+// (`sorts` decides between the paths only: digit width, passes and tiles, and with them the workspace, do not depend on it)
 inline PassPlan pass_plan(int64_t n, int key_bits, int sorts) {
   PassPlan pp;
   pp.small = ceil_div(n > 0 ? n : 1, (int64_t)kSortThreads * kSmallKpt) * sorts <= kSmallMaxTiles;
@@ -867,7 +869,8 @@ static int flatten_launch_impl(const int32_t* coords, const PointCells* pts, int
   int cur = 0;
   bool outputs_done = false;
   if (n > 0) {
-    const PassPlan pp = pass_plan(n, max_key_bits, num_sorts);
+    const bool in_block = inv_perm && inv_perm[0];  // only a block asks for the inverse permutations
+    const PassPlan pp = pass_plan(n, max_key_bits, in_block ? num_sorts : 1);
     const int P = pp.passes > 0 ? pp.passes : 1;  // zero key bits: the words are generated in order
     // The last pass can write the outputs itself when its digit contains the whole frame field.
     bool fuse = pp.passes > 0;

@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 import torch
 
+import ffsynth
 import oracle
 import paper_2301_08739_amd as ff
 from gpu_util import geoms, gpu_flatten
@@ -209,15 +210,17 @@ def test_coordinate_check_and_safety_outside_the_geometry():
         assert 0 < k <= 5000 // 16 + 3 and int(goff[k].item()) == 5000
 
 
-@pytest.mark.parametrize("sorts,n", [(4, 32768), (4, 32769), (3, 43008), (3, 43009), (2, 65536), (2, 65537), (4, 131073)])
-def test_batched_sorts_where_the_path_changes(sorts, n):
-    """The tiles of all sorts of a call decide whether a pass adds the digit tables up itself: both sides of the line,
-    against single sorts, which still take the other path at these sizes."""
+@pytest.mark.parametrize("layers,n", [(4, 32768), (4, 32769), (3, 43008), (3, 43009), (2, 65536), (2, 65537), (4, 131073)])
+def test_block_where_the_sort_path_changes(layers, n):
+    """Inside a block the tiles of all its sorts decide whether a pass adds the digit tables up itself: both sides of
+    the line, against single sorts, which take the other path at these sizes, and layers one by one, bit for bit."""
     coords = _rand_coords(n, 3, 300, 200, seed=n)
     g = ff.Geometry(3, 300, 200, 13, 9)
-    pairs = [(0, 0), (1, 0), (0, 1), (1, 1)][:sorts]
     ct = torch.from_numpy(coords).to("cuda")
-    for (axis, shift), (perm, goff, ng) in zip(pairs, ff.ff_flatten_batch(ct, g, pairs, 50)):
-        wperm, woff, wng, _, _ = gpu_flatten(coords, g, axis, shift, 50, want_keys=False)
-        assert int(ng.item()) == wng
-        assert np.array_equal(perm.cpu().numpy(), wperm) and np.array_equal(goff.cpu().numpy()[:wng + 1], woff)
+    x = torch.randn(n, 64, device="cuda", generator=torch.Generator(device="cuda").manual_seed(n)).bfloat16()
+    stack = [ff.LayerWeights(ffsynth.layer_params(64, 128, 4, seed=s), ff.FF_BF16, "cuda") for s in range(layers)]
+    got, want = ff.ff_fwa_block(ct, g, 50, stack, ff.FF_BF16, x), x
+    for layer, (axis, shift) in zip(stack, [(0, 0), (1, 0), (0, 1), (1, 1)]):
+        perm, goff, ng, _ = ff.ff_flatten(ct, g, axis, shift, 50)
+        want = ff.ff_group_attention(want, perm, goff, ng, -(-n // 50) + 3, layer, 50, ff.FF_BF16)
+    assert torch.equal(got, want)
