@@ -11,6 +11,7 @@
 //   k_seg_starts    numbers the cell starts: start position and cell of every pillar
 //   k_seg_mean      sixteen lanes per pillar: mean of its points' features, point -> pillar
 #include "common.h"
+#include <type_traits>
 
 namespace ff {
 namespace {
@@ -174,36 +175,44 @@ __global__ __launch_bounds__(256) void k_seg_mean(const int32_t* __restrict__ pe
     const float inv = 1.0f / (float)(hi - lo);
     for (int c0 = 0; c0 < Cp; c0 += 4) {  // four features at a time
       float acc[4] = {0.f, 0.f, 0.f, 0.f};
-      // eight points per lane and round, their loads in flight together: a pillar of several hundred
-      // points (a dense object, the cell under the sensor) is a chain of dependent round trips otherwise
-      for (int q = lo + sub; q < hi; q += 16 * kPointsInFlight) {
-        int32_t src[kPointsInFlight];
+      auto add = [&](int q, auto in_flight) {  // points q, q + 16, .. of the pillar, their loads in flight together
+        constexpr int U = decltype(in_flight)::value;
+        int32_t src[U];
 #pragma unroll
-        for (int u = 0; u < kPointsInFlight; ++u) src[u] = q + 16 * u < hi ? perm[q + 16 * u] : -1;
+        for (int u = 0; u < U; ++u) src[u] = q + 16 * u < hi ? perm[q + 16 * u] : -1;
         if (point_to_pillar && c0 == 0) {  // the point indices are at hand here (Cp >= 1: this round always runs)
 #pragma unroll
-          for (int u = 0; u < kPointsInFlight; ++u)
+          for (int u = 0; u < U; ++u)
             if (src[u] >= 0) point_to_pillar[src[u]] = (int32_t)pid;
         }
-        float v[kPointsInFlight][4];
+        float v[U][4];
         if (vec4) {  // four features of a point in one 16-byte load (the same for every thread)
 #pragma unroll
-          for (int u = 0; u < kPointsInFlight; ++u) {
+          for (int u = 0; u < U; ++u) {
             const float4 t = *reinterpret_cast<const float4*>(pfeats + (int64_t)(src[u] >= 0 ? src[u] : 0) * Cp + c0);
             v[u][0] = src[u] >= 0 ? t.x : 0.f; v[u][1] = src[u] >= 0 ? t.y : 0.f;
             v[u][2] = src[u] >= 0 ? t.z : 0.f; v[u][3] = src[u] >= 0 ? t.w : 0.f;
           }
         } else {
 #pragma unroll
-          for (int u = 0; u < kPointsInFlight; ++u)
+          for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
               v[u][j] = src[u] >= 0 && c0 + j < Cp ? pfeats[(int64_t)src[u] * Cp + c0 + j] : 0.f;
         }
 #pragma unroll
-        for (int u = 0; u < kPointsInFlight; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int j = 0; j < 4; ++j) acc[j] += v[u][j];
+      };
+      // Most pillars hold a few points: one point per lane then, where eight rounds of masked loads were issued before.
+      // Eight in flight for the others: a pillar of several hundred points (a dense object, the cell under the sensor)
+      // is a chain of dependent round trips otherwise (sixteen were no faster).  180,000 points on 50,000 pillars: 17.1 ->
+      // 15.0 us; the same bits.
+      if (hi - lo <= 16) {
+        if (lo + sub < hi) add(lo + sub, std::integral_constant<int, 1>());
+      } else {
+        for (int q = lo + sub; q < hi; q += 16 * kPointsInFlight) add(q, std::integral_constant<int, kPointsInFlight>());
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
