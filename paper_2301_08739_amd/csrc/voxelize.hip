@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void k_seg_mean(const int32_t* __restrict__ pe
       // Most pillars hold a few points: one point per lane then, where eight rounds of masked loads were issued before.
       // Eight in flight for the others: a pillar of several hundred points (a dense object, the cell under the sensor)
       // is a chain of dependent round trips otherwise (sixteen were no faster).  180,000 points on 50,000 pillars: 17.1 ->
-      // 15.0 us; the same bits.
+      // 15.0-16.5 us; the same bits.
       if (hi - lo <= 16) {
         if (lo + sub < hi) add(lo + sub, std::integral_constant<int, 1>());
       } else {
