@@ -71,8 +71,9 @@ __device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
 }
 // big += hi hi, small += the other five.  The products round towards zero at the size of what they add to: apart, only
-// one in six of them meets the large sum (error of a layer 2.0e-7 in the mean, of the plain kernels 2.1e-7, 3.8e-7 with
-// all six on one accumulator).
+// one in six of them meets the large sum.  For the same reason a sum starts from its bias and the residual is added to
+// the finished sum.  Error of a layer against float64, 9,001 rows, C = 128, G = 64: mean 0.99e-7, largest 1.1e-6; with the
+// residual as the first term 1.7e-7 and 3.7e-6; plain kernels 2.1e-7 and 3.1e-6.
 __device__ __forceinline__ void mma(const Split& a, const Split& b, f32x16& big, f32x16& small) {
   small = mfma_bf16(a.p[2], b.p[0], small);
   small = mfma_bf16(a.p[0], b.p[2], small);
@@ -498,9 +499,12 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
   lds_barrier();
   {
     const f32x16 bo = vec16(P_BO + 32 * s);
+    f32x16 o[PT];
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) x1[pt] += bo;
-    product(x1, wo0, wo_at, row_frags, KS, false, nothing);
+    for (int pt = 0; pt < PT; ++pt) o[pt] = bo;
+    product(o, wo0, wo_at, row_frags, KS, false, nothing);
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt) x1[pt] += o[pt];
   }
   int orow[PT];                            // rows of `out` of my LN1 / store rows
 #pragma unroll
@@ -524,7 +528,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
   Split w10 = w1_at(0, 0);
   lds_barrier();
   {
-    const f32x16 gm = vec16(P_G2 + 32 * s), bt = vec16(P_B2N + 32 * s), b2 = vec16(P_B2 + 32 * s);
+    const f32x16 gm = vec16(P_G2 + 32 * s), bt = vec16(P_B2N + 32 * s);
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt) {
       f32x2 st[NS];
@@ -544,7 +548,6 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
 #pragma unroll
         for (int part = 0; part < 3; ++part) a_at(pt, 2 * s + f, part) = sp.p[part];
       }
-      x1[pt] += b2;
     }
   }
   lds_barrier();
@@ -585,16 +588,22 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
     asm volatile("" ::: "memory");         // (the second tile reads its operands again instead of keeping them in registers)
     product(acc[1], w1_at(1, 0), [&](int ks) { return w1_at(1, ks); }, row_frags, KS, false,
             [&](int k) { gelu_part(acc[0], k * PT * 16 / KS, (k + 1) * PT * 16 / KS); });
+    f32x16 y2[PT];
+    const f32x16 b2 = vec16(P_B2 + 32 * s);
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt) y2[pt] = b2;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const Split w20 = w2_at(u, 0);
       if (u > 0) lds_barrier();            // the unit before has been read
       put_unit(acc[u / 2], u % 2);
       lds_barrier();
-      product(x1, w20, [&](int k) { return w2_at(u, k); }, h_frags, NS, false, [&](int k) {
+      product(y2, w20, [&](int k) { return w2_at(u, k); }, h_frags, NS, false, [&](int k) {
         if (u < 2) gelu_part(acc[1], (u * NS + k) * PT * 8 / NS, (u * NS + k + 1) * PT * 8 / NS);
       });
     }
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt) x1[pt] += y2[pt];
   }
 
   // ---- scatter: whole rows through LDS (16-byte pieces swizzled by row), over A, which is free --------------------

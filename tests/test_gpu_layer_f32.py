@@ -46,3 +46,34 @@ def test_fused_fp32_layer(cfg, C, G, n):
     tail = perm[n - n % G:]                                  # the short last group skips the layer
     assert np.array_equal(got[tail], feats[tail])
     assert n % G == n or np.abs(np.delete(got - want, tail, axis=0)).max() <= 1e-4
+
+
+@pytest.mark.parametrize("C,G,n", [(64, 7, 12007), (64, 32, 9001), (64, 64, 9001), (64, 90, 9001), (64, 128, 9001),
+                                   (128, 9, 12007), (128, 64, 9001), (128, 69, 9001), (128, 128, 9001), (256, 31, 9001),
+                                   (256, 64, 9001)])
+def test_fused_fp32_error_is_not_above_the_plain_kernels(C, G, n):
+    """Two frames, the second starting at no multiple of G behind a short group, both workgroup shapes for small groups:
+    neither the mean nor the largest error against float64 exceeds that of the plain fp32 kernels, with and without an
+    embedding."""
+    rng = np.random.default_rng(7 * C + G)
+    grid, cut = 468, n // 2 - 3
+    coords = np.empty((n, 3), np.int32)
+    for b, lo, hi in ((0, 0, cut), (1, cut, n)):
+        cells = rng.choice(grid * grid, hi - lo, replace=False)
+        coords[lo:hi] = np.stack([np.full(hi - lo, b), cells // grid, cells % grid], 1)
+    coords = coords[rng.permutation(n)]
+    feats = rng.standard_normal((n, C)).astype(np.float32)
+    pe = (0.5 * rng.standard_normal((n, C))).astype(np.float32)
+    p = ffsynth.layer_params(C, 2 * C, HEADS[C], seed=17)
+    perm, off, ng, _, dev = gpu_flatten(coords, ff.Geometry(2, grid, grid, 9, 9), 0, 1, G, want_keys=False)
+    lw = ff.LayerWeights(p, ff.FF_F32, DEV)
+    x = to_dev_feats(feats, ff.FF_F32)
+    for embed in (None, pe):
+        want = oracle.layer(feats, perm, off, p, pos_embed=embed)
+        fused, plain = (np.abs(to_host(ff.ff_group_attention(
+            x, dev[0], dev[1], dev[2], -(-n // G) + 1, lw, G, ff.FF_F32, flags,
+            pos_embed=None if embed is None else to_dev_feats(embed, ff.FF_F32))) - want)
+            for flags in (0, ff.FF_FLAG_FORCE_GENERIC))
+        print(f"C={C} G={G} embed={embed is not None}: fused max {fused.max():.2e} mean {fused.mean():.2e}, plain max "
+              f"{plain.max():.2e} mean {plain.mean():.2e}", flush=True)
+        assert fused.max() <= plain.max() and fused.mean() <= plain.mean()
