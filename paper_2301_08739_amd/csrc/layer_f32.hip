@@ -106,11 +106,13 @@ template <int LPR> __device__ __forceinline__ float lane_sum(float v) {
 }
 
 // GELU(v) = v Phi(v) = max(v, 0) - t Phi(-t), t = |v|, with Phi(-t) = 2^P(t) and P a polynomial fitted to the base-2
-// logarithm of the Gaussian tail on [0, 6] (beyond, t Phi(-t) < 6e-9 |v|).  Without branches: 12 vector operations and one
-// exponential (erff: a branch and some 35).  Error at most 2.4e-7 absolute and 7.2e-8 |v| over [-9, 9]; 0.5 v (1 + erf)
-// in float32 with erf rounded correctly: 4.5e-7 and 1.1e-7 |v|.
+// logarithm of the Gaussian tail on [0, 6].  Beyond, it keeps falling to 2^-50 at t = 8.5, where t stops: what is left
+// of the tail is below 1e-14 whatever v.  max(v, 0) is written (v + |v|) / 2, which keeps a NaN and has, like
+// 0.5 v (1 + erf), no value at minus infinity.  Without branches: 13 vector operations and one exponential (erff: a
+// branch and some 35).  Largest error 2.4e-7 over [-9, 9] and 2.2e-10 on [-9, -6]; 0.5 v (1 + erf) in float32 with erf
+// rounded correctly: 4.5e-7 and 5.9e-9.
 __device__ __forceinline__ float gelu(float v) {
-  const float t = fminf(fabsf(v), 6.0f);
+  const float t = fminf(fabsf(v), 8.5f);
   float p = 4.41011849e-07f;
   p = fmaf(p, t, -8.55969938e-06f);
   p = fmaf(p, t, 6.93239272e-05f);
@@ -121,7 +123,7 @@ __device__ __forceinline__ float gelu(float v) {
   p = fmaf(p, t, -4.59217966e-01f);
   p = fmaf(p, t, -1.15110457f);
   p = fmaf(p, t, -1.0f);
-  return fmaf(-fabsf(v), __builtin_amdgcn_exp2f(p), fmaxf(v, 0.f));
+  return fmaf(-t, __builtin_amdgcn_exp2f(p), fmaf(0.5f, fabsf(v), 0.5f * v));
 }
 
 // Nothing is moved across by the instruction scheduler: it would sink loads issued ahead to where they are used.

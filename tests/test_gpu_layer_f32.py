@@ -77,3 +77,22 @@ def test_fused_fp32_error_is_not_above_the_plain_kernels(C, G, n):
         print(f"C={C} G={G} embed={embed is not None}: fused max {fused.max():.2e} mean {fused.mean():.2e}, plain max "
               f"{plain.max():.2e} mean {plain.mean():.2e}", flush=True)
         assert fused.max() <= plain.max() and fused.mean() <= plain.mean()
+
+
+@pytest.mark.parametrize("shift", [-7.0, -100.0, -1e6])
+def test_fused_fp32_gelu_far_below_zero(cfg, shift):
+    """Hidden units far on the negative side add nothing: the layer stays as close to float64 as the plain kernels."""
+    c = cfg(2, 1)
+    n, C, G = 1003, 128, 64
+    coords = np.ascontiguousarray(c["coords"][:n])
+    p = dict(ffsynth.layer_params(C, 2 * C, HEADS[C], seed=5))
+    p["b1"] = np.where(np.arange(2 * C) % 3 > 0, np.float32(shift), p["b1"]).astype(np.float32)
+    feats = np.random.default_rng(5).standard_normal((n, C)).astype(np.float32)
+    perm, off, ng, _, dev = gpu_flatten(coords, geoms(c)[0], 0, 0, G, want_keys=False)
+    lw, x = ff.LayerWeights(p, ff.FF_F32, DEV), to_dev_feats(feats, ff.FF_F32)
+    want = oracle.layer(feats, perm, off, p)
+    fused, plain = (np.abs(to_host(ff.ff_group_attention(x, dev[0], dev[1], dev[2], -(-n // G), lw, G, ff.FF_F32, flags))
+                           - want) for flags in (0, ff.FF_FLAG_FORCE_GENERIC))
+    print(f"shift {shift}: fused max {fused.max():.2e} mean {fused.mean():.2e}, plain max {plain.max():.2e} mean "
+          f"{plain.mean():.2e}", flush=True)
+    assert fused.max() <= plain.max() and fused.mean() <= plain.mean()
