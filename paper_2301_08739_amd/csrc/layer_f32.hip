@@ -44,7 +44,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 
-struct Split {  // one lane's share of a fragment: hi, mid, lo
+struct Split {  // one lane's share of a fragment: hi, mid, lo (direct form: the eight floats in p[0] and p[1])
   u32x4 p[3];
 };
 
@@ -66,6 +66,23 @@ __device__ __forceinline__ Split split8(const float* v) {
     }
   }
   return s;
+}
+// The same eight numbers as they are (direct form), and back.
+__device__ __forceinline__ Split raw8(const float* v) {
+  Split s;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) s.p[j / 4][j % 4] = __float_as_uint(v[j]);
+  s.p[2] = u32x4{0u, 0u, 0u, 0u};
+  return s;
+}
+__device__ __forceinline__ float raw_at(const Split& s, int j) { return __uint_as_float(s.p[j / 4][j % 4]); }
+// Number j of a split operand: the sum of its parts is exact, and infinite parts stand alone (split_part).
+__device__ __forceinline__ float sum_at(const Split& s, int j) {
+  auto part = [&](int k) {
+    const uint32_t u = s.p[k][j / 2];
+    return __uint_as_float(j % 2 ? u & 0xffff0000u : u << 16);
+  };
+  return part(0) + (part(1) + part(2));
 }
 __device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
@@ -156,17 +173,28 @@ struct Plan {
   static constexpr int TOTAL = A + H + STATS + PAR;
 };
 
-template <int C, int DH, int F, int PT, int GPW, int MINW, bool PE>
-__global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
+// Returns, the same for every thread of the workgroup, whether some result is infinite or no number; nothing has been
+// stored then.  DIRECT: the linear layers on float32 products of the numbers themselves, and the results are stored
+// whatever they are.
+//
+// Why two forms: three parts cannot stand for an infinity (inf - inf is no number), for a number that rounds to one in
+// bfloat16, or for what becomes infinite on the way (a hidden unit), and inf * hi + inf * mid is no number where inf * x
+// is infinite.  Whatever of that happens in a row reaches all its results, as the products are dense and nothing on the
+// way turns it into a number again, so one look at the results finds it.  The workgroup then starts over in the direct
+// form, which gives infinities and NaNs where float32 arithmetic gives them.  The look takes a multiply-add per result.
+template <int C, int DH, int F, int PT, int GPW, bool PE, bool DIRECT>
+__device__ __forceinline__ bool layer_f32_rows(
     const float* __restrict__ feats, float* __restrict__ out, const float* __restrict__ pos_embed,
     const int32_t* __restrict__ perm, const int32_t* __restrict__ goff, const int32_t* __restrict__ num_groups,
-    int max_groups, int n, int G, const int32_t* __restrict__ out_index, int in_sorted, int drop, float eps, Weights wt) {
+    int max_groups, int n, int G, const int32_t* __restrict__ out_index, int in_sorted, int drop, float eps,
+    const Weights& wt, const int tid) {
   using PL = Plan<C, F, PT>;
   constexpr int NS = PL::NS, NT = PL::NT;
   constexpr int KS = C / 16;               // fragments along C
   constexpr int HT = F / 32 / NS;          // hidden tiles of a wavefront
   constexpr int PTG = PT / GPW;            // row blocks of a group
   constexpr int NH = 32 / DH;              // heads of a wavefront
+  constexpr int PARTS = DIRECT ? 2 : 3;    // of an operand in LDS
   constexpr int LPR = C / 16, RPS = 64 / LPR;  // LN1: lanes per row (two runs of 8 features each), rows per step
   static_assert(DH == 16 || DH == 32, "head dim");
   static_assert(PT % GPW == 0 && HT == 2, "whole blocks, two hidden tiles per wavefront");
@@ -179,7 +207,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
   float* const par = reinterpret_cast<float*>(ldsc + PL::A + PL::H + PL::STATS);
   constexpr int P_BQ = 0, P_BO = C, P_G2 = 2 * C, P_B2N = 3 * C, P_B2 = 4 * C, P_B1 = 5 * C;
 
-  const int tid = threadIdx.x, lane = tid & 63, nrow = lane & 31, h = lane >> 5;
+  const int lane = tid & 63, nrow = lane & 31, h = lane >> 5;
   const int s = __builtin_amdgcn_readfirstlane(tid >> 6);  // slice
 
   // ---- weight stream of the slice: wave-uniform base, the lane's part of the address is a 32-bit offset -----------
@@ -192,6 +220,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
     for (int k = 0; k < 3; ++k) r.p[k] = *reinterpret_cast<const u32x4*>(wbase + (frag * 3 + k) * 1024 + lane16);
     return r;
   };
+  auto pack8 = [](const float* v) { return DIRECT ? raw8(v) : split8(v); };
   auto wq_at = [&](int which, int ks) { return w_at(which * KS + ks); };
   auto wo_at = [&](int ks) { return w_at(3 * KS + ks); };
   auto w1_at = [&](int t, int ks) { return w_at((4 + t) * KS + ks); };
@@ -269,6 +298,8 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
     put(P_B2, wt.b2, C); put(P_B1, wt.b1, F);
   }
   const float bv = wt.b_qkv[2 * C + 32 * s + nrow];
+  // The key bias shifts all scores of a query alike and drops out of the softmax, unless it is no finite number.
+  const float bk = wt.b_qkv[C + 32 * s + nrow] * 0.f;
   if (!all_guessed) fetch(position);       // wave-uniform
 
   // ---- LN1 -> A (natural input order) ------------------------------------------------------------------------------
@@ -308,9 +339,9 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
         float z[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) z[i] = y[t][8 * k + i] + (PE && embed ? pe[PE ? t : 0][k][i / 4][i % 4] : 0.f);
-        const Split sp = split8(PE && embed ? z : &y[t][8 * k]);
+        const Split sp = pack8(PE && embed ? z : &y[t][8 * k]);
 #pragma unroll
-        for (int part = 0; part < 3; ++part)
+        for (int part = 0; part < PARTS; ++part)
           Ab[(((row >> 5) * KS + (p >> 1)) * 3 + part) * 64 + (p & 1) * 32 + (row & 31)] = sp.p[part];
       }
     }
@@ -350,7 +381,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
   auto row_frags = [&](int pt, int ks) -> Split {
     Split a;
 #pragma unroll
-    for (int part = 0; part < 3; ++part) a.p[part] = a_at(pt, ks, part);
+    for (int part = 0; part < PARTS; ++part) a.p[part] = a_at(pt, ks, part);
     return a;
   };
 
@@ -359,6 +390,22 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
   // caller; a block's rows are replaced as soon as its products are issued; `beside`: work of the vector units for every
   // step
   auto product = [&](f32x16 (&acc)[PT], Split w0, auto weight, auto rows, int steps, bool swap, auto beside) {
+    if constexpr (DIRECT) {
+#pragma unroll 1
+      for (int k = 0; k < steps; ++k) {
+        const Split w = weight(k);
+#pragma unroll
+        for (int pt = 0; pt < PT; ++pt) {
+          const Split a = rows(pt, k);
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            acc[pt] = swap ? mma2(raw_at(a, j), sum_at(w, j), acc[pt]) : mma2(sum_at(w, j), raw_at(a, j), acc[pt]);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < steps; ++k) beside(k);
+      return;
+    }
     constexpr int DW = PT == 1 ? 5 : 3;
     Split w[DW], a[PT];
     f32x16 lo[PT];
@@ -394,8 +441,9 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
   lds_barrier();
   {
     const f32x16 bq = vec16(P_BQ + 32 * s);
+    const float k0 = __builtin_amdgcn_ballot_w64(bk != 0.f) ? __builtin_nanf("") : 0.f;
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) { Q[pt] = bq; K[pt] = kZero; V[pt] = kZero; }
+    for (int pt = 0; pt < PT; ++pt) { Q[pt] = bq; K[pt] = kZero + k0; V[pt] = kZero; }
     // One after the other (both sums of all three would not fit the registers).
     if constexpr (PE) {  // values from LN(F), queries and keys from LN(F) + PE
       product(V, wq0, [&](int ks) { return wq_at(2, ks); }, row_frags, KS, true, nothing);
@@ -472,9 +520,9 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
             float o[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) o[j] = O[8 * (NH == 2 ? hd : f) + j] * inv;
-            const Split sp = split8(o);
+            const Split sp = pack8(o);
 #pragma unroll
-            for (int part = 0; part < 3; ++part) a_at(qt, 2 * s + (NH == 2 ? hd : f), part) = sp.p[part];
+            for (int part = 0; part < PARTS; ++part) a_at(qt, 2 * s + (NH == 2 ? hd : f), part) = sp.p[part];
           }
         }
       }
@@ -484,7 +532,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
     bool whole = true;
 #pragma unroll
     for (int gl = 0; gl < GPW; ++gl) whole = whole && m[gl] == 32 * PTG;
-    if (whole) attention(std::false_type());
+    if (!DIRECT && whole) attention(std::false_type());
     else attention(std::true_type());
   }
 
@@ -546,9 +594,9 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
       for (int r = 0; r < 16; ++r) z[r] = fmaf((x1[pt][r] - mu) * rstd, gm[r], bt[r]);
 #pragma unroll
       for (int f = 0; f < 2; ++f) {
-        const Split sp = split8(z + 8 * f);
+        const Split sp = pack8(z + 8 * f);
 #pragma unroll
-        for (int part = 0; part < 3; ++part) a_at(pt, 2 * s + f, part) = sp.p[part];
+        for (int part = 0; part < PARTS; ++part) a_at(pt, 2 * s + f, part) = sp.p[part];
       }
     }
   }
@@ -567,15 +615,15 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
       float v[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] = acc[pt][8 * f + j];
-      const Split sp = split8(v);
+      const Split sp = pack8(v);
 #pragma unroll
-      for (int part = 0; part < 3; ++part) Hb[((pt * NS + s) * 3 + part) * 64 + lane] = sp.p[part];
+      for (int part = 0; part < PARTS; ++part) Hb[((pt * NS + s) * 3 + part) * 64 + lane] = sp.p[part];
     }
   };
   auto h_frags = [&](int pt, int k) -> Split {
     Split b;
 #pragma unroll
-    for (int part = 0; part < 3; ++part) b.p[part] = Hb[((pt * NS + k) * 3 + part) * 64 + lane];
+    for (int part = 0; part < PARTS; ++part) b.p[part] = Hb[((pt * NS + k) * 3 + part) * 64 + lane];
     return b;
   };
   {
@@ -608,6 +656,19 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
     for (int pt = 0; pt < PT; ++pt) x1[pt] += y2[pt];
   }
 
+  uint32_t* const unfit = reinterpret_cast<uint32_t*>(stats);  // per wavefront: some result is no finite number
+  if constexpr (!DIRECT) {
+    float z[4] = {0.f, 0.f, 0.f, 0.f};     // 0 x is 0 for a finite x and no number otherwise
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt)
+      if (m[pt / PTG] > 0) {               // (a group past the last one divides by its empty row sums)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z[r % 4] = fmaf(x1[pt][r], 0.f, z[r % 4]);
+      }
+    const uint64_t any = __builtin_amdgcn_ballot_w64((z[0] + z[1]) + (z[2] + z[3]) != 0.f);
+    if (lane == 0) unfit[s] = any != 0;
+  }
+
   // ---- scatter: whole rows through LDS (16-byte pieces swizzled by row), over A, which is free --------------------
 #pragma unroll
   for (int pt = 0; pt < PT; ++pt)
@@ -620,6 +681,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
       *reinterpret_cast<f32x4*>(ldsc + row * (C * 4) + ((p ^ (row & 15)) * 16)) = v;
     }
   lds_barrier();
+  if (!DIRECT && __builtin_amdgcn_ballot_w64(unfit[lane % NS] != 0)) return true;
 #pragma unroll
   for (int t = 0; t < PT; ++t) {
     const int row = (s * PT + t) * RPS + lr;
@@ -634,6 +696,31 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
       }
     }
   }
+  return false;
+}
+
+// What the second form uses of the first form's inputs is read again: kept, it would take registers from the first.
+template <typename T> __device__ __forceinline__ T* again(T* p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+template <int C, int DH, int F, int PT, int GPW, int MINW, bool PE>
+__global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
+    const float* __restrict__ feats, float* __restrict__ out, const float* __restrict__ pos_embed,
+    const int32_t* __restrict__ perm, const int32_t* __restrict__ goff, const int32_t* __restrict__ num_groups,
+    int max_groups, int n, int G, const int32_t* __restrict__ out_index, int in_sorted, int drop, float eps, Weights wt) {
+  if (!layer_f32_rows<C, DH, F, PT, GPW, PE, false>(feats, out, pos_embed, perm, goff, num_groups, max_groups, n, G,
+                                                    out_index, in_sorted, drop, eps, wt, threadIdx.x))
+    return;
+  lds_barrier();                           // every wavefront has read what made it start over
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const Weights w2{again(wt.packed), again(wt.ln1_g), again(wt.ln1_b), again(wt.b_qkv), again(wt.b_o),
+                   again(wt.ln2_g), again(wt.ln2_b), again(wt.b1), again(wt.b2)};
+  layer_f32_rows<C, DH, F, PT, GPW, PE, true>(again(feats), again(out), again(pos_embed), again(perm), again(goff),
+                                              again(num_groups), max_groups, n, G, again(out_index), in_sorted, 0, eps,
+                                              w2, tid);
 }
 
 template <int C, int DH, int F, int PT, int GPW, int MINW>
@@ -697,13 +784,13 @@ int layer_f32_launch(const LayerF32& c, hipStream_t stream) {
   const bool few = c.max_groups <= 512;
   switch (c.w->C) {
     case 64:
-      if (G <= 32 && few) return launch_cfg<64, 16, 128, 1, 1, 2>(c, stream);
+      if (G <= 32 && few) return launch_cfg<64, 16, 128, 1, 1, 3>(c, stream);
       if (G <= 32) return launch_cfg<64, 16, 128, 2, 2, 2>(c, stream);
       if (G <= 64) return launch_cfg<64, 16, 128, 2, 1, 2>(c, stream);
       if (G <= 96) return launch_cfg<64, 16, 128, 3, 1, 1>(c, stream);
       return launch_cfg<64, 16, 128, 4, 1, 1>(c, stream);
     case 128:
-      if (G <= 32 && few) return launch_cfg<128, 16, 256, 1, 1, 2>(c, stream);
+      if (G <= 32 && few) return launch_cfg<128, 16, 256, 1, 1, 3>(c, stream);
       if (G <= 32) return launch_cfg<128, 16, 256, 2, 2, 2>(c, stream);
       if (G <= 64) return launch_cfg<128, 16, 256, 2, 1, 2>(c, stream);
       if (G <= 96) return launch_cfg<128, 16, 256, 3, 1, 1>(c, stream);

@@ -189,6 +189,14 @@ __device__ __forceinline__ void pack_weights_block(const PackBatch& pb, int laye
 // (h, m) = 32 h + m owns 16 bytes of each: row m and eight inputs.  Q, K, V multiply the LayerNorm output in its natural
 // order: inputs 16 k + 8 h + 0..7.  The other matrices multiply operands that were accumulators: inputs 16 k + 4 h + 0..3
 // and 16 k + 8 + 4 h + 0..3.
+// The next part of v, which keeps the rest.  A number that would round to infinity is cut instead; an infinity or a NaN
+// is a part of its own, with nothing after it: in every case the parts add up to the number.
+__device__ __forceinline__ uint16_t split_part(float& v) {
+  uint16_t part = f32_to_bf16(v);
+  if ((part & 0x7fffu) == 0x7f80u && fabsf(v) < __builtin_inff()) part = (uint16_t)(__float_as_uint(v) >> 16);
+  v = (part & 0x7f80u) == 0x7f80u ? 0.f : v - bf16_to_f32(part);
+  return part;
+}
 __device__ __forceinline__ void pack_weights_f32_block(const PackBatch& pb, int layer, int block, int C, int F,
                                                        int total_frags) {
   const int t = block * 256 + (int)threadIdx.x;
@@ -217,9 +225,7 @@ __device__ __forceinline__ void pack_weights_f32_block(const PackBatch& pb, int 
     uint32_t u[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const uint16_t a = f32_to_bf16(v[2 * j]), b = f32_to_bf16(v[2 * j + 1]);
-      v[2 * j] -= bf16_to_f32(a);
-      v[2 * j + 1] -= bf16_to_f32(b);
+      const uint16_t a = split_part(v[2 * j]), b = split_part(v[2 * j + 1]);
       u[j] = (uint32_t)a | ((uint32_t)b << 16);
     }
     pb.out[layer][(size_t)(frag * 3 + part) * 64 + lane] = make_uint4(u[0], u[1], u[2], u[3]);
