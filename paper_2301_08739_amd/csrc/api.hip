@@ -27,7 +27,12 @@ bool overlaps(const void* a, size_t an, const void* b, size_t bn) {
   const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
   return x < y + bn && y < x + an;
 }
-bool is_16bit(int dtype) { return dtype == FF_BF16 || dtype == FF_F16; }  // the types with a fused matrix-core kernel
+bool is_16bit(int dtype) { return dtype == FF_BF16 || dtype == FF_F16; }
+// Does this call run on a fused matrix-core kernel (layer_mfma.hip, layer_f32.hip)?
+bool takes_fused_path(const ff_layer_weights* w, int64_t n, int G, int dtype, uint32_t flags) {
+  if (flags & FF_FLAG_FORCE_GENERIC) return false;
+  return is_16bit(dtype) ? layer_mfma_supported(w, G) : layer_f32_supported(w, G) && layer_f32_pays(w, G, n);
+}
 
 }  // namespace
 
@@ -156,7 +161,7 @@ size_t ff_group_attention_workspace_bytes(int64_t n, int G, const ff_layer_weigh
     const size_t p = align_up(layer_mfma_packed_bytes(w), 256);
     if (p > b) b = p;
   }
-  if (dtype == FF_F32 && layer_f32_supported(w, G)) {
+  if (dtype == FF_F32 && takes_fused_path(w, n, G, dtype, 0)) {
     const size_t p = align_up(layer_f32_packed_bytes(w), 256);
     if (p > b) b = p;
   }
@@ -166,12 +171,6 @@ size_t ff_group_attention_workspace_bytes(int64_t n, int G, const ff_layer_weigh
 }  // extern "C"
 
 namespace {
-// Does this call run on a fused matrix-core kernel (layer_mfma.hip, layer_f32.hip)?
-bool takes_fused_path(const ff_layer_weights* w, int G, int dtype, uint32_t flags) {
-  if (flags & FF_FLAG_FORCE_GENERIC) return false;
-  return is_16bit(dtype) ? layer_mfma_supported(w, G) : layer_f32_supported(w, G);
-}
-
 // ff_group_attention plus the internal options of the fused kernels that ff_fwa_block uses to hand
 // features from layer to layer in sorted order (see layer_mfma_launch); they need the fused path.
 int group_attention(const void* feats, void* out, int64_t n, const int32_t* perm,
@@ -196,7 +195,7 @@ int group_attention(const void* feats, void* out, int64_t n, const int32_t* perm
   if (drop && n > 0 && max_groups == 0)  // no group can exist: every row skips the layer
     return rows_copy_ungrouped_launch(feats, out, n, perm, group_offsets, num_groups, 0, w->C, G, dtype, out_f32,
                                       (hipStream_t)stream);
-  if (takes_fused_path(w, G, dtype, flags)) {
+  if (takes_fused_path(w, n, G, dtype, flags)) {
     if (n == 0 || max_groups == 0) return FF_OK;
     if (dtype == FF_F32) {
       if (!packed_f32) {
@@ -251,7 +250,7 @@ int ff_group_attention_path(const ff_layer_weights* w, int G, int dtype, uint32_
   if (st != FF_OK) return st;
   if (G < 1) return FF_ERR_ARG;
   if (G > 1024) return FF_ERR_UNSUPPORTED;
-  return is_16bit(dtype) && takes_fused_path(w, G, dtype, flags) ? FF_PATH_FUSED : FF_PATH_PLAIN;
+  return is_16bit(dtype) && takes_fused_path(w, 0, G, dtype, flags) ? FF_PATH_FUSED : FF_PATH_PLAIN;
 }
 
 int ff_gather(const void* src, void* dst, const int32_t* perm, int64_t n, int C, int dtype, void* stream) {
@@ -315,7 +314,7 @@ static int make_block_plan(int64_t n, const ff_geom* g, const FlattenZ* z, int G
   p->off_flat = off;  off += align_up(p->flat_bytes, 256);
   p->off_perm = off;  off += p->sorts * align_up((size_t)n * 4, 256);
   p->chain = num_layers > 1;
-  for (int l = 0; l < num_layers; ++l) p->chain = p->chain && takes_fused_path(&layers[l], G, dtype, 0);
+  for (int l = 0; l < num_layers; ++l) p->chain = p->chain && takes_fused_path(&layers[l], n, G, dtype, 0);
   p->off_inv = off;   off += (p->chain ? p->sorts : 0) * align_up((size_t)n * 4, 256);
   p->off_goff = off;  off += p->sorts * align_up((size_t)(p->max_groups + 1) * 4, 256);
   p->off_ng = off;    off += 256;
@@ -325,7 +324,7 @@ static int make_block_plan(int64_t n, const ff_geom* g, const FlattenZ* z, int G
   // One batched packing launch for the whole stack when every layer has the same packable shape
   // and the caller did not pre-pack.
   p->packed_stride = 0;
-  if (takes_fused_path(&layers[0], G, dtype, 0)) {
+  if (takes_fused_path(&layers[0], n, G, dtype, 0)) {
     bool same = true;
     for (int l = 0; l < num_layers; ++l)
       same = same && layers[l].F == layers[0].F && layers[l].heads == layers[0].heads &&

@@ -150,6 +150,7 @@ struct LayerF32 {
   int in_sorted;             // 0, or non-zero: row p of feats is the pillar at sorted position p
 };
 bool layer_f32_supported(const ff_layer_weights* w, int G);
+bool layer_f32_pays(const ff_layer_weights* w, int G, int64_t n);  // of a supported shape: is it the faster way for n rows
 size_t layer_f32_packed_bytes(const ff_layer_weights* w);
 int layer_f32_pack(const ff_layer_weights* w, void* packed, hipStream_t stream);
 int layer_f32_launch(const LayerF32& c, hipStream_t stream);

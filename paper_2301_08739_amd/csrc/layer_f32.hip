@@ -767,6 +767,21 @@ bool layer_f32_supported(const ff_layer_weights* w, int G) {
   return ((C == 128 && F == 256) || (C == 64 && F == 128)) && d == 16 && G <= 128;
 }
 
+// Groups beyond 64 members take three or four row blocks and with them a wavefront per SIMD: a launch lasts as long as one
+// such workgroup however few there are (C = 64: 53 and 77 us, C = 128: 77 and 108 us), while the plain kernels' time grows
+// with the rows.  Below the lines here they are ahead.  Measured, us a call of fused / plain, G = 69 and 96, 100 and 128:
+//   C = 64   3,000 rows 54 / 45   53 / 54   77 / 55    77 / 63      C = 128   1,000 rows 77 / 53   77 / 62   109 / 63   109 / 71
+//            4,500      54 / 53   53 / 60   78 / 63    77 / 71                2,000      78 / 65   77 / 73   109 / 75   108 / 83
+//            6,000      54 / 56   53 / 64   78 / 67    77 / 74                3,000      77 / 80   77 / 87   109 / 89   108 / 97
+//            8,300      54 / 83   54 / 89   78 / 93    77 / 101               4,500      77 / 111  77 / 116  110 / 119  109 / 128
+// Blocks of four layers (the weights split beside the sort) turn at about nine tenths of these rows.
+bool layer_f32_pays(const ff_layer_weights* w, int G, int64_t n) {
+  if (G <= 64) return true;
+  const bool three = G <= 96;
+  const int beyond = G - (three ? 65 : 97);
+  return w->C == 64 ? n >= (three ? 5120 : 8448) - 70 * beyond : n >= (three ? 2944 : 4096) - 18 * beyond;
+}
+
 size_t layer_f32_packed_bytes(const ff_layer_weights* w) { return (size_t)pack_frag_count_f32(w->C, w->F) * 3072; }
 
 int layer_f32_pack(const ff_layer_weights* w, void* packed, hipStream_t stream) {

@@ -48,9 +48,9 @@ def test_fused_fp32_layer(cfg, C, G, n):
     assert n % G == n or np.abs(np.delete(got - want, tail, axis=0)).max() <= 1e-4
 
 
-@pytest.mark.parametrize("C,G,n", [(64, 7, 12007), (64, 32, 9001), (64, 64, 9001), (64, 90, 9001), (64, 128, 9001),
-                                   (128, 9, 12007), (128, 64, 9001), (128, 69, 9001), (128, 128, 9001), (256, 31, 9001),
-                                   (256, 64, 9001)])
+@pytest.mark.parametrize("C,G,n", [(64, 7, 12007), (64, 32, 9001), (64, 64, 9001), (64, 65, 9001), (64, 96, 9001),
+                                   (64, 97, 9001), (64, 128, 9001), (128, 9, 12007), (128, 64, 9001), (128, 69, 9001),
+                                   (128, 97, 9001), (128, 128, 9001), (256, 31, 9001), (256, 64, 9001)])
 def test_fused_fp32_error_is_not_above_the_plain_kernels(C, G, n):
     """Two frames, the second starting at no multiple of G behind a short group, both workgroup shapes for small groups:
     neither the mean nor the largest error against float64 exceeds that of the plain fp32 kernels, with and without an
@@ -77,6 +77,13 @@ def test_fused_fp32_error_is_not_above_the_plain_kernels(C, G, n):
         print(f"C={C} G={G} embed={embed is not None}: fused max {fused.max():.2e} mean {fused.mean():.2e}, plain max "
               f"{plain.max():.2e} mean {plain.mean():.2e}", flush=True)
         assert fused.max() <= plain.max() and fused.mean() <= plain.mean()
+    # dropped tails: rows of the short groups stay as they are, the others do not change by it
+    dperm, doff, dng, _ = ff.ff_flatten(torch.from_numpy(coords).to(DEV), ff.Geometry(2, grid, grid, 9, 9), 0, 1, G,
+                                        ff.FF_TAIL_DROP)
+    got = to_host(ff.ff_group_attention(x, dperm, doff, dng, n // G, lw, G, ff.FF_F32, ff.FF_FLAG_TAIL_DROP))
+    short = np.concatenate([perm[off[g]:off[g + 1]] for g in range(ng) if off[g + 1] - off[g] < G] + [perm[:0]])
+    assert len(short) == cut % G + (n - cut) % G and np.array_equal(got[short], feats[short])
+    assert np.abs(np.delete(got - oracle.layer(feats, perm, off, p), short, axis=0)).max() <= 1e-4
 
 
 @pytest.mark.parametrize("shift", [-7.0, -100.0, -1e6])
@@ -96,3 +103,23 @@ def test_fused_fp32_gelu_far_below_zero(cfg, shift):
     print(f"shift {shift}: fused max {fused.max():.2e} mean {fused.mean():.2e}, plain max {plain.max():.2e} mean "
           f"{plain.mean():.2e}", flush=True)
     assert fused.max() <= plain.max() and fused.mean() <= plain.mean()
+
+
+@pytest.mark.parametrize("C,G,n", [(64, 69, 4096), (64, 128, 6000), (128, 69, 2800), (128, 128, 3500)])
+def test_few_rows_in_large_groups_run_the_plain_kernels(cfg, C, G, n):
+    """Below the line where the fused kernel pays, a call and a block give the plain kernels' results bit for bit."""
+    c = cfg(2, 1)
+    coords = torch.from_numpy(np.ascontiguousarray(c["coords"][:n])).to(DEV)
+    g = geoms(c)[0]
+    layers = [ff.LayerWeights(ffsynth.layer_params(C, 2 * C, HEADS[C], seed=50 + i), ff.FF_F32, DEV) for i in range(2)]
+    x = to_dev_feats(np.random.default_rng(2).standard_normal((n, C)), ff.FF_F32)
+
+    def calls(flags):
+        cur = x
+        for i, lw in enumerate(layers):
+            perm, goff, ng, _ = ff.ff_flatten(coords, g, i, 0, G)
+            cur = ff.ff_group_attention(cur, perm, goff, ng, -(-n // G), lw, G, ff.FF_F32, flags)
+        return cur
+    want = calls(ff.FF_FLAG_FORCE_GENERIC)
+    assert torch.equal(calls(0), want)
+    assert torch.equal(ff.ff_fwa_block(coords, g, G, layers, ff.FF_F32, x), want)
