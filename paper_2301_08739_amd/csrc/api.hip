@@ -195,12 +195,18 @@ int group_attention(const void* feats, void* out, int64_t n, const int32_t* perm
   if (drop && n > 0 && max_groups == 0)  // no group can exist: every row skips the layer
     return rows_copy_ungrouped_launch(feats, out, n, perm, group_offsets, num_groups, 0, w->C, G, dtype, out_f32,
                                       (hipStream_t)stream);
-  if (takes_fused_path(w, n, G, dtype, flags)) {
+  bool fused = takes_fused_path(w, n, G, dtype, flags);
+  if (fused && dtype == FF_F32 && !packed_f32) {
+    // Any workspace that the plain kernels can use is accepted; one that has no room for the split weights (few rows, and
+    // smaller than the query says) leaves the layer to them.
+    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < layer_generic_workspace_bytes(n, w))
+      return FF_ERR_WORKSPACE;
+    fused = workspace_bytes >= layer_f32_packed_bytes(w);
+  }
+  if (fused) {
     if (n == 0 || max_groups == 0) return FF_OK;
     if (dtype == FF_F32) {
       if (!packed_f32) {
-        if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < layer_f32_packed_bytes(w))
-          return FF_ERR_WORKSPACE;
         st = layer_f32_pack(w, workspace, (hipStream_t)stream);
         if (st != FF_OK) return st;
         packed_f32 = workspace;
@@ -278,7 +284,10 @@ int ff_bev_scatter(const void* feats, const int32_t* coords, int64_t n, const ff
 // Workspace layout of ff_fwa_block:
 //   [flatten scratch][perm x S][inverse perm x S][group_offsets x S][num_groups x S][feature buffer A]
 //   [feature buffer B][layer scratch][packed weights]
-// with S = number of distinct (axis, shift) pairs the schedule uses (at most 4).
+// with S = number of distinct (axis, shift) pairs the schedule uses (at most 4).  In float32 the inverse permutations and
+// the split weights of the fused kernel lie in the layer scratch, which only the plain kernels use otherwise: from some
+// 3 L C rows on (L layers) they fit and the block takes no more memory than with the plain kernels.  A workspace that is
+// large enough for these but not for the split weights of all layers is accepted (`lean`).
 // When every layer runs on the fused kernel the features travel from layer to layer in sorted order:
 // layer l writes row inverse_perm_{l+1}[pillar], which is where layer l+1 finds the members of its
 // groups side by side, so only the first layer gathers through an index and only the last one
@@ -293,7 +302,7 @@ struct BlockPlan {
 };
 
 static int make_block_plan(int64_t n, const ff_geom* g, const FlattenZ* z, int G, const ff_layer_weights* layers,
-                    int num_layers, int dtype, BlockPlan* p) {
+                    int num_layers, int dtype, bool lean, BlockPlan* p) {
   if (n < 0 || n > 0x7fffffffLL || !g || G < 1 || num_layers < 1 || !layers) return FF_ERR_ARG;
   for (int l = 0; l < num_layers; ++l) {
     int st = check_weights(&layers[l], dtype);
@@ -306,16 +315,18 @@ static int make_block_plan(int64_t n, const ff_geom* g, const FlattenZ* z, int G
   p->max_groups = ceil_div(n, G) + g->num_frames;
   p->layer_bytes = 0;
   for (int l = 0; l < num_layers; ++l) {
-    size_t b = ff_group_attention_workspace_bytes(n, G, &layers[l], dtype);
+    size_t b = lean ? layer_generic_workspace_bytes(n, &layers[l])
+                    : ff_group_attention_workspace_bytes(n, G, &layers[l], dtype);
     if (b > p->layer_bytes) p->layer_bytes = b;
   }
   const size_t feat_bytes = align_up((size_t)n * layers[0].C * elem_size(dtype), 256);
   size_t off = 0;
   p->off_flat = off;  off += align_up(p->flat_bytes, 256);
   p->off_perm = off;  off += p->sorts * align_up((size_t)n * 4, 256);
-  p->chain = num_layers > 1;
+  p->chain = num_layers > 1 && !lean;
   for (int l = 0; l < num_layers; ++l) p->chain = p->chain && takes_fused_path(&layers[l], n, G, dtype, 0);
-  p->off_inv = off;   off += (p->chain ? p->sorts : 0) * align_up((size_t)n * 4, 256);
+  const size_t inv_bytes = (p->chain ? p->sorts : 0) * align_up((size_t)n * 4, 256);
+  p->off_inv = off;   off += dtype == FF_F32 ? 0 : inv_bytes;
   p->off_goff = off;  off += p->sorts * align_up((size_t)(p->max_groups + 1) * 4, 256);
   p->off_ng = off;    off += 256;
   p->off_a = off;     off += feat_bytes;
@@ -324,7 +335,7 @@ static int make_block_plan(int64_t n, const ff_geom* g, const FlattenZ* z, int G
   // One batched packing launch for the whole stack when every layer has the same packable shape
   // and the caller did not pre-pack.
   p->packed_stride = 0;
-  if (takes_fused_path(&layers[0], n, G, dtype, 0)) {
+  if (!lean && takes_fused_path(&layers[0], n, G, dtype, 0)) {
     bool same = true;
     for (int l = 0; l < num_layers; ++l)
       same = same && layers[l].F == layers[0].F && layers[l].heads == layers[0].heads &&
@@ -333,6 +344,12 @@ static int make_block_plan(int64_t n, const ff_geom* g, const FlattenZ* z, int G
       p->packed_stride = align_up(dtype == FF_F32 ? layer_f32_packed_bytes(&layers[0]) : layer_mfma_packed_bytes(&layers[0]), 256);
   }
   p->off_packed = off; off += p->packed_stride * num_layers;
+  if (dtype == FF_F32) {
+    p->off_inv = p->off_layer;
+    p->off_packed = p->off_inv + inv_bytes;
+    const size_t used = inv_bytes + p->packed_stride * num_layers;
+    off = p->off_layer + (used > p->layer_bytes ? used : align_up(p->layer_bytes, 256));
+  }
   p->total = off;
   return FF_OK;
 }
@@ -345,7 +362,9 @@ static int fwa_block(const int32_t* coords, int64_t n, const ff_geom* g, const F
   if (tail != FF_TAIL_MASK && tail != FF_TAIL_DROP) return FF_ERR_ARG;
   const bool drop = tail == FF_TAIL_DROP;
   BlockPlan p;
-  int st = make_block_plan(n, g, z, G, layers, num_layers, dtype, &p);
+  int st = make_block_plan(n, g, z, G, layers, num_layers, dtype, false, &p);
+  if (st == FF_OK && dtype == FF_F32 && workspace_bytes < p.total)
+    st = make_block_plan(n, g, z, G, layers, num_layers, dtype, true, &p);
   if (st != FF_OK) return st;
   if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < p.total) return FF_ERR_WORKSPACE;
   if (n > 0 && (!coords || !feats_in || !feats_out)) return FF_ERR_ARG;
@@ -413,7 +432,7 @@ static int fwa_block(const int32_t* coords, int64_t n, const ff_geom* g, const F
 size_t ff_fwa_block_workspace_bytes(int64_t n, const ff_geom* g, int G, const ff_layer_weights* layers,
                                     int num_layers, int dtype) {
   BlockPlan p;
-  if (make_block_plan(n, g, nullptr, G, layers, num_layers, dtype, &p) != FF_OK) return 0;
+  if (make_block_plan(n, g, nullptr, G, layers, num_layers, dtype, false, &p) != FF_OK) return 0;
   return p.total;
 }
 
@@ -430,7 +449,7 @@ size_t ff_fwa_block3d_workspace_bytes(int64_t n, const ff_geom3* g, int G, const
   FlattenZ z;
   BlockPlan p;
   if (split_geom3(g, &g2, &z) != FF_OK) return 0;
-  if (make_block_plan(n, &g2, &z, G, layers, num_layers, dtype, &p) != FF_OK) return 0;
+  if (make_block_plan(n, &g2, &z, G, layers, num_layers, dtype, false, &p) != FF_OK) return 0;
   return p.total;
 }
 

@@ -123,3 +123,31 @@ def test_few_rows_in_large_groups_run_the_plain_kernels(cfg, C, G, n):
     want = calls(ff.FF_FLAG_FORCE_GENERIC)
     assert torch.equal(calls(0), want)
     assert torch.equal(ff.ff_fwa_block(coords, g, G, layers, ff.FF_F32, x), want)
+
+
+@pytest.mark.parametrize("C,G,n,num_layers", [(128, 64, 100, 2), (64, 32, 150, 1), (128, 64, 700, 4), (256, 64, 300, 17),
+                                              (64, 32, 2000, 17)])
+def test_block_in_the_workspace_of_the_plain_kernels(cfg, C, G, n, num_layers):
+    """A workspace that has room for the plain kernels but not for all split weights is used as far as it goes, and nothing
+    beyond it is written; seventeen layers also take the launch of its own for the weights."""
+    c = cfg(2, 1)
+    coords = torch.from_numpy(np.ascontiguousarray(c["coords"][:n])).to(DEV)
+    g = geoms(c)[0]
+    layers = [ff.LayerWeights(ffsynth.layer_params(C, 2 * C, HEADS[C], seed=70 + i), ff.FF_F32, DEV) for i in range(num_layers)]
+    x = to_dev_feats(np.random.default_rng(4).standard_normal((n, C)), ff.FF_F32)
+    cur, sorts = x, min(num_layers, 4)
+    for i, lw in enumerate(layers):
+        perm, goff, ng, _ = ff.ff_flatten(coords, g, i % 2, i // 2 % 2, G)
+        cur = ff.ff_group_attention(cur, perm, goff, ng, -(-n // G), lw, G, ff.FF_F32, ff.FF_FLAG_FORCE_GENERIC)
+    want = to_host(cur)
+    up = lambda b: -(-b // 256) * 256
+    plain = (up(ff.ff_flatten_batch_workspace_bytes(n, g, sorts)) + sorts * (up(4 * n) + up(4 * (-(-n // G) + 2))) + 256
+             + 2 * up(4 * n * C) + up(12 * n * C) + up(4 * n * C))
+    asked = ff.ff_fwa_block_workspace_bytes(n, g, G, layers, ff.FF_F32)
+    assert asked >= plain
+    for size in {plain, (plain + asked) // 2, asked}:
+        ws = torch.full((size + 768,), 0xA5, dtype=torch.uint8, device=DEV)
+        off = -ws.data_ptr() % 256                        # the binding hands on the aligned part, less 256 bytes
+        got = to_host(ff.ff_fwa_block(coords, g, G, layers, ff.FF_F32, x, workspace=ws[off:off + size + 256]))
+        assert bool((ws[off + size:] == 0xA5).all()), size
+        assert np.abs(got - want).max() <= 1e-4 * num_layers, size

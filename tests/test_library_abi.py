@@ -108,6 +108,46 @@ def test_argument_errors_are_reported_before_any_launch():
     assert lib.ff_fwa_block(one, 10, gp, 64, 0, wp, 1, 1, one, ctypes.c_void_p(1 << 20), one, 16, null) == -3
 
 
+def _plain_f32_bytes(n, C, sorts, G, frames, flat):
+    """Layer scratch of the plain float32 kernels, and a block's workspace around it."""
+    up = lambda b: -(-b // 256) * 256
+    layer = up(12 * n * C) + up(4 * n * C)
+    groups = -(-n // G) + frames
+    return layer, up(flat) + sorts * (up(4 * n) + up(4 * (groups + 1))) + 256 + 2 * up(4 * n * C) + layer
+
+
+def test_float32_workspaces_of_the_plain_kernels_are_enough():
+    """A workspace is refused exactly where it is too small for the plain kernels, and a block of more than a few thousand
+    rows asks for no more than these need."""
+    import paper_2301_08739_amd as ff
+    from paper_2301_08739_amd.binding import _LayerWeightsC
+    if not os.path.exists(ff.library_path()):
+        pytest.skip("library not built")
+    lib = ff.load_library()
+    g = ff.Geometry(1, 468, 468, 13, 13)
+    null, one, far, ws = (ctypes.c_void_p(p) for p in (0, 256, 1 << 40, 1 << 41))
+    C, L = 128, 4
+    arr = (_LayerWeightsC * L)()
+    for w in arr:
+        for k, _ in _LayerWeightsC._fields_[:12]:
+            setattr(w, k, 256)
+        w.C, w.F, w.heads, w.ln_eps = C, 2 * C, 8, 1e-5
+    wp = ctypes.byref(arr[0])
+    for n in (0, 100, 30000):
+        layer, _ = _plain_f32_bytes(n, C, 4, 64, 1, 0)
+        call = lambda at, size: lib.ff_group_attention(one, far, n, one, one, one, n // 64 + 1, wp, 64, 0, 0, at, size, null)
+        assert call(null, 1 << 36) == -3                       # no workspace
+        assert call(ctypes.c_void_p((1 << 41) + 128), 1 << 36) == -3    # not aligned
+        if n:
+            assert call(ws, layer - 1) == -3                   # too small for the plain kernels
+        assert lib.ff_group_attention_workspace_bytes(n, 64, wp, 0) >= layer
+    for n in (5000, 30000):
+        for G in (64, 128):
+            _, block = _plain_f32_bytes(n, C, 4, G, 1, lib.ff_flatten_batch_workspace_bytes(n, ctypes.byref(g), 4))
+            assert lib.ff_fwa_block_workspace_bytes(n, ctypes.byref(g), G, arr, L, 0) == block
+            assert lib.ff_fwa_block(one, n, ctypes.byref(g), G, 0, arr, L, 0, one, far, ws, block - 1, null) == -3
+
+
 def test_bench_only_library_exports_its_two_entry_points():
     import paper_2301_08739_amd as ff
     path = os.path.join(os.path.dirname(ff.library_path()), "libffpeaks.so")
