@@ -220,9 +220,12 @@ size_t ff_group_attention_workspace_bytes(int64_t n, int G, const ff_layer_weigh
  * such row of `out` receives the row of `feats` (converted when the storage types differ), which
  * is what skipping the layer means for a residual layer; max_groups may then be as small as
  * floor(n/G), and 0 copies everything.
- * dtype FF_F32: fp32 arithmetic throughout (the fused fp32 kernel, for the fused shapes below with G <= 128, C = 256: G <= 64,
- * multiplies numbers split exactly into three bfloat16 parts and sums in fp32: fp32 precision).  FF_BF16 / FF_F16: 16-bit storage, matrix-core operands
- * of that type, fp32 accumulation, statistics, softmax and GELU.
+ * dtype FF_F32: fp32 arithmetic throughout.  The fused shapes below (G <= 128, C = 256: G <= 64; beyond G = 64 from a few
+ * thousand rows on) run on one fused kernel that multiplies numbers split exactly into three bfloat16 parts and sums in
+ * fp32; its results are no further from exact ones than the plain kernels', and infinities and NaNs come out as there.
+ * It splits the weights into the workspace on every call (one small extra launch; there is no pre-packed form) where
+ * the workspace has room for that, which ff_group_attention_workspace_bytes sees to.  FF_BF16 / FF_F16: 16-bit storage,
+ * matrix-core operands of that type, fp32 accumulation, statistics, softmax and GELU.
  * Limits (FF_ERR_UNSUPPORTED otherwise): C % heads == 0, C*sizeof(dtype) % 16 == 0, 1 <= G <= 1024. */
 int ff_group_attention(const void* feats, void* out, int64_t n,
                        const int32_t* perm, const int32_t* group_offsets,
@@ -230,11 +233,12 @@ int ff_group_attention(const void* feats, void* out, int64_t n,
                        const ff_layer_weights* w, int G, int dtype, uint32_t flags,
                        void* workspace, size_t workspace_bytes, void* stream);
 
-/* Which kernels a call of ff_group_attention with these weights, group size, dtype and flags would run
- * (host-side, launches nothing): FF_PATH_FUSED, the single matrix-core kernel (16-bit dtypes; shapes
- * (C, head dim, F) = (128, 16, 256), (256, 32, 512) and (64, 16, 128) with G <= 128), or FF_PATH_PLAIN, the
- * fp32-arithmetic kernels that serve every other shape, FF_F32 (where a fused fp32 kernel exists for the same shapes,
- * see ff_group_attention) and FF_FLAG_FORCE_GENERIC, at a fraction of the speed.  A negative value is the ff_status the call itself would return for these arguments. */
+/* Which arithmetic a call of ff_group_attention with these weights, group size, dtype and flags would run on
+ * (host-side, launches nothing): FF_PATH_FUSED, 16-bit matrix-core operands in one kernel (16-bit dtypes; shapes
+ * (C, head dim, F) = (128, 16, 256), (256, 32, 512) and (64, 16, 128) with G <= 128), or FF_PATH_PLAIN, fp32
+ * arithmetic: for a 16-bit dtype that means the plain kernels, at a fraction of the speed; FF_F32 always answers so,
+ * also where its fused kernel runs (see ff_group_attention), which depends on n as well.  A negative value is the
+ * ff_status the call itself would return for these arguments. */
 #define FF_PATH_PLAIN 0
 #define FF_PATH_FUSED 1
 int ff_group_attention_path(const ff_layer_weights* w, int G, int dtype, uint32_t flags);

@@ -237,7 +237,8 @@ FF_PATH_PLAIN, FF_PATH_FUSED = 0, 1
 
 
 def ff_group_attention_path(weights, G, dtype, flags=0):
-    """FF_PATH_FUSED or FF_PATH_PLAIN: the kernels ff_group_attention would run for these arguments."""
+    """FF_PATH_FUSED (16-bit matrix-core operands) or FF_PATH_PLAIN (fp32 arithmetic, always so for FF_F32): what
+    ff_group_attention would run on for these arguments."""
     s = weights.struct()
     st = load_library().ff_group_attention_path(C.byref(s), int(G), int(dtype), int(flags))
     if st < 0:
