@@ -794,9 +794,14 @@ int layer_f32_pack(const ff_layer_weights* w, void* packed, hipStream_t stream) 
 int layer_f32_launch(const LayerF32& c, hipStream_t stream) {
   if (c.max_groups == 0 || c.n == 0) return FF_OK;
   const int G = c.G;
-  // G <= 32: a workgroup per group while that fills the chip better; two groups share the weight stream otherwise
-  // (it would be what bounds a launch of many: 3 KB per 192 cycles of products and wavefront).
-  const bool few = c.max_groups <= 512;
+  // G <= 32: a workgroup per group while all of them run at once (three wavefronts per SIMD on 256 compute units); two
+  // groups share the weight stream otherwise (it would be what bounds a launch of many: 3 KB per 192 cycles of products
+  // and wavefront).  Measured, G = 32, us a call with one group / two groups per workgroup:
+  //   C = 64    512 groups 22 / 25   768 23 / 34   1,024 24 / 34   1,536 32 / 37   2,048 46 / 51   6,000 117 / 111
+  //   C = 128   400 groups 33 / 34   600 45 / 52     768 51 / 52     850 61 / 53   1,536 93 / 84   6,000 339 / 307
+  // C = 256 has the form with two groups only.
+  const bool few = c.max_groups <= 256 * 12 * 32 / c.w->C;
+  // (Three wavefronts per SIMD have to be asked for: the direct form alone would take two registers too many.)
   switch (c.w->C) {
     case 64:
       if (G <= 32 && few) return launch_cfg<64, 16, 128, 1, 1, 3>(c, stream);
