@@ -1,5 +1,6 @@
 """The fused float32 layer: every block count of rows, ragged groups, both workgroup shapes for small groups, dropped
-tails and positional embedding, against the oracle and no further from it than the plain kernels."""
+tails and positional embedding, against the oracle and no further from it than the plain kernels; where calls go to the
+plain kernels, and the workspaces they accept."""
 import numpy as np
 import pytest
 import torch
@@ -14,9 +15,10 @@ pytestmark = pytest.mark.gpu
 HEADS = {64: 4, 128: 8, 256: 8}
 
 
-@pytest.mark.parametrize("C,G,n", [(64, 1, 70), (64, 32, 1003), (64, 33, 1003), (64, 96, 1003), (64, 97, 1003),
-                                   (128, 31, 1003), (128, 32, 17003), (128, 64, 1024), (128, 64, 1003), (128, 65, 1003),
-                                   (128, 128, 1003), (256, 20, 1003), (256, 64, 1003), (256, 65, 500)])
+# (groups beyond 64 members: enough rows for the fused kernel, see test_few_rows_in_large_groups_run_the_plain_kernels)
+@pytest.mark.parametrize("C,G,n", [(64, 1, 70), (64, 32, 1003), (64, 33, 1003), (64, 96, 3003), (64, 97, 9003),
+                                   (128, 31, 1003), (128, 32, 17003), (128, 64, 1024), (128, 64, 1003), (128, 65, 3003),
+                                   (128, 128, 4003), (256, 20, 1003), (256, 64, 1003), (256, 65, 500)])
 def test_fused_fp32_layer(cfg, C, G, n):
     c = cfg(2, 1)
     coords = np.ascontiguousarray(c["coords"][:n])
