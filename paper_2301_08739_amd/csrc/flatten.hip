@@ -35,9 +35,10 @@ namespace {
 constexpr int kMaxSorts = 4;
 // Small clouds: tiles of 1024 words, up to 128 of them.  Inside a block the tiles of all its sorts count, because every
 // workgroup of a pass reads the tables of its sort: with four sorts and four layers behind them (C = 128, us, small path
-// against scanned tables) 30,000 words 93.5 / 95.3, 40,000 122 / 115, 80,000 216 / 202, 130,000 283 / 256.  A batch of
-// sorts by itself is bound by its launches, of which the scanned path has twice as many (50,000 words in two frames, four
-// sorts: 66 / 79), so it counts like a single sort (80,000 words 37 / 39, 120,000 46 / 48).
+// against scanned tables) 30,000 words 93.5 / 95.3, 40,000 122 / 115, 80,000 216 / 202, 130,000 283 / 256; two sorts and
+// layers 80,000 words 122 / 116, 120,000 153 / 141 (C = 64: 70,000 84.5 / 75.7); three 45,000 95.8 / 90.9, 100,000 203 /
+// 190.  A batch of sorts by itself is bound by its launches, of which the scanned path has twice as many (50,000 words in
+// two frames, four sorts: 66 / 79), so it counts like a single sort (80,000 words 37 / 39, 120,000 46 / 48).
 constexpr int kSmallKpt = 4, kSmallMaxTiles = 128;
 constexpr int kLargeKpt = 16;                       // larger clouds: tiles of 4096 words
 // In between, the tables are scanned by their own kernel as for larger clouds, but tiles of 4096 words

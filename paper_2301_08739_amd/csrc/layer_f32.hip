@@ -27,7 +27,7 @@
 //
 // What bounds it: the matrix pipe, about 37k cycles per wavefront at C = 128, G = 64, two wavefronts per SIMD (30k rows:
 // two groups on most compute units), and nearly as many issue cycles of GELU, exponentials, splits and LayerNorm beside
-// it.  Measured, 30,000 rows at C = 128, G = 64: 56 us a layer = 157 TFLOP/s (the plain kernels: 455 us); 2,000 rows at
+// it.  Measured, 30,000 rows at C = 128, G = 64: 57 us a layer = 155 TFLOP/s (the plain kernels: 455 us); 2,000 rows at
 // C = 64, G = 32: 13 us (31 us).
 #include "common.h"
 #include "pack_weights.h"
