@@ -207,9 +207,12 @@ __global__ __launch_bounds__(256) void k_seg_mean(const int32_t* __restrict__ pe
       };
       // Most pillars hold a few points: one point per lane then, where eight rounds of masked loads were issued before.
       // Eight in flight for the others: a pillar of several hundred points (a dense object, the cell under the sensor)
-      // is a chain of dependent round trips otherwise (sixteen were no faster).  180,000 points on 50,000 pillars: 17.1 ->
-      // 15.0-16.5 us; the same bits.
-      if (hi - lo <= 16) {
+      // is a chain of dependent round trips otherwise (sixteen were no faster).  The four pillars of a wavefront go the
+      // same way: with one of them long, the others' single round would come on top of its rounds.  The whole call, us,
+      // eight rounds for all / each pillar its own way / this: 180,000 points of 3, 4, 5 and 8 features 62 / 63 / 57, 60 /
+      // 53 / 53, 71 / 74 / 67, 67 / 60 / 60; 1.44 M of 3 and 5 155 / 157 / 148 and 191 / 187 / 177; 60,000 of 5 50 / 52 / 51.
+      // The same bits.
+      if (!__builtin_amdgcn_ballot_w64(hi - lo > 16)) {
         if (lo + sub < hi) add(lo + sub, std::integral_constant<int, 1>());
       } else {
         for (int q = lo + sub; q < hi; q += 16 * kPointsInFlight) add(q, std::integral_constant<int, kPointsInFlight>());
