@@ -1136,11 +1136,11 @@ int FF_LAYER_SYM(layer_mfma_launch)(const void* feats, void* out, int64_t n, con
       // G <= 32: four or eight groups per workgroup (1301 groups 14.8 / 13.2 us, 2602: 21.9 / 23.5, 9009: 63 / 56);
       // G <= 64: two or four (466 groups 12.1 / 13.5, 942: 16.6 / 14.4, 1302: 23.7 / 26.0, 3407: 54 / 51); G <= 80 and
       // <= 96: two of five or six wavefronts against one of eight (466 groups 18.8 -> 12.5 and 19.6 -> 13.7, 3400: 121
-      // -> 75 and 125 -> 84); above: one or two (466: 18.9 / 16.7, 627: 27.4 / 30.1, 3414: 123 / 104).
+      // -> 75 and 125 -> 84); above: one or two (466: 18.9 / 16.7, 627: 27.4 / 30.1, 1172: 44.6 / 44.9, 3414: 123 / 104).
       if (G <= 32) variant = rounds(4) * 70 <= rounds(8) * 118 ? 1 : 3;
       else if (G <= 64) variant = rounds(2) * 79 <= rounds(4) * 129 ? 2 : 8;
       else if (G <= 96) variant = rounds(1) == 1 ? 4 : G <= 80 ? 5 : 6;
-      else variant = rounds(1) * 90 <= rounds(2) * 148 ? 4 : 7;
+      else variant = rounds(1) * 90 <= rounds(2) * 151 ? 4 : 7;
     }
     switch (variant) {
       case 1: if (G <= 32) FF_GO(64, 16, 128, 1, 2, 8, 2); break;
