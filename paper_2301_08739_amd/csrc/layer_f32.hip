@@ -389,7 +389,7 @@ __device__ __forceinline__ bool layer_f32_rows(
   // to L2), the first one from the
   // caller; a block's rows are replaced as soon as its products are issued; `beside`: work of the vector units for every
   // step
-  auto product = [&](f32x16 (&acc)[PT], Split w0, auto weight, auto rows, int steps, bool swap, auto beside) {
+  auto product_on = [&](f32x16 (&acc)[PT], f32x16 (&lo)[PT], Split w0, auto weight, auto rows, int steps, bool swap, auto beside) {
     if constexpr (DIRECT) {
 #pragma unroll 1
       for (int k = 0; k < steps; ++k) {
@@ -408,13 +408,12 @@ __device__ __forceinline__ bool layer_f32_rows(
     }
     constexpr int DW = PT == 1 ? 5 : 3;
     Split w[DW], a[PT];
-    f32x16 lo[PT];
     w[0] = w0;
 #pragma unroll
     for (int d = 1; d < DW - 1; ++d)
       if (d < steps) w[d] = weight(d);
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) { a[pt] = rows(pt, 0); lo[pt] = kZero; }
+    for (int pt = 0; pt < PT; ++pt) a[pt] = rows(pt, 0);
 #pragma unroll
     for (int k = 0; k < steps; ++k) {
       fence();
@@ -431,6 +430,12 @@ __device__ __forceinline__ bool layer_f32_rows(
       beside(k);
     }
     fence();
+  };
+  auto product = [&](f32x16 (&acc)[PT], Split w0, auto weight, auto rows, int steps, bool swap, auto beside) {
+    f32x16 lo[PT];
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt) lo[pt] = kZero;
+    product_on(acc, lo, w0, weight, rows, steps, swap, beside);
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt) acc[pt] += lo[pt];
   };
@@ -638,22 +643,22 @@ __device__ __forceinline__ bool layer_f32_rows(
     asm volatile("" ::: "memory");         // (the second tile reads its operands again instead of keeping them in registers)
     product(acc[1], w1_at(1, 0), [&](int ks) { return w1_at(1, ks); }, row_frags, KS, false,
             [&](int k) { gelu_part(acc[0], k * PT * 16 / KS, (k + 1) * PT * 16 / KS); });
-    f32x16 y2[PT];
+    f32x16 y2[PT], y2lo[PT];               // both sums go on over the four units
     const f32x16 b2 = vec16(P_B2 + 32 * s);
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) y2[pt] = b2;
+    for (int pt = 0; pt < PT; ++pt) { y2[pt] = b2; y2lo[pt] = kZero; }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const Split w20 = w2_at(u, 0);
       if (u > 0) lds_barrier();            // the unit before has been read
       put_unit(acc[u / 2], u % 2);
       lds_barrier();
-      product(y2, w20, [&](int k) { return w2_at(u, k); }, h_frags, NS, false, [&](int k) {
+      product_on(y2, y2lo, w20, [&](int k) { return w2_at(u, k); }, h_frags, NS, false, [&](int k) {
         if (u < 2) gelu_part(acc[1], (u * NS + k) * PT * 8 / NS, (u * NS + k + 1) * PT * 8 / NS);
       });
     }
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) x1[pt] += y2[pt];
+    for (int pt = 0; pt < PT; ++pt) x1[pt] += y2[pt] + y2lo[pt];
   }
 
   uint32_t* const unfit = reinterpret_cast<uint32_t*>(stats);  // per wavefront: some result is no finite number
