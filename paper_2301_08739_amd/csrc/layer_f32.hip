@@ -181,7 +181,7 @@ struct Plan {
 // bfloat16, or for what becomes infinite on the way (a hidden unit), and inf * hi + inf * mid is no number where inf * x
 // is infinite.  Whatever of that happens in a row reaches all its results, as the products are dense and nothing on the
 // way turns it into a number again, so one look at the results finds it.  The workgroup then starts over in the direct
-// form, which gives infinities and NaNs where float32 arithmetic gives them.  The look takes a multiply-add per result.
+// form, which gives infinities and NaNs where float32 arithmetic gives them.  The look takes half an instruction per result.
 template <int C, int DH, int F, int PT, int GPW, bool PE, bool DIRECT>
 __device__ __forceinline__ bool layer_f32_rows(
     const float* __restrict__ feats, float* __restrict__ out, const float* __restrict__ pos_embed,
@@ -663,14 +663,14 @@ __device__ __forceinline__ bool layer_f32_rows(
 
   uint32_t* const unfit = reinterpret_cast<uint32_t*>(stats);  // per wavefront: some result is no finite number
   if constexpr (!DIRECT) {
-    float z[4] = {0.f, 0.f, 0.f, 0.f};     // 0 x is 0 for a finite x and no number otherwise
+    float z[2] = {0.f, 0.f};               // largest magnitude, NaN where there is one
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt)
       if (m[pt / PTG] > 0) {               // (a group past the last one divides by its empty row sums)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) z[r % 4] = fmaf(x1[pt][r], 0.f, z[r % 4]);
+        for (int r = 0; r < 16; ++r) z[r / 2 % 2] = __builtin_elementwise_maximum(z[r / 2 % 2], fabsf(x1[pt][r]));
       }
-    const uint64_t any = __builtin_amdgcn_ballot_w64((z[0] + z[1]) + (z[2] + z[3]) != 0.f);
+    const uint64_t any = __builtin_amdgcn_ballot_w64(!(__builtin_elementwise_maximum(z[0], z[1]) < __builtin_inff()));
     if (lane == 0) unfit[s] = any != 0;
   }
 
@@ -686,7 +686,17 @@ __device__ __forceinline__ bool layer_f32_rows(
       *reinterpret_cast<f32x4*>(ldsc + row * (C * 4) + ((p ^ (row & 15)) * 16)) = v;
     }
   lds_barrier();
-  if (!DIRECT && __builtin_amdgcn_ballot_w64(unfit[lane % NS] != 0)) return true;
+  const uint32_t over = DIRECT ? 0 : unfit[lane % NS];
+  f32x4 v[PT][4];                          // read beside the flags
+#pragma unroll
+  for (int t = 0; t < PT; ++t)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int row = (s * PT + t) * RPS + lr, p = lc + LPR * k;
+      v[t][k] = *reinterpret_cast<const f32x4*>(ldsc + row * (C * 4) + ((p ^ (row & 15)) * 16));
+    }
+  fence();
+  if (!DIRECT && __builtin_amdgcn_ballot_w64(over != 0)) return true;
 #pragma unroll
   for (int t = 0; t < PT; ++t) {
     const int row = (s * PT + t) * RPS + lr;
@@ -695,9 +705,8 @@ __device__ __forceinline__ bool layer_f32_rows(
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int p = lc + LPR * k;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(ldsc + row * (C * 4) + ((p ^ (row & 15)) * 16));
         // non-temporal: the next reader is another XCD, and the kernel's end has less to write back
-        __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(out + (size_t)orow[t] * C + p * 4));
+        __builtin_nontemporal_store(v[t][k], reinterpret_cast<f32x4*>(out + (size_t)orow[t] * C + p * 4));
       }
     }
   }
