@@ -135,6 +135,23 @@ int layer_mfma_launch_f16(const void* feats, void* out, int64_t n, const int32_t
                           bool out_f32, bool drop, const void* packed, int variant, const int32_t* out_index,
                           int in_sorted, hipStream_t stream);
 
+// Fused 16-bit layer whose wavefronts cut the features (layer_slice.hip); reads the packed weights of layer_mfma_pack
+struct LayerSlice {
+  const void* feats;
+  void* out;
+  int n;
+  const int32_t *perm, *group_offsets, *num_groups;
+  int32_t max_groups;
+  const ff_layer_weights* w;
+  int G;
+  bool drop, out_f32;
+  const void* packed;
+  const int32_t* out_index;  // as for layer_mfma_launch
+  int in_sorted;             // as for layer_mfma_launch
+};
+int layer_slice_launch(const LayerSlice& c, hipStream_t stream);
+int layer_slice_launch_f16(const LayerSlice& c, hipStream_t stream);
+
 // Fused float32 layer (layer_f32.hip)
 struct LayerF32 {
   const void* feats;

@@ -1,5 +1,5 @@
-// Group attention layer (paper Sec. 4.2.2, Eq. (2); Sec. 4.3 'Efficient MHSA' / 'Efficient FFN')
-// as ONE fused kernel on the bf16 matrix cores of gfx950:
+// Group attention layer (paper Sec. 4.2.2, Eq. (2); Sec. 4.3 'Efficient MHSA' / 'Efficient FFN') in 16-bit storage at 64
+// features as ONE fused kernel on the matrix cores of gfx950 (128 and 256 features: layer_slice.hip; this file chooses):
 //
 //   gather -> LN1 -> packed QKV projection -> per-head softmax(Q K^T / sqrt(d)) V -> out-proj
 //   + residual -> LN2 -> Linear + GELU -> Linear + residual -> scatter
@@ -18,69 +18,20 @@
 // exactly the A operand P*V needs.  LayerNorm statistics and the softmax need only a reduction
 // over the four lanes that share a pillar.
 //
-// Weights reach the matrix cores through LDS.  The packed stream is cut into 16 KB chunks that the
+// Weights reach the matrix cores through LDS.  The packed stream is cut into 8 KB chunks that the
 // workgroup copies asynchronously (global memory -> LDS, no registers) into a ring of as many slots
 // as the LDS holds; slots are refilled only at workgroup barriers (one per head-dim unit, where the
 // group's K and V are exchanged anyway, and a few in the FFN).  Every wavefront reads the fragments
 // in stream order through a window of 8 fragments in registers, requested 8 products ahead of
 // their use, so that LDS latency is hidden behind the matrix cores.
 #include "common.h"
+#include "elem16.h"
 #include "pack_weights.h"
 #include <atomic>
 
 namespace ff {
 namespace {
 
-// ---- number format of the 16-bit storage and of the matrix-core operands --------------------------------
-// This source builds the bfloat16 kernels; layer_mfma_f16.hip defines FF_LAYER_F16 and includes it
-// to build the IEEE half kernels (the precision the paper runs in, Sec. 5.1) from the same code.
-#ifdef FF_LAYER_F16
-typedef _Float16 el8 __attribute__((ext_vector_type(8)));
-typedef _Float16 el4 __attribute__((ext_vector_type(4)));
-typedef _Float16 el2 __attribute__((ext_vector_type(2)));
-constexpr uint32_t kOnePair = 0x3c003c00u;  // two ones
-__device__ __forceinline__ float el_to_f32(uint16_t h) { return (float)__builtin_bit_cast(_Float16, h); }
-__device__ __forceinline__ float el_lo(uint32_t u) { return el_to_f32((uint16_t)(u & 0xffffu)); }
-__device__ __forceinline__ float el_hi(uint32_t u) { return el_to_f32((uint16_t)(u >> 16)); }
-#define FF_LAYER_SYM(name) name##_f16
-#else
-typedef __bf16 el8 __attribute__((ext_vector_type(8)));
-typedef short el4 __attribute__((ext_vector_type(4)));
-typedef __bf16 el2 __attribute__((ext_vector_type(2)));
-constexpr uint32_t kOnePair = 0x3f803f80u;  // two ones
-__device__ __forceinline__ float el_to_f32(uint16_t h) { return bf16_to_f32(h); }
-__device__ __forceinline__ float el_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ __forceinline__ float el_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
-#define FF_LAYER_SYM(name) name
-#endif
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-union Frag8 {  // eight 16-bit elements = one operand of the k=32 product
-  el8 v;
-  uint32_t u[4];
-  u32x4 q;
-};
-union Frag4 {  // four 16-bit elements = one operand of the k=16 product
-  el4 v;
-  uint32_t u[2];
-  u32x2 d;
-};
-
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
-  f32x2 f = {lo, hi};
-  el2 r = __builtin_convertvector(f, el2);  // round to nearest even
-  return *reinterpret_cast<uint32_t*>(&r);
-}
-__device__ __forceinline__ void load4(const uint16_t* p, float* o) {  // 4 consecutive elements -> fp32
-  const uint2 u = *reinterpret_cast<const uint2*>(p);
-  o[0] = el_lo(u.x);
-  o[1] = el_hi(u.x);
-  o[2] = el_lo(u.y);
-  o[3] = el_hi(u.y);
-}
 // Reductions over the 4 lanes that share a pillar (lane, lane^16, lane^32, lane^48), on the
 // vector ALU: v_permlane16_swap / v_permlane32_swap with both operands equal to v return the
 // pair (v from the even half, v from the odd half) in every lane.
@@ -115,20 +66,6 @@ __device__ __forceinline__ f32x4 mfma16_from_zero(const Frag4& a, const Frag4& b
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.v, b.v, z, 0, 0, 0);
 #endif
 }
-// GELU(v) = v * Phi(v) with the upper tail 1 - Phi(t) ~ 0.5 * exp(-(a t + b t^2 + c t^3)), t = |v|
-// (coefficients fitted to the erf form; all positive, so the exponent is monotone for any t):
-//   GELU(v) = max(v, 0) - 0.5 t e = 0.5 (v + t (1 - e)),   e = exp(-(a t + b t^2 + c t^3)),
-// max abs error 8.6e-5.  This returns 2 GELU(v); the factor 0.5 is folded into the packed W2
-// (exact in bf16).  Five vector operations and one transcendental per element.
-__device__ __forceinline__ float gelu2_fast(float v) {
-  constexpr float L2E = 1.44269504088896340736f;
-  const float t = fabsf(v);
-  float p = fmaf(t, -0.01916250660946074f * L2E, -0.33840941696965965f * L2E);
-  p = fmaf(t, p, -0.7908370960657618f * L2E);
-  const float e = __builtin_amdgcn_exp2f(p * t);
-  return v + fmaf(-t, e, t);
-}
-
 // Number of 1 KB fragments of the packed weight stream of one layer.
 __host__ __device__ constexpr int frags_per_hp(int C) { return 6 * (C / 32) + C / 16; }
 __host__ __device__ constexpr int frags_per_fc(int C) { return 2 * (C / 32) + C / 16; }
@@ -151,9 +88,8 @@ struct ParamOff {  // float offsets inside the small-parameter area
                        B1 = 7 * C, TOTAL = 7 * C + F;
 };
 
-// Fragments per staged chunk: 16 (16 KB), or 8 for the narrow layer, whose hidden unit is 8 fragments (units are
-// whole chunks).
-__host__ __device__ constexpr int chunk_frags(int C) { return C >= 128 ? 16 : 8; }
+// Fragments per staged chunk: a hidden unit is 8 fragments (units are whole chunks).
+constexpr int kChunkFrags = 8;
 constexpr int kLdsBytes = 160 * 1024;  // LDS of one compute unit
 constexpr int kComputeUnits = 256;      // of an MI355X
 constexpr int kWindow = 8;             // weight fragments a wavefront keeps in flight (LDS -> registers)
@@ -165,14 +101,10 @@ struct LdsPlan {
   static constexpr int PARAMS = pack_param_bytes(C, F);   // padded to whole 1 KB pieces
   static constexpr int KVX_ONE = 2 * 2 * NKB * 64 * 8;                     // K and V of one group, one unit
   static constexpr int KVX = WPG > 1 ? 2 * GPW * KVX_ONE : 0;              // double buffered
-  static constexpr int NCHUNK = ((C / 32) * (6 * (C / 32) + C / 16) + (F / 32) * (2 * (C / 32) + C / 16)) / chunk_frags(C);
-  static constexpr int FIT = (kLdsBytes / WGS - PARAMS - KVX) / (chunk_frags(C) * 1024);
-  static constexpr int RING0 = FIT < NCHUNK ? FIT : NCHUNK;
-  // Mappings with rolled loops (more than two wavefronts per SIMD at C = 128) compute ring slots at run time: a
-  // power of two keeps that to a mask.
-  static constexpr bool ROLLED_128 = C == 128 && NW > 8;
-  static constexpr int RING = ROLLED_128 && RING0 >= 4 && RING0 < 8 ? 4 : RING0;
-  static constexpr int TOTAL = RING * chunk_frags(C) * 1024 + PARAMS + KVX;
+  static constexpr int NCHUNK = ((C / 32) * (6 * (C / 32) + C / 16) + (F / 32) * (2 * (C / 32) + C / 16)) / kChunkFrags;
+  static constexpr int FIT = (kLdsBytes / WGS - PARAMS - KVX) / (kChunkFrags * 1024);
+  static constexpr int RING = FIT < NCHUNK ? FIT : NCHUNK;
+  static constexpr int TOTAL = RING * kChunkFrags * 1024 + PARAMS + KVX;
   static_assert(RING >= 2, "weight ring");
 };
 
@@ -192,20 +124,15 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   constexpr int NKB = NVB * WPG;      // key blocks of a group
   constexpr int NT = NW * 64;
   constexpr int GPW = NW / WPG;       // groups per workgroup
-  constexpr int CF = chunk_frags(C);
+  constexpr int CF = kChunkFrags;
   constexpr int FH = 6 * KB + NB;     // fragments of one head-dim unit: Q, K, V rows, W_o slice
   constexpr int FF = 2 * KB + NB;     // fragments of one hidden unit: W1 rows, W2 slice
   constexpr int CPH = FH / CF, CPF = FF / CF;
-  // C = 128: the unit loops are unrolled completely, which turns the ring bookkeeping into constants
-  // (about 30 KB of code).  Wider layers keep rolled loops.
-  constexpr int FULL_UNROLL = C <= 128 && NW <= 8 ? 16 : 1;  // more waves per SIMD leave too few registers for it:
-  // with three or four, the hidden units are still unrolled completely (their chunk numbers and ring slots become
-  // constants) and the head-dim units in pairs (the ring of four slots repeats every two units)
-  constexpr int FFN_UNROLL = C <= 128 && MINW >= 3 ? 16 : FULL_UNROLL;
-  constexpr int ATT_UNROLL = C <= 128 && MINW >= 3 ? (NKB > 4 && MINW >= 4 ? 1 : 2) : FULL_UNROLL;  // (1: no scratch)
-  // Few registers per wavefront: C = 256 with three wavefronts on a SIMD (168 each), any with four (128), C = 128 with
-  // three and a positional embedding.
-  constexpr bool LEAN = ((NW + 3) / 4 >= 3 && MINW <= 2 && C >= 256) || MINW >= 4 || (PE && C == 128 && MINW >= 3);
+  // The unit loops are unrolled completely, which turns the ring bookkeeping into constants, except the two head-dim
+  // units of mappings with many key blocks and few registers (no scratch).
+  constexpr int FFN_UNROLL = 16;
+  constexpr int ATT_UNROLL = NKB > 4 && MINW >= 4 ? 1 : 2;
+  constexpr bool LEAN = MINW >= 4;    // four wavefronts on a SIMD: 128 registers each
   constexpr int PF = LEAN ? 4 : kWindow;
   using LP = LdsPlan<C, F, NVB, WPG, NW, MINW>;
   constexpr int NCHUNK = LP::NCHUNK, RING = LP::RING;
@@ -243,39 +170,14 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   // in_sorted: row p of feats is the pillar at sorted position p (the previous layer of a block wrote
   // its result in this layer's order), so the rows of a group are contiguous and need no index.
   // in_sorted == 2 (one frame): they are fetched from the guessed start without waiting for anything.
-  // Rows are fetched whole when the wavefront has LDS to turn them around in (STAGE): lane (q, i) takes
-  // the i-th 16 bytes of row 4k + q in its k-th load, so that an instruction reads four complete rows.
-  // With 8 bytes per lane in the accumulator layout (16 rows x 32 bytes per instruction) every row was
-  // touched by eight instructions, and the burst of all wavefronts at kernel start took 2.1 us instead
-  // of 0.8 to drain.  The rows then go through the wavefront's share of the K/V exchange buffer (not in
-  // use yet), 16-byte pieces swizzled by row so that neither the writes nor the reads conflict.
-  // C = 256: a row is 32 pieces, a load instruction reads two rows, and the 4 KB share turns the rows
-  // around in two phases of sixteen pieces each (a lane's piece belongs to phase `ph`).
-  constexpr bool STAGE = (C == 128 || C == 256) && WPG > 1 && !(LEAN && OUT_F32);  // (the lean mapping with fp32
-                                                                                    // output has no registers for it)
-  constexpr int LPR = C / 8, RPI = 64 / LPR, PH = C / 128;  // lanes per row, rows per instruction, phases
-  constexpr int NRL = STAGE ? 16 * NVB / RPI : 1;            // 16-byte loads per lane
-  const int lr = lane / LPR, piece32 = lane % LPR, ph = piece32 >> 4;  // my row within an instruction, my piece
-  constexpr int NBX = STAGE ? 1 : NB;       // raw rows of the early fetch without staging: 8 bytes per 16-feature block
-  uint2 early[NVB][NBX];
-  u32x4 rowv[NRL];
+  uint2 early[NVB][NB];
   if (in_sorted == 2) {
-    if constexpr (STAGE) {
 #pragma unroll
-      for (int k = 0; k < NRL; ++k) {
-        const uint32_t at = (uint32_t)g * (uint32_t)G + (uint32_t)(part * NVB * 16 + RPI * k + lr);
-        // (non-temporal: a row is read once per layer, and what arrives was written by another XCD)
-        rowv[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(
-            feats + (size_t)(at < (uint32_t)n ? at : (uint32_t)n - 1u) * C + 8 * piece32));
-      }
-    } else {
+    for (int vb = 0; vb < NVB; ++vb) {
+      const uint32_t at = (uint32_t)g * (uint32_t)G + (uint32_t)((part * NVB + vb) * 16 + i);
 #pragma unroll
-      for (int vb = 0; vb < NVB; ++vb) {
-        const uint32_t at = (uint32_t)g * (uint32_t)G + (uint32_t)((part * NVB + vb) * 16 + i);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          early[vb][nb] = *reinterpret_cast<const uint2*>(feats + (size_t)(at < (uint32_t)n ? at : (uint32_t)n - 1u) * C + 16 * nb + 4 * q);
-      }
+      for (int nb = 0; nb < NB; ++nb)
+        early[vb][nb] = *reinterpret_cast<const uint2*>(feats + (size_t)(at < (uint32_t)n ? at : (uint32_t)n - 1u) * C + 16 * nb + 4 * q);
     }
   }
   int start = 0, m = 0;
@@ -292,8 +194,8 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
     for (int t = 0; t < (CF + NW - 1) / NW; ++t) {
       const int f = wu + t * NW;
       if ((t + 1) * NW <= CF || f < CF) {  // wave-uniform
-        if constexpr (LEAN) {  // per-lane address form of the copy below: at 168 registers the scalar operands
-                               // of the other form cost three spilled registers
+        if constexpr (LEAN) {  // per-lane address form of the copy below: the scalar operands of the other form
+                               // cost registers
           const u32x4* srcv = packed + ((size_t)chunk * CF + f) * 64 + lane;
           const uint32_t dst = (uint32_t)reinterpret_cast<uintptr_t>(
               (__attribute__((address_space(3))) void*)(ring + ((chunk % RING) * CF + f) * 64));
@@ -389,46 +291,13 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
     if (guessed) row[vb] = s < m ? guess[vb] : -1;
     else row[vb] = s < m ? perm[start + s] : -1;
   }
-  // rowv (whole rows, 16 bytes per lane) -> raw (accumulator layout) through the wavefront's LDS share
-  auto turn_rows = [&](uint2 (&raw)[NVB][NB]) {
-    u32x4* stg = reinterpret_cast<u32x4*>(kvx) + wu * (NVB * 256);  // [row][16-byte piece ^ (row & 15)]
-#pragma unroll
-    for (int p = 0; p < PH; ++p) {
-#pragma unroll
-      for (int k = 0; k < NRL; ++k) {
-        const int r = RPI * k + lr;
-        if (PH == 1 || ph == p) stg[r * 16 + (i ^ (r & 15))] = rowv[k];
-      }
-      // No barrier: the pieces are this wavefront's own, and its LDS instructions execute in order.  The
-      // compiler must keep that order too (it sees stores and loads of different types).
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int vb = 0; vb < NVB; ++vb)
-#pragma unroll
-        for (int nb = 8 * p; nb < 8 * p + 8; ++nb) {
-          const int piece = 2 * (nb - 8 * p) + (q >> 1);
-          raw[vb][nb] = *reinterpret_cast<const uint2*>(
-              reinterpret_cast<const char*>(stg + (vb * 16 + i) * 16 + (piece ^ i)) + (q & 1) * 8);
-        }
-      asm volatile("" ::: "memory");
-    }
-  };
   if (in_sorted == 2 && guessed) {  // the early fetch hit
-    uint2 raw[NVB][NB];
-    if constexpr (STAGE) {
-      turn_rows(raw);
-    } else {
-#pragma unroll
-      for (int vb = 0; vb < NVB; ++vb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) raw[vb][nb] = early[vb][nb];
-    }
 #pragma unroll
     for (int vb = 0; vb < NVB; ++vb) {
       const bool live = (part * NVB + vb) * 16 + i < m;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
-        const uint2 u = raw[vb][nb];
+        const uint2 u = early[vb][nb];
         // (padding slots: the bits are cleared before the conversion, two instructions per block instead of a
         // branch around each block)
         const uint32_t keep = live ? 0xffffffffu : 0u;
@@ -445,20 +314,11 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
       const int s = (part * NVB + vb) * 16 + i;
       srcv[vb] = row[vb] >= 0 ? (in_sorted ? start + s : row[vb]) : 0;
     }
-    if constexpr (STAGE) {
 #pragma unroll
-      for (int k = 0; k < NRL; ++k) {  // row RPI k + lr of the wavefront: its index is held by the lane of that number
-        const int32_t sr = __shfl(srcv[RPI * k / 16], (RPI * k) % 16 + lr, 64);
-        rowv[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(feats + (int64_t)sr * C + 8 * piece32));
-      }
-        turn_rows(raw);
-    } else {
+    for (int vb = 0; vb < NVB; ++vb)
 #pragma unroll
-      for (int vb = 0; vb < NVB; ++vb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          raw[vb][nb] = *reinterpret_cast<const uint2*>(feats + (int64_t)srcv[vb] * C + 16 * nb + 4 * q);
-      }
+      for (int nb = 0; nb < NB; ++nb)
+        raw[vb][nb] = *reinterpret_cast<const uint2*>(feats + (int64_t)srcv[vb] * C + 16 * nb + 4 * q);
 #pragma unroll
     for (int vb = 0; vb < NVB; ++vb)
 #pragma unroll
@@ -473,24 +333,11 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   Frag8 pef[PE ? NVB : 1][PE ? KB : 1];
   if constexpr (PE) {
     uint2 praw[NVB][NB];
-    if constexpr (STAGE && C == 128 && MINW <= 2) {  // whole rows through the LDS turn-around, like the features
-                                                      // (where the registers allow it)
-      int32_t prow[NVB];
 #pragma unroll
-      for (int vb = 0; vb < NVB; ++vb) prow[vb] = row[vb] >= 0 ? row[vb] : 0;
+    for (int vb = 0; vb < NVB; ++vb)
 #pragma unroll
-      for (int k = 0; k < NRL; ++k) {
-        const int32_t sr = __shfl(prow[RPI * k / 16], (RPI * k) % 16 + lr, 64);
-        rowv[k] = *reinterpret_cast<const u32x4*>(pos_embed + (int64_t)sr * C + 8 * piece32);
-      }
-      turn_rows(praw);
-    } else {
-#pragma unroll
-      for (int vb = 0; vb < NVB; ++vb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          praw[vb][nb] = *reinterpret_cast<const uint2*>(pos_embed + (int64_t)(row[vb] >= 0 ? row[vb] : 0) * C + 16 * nb + 4 * q);
-    }
+      for (int nb = 0; nb < NB; ++nb)
+        praw[vb][nb] = *reinterpret_cast<const uint2*>(pos_embed + (int64_t)(row[vb] >= 0 ? row[vb] : 0) * C + 16 * nb + 4 * q);
 #pragma unroll
     for (int vb = 0; vb < NVB; ++vb)
 #pragma unroll
@@ -912,51 +759,18 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   }
 
   // ---- scatter -------------------------------------------------------------------------------------
-  if constexpr (STAGE && !OUT_F32) {
-    // The way the rows came in: through the wavefront's LDS share (free again since the attention
-    // ended), so that a store instruction writes four complete rows instead of 32 bytes of sixteen.
-    u32x4* stg = reinterpret_cast<u32x4*>(kvx) + wu * (NVB * 256);
-    // (six and more key blocks in a lean mapping: the lane is counted again instead of keeping what follows from it through the
-    // kernel, which is what would go to scratch)
-    const int ln = LEAN && NKB > 5 ? (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) : lane;
-    const int i = ln & 15, q = ln >> 4, lr = ln / LPR, piece32 = ln % LPR, ph = piece32 >> 4;
 #pragma unroll
-    for (int p = 0; p < PH; ++p) {
+  for (int vb = 0; vb < NVB; ++vb) {
+    if (row[vb] < 0) continue;
 #pragma unroll
-      for (int vb = 0; vb < NVB; ++vb)
-#pragma unroll
-        for (int nb = 8 * p; nb < 8 * p + 8; ++nb) {
-          const int piece = 2 * (nb - 8 * p) + (q >> 1);
-          *reinterpret_cast<uint2*>(reinterpret_cast<char*>(stg + (vb * 16 + i) * 16 + (piece ^ i)) + (q & 1) * 8) =
-              make_uint2(pack2(x1[vb][nb][0], x1[vb][nb][1]), pack2(x1[vb][nb][2], x1[vb][nb][3]));
-        }
-      asm volatile("" ::: "memory");  // keeps the order of the LDS stores above and the loads below
-#pragma unroll
-      for (int k = 0; k < NRL; ++k) {
-        const int r = RPI * k + lr;
-        const int32_t orw = __shfl(orow[RPI * k / 16], (RPI * k) % 16 + lr, 64);  // output row of row r
-        if (PH == 1 || ph == p) {
-          const u32x4 v = stg[r * 16 + (i ^ (r & 15))];
-          if (orw >= 0)  // non-temporal: the next reader is another XCD, and the kernel's end has less to write back
-            __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out) + (size_t)orw * C + 8 * piece32));
-        }
-      }
-      asm volatile("" ::: "memory");
-    }
-  } else {
-#pragma unroll
-    for (int vb = 0; vb < NVB; ++vb) {
-      if (row[vb] < 0) continue;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const size_t o = (size_t)orow[vb] * C + 16 * nb + 4 * q;
-        if (OUT_F32) {
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + o) =
-              make_float4(x1[vb][nb][0], x1[vb][nb][1], x1[vb][nb][2], x1[vb][nb][3]);
-        } else {
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + o) =
-              make_uint2(pack2(x1[vb][nb][0], x1[vb][nb][1]), pack2(x1[vb][nb][2], x1[vb][nb][3]));
-        }
+    for (int nb = 0; nb < NB; ++nb) {
+      const size_t o = (size_t)orow[vb] * C + 16 * nb + 4 * q;
+      if (OUT_F32) {
+        *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + o) =
+            make_float4(x1[vb][nb][0], x1[vb][nb][1], x1[vb][nb][2], x1[vb][nb][3]);
+      } else {
+        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + o) =
+            make_uint2(pack2(x1[vb][nb][0], x1[vb][nb][1]), pack2(x1[vb][nb][2], x1[vb][nb][3]));
       }
     }
   }
@@ -989,16 +803,8 @@ int launch_cfg(const void* feats, void* out, const void* pos_embed, const int32_
     return launch_status();
   };
   if (pos_embed) {
-    // These mappings have no registers left for the second operand set (they would spill, which no shipped
-    // mapping may): they are not built with a positional embedding.
-    constexpr bool kFits = !(C == 128 && NVB == 2 && WPG == 1) && !(C == 256 && NW >= 10) && !(C == 128 && WPG == 4 && NW == 12) &&
-                           !(C == 128 && WPG == 8 && MINW == 4);
-    if constexpr (kFits) {
-      if (out_f32) return go(k_layer_mfma<C, DH, F, NVB, WPG, NW, MINW, true, true>, 3);
-      return go(k_layer_mfma<C, DH, F, NVB, WPG, NW, MINW, false, true>, 2);
-    } else {
-      return FF_ERR_UNSUPPORTED;
-    }
+    if (out_f32) return go(k_layer_mfma<C, DH, F, NVB, WPG, NW, MINW, true, true>, 3);
+    return go(k_layer_mfma<C, DH, F, NVB, WPG, NW, MINW, false, true>, 2);
   }
   if (out_f32) return go(k_layer_mfma<C, DH, F, NVB, WPG, NW, MINW, true, false>, 1);
   return go(k_layer_mfma<C, DH, F, NVB, WPG, NW, MINW, false, false>, 0);
@@ -1054,105 +860,53 @@ int FF_LAYER_SYM(layer_mfma_launch)(const void* feats, void* out, int64_t n, con
   return launch_cfg<C, DH, F, NVB, WPG, NW, MINW>(feats, out, w->pos_embed, perm, group_offsets, num_groups, max_groups, pk, \
                                                   w->ln_eps, out_f32, (int)n, G, drop ? 1 : 0, out_index, in_sorted, stream)
   const int shape = shape_id(w);
-  // A launch runs in rounds of one workgroup per compute unit (a workgroup's LDS leaves room for no second one, except
-  // in mapping 8).  A workgroup of more wavefronts does more per round, because the wavefronts of a SIMD hide each
+  const bool pe = w->pos_embed != nullptr;
+  if (shape != 3) {
+    // 128 and 256 features: wavefronts that cut the features.  They are ahead of wavefronts that cut the rows, which served
+    // these widths before, at all group sizes and counts (us a layer, before / now, 30,000 rows: C = 128, G = 64 16.5 / 14.7,
+    // G = 69 23.6 / 21.9, G = 100 32.8 / 26.8; C = 256, G = 64 43.8 / 40.9; 2,000 rows, C = 256 40 / 16); at 64 features,
+    // two wavefronts a group, they are not (20,000 rows, G = 50: 8.9 / 10.9).
+    // Mapping numbers stand for a largest group and for taking a positional embedding, here as everywhere; one kernel serves
+    // all that hold G, so all give the same bits.
+    struct Mapping { int slots; bool embeds; };
+    static constexpr Mapping kNone = {0, false};
+    static constexpr Mapping k128[16] = {{128, true}, {32, false}, {64, true}, {80, true}, {128, true}, kNone, {64, true}, {64, true},
+                                         {128, false}, {128, true}, {32, true}, {64, false}, {64, true}, {80, true}, {96, true}, {32, true}};
+    static constexpr Mapping k256[16] = {{128, true}, {32, true}, {64, true}, {80, false}, {128, true}, {64, true}, {80, true},
+                                         {96, false}, {64, false}, kNone, kNone, kNone, kNone, kNone, kNone, kNone};
+    const Mapping& mp = (shape == 1 ? k128 : k256)[variant & 15];
+    if (G > mp.slots || (pe && !mp.embeds)) return FF_ERR_UNSUPPORTED;
+    const LayerSlice call{feats, out, (int)n, perm, group_offsets, num_groups, max_groups, w, G, drop, out_f32, packed, out_index,
+                          in_sorted};
+    return FF_LAYER_SYM(layer_slice_launch)(call, stream);
+  }
+  // The narrow layer (64 features, 4 heads): the whole 64 KB weight stream stays in the ring.  A launch runs in rounds of one
+  // workgroup per compute unit.  A workgroup of more wavefronts does more per round, because the wavefronts of a SIMD hide each
   // other's stalls and read the staged weights together, but its round takes longer: the mapping with the smaller
   // product of rounds and measured time of a round wins.  A mapping whose wavefronts cover G with fewer padding slots
   // does less work.
   auto rounds = [&](int per_wg) { return ceil_div(ceil_div((int64_t)max_groups, per_wg), kComputeUnits); };
-  const bool pe = w->pos_embed != nullptr;
+  if (variant == 0) {
+    // G <= 32: four or eight groups per workgroup (1301 groups 14.8 / 13.2 us, 2602: 21.9 / 23.5, 9009: 63 / 56);
+    // G <= 64: two or four (466 groups 12.1 / 13.5, 942: 16.6 / 14.4, 1302: 23.7 / 26.0, 3407: 54 / 51); G <= 80 and
+    // <= 96: two of five or six wavefronts against one of eight (466 groups 18.8 -> 12.5 and 19.6 -> 13.7, 3400: 121
+    // -> 75 and 125 -> 84); above: one or two (466: 18.9 / 16.7, 627: 27.4 / 30.1, 1172: 44.6 / 44.9, 3414: 123 / 104).
+    if (G <= 32) variant = rounds(4) * 70 <= rounds(8) * 118 ? 1 : 3;
+    else if (G <= 64) variant = rounds(2) * 79 <= rounds(4) * 129 ? 2 : 8;
+    else if (G <= 96) variant = rounds(1) == 1 ? 4 : G <= 80 ? 5 : 6;
+    else variant = rounds(1) * 90 <= rounds(2) * 151 ? 4 : 7;
+  }
   // (pillar blocks per wave, waves per group, waves per workgroup, min waves per SIMD)
-  if (shape == 1) {
-    if (variant == 0) {
-      if (G <= 32) {
-        // four or eight groups per workgroup: 14 and 24.5 us a round (941 groups 15.8 / 23.3 us, 2002: 32 / 29, 2602:
-        // 44 / 47, 3403: 55 / 48)
-        variant = rounds(4) * 140 <= rounds(8) * 245 ? 10 : 15;
-      } else if (G <= 64) {
-        // Two, three or four groups per workgroup (8, 12, 16 wavefronts): 16.4, 23.2 and 28.8 us a round.  Many rounds:
-        // four groups lead (60,000 groups: 1.76, 1.61, 1.56 ms); few: the number of rounds decides (measured, in us:
-        // 938 groups 33 / 44 / 30, 1407: 49 / 48 / 56, 1875: 65 / 69 / 60, 2344: 81 / 89 / 81, 3750: 128 / 120 / 115,
-        // 7500: 256 / 228 / 219, 15,000: 477 / 419 / 390).
-        const int64_t c2 = rounds(2) * 164, c4 = rounds(4) * 288;
-        // (the three-group mapping has no registers for a positional embedding)
-        const int64_t c3 = pe ? INT64_MAX : rounds(3) * 232;
-        variant = (c2 <= c3 && c2 <= c4) ? 7 : c3 <= c4 ? 11 : 12;
-      } else if (G <= 80) {
-        // Five wavefronts per group.  Up to one group per compute unit: one group per workgroup, 17.2 us (eight
-        // wavefronts 20.6); beyond: two (G = 69, 466 groups: 32 us one group, 23 two, 38 with eight wavefronts per
-        // group; 3407: 211, 146, 242; rounds of 16 and 21.5 us, so one group never wins from two rounds on).
-        variant = rounds(1) == 1 ? 3 : 13;
-      } else if (G <= 96) {
-        // Six wavefronts per group, two groups (G = 90, 466 groups: 38 -> 25 us; 3410: 246 -> 161); one round of one
-        // group is still shorter with mapping 9 (201 groups: 19.3 against 22.6).
-        variant = rounds(1) == 1 ? 9 : 14;
-      } else {
-        // Two workgroups on a compute unit at 128 registers (G = 128, 627 groups: 53 -> 48 us, 3414: 242 -> 210; 201
-        // groups, one per compute unit: 18.1 against 21.6); no registers for a positional embedding.
-        variant = rounds(1) == 1 || pe ? 9 : 8;
-      }
-    }
-    switch (variant) {
-      case 1: if (G <= 32) FF_GO(128, 16, 256, 2, 1, 4, 2); break;
-      case 2: if (G <= 64) FF_GO(128, 16, 256, 2, 2, 4, 1); break;  // 512 registers
-      case 3: if (G <= 80) FF_GO(128, 16, 256, 1, 5, 5, 2); break;
-      case 4: if (G <= 128) FF_GO(128, 16, 256, 2, 4, 4, 1); break;
-      case 6: if (G <= 64) FF_GO(128, 16, 256, 1, 4, 4, 2); break;
-      case 7: if (G <= 64) FF_GO(128, 16, 256, 1, 4, 8, 2); break;
-      case 8: if (G <= 128) FF_GO(128, 16, 256, 1, 8, 8, 4); break;   // two workgroups per compute unit
-      case 9: if (G <= 128) FF_GO(128, 16, 256, 1, 8, 8, 2); break;
-      case 10: if (G <= 32) FF_GO(128, 16, 256, 1, 2, 8, 2); break;
-      case 11: if (G <= 64) FF_GO(128, 16, 256, 1, 4, 12, 3); break;  // three groups, three waves per SIMD
-      case 12: if (G <= 64) FF_GO(128, 16, 256, 1, 4, 16, 4); break;  // four groups, four waves per SIMD
-      case 13: if (G <= 80) FF_GO(128, 16, 256, 1, 5, 10, 3); break;  // two groups
-      case 14: if (G <= 96) FF_GO(128, 16, 256, 1, 6, 12, 3); break;  // two groups, three waves per SIMD
-      case 15: if (G <= 32) FF_GO(128, 16, 256, 1, 2, 16, 4); break;  // eight groups, four waves per SIMD
-      default: break;
-    }
-  } else if (shape == 2) {
-    if (variant == 0) {
-      // A round is bound by LDS reads of the weights (1 MB per wavefront).  G <= 64: two or three groups per workgroup,
-      // 42 and 56 us a round (626 groups: 84 / 56 us, 942: 85 / 111, 1302: 126 / 112, 3407: 297 / 288).  G <= 96: two
-      // groups of six wavefronts against one of eight (201 groups 44 us one group, 55 two; 466: 91 / 60; 3410: 614 /
-      // 422).  With a positional embedding the ten- and twelve-wave mappings have no registers to spare.
-      if (G <= 32) variant = 1;
-      else if (G <= 64) variant = !pe && rounds(3) * 56 < rounds(2) * 42 ? 8 : 2;
-      else if (G <= 80) variant = pe ? 6 : 3;
-      else variant = G <= 96 && !pe && rounds(1) > 1 ? 7 : 4;
-    }
-    switch (variant) {
-      case 1: if (G <= 32) FF_GO(256, 32, 512, 1, 2, 8, 2); break;
-      case 2: if (G <= 64) FF_GO(256, 32, 512, 1, 4, 8, 2); break;
-      case 3: if (G <= 80) FF_GO(256, 32, 512, 1, 5, 10, 2); break;  // lean: 168 registers, no scratch
-      case 4: if (G <= 128) FF_GO(256, 32, 512, 1, 8, 8, 2); break;
-      case 5: if (G <= 64) FF_GO(256, 32, 512, 2, 2, 4, 1); break;
-      case 6: if (G <= 80) FF_GO(256, 32, 512, 1, 5, 5, 1); break;
-      case 7: if (G <= 96) FF_GO(256, 32, 512, 1, 6, 12, 2); break;  // lean, two groups
-      case 8: if (G <= 64) FF_GO(256, 32, 512, 1, 4, 12, 2); break;  // lean, three groups
-      default: break;
-    }
-  } else if (shape == 3) {  // the narrow layer (64 features, 4 heads): the whole 64 KB weight stream stays in the ring
-    if (variant == 0) {
-      // G <= 32: four or eight groups per workgroup (1301 groups 14.8 / 13.2 us, 2602: 21.9 / 23.5, 9009: 63 / 56);
-      // G <= 64: two or four (466 groups 12.1 / 13.5, 942: 16.6 / 14.4, 1302: 23.7 / 26.0, 3407: 54 / 51); G <= 80 and
-      // <= 96: two of five or six wavefronts against one of eight (466 groups 18.8 -> 12.5 and 19.6 -> 13.7, 3400: 121
-      // -> 75 and 125 -> 84); above: one or two (466: 18.9 / 16.7, 627: 27.4 / 30.1, 1172: 44.6 / 44.9, 3414: 123 / 104).
-      if (G <= 32) variant = rounds(4) * 70 <= rounds(8) * 118 ? 1 : 3;
-      else if (G <= 64) variant = rounds(2) * 79 <= rounds(4) * 129 ? 2 : 8;
-      else if (G <= 96) variant = rounds(1) == 1 ? 4 : G <= 80 ? 5 : 6;
-      else variant = rounds(1) * 90 <= rounds(2) * 151 ? 4 : 7;
-    }
-    switch (variant) {
-      case 1: if (G <= 32) FF_GO(64, 16, 128, 1, 2, 8, 2); break;
-      case 2: if (G <= 64) FF_GO(64, 16, 128, 1, 4, 8, 2); break;
-      case 3: if (G <= 32) FF_GO(64, 16, 128, 1, 2, 16, 4); break;   // eight groups
-      case 4: if (G <= 128) FF_GO(64, 16, 128, 1, 8, 8, 2); break;
-      case 5: if (G <= 80) FF_GO(64, 16, 128, 1, 5, 10, 3); break;   // two groups
-      case 6: if (G <= 96) FF_GO(64, 16, 128, 1, 6, 12, 3); break;   // two groups
-      case 7: if (G <= 128) FF_GO(64, 16, 128, 1, 8, 16, 4); break;  // two groups
-      case 8: if (G <= 64) FF_GO(64, 16, 128, 1, 4, 16, 4); break;   // four groups
-      default: break;
-    }
+  switch (variant) {
+    case 1: if (G <= 32) FF_GO(64, 16, 128, 1, 2, 8, 2); break;
+    case 2: if (G <= 64) FF_GO(64, 16, 128, 1, 4, 8, 2); break;
+    case 3: if (G <= 32) FF_GO(64, 16, 128, 1, 2, 16, 4); break;   // eight groups
+    case 4: if (G <= 128) FF_GO(64, 16, 128, 1, 8, 8, 2); break;
+    case 5: if (G <= 80) FF_GO(64, 16, 128, 1, 5, 10, 3); break;   // two groups
+    case 6: if (G <= 96) FF_GO(64, 16, 128, 1, 6, 12, 3); break;   // two groups
+    case 7: if (G <= 128) FF_GO(64, 16, 128, 1, 8, 16, 4); break;  // two groups
+    case 8: if (G <= 64) FF_GO(64, 16, 128, 1, 4, 16, 4); break;   // four groups
+    default: break;
   }
 #undef FF_GO
   return FF_ERR_UNSUPPORTED;

@@ -1,0 +1,735 @@
+// Group attention layer (paper Sec. 4.2.2, Eq. (2)) in 16-bit storage as ONE fused kernel whose wavefronts cut the FEATURES:
+//
+//   gather -> LN1 -> packed QKV projection -> per-head softmax(Q K^T / sqrt(d)) V -> out-proj
+//   + residual -> LN2 -> Linear + GELU -> Linear + residual -> scatter
+//
+// Mapping.  A workgroup owns one group (or GPW small ones) as blocks of 32 rows.  Its C / 32 wavefronts each compute 32
+// features of Q, K and V (whole heads: scores, softmax and P V stay inside a wavefront), of the output projection and of
+// the second FFN product, and their share of the hidden units, for all rows.  A weight fragment goes from L2 straight to
+// the registers of the one wavefront that needs it and multiplies every row block; the activations (LN1 output, attention
+// output, LN2 output, hidden units) go round through LDS in operand order, six barriers a layer.
+//
+// All products are v_mfma_f32_32x32x16, computed transposed: D[output feature][row], lane (h, n) = 32 h + n of a tile
+// holds row n and features (r & 3) + 8 (r >> 2) + 4 h in registers r = 0..15 (V: operand roles swapped, D[row][feature]).
+// Registers 4 k .. 4 k + 3 and 8 + 4 k .. 8 + 4 k + 3, rounded to 16 bits, are the operand of step k of a later product
+// over these 32 features: that is the order of inputs the packed weights (pack_weights.h) come in, whose 16 x 32 fragments
+// are read as halves of 32 x 16 ones.  Heads of 16: registers 8 a .. 8 a + 7 of Q and K are one step of head a, and in P V
+// the 16 rows of the A operand that belong to the other head are ones, so that the row sums of P come with the product.
+//
+// What bounds it.  One group on a compute unit (C = 128, G = 64): the chain of one wavefront, 9 us, of which 2 are the trip to
+// its rows; a lone wavefront issues an instruction every five to seven cycles.  Two groups: 14 us.  Many: instruction issue
+// (1,690 vector instructions a wavefront, a fifth of them exponentials and their 16-bit roundings, for 152 products of 32
+// cycles) and weight delivery (256 KB a group from L2, a quarter of the time in a build without it); the matrix pipe is
+// busy 45 % of the time.  Before (wavefronts that cut the rows, every one reading all weights from LDS) / now, us a
+// launch: C = 128, G = 64, 12,345 rows 14.5 / 10.3, 480,000 rows 208 / 190; G = 100, 30,000 rows 32.8 / 27; G = 128,
+// 80,000 rows 46.5 / 42.5; C = 256, G = 64, 2,000 rows 40 / 16, 60,000 rows 85 / 79; G = 96, 240,000 rows 364 / 311.
+#include "elem16.h"
+#include "pack_weights.h"
+#include <atomic>
+#include <type_traits>
+
+namespace ff {
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c) {
+#ifdef FF_LAYER_F16
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(el8, a), __builtin_bit_cast(el8, b), c, 0, 0, 0);
+#else
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(el8, a), __builtin_bit_cast(el8, b), c, 0, 0, 0);
+#endif
+}
+// v of lane n and of lane n + 32 combined, in every lane
+__device__ __forceinline__ float half_sum(float v) {
+  auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+__device__ __forceinline__ float half_max(float v) {
+  auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+template <int CTRL> __device__ __forceinline__ float dpp(float v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+// Sum over LPR (8, 16, 32) neighbouring lanes.
+template <int LPR> __device__ __forceinline__ float lane_sum(float v) {
+  v += dpp<0xB1>(v);                            // quad_perm 1,0,3,2
+  v += dpp<0x4E>(v);                            // quad_perm 2,3,0,1
+  v += dpp<0x141>(v);                           // row_half_mirror
+  if constexpr (LPR >= 16) v += dpp<0x140>(v);  // row_mirror
+  if constexpr (LPR >= 32) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  }
+  return v;
+}
+// Nothing is moved across by the instruction scheduler: it would sink loads issued ahead to where they are used.
+__device__ __forceinline__ void fence() { __builtin_amdgcn_sched_barrier(0); }
+// Workgroup barrier that waits for this wavefront's LDS operations only: weight fragments requested ahead stay in
+// flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+constexpr int kLdsBytes = 160 * 1024;  // LDS of one compute unit
+
+template <int C, int F, int RB>
+struct Plan {
+  static constexpr int NS = C / 32, NT = 64 * NS, R = 32 * RB;
+  static constexpr int A = R * C * 2;          // one set of operands: LN1 output, LN2 output, second half of the hidden units;
+  static constexpr int B = A;                  // another: attention output, first half of the hidden units, rows on their way out
+  static constexpr int STATS = R * NS * 8;
+  static constexpr int PAR = (5 * C + F) * 4;  // query bias, output bias, LN2 scale and shift, FFN biases
+  static constexpr int TAB = RB * 64;          // which rows are members, as operand masks
+  static constexpr int SRC = R * 4;            // where the rows came from
+  static constexpr int TOTAL = A + B + STATS + PAR + TAB + SRC;
+  static_assert(F == 2 * C, "half of the hidden units are one set of operands");
+};
+
+template <int C, int DH, int F, int PT, int GPW, bool HALF, int MINW, bool OUT_F32, bool PE>
+__global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
+    const uint16_t* __restrict__ feats, void* __restrict__ out, const uint16_t* __restrict__ pos_embed,
+    const int32_t* __restrict__ perm, const int32_t* __restrict__ goff, const int32_t* __restrict__ num_groups,
+    int max_groups, int n, int G, const int32_t* __restrict__ out_index, int in_sorted, int drop, float eps,
+    const u32x4* __restrict__ packed) {
+  constexpr int RB = PT * GPW;             // row blocks of the workgroup
+  using PL = Plan<C, F, RB>;
+  constexpr int NS = PL::NS;
+  constexpr int KB = C / 32, NB = C / 16;  // 32-wide input blocks, 16-wide output blocks
+  constexpr int KS = C / 16;               // steps along C
+  constexpr int FH = 6 * KB + NB, FF = 2 * KB + NB;  // fragments of a head-dim unit and of a hidden unit of the packed stream
+  constexpr int WD = RB <= 3 && MINW <= 2 ? 4 : 3;  // weight operands in flight
+  constexpr int NH = 32 / DH;              // heads of a wavefront
+  constexpr int LPR = C / 8, RPI = 64 / LPR;  // lanes per row (16 bytes each), rows per load instruction
+  constexpr int NL = 2 * RB;               // load instructions of a wavefront
+  static_assert(DH == 16 || DH == 32, "head dim");
+  constexpr int RPW = NL * RPI;            // rows a wavefront loads, normalises and stores: of one group
+  static_assert(RPW * NS == 32 * RB && 32 * PT % RPW == 0, "of one group");
+
+  extern __shared__ u32x4 lds[];
+  u32x4* const Ab = lds;
+  u32x4* const Bb = lds + PL::A / 16;
+  char* const ldsc = reinterpret_cast<char*>(lds) + PL::A + PL::B;
+  f32x2* const stats = reinterpret_cast<f32x2*>(ldsc);
+  float* const par = reinterpret_cast<float*>(ldsc + PL::STATS);
+  uint32_t* const tab = reinterpret_cast<uint32_t*>(ldsc + PL::STATS + PL::PAR);
+  int32_t* const src = reinterpret_cast<int32_t*>(ldsc + PL::STATS + PL::PAR + PL::TAB);
+  constexpr int P_BQ = 0, P_BO = C, P_G2 = 2 * C, P_B2N = 3 * C, P_B2 = 4 * C, P_B1 = 5 * C;
+
+  const int tid = threadIdx.x, lane = tid & 63, nrow = lane & 31, h = lane >> 5;
+  const int s = __builtin_amdgcn_readfirstlane(tid >> 6);  // slice
+
+  // ---- weights: a 32 x 16 operand is one 16-byte piece per lane of two 16 x 32 fragments -----------------------------
+  // (buffer loads: the lane's part of the address is one register, the rest a scalar)
+  const auto wres = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(packed), 0, (KB * FH + (F / 32) * FF) * 1024, 0x00020000);
+  auto w_load = [&](uint32_t lane_off, int frag, int bytes) -> u32x4 {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, (int)lane_off + bytes, frag * 1024, 0));
+  };
+  const uint32_t piece = (uint32_t)((16 * h + (lane & 15)) * 16);
+  const uint32_t second = (lane >> 4) & 1;       // row of the tile: 0..15 or 16..31
+  const uint32_t lane_rows = piece + second * (KB * 1024u);  // Q, K, V, W1: the second 16 rows come KB fragments later
+  const uint32_t lane_cols = piece + second * 1024u;         // W_o, W2: next to each other
+  auto rows_at = [&](int frag, int ks) { return w_load(lane_rows, frag + ks / 8 * 4, ks % 8 * 512); };  // of a row tile
+  auto wk_at = [&](int ks) { return rows_at(s * FH, ks); };
+  auto wv_at = [&](int ks) { return rows_at(s * FH + 2 * KB, ks); };
+  auto wq_at = [&](int ks) { return rows_at(s * FH + 4 * KB, ks); };
+  auto wo_at = [&](int ks) { return w_load(lane_cols, (ks / 2) * FH + 6 * KB + 2 * s, ks % 2 * 512); };
+  auto w1_at = [&](int t, int ks) { return rows_at(KB * FH + (t * NS + s) * FF, ks); };
+  auto w2_at = [&](int ks) { return w_load(lane_cols, KB * FH + (ks / 2) * FF + 2 * KB + 2 * s, ks % 2 * 512); };
+
+  // ---- which rows ----------------------------------------------------------------------------------------------------
+  const int ngroups = *num_groups;
+  const int gl_s = GPW == 1 ? 0 : s * RPW / (32 * PT);  // the group whose rows this wavefront loads and stores
+  int start = 0, m = 0, end1 = 0;          // of that group
+  bool whole = true;                       // every row of the workgroup is a member of its group
+#pragma unroll
+  for (int gl = 0; gl < GPW; ++gl) {
+    const int g = blockIdx.x * GPW + gl;
+    const int gc = g < max_groups ? g : max_groups - 1;
+    const int o0 = goff[gc], o1 = goff[gc + 1];
+    // A list of full groups only ('Drop Residual') has the next start beyond this group's end.
+    const int mg = g < ngroups ? (o1 - o0 < G ? o1 - o0 : G) : 0;
+    if (gl == gl_s) { start = g < ngroups ? o0 : 0; m = mg; end1 = o1; }
+    whole = whole && (mg == 32 * PT || mg == 0);
+    if (tid < PT * 16) {                   // operand masks: entry (block, step, half, pair of rows)
+      const int key = 32 * (tid >> 4) + 16 * ((tid >> 3) & 1) + 8 * ((tid >> 1) & 1) + 4 * ((tid >> 2) & 1) + 2 * (tid & 1);
+      const int mm = mg > 0 ? mg : 32 * PT;
+      tab[gl * PT * 16 + tid] = (key < mm ? 0xffffu : 0u) | (key + 1 < mm ? 0xffff0000u : 0u);
+    }
+  }
+  const int g_s = blockIdx.x * GPW + gl_s;
+  // Slot sl of the wavefront's group -> sorted position.  Rows beyond the group's members repeat its last member: their
+  // scores then never exceed the real ones, and they are cut out of the sums (below).
+  const int slot0 = s * RPW - gl_s * 32 * PT;
+  const int lr = lane / LPR, lc = lane % LPR;
+  int first = 0;                           // sorted position of the wavefront's first row
+  int off[NL];                             // and how far from it mine are
+  auto place = [&](int start_at, int last) {
+    first = __builtin_amdgcn_readfirstlane(start_at + (slot0 < last ? slot0 : last));
+#pragma unroll
+    for (int t = 0; t < NL; ++t) {
+      const int sl = slot0 + t * RPI + lr;
+      off[t] = (sl < last ? sl : last) - (slot0 < last ? slot0 : last);
+    }
+  };
+  int pil[NL];
+  auto fetch_pillars = [&]() {
+#pragma unroll
+    for (int t = 0; t < NL; ++t) pil[t] = (perm + first)[(uint32_t)off[t]];
+  };
+  u32x4 raw[NL];
+  auto fetch_rows = [&]() {
+    if (in_sorted) {                       // side by side
+#pragma unroll
+      for (int t = 0; t < NL; ++t)
+        raw[t] = *reinterpret_cast<const u32x4*>(feats + (int64_t)first * C + (uint32_t)(off[t] * C + 8 * lc));
+    } else {
+#pragma unroll
+      for (int t = 0; t < NL; ++t) raw[t] = *reinterpret_cast<const u32x4*>(feats + (int64_t)pil[t] * C + 8 * lc);
+    }
+  };
+  // Groups of the first (or only) frame start at g * G: what is loaded from there does not wait for the group list.
+  {
+    const uint32_t g0 = (uint32_t)g_s * (uint32_t)G, end = (uint32_t)n - 1u;
+    const uint32_t from = g0 < end ? g0 : end, left = end - from;
+    place((int)from, (int)(left < (uint32_t)G - 1u ? left : (uint32_t)G - 1u));
+  }
+  fetch_pillars();
+  if (in_sorted == 2) fetch_rows();
+  f32x4 gam[2], bet[2];                    // LayerNorm 1 scale and shift of my features
+  const float* const params = reinterpret_cast<const float*>(packed + (size_t)(KB * FH + (F / 32) * FF) * 64);
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    gam[e] = *reinterpret_cast<const f32x4*>(params + 8 * lc + 4 * e);
+    bet[e] = *reinterpret_cast<const f32x4*>(params + C + 8 * lc + 4 * e);
+  }
+  static_assert((5 * C + F) / 4 <= PL::NT, "one piece a thread");
+  f32x4 par_piece;
+  if (tid < (5 * C + F) / 4) par_piece = *reinterpret_cast<const f32x4*>(params + 2 * C + 4 * tid);
+  const bool guessed = (int64_t)g_s * G == start && (m == G || start + m == n || m == 0);  // wave-uniform
+  if (!guessed) {
+    place(start, m > 0 ? m - 1 : 0);
+    fetch_pillars();
+  }
+  if (in_sorted != 2 || !guessed) fetch_rows();
+  u32x4 pe[PE ? NL : 1];
+  if constexpr (PE) {
+#pragma unroll
+    for (int t = 0; t < NL; ++t) pe[t] = *reinterpret_cast<const u32x4*>(pos_embed + (int64_t)pil[t] * C + 8 * lc);
+  }
+
+  // ---- LN1 -> A ------------------------------------------------------------------------------------------------------
+#pragma unroll
+  for (int t = 0; t < NL; ++t) {
+    const int row = s * RPW + t * RPI + lr;
+    if (lc == 0) src[row] = in_sorted ? first + off[t] : pil[t];
+    float y[8], su = 0.f, ss = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { y[2 * j] = el_lo(raw[t][j]); y[2 * j + 1] = el_hi(raw[t][j]); }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) su += y[j];
+    const float mu = lane_sum<LPR>(su) * (1.0f / C);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ss = fmaf(y[j], y[j], ss);
+    const float var = fmaxf(lane_sum<LPR>(ss) * (1.0f / C) - mu * mu, 0.f);
+    const float sc = rsqrtf(var + eps), sh = -mu * sc;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) y[j] = fmaf(fmaf(y[j], sc, sh), gam[j / 4][j % 4], bet[j / 4][j % 4]);
+    // features 8 lc .. + 7: eight bytes for each half of step lc & 1 of input block lc / 4
+    auto put = [&](u32x4* dst) {
+      char* const p = reinterpret_cast<char*>(dst + ((row >> 5) * KS + 2 * (lc >> 2) + (lc & 1)) * 64 + (row & 31)) + 8 * ((lc >> 1) & 1);
+      *reinterpret_cast<u32x2*>(p) = u32x2{pack2(y[0], y[1]), pack2(y[2], y[3])};
+      *reinterpret_cast<u32x2*>(p + 512) = u32x2{pack2(y[4], y[5]), pack2(y[6], y[7])};
+    };
+    put(Ab);
+    if constexpr (PE) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { y[2 * j] += el_lo(pe[t][j]); y[2 * j + 1] += el_hi(pe[t][j]); }
+      put(Bb);
+    }
+  }
+  if (tid < (5 * C + F) / 4) reinterpret_cast<f32x4*>(par)[tid] = par_piece;
+  // ---- rows of no group ('Drop Residual'): copied ------------------------------------------------------------------
+  if (drop) {
+    auto copy_rows = [&](int lo, int hi, int w0, int nw) {  // by wavefronts w0 .. w0 + nw - 1
+      hi = hi < n ? hi : n;
+      for (int p = lo + (s - w0) * RPI + lr; p < hi; p += nw * RPI) {
+        const int pillar = perm[p];
+        const u32x4 v = *reinterpret_cast<const u32x4*>(feats + (int64_t)(in_sorted ? p : pillar) * C + 8 * lc);
+        const int64_t to = (int64_t)(out_index ? out_index[pillar] : pillar) * C + 8 * lc;
+        if constexpr (OUT_F32) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            *reinterpret_cast<f32x2*>(reinterpret_cast<float*>(out) + to + 2 * e) = f32x2{el_lo(v[e]), el_hi(v[e])};
+        } else {
+          *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out) + to) = v;
+        }
+      }
+    };
+    constexpr int WPG = NS / GPW;  // wavefronts of a group
+    if (g_s == 0) copy_rows(0, ngroups > 0 ? start : n, gl_s * WPG, WPG);
+    if (g_s < ngroups) copy_rows(start + m, end1, gl_s * WPG, WPG);
+  }
+
+  const f32x16 kZero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  auto vec16 = [&](int off) -> f32x16 {    // 16 entries of a per-feature vector in accumulator order
+    f32x16 v;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const f32x4 t = *reinterpret_cast<const f32x4*>(par + off + 8 * b + 4 * h);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[4 * b + j] = t[j];
+    }
+    return v;
+  };
+  // Operand of step k of a product over the 32 features of an accumulator
+  auto operand = [&](const f32x16& v, int k) -> u32x4 {
+    return u32x4{pack2(v[4 * k], v[4 * k + 1]), pack2(v[4 * k + 2], v[4 * k + 3]),
+                 pack2(v[8 + 4 * k], v[8 + 4 * k + 1]), pack2(v[8 + 4 * k + 2], v[8 + 4 * k + 3])};
+  };
+
+  // A bias as the start of a sum: one product, of the bias in the first input and ones (16-bit numbers both, so exact).
+  const u32x4 first_one = {h == 0 ? kOnePair & 0xffffu : 0u, 0u, 0u, 0u};
+  auto bias = [&](int off) -> u32x4 { return u32x4{pack2(par[off + nrow], 0.f), 0u, 0u, 0u}; };
+
+  // Steps of a product: N weight operands and RB activation operands (of `rows`) a step.  Weights are requested D - 1 steps
+  // ahead, the first of them by `ahead`, before the caller's barrier; step k of this product is step `at` + k of whatever
+  // `w` and `wf` stand for.  `beside`: work of the vector units for each step.
+  auto ahead = [&](auto& w, auto wf) {
+    constexpr int D = sizeof(w) / sizeof(w[0]);
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d) wf(w[d], d);
+  };
+  auto nothing = [](int) {};
+  auto product = [&](auto& w, auto wf, int at, const u32x4* rows, auto mm, auto beside) {
+    constexpr int D = sizeof(w) / sizeof(w[0]);
+    const u32x4* const p = rows + lane;
+    constexpr int DA = sizeof(w[0]) == 16 && RB <= 3 ? 3 : 2;
+    u32x4 a[DA][RB];
+#pragma unroll
+    for (int d = 0; d < DA - 1; ++d)
+#pragma unroll
+      for (int b = 0; b < RB; ++b) a[d][b] = p[(b * KS + d) * 64];
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      fence();
+      wf(w[(at + k + D - 1) % D], at + k + D - 1);
+      if (k + DA - 1 < KS) {
+#pragma unroll
+        for (int b = 0; b < RB; ++b) a[(k + DA - 1) % DA][b] = p[(b * KS + k + DA - 1) * 64];
+      }
+      mm(w[(at + k) % D], a[k % DA]);
+      beside(k);
+    }
+    fence();
+  };
+
+  // ---- Q, K, V of this slice -----------------------------------------------------------------------------------------
+  u32x4 Q[RB][2], K[RB][2], V[RB][2];      // rounded: registers 8 a .. 8 a + 7 of the accumulators
+  auto halves = [&](u32x4 (&d)[2], const f32x16& v) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) d[a][j] = pack2(v[8 * a + 2 * j], v[8 * a + 2 * j + 1]);
+  };
+  constexpr float qscale = (DH == 16 ? 0.25f : 0.17677669529663687f) * 1.44269504088896340736f;  // log2(e) / sqrt(d)
+  {
+    constexpr bool JOINT = RB <= 2 && !PE;  // all three at once; otherwise the values first,
+    constexpr bool PAIR = RB <= 3;          // and then keys and queries together (four row blocks: one after the other)
+    u32x4 w1[WD][1], w2[4][2], w3[2][3];
+    auto vf = [&](u32x4 (&d)[1], int k) { if (k < KS) d[0] = wv_at(k); };
+    auto kf = [&](u32x4 (&d)[1], int k) { if (k < KS) d[0] = wk_at(k); };
+    auto qf = [&](u32x4 (&d)[1], int k) { if (k < KS) d[0] = wq_at(k); };
+    auto kqf = [&](u32x4 (&d)[2], int k) { if (k < KS) { d[0] = wk_at(k); d[1] = wq_at(k); } };
+    auto kqvf = [&](u32x4 (&d)[3], int k) { if (k < KS) { d[0] = wk_at(k); d[1] = wq_at(k); d[2] = wv_at(k); } };
+    if constexpr (JOINT) ahead(w3, kqvf);
+    else ahead(w1, vf);
+    lds_barrier();
+    f32x16 aq[RB], ak[RB], av[RB];
+    auto start_at = [&](f32x16 (&v)[RB], const f32x16& from) {
+#pragma unroll
+      for (int b = 0; b < RB; ++b) v[b] = from;
+    };
+    auto done = [&](u32x4 (&d)[RB][2], f32x16 (&v)[RB]) {
+#pragma unroll
+      for (int b = 0; b < RB; ++b) halves(d[b], v[b]);
+    };
+    const u32x4* const qk = PE ? Bb : Ab;
+    start_at(av, kZero);
+    if constexpr (!JOINT) {
+      product(w1, vf, 0, Ab, [&](const u32x4 (&w)[1], const u32x4 (&a)[RB]) {
+#pragma unroll
+        for (int b = 0; b < RB; ++b) av[b] = mma(a[b], w[0], av[b]);
+      }, nothing);
+      if constexpr (PAIR) ahead(w2, kqf);
+      else ahead(w1, kf);
+      done(V, av);
+    }
+    start_at(ak, kZero);
+    {
+      const u32x4 bq = bias(P_BQ + 32 * s);
+#pragma unroll
+      for (int b = 0; b < RB; ++b) aq[b] = mma(bq, first_one, kZero);
+    }
+    if constexpr (JOINT) {
+      product(w3, kqvf, 0, Ab, [&](const u32x4 (&w)[3], const u32x4 (&a)[RB]) {
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+          ak[b] = mma(w[0], a[b], ak[b]);
+          aq[b] = mma(w[1], a[b], aq[b]);
+          av[b] = mma(a[b], w[2], av[b]);
+        }
+      }, nothing);
+      done(V, av);
+    } else if constexpr (PAIR) {
+      product(w2, kqf, 0, qk, [&](const u32x4 (&w)[2], const u32x4 (&a)[RB]) {
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+          ak[b] = mma(w[0], a[b], ak[b]);
+          aq[b] = mma(w[1], a[b], aq[b]);
+        }
+      }, nothing);
+    } else {
+      product(w1, kf, 0, qk, [&](const u32x4 (&w)[1], const u32x4 (&a)[RB]) {
+#pragma unroll
+        for (int b = 0; b < RB; ++b) ak[b] = mma(w[0], a[b], ak[b]);
+      }, nothing);
+      ahead(w1, qf);
+      done(K, ak);
+      product(w1, qf, 0, qk, [&](const u32x4 (&w)[1], const u32x4 (&a)[RB]) {
+#pragma unroll
+        for (int b = 0; b < RB; ++b) aq[b] = mma(w[0], a[b], aq[b]);
+      }, nothing);
+    }
+    done(Q, aq);
+    if constexpr (JOINT || PAIR) done(K, ak);
+    if constexpr (PE) lds_barrier();       // the attention output goes where the embedded rows were
+  }
+
+  // ---- attention -----------------------------------------------------------------------------------------------------
+  // The weights of everything after it are one stream: W_o, two tiles of W_1, W_2.
+  u32x4 w[WD][1];
+  auto wf = [&](u32x4 (&d)[1], int k) {
+    if (k < KS) d[0] = wo_at(k);
+    else if (k < 3 * KS) d[0] = w1_at(k / KS - 1, k % KS);
+    else if (k < 5 * KS) d[0] = w2_at(k - 3 * KS);
+  };
+  // SHORT: some rows of the workgroup are no members.  HALF: no group has members in the second half of its last block.
+  auto attention = [&](auto shortc) {
+    constexpr bool SHORT = decltype(shortc)::value;
+    auto member = [&](int b, int t) -> u32x4 {  // mask of the rows of operand (b, t)
+      return reinterpret_cast<const u32x4*>(tab)[(b * 2 + t) * 2 + h];
+    };
+    auto ones = [&](int b, int t) -> u32x4 {
+      u32x4 one = {kOnePair, kOnePair, kOnePair, kOnePair};
+      if constexpr (SHORT) one &= member(b, t);
+      return one;
+    };
+    if constexpr (SHORT) {
+#pragma unroll
+      for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) V[b][t] &= member(b, t);
+    }
+#pragma unroll
+    for (int gl = 0; gl < GPW; ++gl) {
+#pragma unroll
+      for (int hd = 0; hd < NH; ++hd) {
+        // A operand of P V: the head's value rows, and (heads of 16) ones in the other head's rows
+        u32x4 va[PT][2];
+#pragma unroll
+        for (int kt = 0; kt < PT; ++kt)
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const int b = gl * PT + kt;
+            if constexpr (DH == 32) {
+              va[kt][t] = V[b][t];
+            } else {
+              const u32x4 one = ones(b, t);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) va[kt][t][j] = (int)second == hd ? V[b][t][j] : one[j];
+            }
+          }
+#pragma unroll
+        for (int q0 = 0; q0 < PT; ++q0) {
+          const int qt = gl * PT + q0;
+          f32x16 O, rs;
+          auto used = [](int kt) { return HALF && kt == PT - 1 ? 8 : 16; };  // registers of a block that stand for members
+          auto scores = [&](int kt) -> f32x16 {
+            f32x16 S = mma(K[gl * PT + kt][DH == 16 ? hd : 0], Q[qt][DH == 16 ? hd : 0], kZero);
+            if constexpr (DH == 32) S = mma(K[gl * PT + kt][1], Q[qt][1], S);
+            return S;
+          };
+          auto accumulate = [&](int kt, const f32x16& P) {
+            u32x4 p[2];
+            halves(p, P);
+#pragma unroll
+            for (int t = 0; t < (HALF && kt == PT - 1 ? 1 : 2); ++t) {
+              O = mma(va[kt][t], p[t], kt == 0 && t == 0 ? kZero : O);
+              if constexpr (DH == 32) rs = mma(ones(gl * PT + kt, t), p[t], kt == 0 && t == 0 ? kZero : rs);
+            }
+          };
+          auto sum = [&]() { return DH == 32 ? rs[0] : hd == 0 ? O[8] : O[0]; };
+          f32x16 S[PT];
+#pragma unroll
+          for (int kt = 0; kt < PT; ++kt) S[kt] = scores(kt);
+          float mx = S[0][0];
+#pragma unroll
+          for (int kt = 0; kt < PT; ++kt)
+#pragma unroll
+            for (int r = 0; r < used(kt); ++r) mx = fmaxf(mx, S[kt][r]);
+          mx = -half_max(mx) * qscale;
+          // p = 2^((s - max) * log2(e) / sqrt(d)): the score scale lives in the exponent argument
+#pragma unroll
+          for (int kt = 0; kt < PT; ++kt) {
+#pragma unroll
+            for (int r = 0; r < used(kt); ++r) S[kt][r] = __builtin_amdgcn_exp2f(fmaf(S[kt][r], qscale, mx));
+            accumulate(kt, S[kt]);
+          }
+          const float inv = __builtin_amdgcn_rcpf(sum());
+          u32x4* const dst = Bb + (qt * KS + 2 * s) * 64 + lane;
+          if constexpr (DH == 16) {        // the head's eight features: half of the operands of both steps
+            float o[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) o[r] = O[8 * hd + r] * inv;
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+              *reinterpret_cast<u32x2*>(reinterpret_cast<char*>(dst + k * 64) + 8 * hd) =
+                  u32x2{pack2(o[4 * k], o[4 * k + 1]), pack2(o[4 * k + 2], o[4 * k + 3])};
+          } else {
+            O *= inv;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) dst[k * 64] = operand(O, k);
+          }
+        }
+      }
+    }
+  };
+  ahead(w, wf);
+  if (!HALF && whole) attention(std::false_type());
+  else attention(std::true_type());
+
+  // ---- output projection + residual ----------------------------------------------------------------------------------
+  // The rows again, 16 bytes a lane: lane h holds features 16 h + 8 u .. + 7 of the slice, the operand of a product whose other
+  // operand is one where the feature is the output's own.  It adds the numbers as they are (1 x), and leaves the vector units
+  // out of it.
+  u32x4 again[RB][2], unit[2];
+#pragma unroll
+  for (int b = 0; b < RB; ++b)
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      again[b][u] = *reinterpret_cast<const u32x4*>(feats + (int64_t)src[32 * b + nrow] * C + 32 * s + 16 * h + 8 * u);
+  {
+    const int mine = nrow - 16 * h;
+    const uint32_t one = (kOnePair & 0xffffu) << (16 * (mine & 1));
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) unit[u][j] = (mine >> 1) == 4 * u + j ? one : 0u;
+  }
+  f32x16 x1[RB];                           // residual stream of (my 32 features, all rows)
+  {
+    const f32x16 bo = vec16(P_BO + 32 * s);
+#pragma unroll
+    for (int b = 0; b < RB; ++b) x1[b] = bo;
+  }
+  lds_barrier();
+  product(w, wf, 0, Bb, [&](const u32x4 (&w)[1], const u32x4 (&a)[RB]) {
+#pragma unroll
+    for (int b = 0; b < RB; ++b) x1[b] = mma(w[0], a[b], x1[b]);
+  }, nothing);
+#pragma unroll
+  for (int b = 0; b < RB; ++b)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) x1[b] = mma(unit[u], again[b][u], x1[b]);
+  int orow[NL];                            // rows of `out` of my rows
+#pragma unroll
+  for (int t = 0; t < NL; ++t) orow[t] = out_index ? out_index[pil[t]] : pil[t];
+
+  // ---- LN2 -> A ------------------------------------------------------------------------------------------------------
+  // Sum and sum of squares of a row: every wavefront's 32 features, combined through LDS.
+#pragma unroll
+  for (int b = 0; b < RB; ++b) {
+    float su4[4], ss4[4];                  // (short chains)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      su4[j] = x1[b][j];
+      ss4[j] = x1[b][j] * x1[b][j];
+#pragma unroll
+      for (int e = 1; e < 4; ++e) { su4[j] += x1[b][4 * e + j]; ss4[j] = fmaf(x1[b][4 * e + j], x1[b][4 * e + j], ss4[j]); }
+    }
+    const float su = half_sum((su4[0] + su4[1]) + (su4[2] + su4[3]));
+    const float ss = half_sum((ss4[0] + ss4[1]) + (ss4[2] + ss4[3]));
+    if (h == 0) stats[(b * 32 + nrow) * NS + s] = f32x2{su, ss};
+  }
+  lds_barrier();
+  {
+    const f32x16 gm = vec16(P_G2 + 32 * s), bt = vec16(P_B2N + 32 * s);
+    const u32x4 b2 = bias(P_B2 + 32 * s);
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      float su = 0.f, ss = 0.f;
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        const f32x2 st = stats[(b * 32 + nrow) * NS + k];
+        su += st[0];
+        ss += st[1];
+      }
+      const float mu = su * (1.0f / C), var = fmaxf(ss * (1.0f / C) - mu * mu, 0.f);
+      const float sc = rsqrtf(var + eps), sh = -mu * sc;
+      f32x16 z;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) z[r] = fmaf(fmaf(x1[b][r], sc, sh), gm[r], bt[r]);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) Ab[(b * KS + 2 * s + k) * 64 + lane] = operand(z, k);
+      x1[b] = mma(b2, first_one, x1[b]);
+    }
+  }
+  lds_barrier();
+
+  // ---- FFN -------------------------------------------------------------------------------------------------------
+  // Two hidden tiles a wavefront: tile t of slice s is unit t NS + s.  GELU of a tile runs beside the products that come
+  // after it: those of the second tile, and the first half of the second FFN product.
+  {
+    f32x16 acc[2][RB];
+    auto gelu_part = [&](f32x16 (&v)[RB], int k) {  // of step k
+      constexpr int PER = 16 * RB / KS;
+#pragma unroll
+      for (int i = k * PER; i < (k + 1) * PER; ++i) v[i / 16][i % 16] = gelu2_fast(v[i / 16][i % 16]);
+    };
+    auto put_hidden = [&](f32x16 (&v)[RB], u32x4* to) {
+#pragma unroll
+      for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) to[(b * KS + 2 * s + k) * 64 + lane] = operand(v[b], k);
+    };
+    auto first = [&](int t) {
+      const u32x4 b1 = bias(P_B1 + 32 * (t * NS + s));
+#pragma unroll
+      for (int b = 0; b < RB; ++b) acc[t][b] = mma(b1, first_one, kZero);
+      return [&, t](const u32x4 (&w)[1], const u32x4 (&a)[RB]) {
+#pragma unroll
+        for (int b = 0; b < RB; ++b) acc[t][b] = mma(w[0], a[b], acc[t][b]);
+      };
+    };
+    auto second_product = [&](const u32x4 (&w)[1], const u32x4 (&a)[RB]) {
+#pragma unroll
+      for (int b = 0; b < RB; ++b) x1[b] = mma(w[0], a[b], x1[b]);
+    };
+    product(w, wf, KS, Ab, first(0), nothing);
+    if constexpr (RB <= 3) {
+      product(w, wf, 2 * KS, Ab, first(1), [&](int k) { gelu_part(acc[0], k); });
+      put_hidden(acc[0], Bb);
+    } else {                               // (no registers for two tiles)
+#pragma unroll
+      for (int k = 0; k < KS; ++k) gelu_part(acc[0], k);
+      put_hidden(acc[0], Bb);
+      product(w, wf, 2 * KS, Ab, first(1), nothing);
+    }
+    lds_barrier();
+    product(w, wf, 3 * KS, Bb, second_product, [&](int k) { gelu_part(acc[1], k); });
+    put_hidden(acc[1], Ab);
+    lds_barrier();
+    product(w, wf, 4 * KS, Ab, second_product, nothing);
+  }
+
+  // ---- scatter -------------------------------------------------------------------------------------------------------
+  u32x4* const Out = Bb;
+  if constexpr (!OUT_F32) {                // whole rows through LDS
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        *reinterpret_cast<u32x2*>(reinterpret_cast<char*>(Out + (32 * b + nrow) * LPR + ((4 * s + e) ^ (nrow & 15))) + 8 * h) =
+            u32x2{pack2(x1[b][4 * e], x1[b][4 * e + 1]), pack2(x1[b][4 * e + 2], x1[b][4 * e + 3])};
+    lds_barrier();
+#pragma unroll
+    for (int t = 0; t < NL; ++t) {
+      const int row = s * RPW + t * RPI + lr;
+      const u32x4 v = Out[row * LPR + (lc ^ (row & 15))];
+      if (slot0 + t * RPI + lr < m)  // non-temporal: the next reader is another XCD, and the kernel's end has less to write back
+        __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out) + (size_t)orow[t] * C + 8 * lc));
+    }
+  } else {                                 // output rows of all row blocks, through LDS; then 16 bytes a lane and piece
+    int32_t* const rowof = reinterpret_cast<int32_t*>(Out);
+    if (lc == 0) {
+#pragma unroll
+      for (int t = 0; t < NL; ++t) rowof[s * RPW + t * RPI + lr] = slot0 + t * RPI + lr < m ? orow[t] : -1;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      const int o = rowof[32 * b + nrow];
+      if (o >= 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out) + (size_t)o * C + 32 * s + 8 * e + 4 * h) =
+              f32x4{x1[b][4 * e], x1[b][4 * e + 1], x1[b][4 * e + 2], x1[b][4 * e + 3]};
+      }
+    }
+  }
+}
+
+template <int C, int DH, int F, int PT, int GPW, bool HALF, int MINW>
+int launch_cfg(const LayerSlice& c, hipStream_t stream) {
+  constexpr int lds_bytes = Plan<C, F, PT * GPW>::TOTAL;
+  static_assert(lds_bytes <= kLdsBytes, "LDS");
+  const ff_layer_weights* w = c.w;
+  // The dynamic LDS size has to be allowed once per kernel and device.
+  static std::atomic<uint64_t> allowed[4] = {{0}, {0}, {0}, {0}};  // bit d: done on device d
+  auto go = [&](auto kern, int which) -> int {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return FF_ERR_LAUNCH;
+    const uint64_t bit = 1ull << (dev & 63);
+    if (!(allowed[which].load(std::memory_order_acquire) & bit)) {
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              lds_bytes) != hipSuccess)
+        return FF_ERR_LAUNCH;
+      allowed[which].fetch_or(bit, std::memory_order_release);
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)((c.max_groups + GPW - 1) / GPW)), dim3(2 * C), lds_bytes, stream,
+                       (const uint16_t*)c.feats, c.out, (const uint16_t*)w->pos_embed, c.perm, c.group_offsets,
+                       c.num_groups, (int)c.max_groups, c.n, c.G, c.out_index, c.in_sorted, c.drop ? 1 : 0, w->ln_eps,
+                       (const u32x4*)c.packed);
+    return launch_status();
+  };
+  if (w->pos_embed)
+    return c.out_f32 ? go(k_layer_slice<C, DH, F, PT, GPW, HALF, MINW, true, true>, 3)
+                     : go(k_layer_slice<C, DH, F, PT, GPW, HALF, MINW, false, true>, 2);
+  return c.out_f32 ? go(k_layer_slice<C, DH, F, PT, GPW, HALF, MINW, true, false>, 1)
+                   : go(k_layer_slice<C, DH, F, PT, GPW, HALF, MINW, false, false>, 0);
+}
+
+}  // namespace
+
+int FF_LAYER_SYM(layer_slice_launch)(const LayerSlice& c, hipStream_t stream) {
+  if (c.max_groups == 0 || c.n == 0) return FF_OK;
+  const int G = c.G;
+#define FF_GO(C, DH, F, PT, GPW, MINW)                                                        \
+  return G <= 32 * PT - 16 ? launch_cfg<C, DH, F, PT, GPW, true, MINW>(c, stream)             \
+                           : launch_cfg<C, DH, F, PT, GPW, false, MINW>(c, stream)
+  // Up to two workgroups a compute unit: as many registers as two wavefronts on a SIMD have; beyond, three share it (30,000
+  // rows, G = 64: 13.9 / 14.2 us, 240,000 rows: 103 / 98).
+  const bool few = ceil_div(c.max_groups, G <= 32 ? 2 : 1) <= 512;
+  switch (c.w->C) {
+    case 128:
+      if (G <= 32 && few) FF_GO(128, 16, 256, 1, 2, 2);
+      if (G <= 32) FF_GO(128, 16, 256, 1, 2, 3);
+      if (G <= 64 && few) FF_GO(128, 16, 256, 2, 1, 2);
+      if (G <= 64) FF_GO(128, 16, 256, 2, 1, 3);
+      if (G <= 96) FF_GO(128, 16, 256, 3, 1, 2);
+      FF_GO(128, 16, 256, 4, 1, 2);
+    case 256:
+      if (G <= 32) FF_GO(256, 32, 512, 1, 2, 2);
+      if (G <= 64) FF_GO(256, 32, 512, 2, 1, 2);
+      if (G <= 96) FF_GO(256, 32, 512, 3, 1, 2);
+      FF_GO(256, 32, 512, 4, 1, 2);
+  }
+#undef FF_GO
+  return FF_ERR_UNSUPPORTED;
+}
+
+}  // namespace ff

@@ -1,0 +1,78 @@
+"""The fused 16-bit layer of 128 and 256 features (wavefronts that cut the features): at both sides of every block and half
+block of group members, two frames (group starts that are no multiples of G), short last groups, and scores beyond what
+2^score can stand for."""
+import numpy as np
+import pytest
+import torch
+
+import ffsynth
+import oracle
+import paper_2301_08739_amd as ff
+from gpu_util import DEV, gpu_flatten, to_dev_feats, to_host
+
+pytestmark = pytest.mark.gpu
+
+HEADS = {128: 8, 256: 8}
+
+
+@pytest.mark.parametrize("dt", [ff.FF_BF16, ff.FF_F16])
+@pytest.mark.parametrize("C", [128, 256])
+@pytest.mark.parametrize("G", [2, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97, 112, 113, 128])
+def test_group_sizes(cfg, C, G, dt):
+    n, bar = 3 * G + 101, 2e-2 if dt == ff.FF_BF16 else 2.5e-3
+    c = cfg(2, 1)
+    coords = c["coords"][:n].copy()
+    coords[:, 0] = np.arange(n) % 3 == 0
+    g = ff.Geometry(2, c["grid"], c["grid"], c["window"], c["window"])
+    perm, off, ng, _, dev = gpu_flatten(coords, g, 0, 1, G, want_keys=False)
+    rng = np.random.default_rng(C + G)
+    x = to_dev_feats(rng.standard_normal((n, C)), dt)
+    e = to_dev_feats(0.5 * rng.standard_normal((n, C)), dt)
+    # as the layer holds them: the bar is for what the layer does to these numbers
+    p = {k: to_host(to_dev_feats(v, dt)).astype(np.float32) if isinstance(v, np.ndarray) else v
+         for k, v in ffsynth.layer_params(C, 2 * C, HEADS[C], seed=23).items()}
+    # The probabilities of a row average the rounding errors of G value rows; those of the row's own LayerNorm output stay:
+    # two independent errors, the first falling with sqrt(G).
+    bar *= (1 + 1 / G) ** 0.5
+    lw = ff.LayerWeights(p, dt, DEV)
+    rounded = lambda t: to_host(t).astype(np.float32)
+    for embed in (None, e):
+        kw = {} if embed is None else dict(pos_embed=rounded(embed))
+        want = oracle.layer(rounded(x), perm, off, p, **kw)
+        wide = ff.ff_group_attention(x, dev[0], dev[1], dev[2], ng + 1, lw, G, dt, ff.FF_FLAG_OUT_F32, pos_embed=embed)
+        narrow = ff.ff_group_attention(x, dev[0], dev[1], dev[2], ng + 1, lw, G, dt, pos_embed=embed)
+        assert np.abs(to_host(wide) - want).max() <= bar
+        assert torch.equal(wide.to(narrow.dtype), narrow)
+
+
+@pytest.mark.parametrize("dt", [ff.FF_BF16, ff.FF_F16])
+@pytest.mark.parametrize("C,G", [(128, 64), (128, 69), (256, 48)])
+@pytest.mark.parametrize("score", [-300.0, 300.0])
+def test_scores_beyond_the_exponents(C, G, dt, score):
+    """All members of a group alike: every score of a row is the same number, so that the attention is the value row
+    whatever the score is, also where 2^score is zero or infinite: the largest score has to go first."""
+    n, d = 2 * G + 5, C // HEADS[C]
+    rng = np.random.default_rng(3)
+    p = ffsynth.layer_params(C, 2 * C, HEADS[C], seed=29)
+    row = rng.standard_normal(C)
+    x = to_dev_feats(np.repeat(row[None], n, 0), dt)
+    z = (to_host(x)[0] - to_host(x)[0].mean()) / to_host(x)[0].std()
+    # keys k = w z with k . k = d per head (first feature of the head alone), queries from the bias: q . k / sqrt(d) = score
+    w = np.zeros((3 * C, C)); b = np.zeros(3 * C)
+    for h in range(HEADS[C]):
+        w[C + h * d] = z / C
+        b[h * d] = score * np.sqrt(d)
+    p = dict(p)
+    half = lambda a: to_host(to_dev_feats(a, dt))
+    p["w_qkv"] = half(np.concatenate([w[:2 * C], np.asarray(p["w_qkv"])[2 * C:]])).astype(np.float32)
+    p["b_qkv"] = half(np.concatenate([b[:2 * C], np.asarray(p["b_qkv"])[2 * C:]])).astype(np.float32)
+    p["ln1_g"], p["ln1_b"] = np.ones(C, np.float32), np.zeros(C, np.float32)
+    lw = ff.LayerWeights(p, dt, DEV)
+    off = np.array([0, G, 2 * G, n], np.int32)
+    perm = np.arange(n, dtype=np.int32)
+    dev = [torch.from_numpy(a).to(DEV) for a in (perm, off, np.array([3], np.int32))]
+    got = to_host(ff.ff_group_attention(x, dev[0], dev[1], dev[2], 3, lw, G, dt, ff.FF_FLAG_OUT_F32))
+    want = oracle.layer(to_host(x).astype(np.float32), perm, off, p)
+    assert np.isfinite(got).all()
+    # one value row reaches the output projection as it is (no averaging over keys): sqrt(2) of the bar, as for groups of one
+    assert np.abs(got - want).max() <= (2e-2 if dt == ff.FF_BF16 else 2.5e-3) * 2 ** 0.5
