@@ -14,7 +14,8 @@
 //     holds in the order the pass reads them.  Key generation writes the rows of the first pass
 //     (plain stores) and zeroes the others; each pass adds, for every word it places, one to the
 //     row of the tile the word lands in for the next pass.  Nothing has to be cleared beforehand.
-//   * Small clouds (at most 128 tiles of 1024 words, see kSmallMaxTiles: launch and latency bound): digits of up to 10
+//   * Clouds of up to 131,072 pillars over ordinary geometries take no passes at all: k_direct below, one launch.
+//   * Small clouds otherwise (at most 128 tiles of 1024 words, see kSmallMaxTiles: launch and latency bound): digits of up to 10
 //     bits, and a pass reads the whole table of its pass itself (column sums = global digit
 //     starts, rows of earlier tiles = its own offsets): key generation + one launch per pass.
 //   * Larger clouds (bandwidth bound): per-word atomics would dominate, so passes after the first
@@ -27,6 +28,8 @@
 //     the whole frame field; otherwise two small output kernels run.
 #include "common.h"
 #include "pack_weights.h"
+#include <atomic>
+#include <type_traits>
 
 namespace ff {
 
@@ -180,14 +183,15 @@ __device__ __forceinline__ uint64_t exported_key(uint64_t k, const KeyParams& kp
 // attention kernels (pack_weights.h), work that does not depend on the sort and would otherwise cost
 // a launch of its own in front of the first layer.  Such a launch has a wider grid; the workgroups
 // are numbered in dispatch order, the first tiles * sorts of them sort, the rest pack.
-__device__ __forceinline__ void pack_tail(const PackJob& pack, int id) {
+// (id: of 256 threads, of which this is thread t)
+__device__ __forceinline__ void pack_tail(const PackJob& pack, int id, int t) {
   int layer = id / pack.blocks;
-  const int blk = id - layer * pack.blocks;
+  t += (id - layer * pack.blocks) * 256;
   if (layer >= pack.layers) return;
   layer += pack.first;
-  if (pack.mode == kPackF32) pack_weights_f32_block(pack.pb, layer, blk, pack.C, pack.F, pack.total_frags);
-  else if (pack.mode == kPackF16) pack_weights_block<true>(pack.pb, layer, blk, pack.C, pack.F, pack.total_frags);
-  else pack_weights_block<false>(pack.pb, layer, blk, pack.C, pack.F, pack.total_frags);
+  if (pack.mode == kPackF32) pack_weights_f32_thread(pack.pb, layer, t, pack.C, pack.F, pack.total_frags);
+  else if (pack.mode == kPackF16) pack_weights_thread<true>(pack.pb, layer, t, pack.C, pack.F, pack.total_frags);
+  else pack_weights_thread<false>(pack.pb, layer, t, pack.C, pack.F, pack.total_frags);
 }
 
 template <int RB, int KPT>
@@ -195,10 +199,10 @@ __global__ __launch_bounds__(kSortThreads) void k_keygen(const int32_t* __restri
                                                           int64_t tiles, uint64_t* __restrict__ words,
                                                           uint32_t* __restrict__ counts, PackJob pack, PointCells pts) {
   constexpr int BINS = 1 << RB, TILE = kSortThreads * KPT;
-  static_assert(kSortThreads == 256, "pack_weights_block works in workgroups of 256 threads");
+  static_assert(kSortThreads == 256, "pack_tail counts in 256 threads");
   const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;  // dispatch order
   if (wg >= tiles * gridDim.y) {  // the same for the whole workgroup
-    pack_tail(pack, (int)(wg - tiles * gridDim.y));
+    pack_tail(pack, (int)(wg - tiles * gridDim.y), (int)threadIdx.x);
     return;
   }
   __shared__ uint32_t h[BINS];
@@ -345,7 +349,7 @@ __global__ __launch_bounds__(kSortThreads) void k_pass(const uint64_t* __restric
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;  // dispatch order
   if (wg >= tiles * gridDim.y) {  // the same for the whole workgroup
-    pack_tail(pack, (int)(wg - tiles * gridDim.y));
+    pack_tail(pack, (int)(wg - tiles * gridDim.y), (int)threadIdx.x);
     return;
   }
   const int s = (int)(wg / tiles);
@@ -697,6 +701,262 @@ __global__ __launch_bounds__(256) void k_finalize(const uint64_t* __restrict__ s
   if (rel == gi * G && gi < gbase[fb + 1] - gbase[fb]) bt.group_offsets[s][gbase[fb] + gi] = (int32_t)p;
 }
 
+// ---- small clouds in one launch ------------------------------------------------------------------------------------
+// A workgroup owns a range of key values of one sort.  It looks at every pillar of the cloud, works out the key, counts the
+// ones below its range (where its share of the output begins) and takes those inside: into a list, and as bits of a map with
+// one bit per key value.  Prefix counts of the bits are the sorted positions: no digits, no passes, no other workgroup's
+// results.  Fewer bits than pillars say that some share a cell: those are put in order of their index by comparing the
+// entries of a word of the map.  A range with more pillars than the lists hold is halved, down to a single key value, whose
+// pillars leave in the order in which they come.
+//
+// What bounds it: the look at all pillars, 12 bytes and some 20 vector instructions each in every workgroup, 0.23 us for
+// every thousand of them, and 6 us for the launch, the scan and the way out; the radix path is three dependent launches of
+// 5 to 12 us.  Measured, radix path / this one, us a call: one sort, 2,000 pillars 21 / 8.6, 12,345 22.5 / 11.2, 30,000
+// 23 / 15, 131,072 41 / 37.5; four sorts, 30,000 35.5 / 25, 80,000 61.5 / 38.
+constexpr int kDirectThreads = 1024;
+constexpr int kDirectWaves = kDirectThreads / 64;
+constexpr int kDirectList = 1024;           // pillars of a range at a time that a wavefront finds (4 bytes each),
+constexpr int kDirectSorted = 2048;         // and of all wavefronts when some share a cell
+constexpr int kDirectMaxRows = 131072;      // pillars,
+constexpr int kDirectMaxCodes = 131072;     // and key values of a workgroup's range; a list entry of 32 bits holds one of each
+constexpr int kDirectMaxFrames = 16;
+constexpr int kDirectMaxGrid = 4096;        // cells an axis, shift included: windows by a 24-bit multiplication
+
+// How a sort makes its keys.  Window of a shifted coordinate X: w = (X * mul) >> 20, exact below 4096 for windows up to 256.
+// With the local coordinate X - w win in its field, unit_l, and the window in its own, unit_w, an axis adds
+// X unit_l + w (unit_w - win unit_l).
+struct DirectAxis { int32_t shift; uint32_t max, mul, unit_l, rest_w; };  // max: largest shifted coordinate
+struct DirectKeys { DirectAxis x, y, z; uint32_t unit_b; };
+struct DirectBatch {
+  DirectKeys k[kMaxSorts];
+  uint32_t range;    // key values of a workgroup
+  int32_t parts;     // workgroups of a sort
+};
+
+template <bool Z, bool FRAMES>
+__device__ __forceinline__ uint32_t direct_key(const int32_t* c, const DirectKeys& k, uint32_t last_frame) {
+  // A coordinate outside the geometry counts as the last cell: its key stays in range, whatever it is.
+  auto axis = [](uint32_t key, int32_t v, const DirectAxis& a) -> uint32_t {
+    const uint32_t at = (uint32_t)(v + a.shift), X = at < a.max ? at : a.max;
+    return __umul24(__umul24(X, a.mul) >> 20, a.rest_w) + (__umul24(X, a.unit_l) + key);
+  };
+  uint32_t key = 0;
+  if constexpr (FRAMES) {
+    const uint32_t f = (uint32_t)c[0], b = f < last_frame ? f : last_frame;
+    key = __umul24(b, k.unit_b);
+  }
+  key = axis(axis(key, c[1], k.x), c[2], k.y);
+  if constexpr (Z) key = axis(key, c[3], k.z);
+  return key;
+}
+
+// The group list of a sort from the frames' sizes alone, by one workgroup.
+__device__ __forceinline__ void direct_groups(const int32_t* __restrict__ coords, int stride, int n, int B, int G, int drop,
+                                              int32_t* __restrict__ goff, int32_t* __restrict__ num_groups,
+                                              uint32_t* starts /*[kDirectMaxFrames]*/) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (tid < kDirectMaxFrames) starts[tid] = 0u;
+  __syncthreads();
+  if (B > 1) {
+    uint32_t count = 0;                      // lane b: rows of frames below b that this wavefront has seen
+    for (int i0 = 0; i0 < n; i0 += kDirectThreads * 8) {
+      uint32_t f[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int i = i0 + u * kDirectThreads + tid;
+        f[u] = i < n ? (uint32_t)coords[(uint32_t)(i * stride)] : ~0u;  // (nobody's, like ids outside, which count as the last frame)
+      }
+      for (int b = 1; b < B; ++b) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c += (uint32_t)__popcll(__ballot(f[u] < (uint32_t)b));
+        count += lane == b ? c : 0u;
+      }
+    }
+    if (lane < B) atomicAdd(&starts[lane], count);
+    __syncthreads();
+  }
+  uint32_t groups = 0;
+  for (int b = 0; b < B; ++b) {
+    const uint32_t from = starts[b], to = b + 1 < B ? starts[b + 1] : (uint32_t)n;
+    const uint32_t g = groups_of(to - from, G, drop);
+    for (uint32_t k = tid; k < g; k += kDirectThreads) goff[groups + k] = (int32_t)(from + k * (uint32_t)G);
+    groups += g;
+  }
+  if (tid == 0) {
+    *num_groups = (int32_t)groups;
+    goff[groups] = n;
+  }
+}
+
+template <bool Z, bool FRAMES>
+__global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __restrict__ coords, int n, int S, Batch bt,
+                                                               DirectBatch db, int G, int drop, PackJob pack) {
+  constexpr int STRIDE = Z ? 4 : 3, ROWS = 4;  // rows of a thread in a round; the next round's are on their way meanwhile
+  constexpr int ROUND = kDirectThreads * ROWS;
+  __shared__ uint32_t wave_totals[kDirectWaves], starts[kDirectMaxFrames];
+  __shared__ uint32_t taken, below, full;
+  extern __shared__ uint32_t bits[];                            // [range / 32]
+  uint32_t* const first = bits + db.range / 32;                 // [range / 32] position of a word's first pillar
+  uint32_t* const sorted = first + db.range / 32;               // [kDirectSorted] (key - lo) << idx_bits | index
+  uint32_t* const list = sorted + kDirectSorted;                // [kDirectWaves][kDirectList]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int parts = db.parts;
+  if ((int)blockIdx.x >= S * (parts + 1)) {
+    pack_tail(pack, ((int)blockIdx.x - S * (parts + 1)) * (kDirectThreads / 256) + (tid >> 8), tid & 255);
+    return;
+  }
+  if ((int)blockIdx.x >= S * parts) {
+    const int s = blockIdx.x - S * parts;
+    direct_groups(coords, STRIDE, n, bt.kp[s].B, G, drop, bt.group_offsets[s], bt.num_groups[s], starts);
+    return;
+  }
+
+  const int s = blockIdx.x % S, part = blockIdx.x / S;
+  const DirectKeys dk = db.k[s];
+  const int idx_bits = bt.kp[s].idx_bits;
+  const uint32_t idx_mask = (1u << idx_bits) - 1u;
+  const uint32_t last_frame = (uint32_t)bt.kp[s].B - 1u, end = 1u << bt.kp[s].key_bits;
+  uint32_t lo = (uint32_t)part * db.range;
+  if (lo >= end) return;
+  const uint32_t hi = end - lo < db.range ? end : lo + db.range;
+  int32_t* __restrict__ const perm_s = bt.perm[s];
+  int32_t* __restrict__ const inv_s = bt.inv_perm[s];
+  uint64_t* __restrict__ const keys_s = bt.keys_sorted[s];
+  auto put = [&](uint32_t pos, uint32_t key, uint32_t i) {
+    perm_s[pos] = (int32_t)i;
+    if (inv_s) inv_s[i] = (int32_t)pos;
+    if (keys_s) {
+      uint32_t b;
+      keys_s[pos] = exported_key(key, bt.kp[s], &b);
+    }
+  };
+  struct Row { int32_t c[STRIDE]; };
+  auto fetch = [&](Row (&r)[ROWS], int i0) {
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+      const int i = i0 + u * kDirectThreads + tid;
+      const uint32_t at = __umul24((uint32_t)(i < n ? i : n - 1), (uint32_t)sizeof(Row));
+      r[u] = *reinterpret_cast<const Row*>(reinterpret_cast<const char*>(coords) + at);
+    }
+  };
+  uint32_t* const mine = list + (tid >> 6) * kDirectList;
+  uint32_t base = 0, len = hi - lo;
+  bool count_below = true;
+  while (lo < hi) {  // (the same for the whole workgroup, as is everything that decides below)
+    const uint32_t words = (len + 31u) >> 5;
+    for (uint32_t w = tid; w < words; w += kDirectThreads) bits[w] = 0u;
+    if (tid == 0) { taken = 0u; below = 0u; full = 0u; }
+    __syncthreads();
+    Row r[2][ROWS];
+    int begin = 0;
+    asm volatile("" : "+s"(begin));          // (or the addresses of the first round would be kept through everything that follows)
+    fetch(r[0], begin);
+    uint32_t less = 0, count = 0;            // count: of the wavefront
+    auto look = [&](Row (&now)[ROWS], int i0, auto whole) {
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) {
+        uint32_t key = direct_key<Z, FRAMES>(now[u].c, dk, last_frame);
+        asm volatile("" : "+v"(key));        // (computed by every lane: under a condition its load would be waited for alone)
+        const uint32_t i = (uint32_t)(i0 + u * kDirectThreads + tid);
+        if (!decltype(whole)::value) key = i < (uint32_t)n ? key : 0xffffffffu;
+        less += key < lo ? 1u : 0u;
+        const uint32_t code = key - lo;
+        const uint64_t in = __ballot(code < len);
+        if (code < len) {
+          const uint32_t at = count + __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));
+          if (at < (uint32_t)kDirectList) mine[at] = (code << idx_bits) | i;
+          atomicOr(&bits[code >> 5], 1u << (code & 31u));
+        }
+        count += (uint32_t)__popcll(in);
+      }
+    };
+    int i0 = begin;
+    for (; i0 + 2 * ROUND <= n; i0 += 2 * ROUND) {
+      fetch(r[1], i0 + ROUND);
+      look(r[0], i0, std::true_type());
+      fetch(r[0], i0 + 2 * ROUND);
+      look(r[1], i0 + ROUND, std::true_type());
+    }
+    if (i0 + ROUND < n) {
+      fetch(r[1], i0 + ROUND);
+      look(r[0], i0, std::true_type());
+      look(r[1], i0 + ROUND, std::false_type());
+    } else if (i0 < n) {
+      look(r[0], i0, std::false_type());
+    }
+    if (count_below) {
+      const uint32_t w = wave_inclusive_scan(less);
+      if (lane == 63) atomicAdd(&below, w);
+    }
+    if (lane == 0) {
+      atomicAdd(&taken, count);
+      if (count > (uint32_t)kDirectList) full = 1u;
+    }
+    __syncthreads();
+    if (count_below) { base = below; count_below = false; }
+    const uint32_t T = taken;
+    const uint32_t per = (words + kDirectThreads - 1u) / kDirectThreads, w0 = tid * per;
+    uint32_t sum = 0, cells;
+    for (uint32_t w = w0; w < w0 + per && w < words; ++w) sum += (uint32_t)__popc(bits[w]);
+    uint32_t run = block_exclusive_scan<kDirectThreads>(sum, wave_totals, &cells);
+    const bool plain = cells == T;           // no two pillars share a cell
+    if (len > 1u && (full || (!plain && T > (uint32_t)kDirectSorted))) {
+      len = (len + 1u) >> 1;
+      __syncthreads();
+      continue;
+    }
+    if (plain) {
+      for (uint32_t w = w0; w < w0 + per && w < words; ++w) {
+        first[w] = run;
+        run += (uint32_t)__popc(bits[w]);
+      }
+      __syncthreads();
+      for (uint32_t e = lane; e < count; e += 64) {
+        const uint32_t v = mine[e], code = v >> idx_bits, w = code >> 5;
+        put(base + first[w] + (uint32_t)__popc(bits[w] & ((1u << (code & 31u)) - 1u)), lo + code, v & idx_mask);
+      }
+    } else if (len == 1u) {                  // one key value: in order of the index
+      uint32_t done = 0;
+      for (int i0 = 0; i0 < n; i0 += kDirectThreads) {
+        const int i = i0 + tid;
+        const bool in = i < n && direct_key<Z, FRAMES>(coords + (uint32_t)(i < n ? i : 0) * STRIDE, dk, last_frame) == lo;
+        uint32_t total;
+        const uint32_t at = block_exclusive_scan<kDirectThreads>(in ? 1u : 0u, wave_totals, &total);
+        if (in) put(base + done + at, lo, (uint32_t)i);
+        done += total;
+      }
+    } else {                                 // pillars of a word instead of its bits
+      __syncthreads();
+      for (uint32_t w = tid; w < words; w += kDirectThreads) bits[w] = 0u;
+      __syncthreads();
+      for (uint32_t e = lane; e < count; e += 64) atomicAdd(&bits[mine[e] >> (idx_bits + 5)], 1u);
+      __syncthreads();
+      sum = 0;
+      for (uint32_t w = w0; w < w0 + per && w < words; ++w) sum += bits[w];
+      run = block_exclusive_scan<kDirectThreads>(sum, wave_totals, nullptr);
+      for (uint32_t w = w0; w < w0 + per && w < words; ++w) {
+        const uint32_t v = bits[w];
+        first[w] = bits[w] = run;            // bits: where the word's next pillar goes
+        run += v;
+      }
+      __syncthreads();
+      for (uint32_t e = lane; e < count; e += 64) sorted[atomicAdd(&bits[mine[e] >> (idx_bits + 5)], 1u)] = mine[e];
+      __syncthreads();
+      for (uint32_t e = tid; e < T; e += kDirectThreads) {
+        const uint32_t v = sorted[e], q0 = first[v >> (idx_bits + 5)], q1 = bits[v >> (idx_bits + 5)];
+        uint32_t pos = q0;
+        for (uint32_t q = q0; q < q1; ++q) pos += sorted[q] < v ? 1u : 0u;
+        put(base + pos, lo + (v >> idx_bits), v & idx_mask);
+      }
+    }
+    base += T;
+    lo += len;
+    len = hi - lo;
+    __syncthreads();
+  }
+}
+
 // Pass plan for keys of `key_bits` bits: digit width and number of passes.
 struct PassPlan { bool small; int kpt, rb, passes; int64_t tiles; };
 // (`sorts` decides between the paths only: digit width, passes and tiles, and with them the workspace, do not depend on it)
@@ -711,6 +971,44 @@ inline PassPlan pass_plan(int64_t n, int key_bits, int sorts) {
   pp.rb = 8 * pp.passes >= key_bits ? 8 : 9 * pp.passes >= key_bits ? 9 : 10;
   pp.tiles = ceil_div(n > 0 ? n : 1, (int64_t)kSortThreads * pp.kpt);
   return pp;
+}
+
+// Whether this cloud is sorted in one launch (k_direct), and how.
+bool direct_plan(int64_t n, const ff_geom* g, const FlattenZ* z, int sorts, const Batch& bt, int key_bits, DirectBatch* db) {
+  if (n > kDirectMaxRows || g->num_frames > kDirectMaxFrames || key_bits > 24) return false;
+  const int64_t codes = (int64_t)1 << key_bits;
+  const int code_bits = 32 - bt.kp[0].idx_bits;
+  const int64_t most = code_bits >= 17 ? kDirectMaxCodes : (int64_t)1 << code_bits;
+  // As many workgroups as fill the chip with all sorts (an eighth of it left to the weight packing), fewer for few pillars.
+  int64_t parts = sorts >= 4 ? 56 : 64;
+  const int64_t enough = ceil_div(n, 128);
+  if (parts > enough) parts = enough;
+  if (parts * most < codes) parts = ceil_div(codes, most);
+  // Beyond one workgroup a compute unit there is a second round: it pays for few pillars (four sorts of eight frames, 512
+  // workgroups, radix path / this one: 16,000 pillars 39 / 26 us, 60,000 52 / 57).
+  if (parts * sorts > 512 || (parts * sorts > 256 && n > 32768)) return false;
+  db->parts = (int32_t)parts;
+  db->range = (uint32_t)(ceil_div(ceil_div(codes, parts), (int64_t)32) * 32);
+  for (int s = 0; s < sorts; ++s) {
+    const KeyParams& kp = bt.kp[s];
+    DirectKeys& k = db->k[s];
+    const int at_l2 = kp.bits_l3, at_l1 = at_l2 + kp.bits_l2, at_w3 = at_l1 + kp.bits_l1, at_w2 = at_w3 + kp.bits_w3,
+              at_w1 = at_w2 + kp.bits_w2;
+    auto axis = [](DirectAxis& a, int64_t grid, int shift, int win, int at_w, int at_l) {
+      a.shift = shift;
+      a.max = (uint32_t)(grid + shift - 1);
+      a.mul = ((1u << 20) + (uint32_t)win - 1u) / (uint32_t)win;
+      a.unit_l = 1u << at_l;
+      a.rest_w = (1u << at_w) - (uint32_t)win * a.unit_l;  // (the window's field begins where the local one's values end)
+      return grid + shift <= kDirectMaxGrid;
+    };
+    if (!axis(k.x, g->grid_x, kp.sx, kp.win_x, kp.axis == 0 ? at_w1 : at_w2, kp.axis == 0 ? at_l1 : at_l2) ||
+        !axis(k.y, g->grid_y, kp.sy, kp.win_y, kp.axis == 0 ? at_w2 : at_w1, kp.axis == 0 ? at_l2 : at_l1) ||
+        !axis(k.z, z ? z->grid_z : 1, kp.sz, kp.win_z, at_w3, 0))
+      return false;
+    k.unit_b = 1u << (at_w1 + kp.bits_w1);
+  }
+  return true;
 }
 
 struct Layout {
@@ -866,6 +1164,31 @@ static int flatten_launch_impl(const int32_t* coords, const PointCells* pts, int
   uint32_t* counts = (uint32_t*)(ws + L.off_counts);
   uint32_t* totals = (uint32_t*)(ws + L.off_totals);
   int32_t* frame_tab = (int32_t*)(ws + L.off_frames);
+
+  DirectBatch db;
+  if (n > 0 && !pts && direct_plan(n, g, z, num_sorts, bt, max_key_bits, &db)) {
+    PackJob job = PackJob();
+    job.layers = 0; job.blocks = 1;
+    if (pack) job = *pack;
+    const unsigned blocks = (unsigned)(num_sorts * (db.parts + 1) + ceil_div((int64_t)job.layers * job.blocks, kDirectThreads / 256));
+    const size_t lds = (size_t)(kDirectWaves * kDirectList + kDirectSorted) * 4 + db.range / 32 * 8;
+    static std::atomic<uint64_t> allowed[4] = {{0}, {0}, {0}, {0}};  // bit d: the largest dynamic LDS size is allowed on device d
+    auto go = [&](auto kern, int which) -> int {
+      int dev = 0;
+      if (hipGetDevice(&dev) != hipSuccess) return FF_ERR_LAUNCH;
+      const uint64_t bit = 1ull << (dev & 63);
+      if (!(allowed[which].load(std::memory_order_acquire) & bit)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (kDirectWaves * kDirectList + kDirectSorted) * 4 + kDirectMaxCodes / 32 * 8) != hipSuccess)
+          return FF_ERR_LAUNCH;
+        allowed[which].fetch_or(bit, std::memory_order_release);
+      }
+      hipLaunchKernelGGL(kern, dim3(blocks), dim3(kDirectThreads), lds, stream, coords, (int)n, num_sorts, bt, db, G, drop, job);
+      return launch_status();
+    };
+    if (g->num_frames > 1) return z ? go(k_direct<true, true>, 3) : go(k_direct<false, true>, 2);
+    return z ? go(k_direct<true, false>, 1) : go(k_direct<false, false>, 0);
+  }
 
   int cur = 0;
   bool outputs_done = false;

@@ -768,7 +768,7 @@ int launch_cfg(const LayerF32& c, hipStream_t stream) {
 }
 
 __global__ __launch_bounds__(256) void k_pack_f32(PackBatch pb, int C, int F, int total_frags) {
-  pack_weights_f32_block(pb, blockIdx.y, blockIdx.x, C, F, total_frags);
+  pack_weights_f32_thread(pb, blockIdx.y, (int)(blockIdx.x * 256 + threadIdx.x), C, F, total_frags);
 }
 
 }  // namespace

@@ -77,7 +77,7 @@ constexpr bool kHalf = true;
 constexpr bool kHalf = false;
 #endif
 __global__ __launch_bounds__(256) void k_pack_weights(PackBatch pb, int C, int F, int total_frags) {
-  pack_weights_block<kHalf>(pb, blockIdx.y, blockIdx.x, C, F, total_frags);
+  pack_weights_thread<kHalf>(pb, blockIdx.y, (int)(blockIdx.x * 256 + threadIdx.x), C, F, total_frags);
 }
 
 // ---- the fused layer ------------------------------------------------------------------------------

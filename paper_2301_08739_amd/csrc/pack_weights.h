@@ -77,16 +77,14 @@ template <bool HALF> __device__ __forceinline__ uint16_t pack_f32_to_el(float f)
 __host__ __device__ constexpr int pack_param_count(int C, int F) { return 7 * C + F; }
 // bytes of the parameter block, padded to whole 1 KB pieces (the unit of the kernel's copy to LDS)
 __host__ __device__ constexpr int pack_param_bytes(int C, int F) { return (pack_param_count(C, F) * 4 + 1023) / 1024 * 1024; }
-// Work of workgroup `block` (256 threads) of layer `layer`.
+// Work of thread t of layer `layer`.
 template <bool HALF>
-__device__ __forceinline__ void pack_weights_block(const PackBatch& pb, int layer, int block, int C, int F,
-                                                   int total_frags) {
+__device__ __forceinline__ void pack_weights_thread(const PackBatch& pb, int layer, int t, int C, int F, int total_frags) {
   const uint16_t* __restrict__ w_qkv = pb.w_qkv[layer];
   const uint16_t* __restrict__ w_o = pb.w_o[layer];
   const uint16_t* __restrict__ w1 = pb.w1[layer];
   const uint16_t* __restrict__ w2 = pb.w2[layer];
   uint4* __restrict__ out = pb.out[layer];
-  const int t = block * 256 + (int)threadIdx.x;
   const int frag = t >> 6, lane = t & 63, i = lane & 15, q = lane >> 4;
   if (frag >= total_frags && t - total_frags * 64 >= 8 * C) {  // the other per-feature vectors, one thread each
     const int pidx = t - total_frags * 64 - 8 * C;             // 0 .. 6C + F - 1; the folded bias sits at [3C, 4C)
@@ -197,9 +195,7 @@ __device__ __forceinline__ uint16_t split_part(float& v) {
   v = (part & 0x7f80u) == 0x7f80u ? 0.f : v - bf16_to_f32(part);
   return part;
 }
-__device__ __forceinline__ void pack_weights_f32_block(const PackBatch& pb, int layer, int block, int C, int F,
-                                                       int total_frags) {
-  const int t = block * 256 + (int)threadIdx.x;
+__device__ __forceinline__ void pack_weights_f32_thread(const PackBatch& pb, int layer, int t, int C, int F, int total_frags) {
   const int frag = t >> 6, lane = t & 63, m = lane & 31, h = lane >> 5;
   if (frag >= total_frags) return;
   const int KS = C / 16, HT = F / C, slice_fr = (4 + HT) * KS + F / 16;
