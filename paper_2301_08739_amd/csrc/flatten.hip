@@ -705,18 +705,25 @@ __global__ __launch_bounds__(256) void k_finalize(const uint64_t* __restrict__ s
 // A workgroup owns a range of key values of one sort.  It looks at every pillar of the cloud, works out the key, counts the
 // ones below its range (where its share of the output begins) and takes those inside: into a list, and as bits of a map with
 // one bit per key value.  Prefix counts of the bits are the sorted positions: no digits, no passes, no other workgroup's
-// results.  Fewer bits than pillars say that some share a cell: those are put in order of their index by comparing the
-// entries of a word of the map.  A range with more pillars than the lists hold is halved, down to a single key value, whose
-// pillars leave in the order in which they come.
+// results.  Fewer bits than pillars say that some share a cell: then the list's entries, which are different numbers in the
+// order wanted, are brought together by words of the map and ranked there, or, where a word has many, sorted as they are.  A
+// range with more pillars than the list holds is cut where counts of its key values say; pillars of a key value that alone has
+// too many leave in the order in which they come.
 //
 // What bounds it: the look at all pillars, 12 bytes and some 20 vector instructions each in every workgroup, 0.23 us for
 // every thousand of them, and 6 us for the launch, the scan and the way out; the radix path is three dependent launches of
 // 5 to 12 us.  Measured, radix path / this one, us a call: one sort, 2,000 pillars 21 / 8.6, 12,345 22.5 / 11.2, 30,000
 // 23 / 15, 131,072 41 / 37.5; four sorts, 30,000 35.5 / 25, 80,000 61.5 / 38.
+// What it is not made for are clouds whose pillars share a window's few cells, tens or hundreds each: one workgroup then has
+// them all (30,000 pillars on a cell 27 / 124, on nine 27 / 440; at three a cell it is even, 28 / 28; 120,000 of which a
+// fifth share one, 41 / 40, four sorts 80 / 62).  Pillars are cells that a cloud of points fills, one each.
 constexpr int kDirectThreads = 1024;
 constexpr int kDirectWaves = kDirectThreads / 64;
-constexpr int kDirectList = 1024;           // pillars of a range at a time that a wavefront finds (4 bytes each),
-constexpr int kDirectSorted = 2048;         // and of all wavefronts when some share a cell
+constexpr int kDirectOwn = 1024;            // pillars of a range that a wavefront finds (4 bytes each),
+constexpr int kDirectList = kDirectWaves * kDirectOwn;  // all together,
+constexpr int kDirectShared = 8192;         // and when some share a cell and the wavefronts' lists have to be joined
+constexpr int kDirectRanked = 256;          // pillars of 32 key values that are ranked by comparing them all (80 each: 28 us a
+                                            // call of 30,000; sorted 45)
 constexpr int kDirectMaxRows = 131072;      // pillars,
 constexpr int kDirectMaxCodes = 131072;     // and key values of a workgroup's range; a list entry of 32 bits holds one of each
 constexpr int kDirectMaxFrames = 16;
@@ -789,17 +796,37 @@ __device__ __forceinline__ void direct_groups(const int32_t* __restrict__ coords
   }
 }
 
+// a[0 .. T) in ascending order; a has room for the next power of two.  Pairs up to 64 apart stay within the 128 entries of a
+// wavefront, whose LDS accesses are in order.
+__device__ __forceinline__ void direct_sort(uint32_t* a, uint32_t T) {
+  uint32_t P = 128;
+  while (P < T) P <<= 1;
+  for (uint32_t e = T + threadIdx.x; e < P; e += kDirectThreads) a[e] = 0xffffffffu;
+  __syncthreads();
+  for (uint32_t k = 2; k <= P; k <<= 1) {
+    for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+      for (uint32_t t = threadIdx.x; t < P / 2; t += kDirectThreads) {
+        const uint32_t i = 2u * t - (t & (j - 1u)), x = a[i], y = a[i + j];
+        if ((x > y) == ((i & k) == 0u)) { a[i] = y; a[i + j] = x; }
+      }
+      if (j > 64u) __syncthreads();
+      else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    if (k > 64u) __syncthreads();            // (the next step pairs further than 64 apart)
+  }
+}
+
 template <bool Z, bool FRAMES>
 __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __restrict__ coords, int n, int S, Batch bt,
                                                                DirectBatch db, int G, int drop, PackJob pack) {
   constexpr int STRIDE = Z ? 4 : 3, ROWS = 4;  // rows of a thread in a round; the next round's are on their way meanwhile
   constexpr int ROUND = kDirectThreads * ROWS;
-  __shared__ uint32_t wave_totals[kDirectWaves], starts[kDirectMaxFrames];
-  __shared__ uint32_t taken, below, full;
+  __shared__ uint32_t wave_totals[kDirectWaves], found[kDirectWaves], starts[kDirectMaxFrames];
+  __shared__ uint32_t taken, below, full, head, cut;
   extern __shared__ uint32_t bits[];                            // [range / 32]
   uint32_t* const first = bits + db.range / 32;                 // [range / 32] position of a word's first pillar
-  uint32_t* const sorted = first + db.range / 32;               // [kDirectSorted] (key - lo) << idx_bits | index
-  uint32_t* const list = sorted + kDirectSorted;                // [kDirectWaves][kDirectList]
+  uint32_t* const joined = first + db.range / 32;               // [kDirectShared] list of all wavefronts, or counts
+  uint32_t* const list = joined + kDirectShared;                // [kDirectList] (key - lo) << idx_bits | index
   const int tid = threadIdx.x, lane = tid & 63;
   const int parts = db.parts;
   if ((int)blockIdx.x >= S * (parts + 1)) {
@@ -840,58 +867,144 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
       r[u] = *reinterpret_cast<const Row*>(reinterpret_cast<const char*>(coords) + at);
     }
   };
-  uint32_t* const mine = list + (tid >> 6) * kDirectList;
-  uint32_t base = 0, len = hi - lo;
-  bool count_below = true;
+  uint32_t* const mine = list + (tid >> 6) * kDirectOwn;
+  // All pillars, one after the other and without haste: use(key, index)
+  auto every_pillar = [&](auto use) {
+    for (int i0 = 0; i0 < n; i0 += ROUND) {
+      Row r[ROWS];
+      fetch(r, i0);
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) {
+        const int i = i0 + u * kDirectThreads + tid;
+        if (i < n) use(direct_key<Z, FRAMES>(r[u].c, dk, last_frame), (uint32_t)i);
+      }
+    }
+  };
+  // Pillars of one key value, in order: wavefronts take consecutive pieces of the cloud.  Returns how many there are.
+  auto in_order = [&](uint32_t key, uint32_t base) -> uint32_t {
+    const int wave = tid >> 6, piece = (n + kDirectThreads - 1) / kDirectThreads * 64, from = wave * piece;
+    const int to = from + piece < n ? from + piece : n;
+    auto go = [&](auto use) {
+#pragma unroll 4
+      for (int i0 = from; i0 < to; i0 += 64) {
+        const int i = i0 + lane;
+        const bool in = i < to && direct_key<Z, FRAMES>(coords + (uint32_t)(i < to ? i : 0) * STRIDE, dk, last_frame) == key;
+        use(in, i, __ballot(in));
+      }
+    };
+    uint32_t count = 0, total = 0;
+    go([&](bool, int, uint64_t all) { count += (uint32_t)__popcll(all); });
+    if (lane == 0) found[wave] = count;
+    __syncthreads();
+    uint32_t at = base;
+    for (int w = 0; w < kDirectWaves; ++w) {
+      at += w < wave ? found[w] : 0u;
+      total += found[w];
+    }
+    go([&](bool in, int i, uint64_t all) {
+      if (in) put(at + __builtin_amdgcn_mbcnt_hi((uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u)), key, (uint32_t)i);
+      at += (uint32_t)__popcll(all);
+    });
+    __syncthreads();
+    return total;
+  };
+  const uint32_t whole = hi - lo, origin = lo, unit = (whole + kDirectShared - 1u) / kDirectShared;  // key values of a count
+  uint32_t base = 0, len = whole;
+  // one_list: a wavefront's list overflowed, the range is gone through again for a list of all; counted: that did as well
+  bool count_below = true, one_list = false, counted = false;
   while (lo < hi) {  // (the same for the whole workgroup, as is everything that decides below)
+    if (counted) {   // as many key values as the list holds, from the first that has pillars
+      if (tid == 0) { head = 0xffffffffu; cut = 0u; }
+      constexpr uint32_t PER = kDirectShared / kDirectThreads;
+      const uint32_t at = (lo - origin) / unit;
+      uint32_t c[PER], sum = 0;
+#pragma unroll
+      for (uint32_t q = 0; q < PER; ++q) {
+        const uint32_t p = (uint32_t)tid * PER + q;
+        c[q] = p >= at ? joined[p] : 0u;
+        sum += c[q];
+      }
+      uint32_t before = block_exclusive_scan<kDirectThreads>(sum, wave_totals, nullptr);
+#pragma unroll
+      for (uint32_t q = 0; q < PER; ++q) {
+        const uint32_t p = (uint32_t)tid * PER + q;
+        if (c[q] != 0u && before == 0u) head = p;
+        before += c[q];
+        if (before <= (uint32_t)kDirectList) atomicMax(&cut, p + 1u);
+      }
+      __syncthreads();
+      if (head == 0xffffffffu) break;
+      lo = origin + head * unit;
+      const bool heavy = cut <= head;
+      const uint32_t to = (heavy ? 1u : cut - head) * unit;
+      len = to < hi - lo ? to : hi - lo;
+      __syncthreads();
+      if (heavy) {
+        for (const uint32_t stop = lo + len; lo < stop; ++lo) base += in_order(lo, base);
+        continue;
+      }
+    }
     const uint32_t words = (len + 31u) >> 5;
     for (uint32_t w = tid; w < words; w += kDirectThreads) bits[w] = 0u;
     if (tid == 0) { taken = 0u; below = 0u; full = 0u; }
     __syncthreads();
-    Row r[2][ROWS];
-    int begin = 0;
-    asm volatile("" : "+s"(begin));          // (or the addresses of the first round would be kept through everything that follows)
-    fetch(r[0], begin);
     uint32_t less = 0, count = 0;            // count: of the wavefront
-    auto look = [&](Row (&now)[ROWS], int i0, auto whole) {
+    if (!one_list) {
+      Row r[2][ROWS];
+      int begin = 0;
+      asm volatile("" : "+s"(begin));          // (or the addresses of the first round would be kept through everything that follows)
+      fetch(r[0], begin);
+      auto look = [&](Row (&now)[ROWS], int i0, auto whole) {
 #pragma unroll
-      for (int u = 0; u < ROWS; ++u) {
-        uint32_t key = direct_key<Z, FRAMES>(now[u].c, dk, last_frame);
-        asm volatile("" : "+v"(key));        // (computed by every lane: under a condition its load would be waited for alone)
-        const uint32_t i = (uint32_t)(i0 + u * kDirectThreads + tid);
-        if (!decltype(whole)::value) key = i < (uint32_t)n ? key : 0xffffffffu;
-        less += key < lo ? 1u : 0u;
-        const uint32_t code = key - lo;
-        const uint64_t in = __ballot(code < len);
-        if (code < len) {
-          const uint32_t at = count + __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));
-          if (at < (uint32_t)kDirectList) mine[at] = (code << idx_bits) | i;
-          atomicOr(&bits[code >> 5], 1u << (code & 31u));
+        for (int u = 0; u < ROWS; ++u) {
+          uint32_t key = direct_key<Z, FRAMES>(now[u].c, dk, last_frame);
+          asm volatile("" : "+v"(key));        // (computed by every lane: under a condition its load would be waited for alone)
+          const uint32_t i = (uint32_t)(i0 + u * kDirectThreads + tid);
+          if (!decltype(whole)::value) key = i < (uint32_t)n ? key : 0xffffffffu;
+          less += key < lo ? 1u : 0u;
+          const uint32_t code = key - lo;
+          const uint64_t in = __ballot(code < len);
+          if (code < len) {
+            const uint32_t at = count + __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));
+            if (at < (uint32_t)kDirectOwn) mine[at] = (code << idx_bits) | i;
+            atomicOr(&bits[code >> 5], 1u << (code & 31u));
+          }
+          count += (uint32_t)__popcll(in);
         }
-        count += (uint32_t)__popcll(in);
+      };
+      int i0 = begin;
+      for (; i0 + 2 * ROUND <= n; i0 += 2 * ROUND) {
+        fetch(r[1], i0 + ROUND);
+        look(r[0], i0, std::true_type());
+        fetch(r[0], i0 + 2 * ROUND);
+        look(r[1], i0 + ROUND, std::true_type());
       }
-    };
-    int i0 = begin;
-    for (; i0 + 2 * ROUND <= n; i0 += 2 * ROUND) {
-      fetch(r[1], i0 + ROUND);
-      look(r[0], i0, std::true_type());
-      fetch(r[0], i0 + 2 * ROUND);
-      look(r[1], i0 + ROUND, std::true_type());
-    }
-    if (i0 + ROUND < n) {
-      fetch(r[1], i0 + ROUND);
-      look(r[0], i0, std::true_type());
-      look(r[1], i0 + ROUND, std::false_type());
-    } else if (i0 < n) {
-      look(r[0], i0, std::false_type());
+      if (i0 + ROUND < n) {
+        fetch(r[1], i0 + ROUND);
+        look(r[0], i0, std::true_type());
+        look(r[1], i0 + ROUND, std::false_type());
+      } else if (i0 < n) {
+        look(r[0], i0, std::false_type());
+      }
+    } else {
+      every_pillar([&](uint32_t key, uint32_t i) {
+        const uint32_t code = key - lo;
+        if (code < len) {
+          const uint32_t at = atomicAdd(&taken, 1u), bit = 1u << (code & 31u);
+          if (at < (uint32_t)kDirectList) list[at] = (code << idx_bits) | i;
+          if (!(bits[code >> 5] & bit)) atomicOr(&bits[code >> 5], bit);
+          if (!counted) atomicAdd(&joined[code / unit], 1u);
+        }
+      });
     }
     if (count_below) {
       const uint32_t w = wave_inclusive_scan(less);
       if (lane == 63) atomicAdd(&below, w);
     }
-    if (lane == 0) {
+    if (lane == 0 && !one_list) {
       atomicAdd(&taken, count);
-      if (count > (uint32_t)kDirectList) full = 1u;
+      found[tid >> 6] = count;
+      if (count > (uint32_t)kDirectOwn) full = 1u;
     }
     __syncthreads();
     if (count_below) { base = below; count_below = false; }
@@ -901,8 +1014,14 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
     for (uint32_t w = w0; w < w0 + per && w < words; ++w) sum += (uint32_t)__popc(bits[w]);
     uint32_t run = block_exclusive_scan<kDirectThreads>(sum, wave_totals, &cells);
     const bool plain = cells == T;           // no two pillars share a cell
-    if (len > 1u && (full || (!plain && T > (uint32_t)kDirectSorted))) {
-      len = (len + 1u) >> 1;
+    if (!one_list && (full || (!plain && T > (uint32_t)kDirectShared))) {
+      one_list = true;
+      for (int p = tid; p < kDirectShared; p += kDirectThreads) joined[p] = 0u;
+      __syncthreads();
+      continue;
+    }
+    if (T > (uint32_t)kDirectList && one_list) {
+      counted = true;
       __syncthreads();
       continue;
     }
@@ -912,42 +1031,57 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
         run += (uint32_t)__popc(bits[w]);
       }
       __syncthreads();
-      for (uint32_t e = lane; e < count; e += 64) {
-        const uint32_t v = mine[e], code = v >> idx_bits, w = code >> 5;
+      const uint32_t* const from = one_list ? list : mine;
+      for (uint32_t e = one_list ? tid : lane; e < (one_list ? T : count); e += one_list ? kDirectThreads : 64) {
+        const uint32_t v = from[e], code = v >> idx_bits, w = code >> 5;
         put(base + first[w] + (uint32_t)__popc(bits[w] & ((1u << (code & 31u)) - 1u)), lo + code, v & idx_mask);
       }
-    } else if (len == 1u) {                  // one key value: in order of the index
-      uint32_t done = 0;
-      for (int i0 = 0; i0 < n; i0 += kDirectThreads) {
-        const int i = i0 + tid;
-        const bool in = i < n && direct_key<Z, FRAMES>(coords + (uint32_t)(i < n ? i : 0) * STRIDE, dk, last_frame) == lo;
-        uint32_t total;
-        const uint32_t at = block_exclusive_scan<kDirectThreads>(in ? 1u : 0u, wave_totals, &total);
-        if (in) put(base + done + at, lo, (uint32_t)i);
-        done += total;
+    } else {
+      uint32_t most = 1u;                    // whether a word has too many pillars for ranking them
+      if (!one_list) {                       // counts of the words' pillars instead of bits
+        __syncthreads();
+        for (uint32_t w = tid; w < words; w += kDirectThreads) bits[w] = 0u;
+        if (tid == 0) cut = 0u;
+        __syncthreads();
+        for (uint32_t e = lane; e < count; e += 64) atomicAdd(&bits[mine[e] >> (idx_bits + 5)], 1u);
+        __syncthreads();
+        sum = 0;
+        uint32_t largest = 0;
+        for (uint32_t w = w0; w < w0 + per && w < words; ++w) {
+          const uint32_t c = bits[w];
+          sum += c;
+          largest = c > largest ? c : largest;
+        }
+        if (largest > (uint32_t)kDirectRanked) cut = 1u;
+        run = block_exclusive_scan<kDirectThreads>(sum, wave_totals, nullptr);
+        for (uint32_t w = w0; w < w0 + per && w < words; ++w) {
+          const uint32_t c = bits[w];
+          first[w] = bits[w] = run;          // bits: where the word's next pillar goes
+          run += c;
+        }
+        __syncthreads();
+        most = cut;
+        for (uint32_t e = lane; e < count; e += 64) {
+          const uint32_t v = mine[e];
+          joined[atomicAdd(&bits[v >> (idx_bits + 5)], 1u)] = v;
+        }
+        __syncthreads();
       }
-    } else {                                 // pillars of a word instead of its bits
-      __syncthreads();
-      for (uint32_t w = tid; w < words; w += kDirectThreads) bits[w] = 0u;
-      __syncthreads();
-      for (uint32_t e = lane; e < count; e += 64) atomicAdd(&bits[mine[e] >> (idx_bits + 5)], 1u);
-      __syncthreads();
-      sum = 0;
-      for (uint32_t w = w0; w < w0 + per && w < words; ++w) sum += bits[w];
-      run = block_exclusive_scan<kDirectThreads>(sum, wave_totals, nullptr);
-      for (uint32_t w = w0; w < w0 + per && w < words; ++w) {
-        const uint32_t v = bits[w];
-        first[w] = bits[w] = run;            // bits: where the word's next pillar goes
-        run += v;
-      }
-      __syncthreads();
-      for (uint32_t e = lane; e < count; e += 64) sorted[atomicAdd(&bits[mine[e] >> (idx_bits + 5)], 1u)] = mine[e];
-      __syncthreads();
-      for (uint32_t e = tid; e < T; e += kDirectThreads) {
-        const uint32_t v = sorted[e], q0 = first[v >> (idx_bits + 5)], q1 = bits[v >> (idx_bits + 5)];
-        uint32_t pos = q0;
-        for (uint32_t q = q0; q < q1; ++q) pos += sorted[q] < v ? 1u : 0u;
-        put(base + pos, lo + (v >> idx_bits), v & idx_mask);
+      if (most == 0u) {                      // few: every pillar looks at all of its word
+        for (uint32_t e = tid; e < T; e += kDirectThreads) {
+          const uint32_t v = joined[e], q0 = first[v >> (idx_bits + 5)], q1 = bits[v >> (idx_bits + 5)];
+          uint32_t pos = q0, q = q0;
+          for (; q + 4u <= q1; q += 4u) {
+            const uint32_t a = joined[q], b = joined[q + 1u], c = joined[q + 2u], d = joined[q + 3u];
+            pos += (a < v ? 1u : 0u) + (b < v ? 1u : 0u) + (c < v ? 1u : 0u) + (d < v ? 1u : 0u);
+          }
+          for (; q < q1; ++q) pos += joined[q] < v ? 1u : 0u;
+          put(base + pos, lo + (v >> idx_bits), v & idx_mask);
+        }
+      } else {
+        uint32_t* const all = one_list ? list : joined;
+        direct_sort(all, T);
+        for (uint32_t e = tid; e < T; e += kDirectThreads) put(base + e, lo + (all[e] >> idx_bits), all[e] & idx_mask);
       }
     }
     base += T;
@@ -1171,7 +1305,7 @@ static int flatten_launch_impl(const int32_t* coords, const PointCells* pts, int
     job.layers = 0; job.blocks = 1;
     if (pack) job = *pack;
     const unsigned blocks = (unsigned)(num_sorts * (db.parts + 1) + ceil_div((int64_t)job.layers * job.blocks, kDirectThreads / 256));
-    const size_t lds = (size_t)(kDirectWaves * kDirectList + kDirectSorted) * 4 + db.range / 32 * 8;
+    const size_t lds = (size_t)(kDirectList + kDirectShared) * 4 + db.range / 32 * 8;
     static std::atomic<uint64_t> allowed[4] = {{0}, {0}, {0}, {0}};  // bit d: the largest dynamic LDS size is allowed on device d
     auto go = [&](auto kern, int which) -> int {
       int dev = 0;
@@ -1179,7 +1313,7 @@ static int flatten_launch_impl(const int32_t* coords, const PointCells* pts, int
       const uint64_t bit = 1ull << (dev & 63);
       if (!(allowed[which].load(std::memory_order_acquire) & bit)) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (kDirectWaves * kDirectList + kDirectSorted) * 4 + kDirectMaxCodes / 32 * 8) != hipSuccess)
+                                (kDirectList + kDirectShared) * 4 + kDirectMaxCodes / 32 * 8) != hipSuccess)
           return FF_ERR_LAUNCH;
         allowed[which].fetch_or(bit, std::memory_order_release);
       }

@@ -1,4 +1,4 @@
-"""Clouds sorted in one launch: where a workgroup's range of key values holds more pillars than its lists (it is halved, down
+"""Clouds sorted in one launch: where a workgroup's range of key values holds more pillars than its lists (it is cut, down
 to a single value), where pillars share cells, and on both sides of the limits of what is sorted this way (frames, grid,
 pillars, key values of a range)."""
 import numpy as np
@@ -33,6 +33,12 @@ CASES = {
     "dense_board": (lambda: _cells(1, 160, 160, 25600, 1), 1, 468, 13),
     "every_cell_twice": (lambda: _cells(1, 120, 120, 28000, 2, each=2), 1, 468, 13),
     "few_shared_cells": (lambda: np.concatenate([_cells(1, 468, 468, 12000, 3), _cells(1, 468, 468, 500, 4)]), 1, 468, 13),
+    "few_cells": (lambda: np.random.default_rng(18).integers(0, 7, (5000, 3)).astype(np.int32) * [0, 1, 1], 1, 468, 13),
+    "hundred_cells": (lambda: np.random.default_rng(13).integers(0, 10, (30000, 3)).astype(np.int32) * [0, 1, 1], 1, 468, 13),
+    "half_in_one_cell": (lambda: np.concatenate([_cells(1, 468, 468, 40000, 14), np.tile(np.array([[0, 9, 9]], np.int32), (40000, 1))])
+                         [np.random.default_rng(15).permutation(80000)], 1, 468, 13),
+    "corner_cells_shared": (lambda: np.random.default_rng(16).integers(0, 120, (131072, 3)).astype(np.int32) * [0, 1, 1], 1, 468, 13),
+    "many_shared_cells": (lambda: np.random.default_rng(17).integers(0, 468, (120000, 3)).astype(np.int32) * [0, 1, 1], 1, 468, 13),
     "sixteen_frames": (lambda: _cells(16, 60, 60, 5000, 5), 16, 60, 6),
     "seventeen_frames": (lambda: _cells(17, 60, 60, 5000, 6), 17, 60, 6),
     "grid_4096": (lambda: _cells(1, 4096, 4096, 7000, 7), 1, 4096, 256),
@@ -47,7 +53,7 @@ CASES = {
 @pytest.mark.parametrize("name", list(CASES))
 def test_against_the_oracle(name):
     make, B, grid, w = CASES[name]
-    coords = np.ascontiguousarray(make())
+    coords = np.ascontiguousarray(make(), dtype=np.int32)
     g, og = ff.Geometry(B, grid, grid, w, w), oracle.Geometry(B, grid, grid, w, w)
     ct = torch.from_numpy(coords).to(DEV)
     pairs = [(0, 0), (1, 0), (0, 1), (1, 1)]
