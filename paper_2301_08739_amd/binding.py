@@ -180,6 +180,15 @@ def ff_flatten_workspace_bytes(n, geom):
     return load_library().ff_flatten_workspace_bytes(int(n), C.byref(geom))
 
 
+def _group_lists(count, cap, device):
+    """`count` pairs (group_offsets of capacity cap, num_groups), -1 throughout.  One fill for all of them: it is a launch,
+    1.3 us in a graph and more in an eager call (a captured call of four sorts of 30,000 pillars: a fill for each tensor
+    25.7 us, one fill 15.2; one sort 15.7 and 14.2)."""
+    width = -(-cap // 64) * 64 + 64  # (each tensor on a 256-byte boundary)
+    both = torch.full((count, width), -1, dtype=torch.int32, device=device)
+    return [(row[:cap], row[width - 64:width - 63]) for row in both.unbind(0)]
+
+
 def ff_flatten(coords, geom, axis, shift, G, tail=FF_TAIL_MASK, want_keys=False, workspace=None):
     """coords: int32 cuda tensor [n,3].  Returns (perm, group_offsets, num_groups, keys_sorted|None),
     all device tensors; group_offsets has capacity ceil(n/G)+num_frames+1."""
@@ -189,8 +198,7 @@ def ff_flatten(coords, geom, axis, shift, G, tail=FF_TAIL_MASK, want_keys=False,
     dev = coords.device
     cap = -(-n // max(G, 1)) + geom.num_frames + 1
     perm = torch.empty(n, dtype=torch.int32, device=dev)
-    goff = torch.full((cap,), -1, dtype=torch.int32, device=dev)
-    ng = torch.full((1,), -1, dtype=torch.int32, device=dev)
+    (goff, ng), = _group_lists(1, cap, dev)
     keys = torch.empty(n, dtype=torch.int64, device=dev) if want_keys else None
     need = lib.ff_flatten_workspace_bytes(n, C.byref(geom))
     ws = workspace if workspace is not None else _workspace(need, dev)
@@ -221,8 +229,7 @@ def ff_flatten_batch(coords, geom, sorts, G, tail=FF_TAIL_MASK, workspace=None, 
     n, dev, S = coords.shape[0], coords.device, len(sorts)
     cap = -(-n // max(G, 1)) + geom.num_frames + 1
     if out is None:
-        out = [(torch.empty(n, dtype=torch.int32, device=dev), torch.full((cap,), -1, dtype=torch.int32, device=dev),
-                torch.full((1,), -1, dtype=torch.int32, device=dev)) for _ in range(S)]
+        out = [(torch.empty(n, dtype=torch.int32, device=dev), goff, ng) for goff, ng in _group_lists(S, cap, dev)]
     axis = (C.c_int * S)(*[int(a) for a, _ in sorts])
     shift = (C.c_int * S)(*[int(b) for _, b in sorts])
     ptrs = [(C.c_void_p * S)(*[t[k].data_ptr() for t in out]) for k in range(3)]
@@ -268,8 +275,7 @@ def ff_flatten3d(coords, geom, axis, shift, G, tail=FF_TAIL_MASK, workspace=None
     dev = coords.device
     cap = -(-n // max(G, 1)) + geom.num_frames + 1
     perm = torch.empty(n, dtype=torch.int32, device=dev)
-    goff = torch.full((cap,), -1, dtype=torch.int32, device=dev)
-    ng = torch.full((1,), -1, dtype=torch.int32, device=dev)
+    (goff, ng), = _group_lists(1, cap, dev)
     need = lib.ff_flatten3d_workspace_bytes(n, C.byref(geom))
     ws = workspace if workspace is not None else _workspace(need, dev)
     st = lib.ff_flatten3d(_ptr(coords), n, C.byref(geom), axis, shift, G, tail, _ptr(perm), _ptr(goff), _ptr(ng),

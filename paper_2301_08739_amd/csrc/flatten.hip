@@ -712,8 +712,8 @@ __global__ __launch_bounds__(256) void k_finalize(const uint64_t* __restrict__ s
 //
 // What bounds it: the look at all pillars, 12 bytes and some 20 vector instructions each in every workgroup, 0.23 us for
 // every thousand of them, and 6 us for the launch, the scan and the way out; the radix path is three dependent launches of
-// 5 to 12 us.  Measured, radix path / this one, us a call: one sort, 2,000 pillars 21 / 8.6, 12,345 22.5 / 11.2, 30,000
-// 23 / 15, 131,072 41 / 37.5; four sorts, 30,000 35.5 / 25, 80,000 61.5 / 38.
+// 5 to 12 us.  Measured, radix path / this one, us a call (two small fills a sort with it): one sort, 2,000 pillars 21 / 8.6,
+// 12,345 22.5 / 11.2, 30,000 23 / 15, 131,072 41 / 37.5; four sorts, 30,000 35.5 / 25, 80,000 61.5 / 38.
 // What it is not made for are clouds whose pillars share a window's few cells, tens or hundreds each: one workgroup then has
 // them all (30,000 pillars on a cell 27 / 124, on nine 27 / 440; at three a cell it is even, 28 / 28; 120,000 of which a
 // fifth share one, 41 / 40, four sorts 80 / 62).  Pillars are cells that a cloud of points fills, one each.
