@@ -339,7 +339,7 @@ def ff_voxelize(xy, frame, point_feats, geom, grid, want_map=True, workspace=Non
     dev = xy.device
     coords = torch.empty((m, 3), dtype=torch.int32, device=dev)
     feats = torch.empty((m, Cp), dtype=torch.float32, device=dev)
-    npil = torch.full((1,), -1, dtype=torch.int32, device=dev)
+    npil = torch.empty(1, dtype=torch.int32, device=dev)  # (always written)
     p2p = torch.empty(m, dtype=torch.int32, device=dev) if want_map else None
     need = lib.ff_voxelize_workspace_bytes(m, C.byref(geom))
     ws = workspace if workspace is not None else _workspace(need, dev)
