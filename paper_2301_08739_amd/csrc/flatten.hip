@@ -14,7 +14,8 @@
 //     holds in the order the pass reads them.  Key generation writes the rows of the first pass
 //     (plain stores) and zeroes the others; each pass adds, for every word it places, one to the
 //     row of the tile the word lands in for the next pass.  Nothing has to be cleared beforehand.
-//   * Clouds of up to 131,072 pillars over ordinary geometries take no passes at all: k_direct below, one launch.
+//   * Clouds over ordinary geometries take no such passes at all: up to 24,576 pillars one launch (k_direct below), up to
+//     4 million two (k_split and k_buckets).
 //   * Small clouds otherwise (at most 128 tiles of 1024 words, see kSmallMaxTiles: launch and latency bound): digits of up to 10
 //     bits, and a pass reads the whole table of its pass itself (column sums = global digit
 //     starts, rows of earlier tiles = its own offsets): key generation + one launch per pass.
@@ -673,10 +674,11 @@ __global__ __launch_bounds__(256) void k_finalize(const uint64_t* __restrict__ s
 // What bounds it: the look at all pillars, 12 bytes and some 20 vector instructions each in every workgroup, 0.23 us for
 // every thousand of them, and 6 us for the launch, the scan and the way out; the radix path is three dependent launches of
 // 5 to 12 us.  Measured, radix path / this one, us a call (two small fills a sort with it): one sort, 2,000 pillars 21 / 8.6,
-// 12,345 22.5 / 11.2, 30,000 23 / 15, 131,072 41 / 37.5; four sorts, 30,000 35.5 / 25, 80,000 61.5 / 38.
-// What it is not made for are clouds whose pillars share a window's few cells, tens or hundreds each: one workgroup then has
-// them all (30,000 pillars on a cell 27 / 124, on nine 27 / 440; at three a cell it is even, 28 / 28; 120,000 of which a
-// fifth share one, 41 / 40, four sorts 80 / 62).  Pillars are cells that a cloud of points fills, one each.
+// 12,345 22.5 / 11.2, 30,000 23 / 15, 131,072 41 / 37.5; four sorts, 30,000 35.5 / 25, 80,000 61.5 / 38.  The line to the two
+// launches of k_split: with one fill a call, one sort and four, 20,000 pillars of two frames 12.4 and 13.0 by this, 24 to 25 by
+// those, 30,000 14.1 and 15.2 by this, 13.4 and 13.9 by those, 60,000 21.0 and 22.5, 14.6 and 16.4.
+// What it is not made for are clouds whose pillars share a window's few cells, tens or hundreds each, which one workgroup then
+// has all to itself.  Pillars are cells that a cloud of points fills, one each.
 constexpr int kDirectThreads = 1024;
 constexpr int kDirectWaves = kDirectThreads / 64;
 constexpr int kDirectOwn = 1024;            // pillars of a range that a wavefront finds (4 bytes each),
@@ -684,7 +686,7 @@ constexpr int kDirectList = kDirectWaves * kDirectOwn;  // all together,
 constexpr int kDirectShared = 8192;         // and when some share a cell and the wavefronts' lists have to be joined
 constexpr int kDirectRanked = 256;          // pillars of 32 key values that are ranked by comparing them all (80 each: 28 us a
                                             // call of 30,000; sorted 45)
-constexpr int kDirectMaxRows = 131072;      // pillars,
+constexpr int kDirectMaxRows = 24576;       // pillars,
 constexpr int kDirectMaxCodes = 131072;     // and key values of a workgroup's range; a list entry of 32 bits holds one of each
 constexpr int kDirectMaxFrames = 16;
 constexpr int kDirectMaxGrid = 4096;        // cells an axis, shift included: windows by a 24-bit multiplication
@@ -756,16 +758,28 @@ __device__ __forceinline__ void direct_groups(const int32_t* __restrict__ coords
   }
 }
 
+// Position of v among a[q0 .. q1) in ascending order, counted from a[0].
+__device__ __forceinline__ uint32_t rank_in_run(const uint32_t* a, uint32_t q0, uint32_t q1, uint32_t v) {
+  uint32_t pos = q0, q = q0;
+  for (; q + 4u <= q1; q += 4u) {
+    const uint32_t x0 = a[q], x1 = a[q + 1u], x2 = a[q + 2u], x3 = a[q + 3u];
+    pos += (x0 < v ? 1u : 0u) + (x1 < v ? 1u : 0u) + (x2 < v ? 1u : 0u) + (x3 < v ? 1u : 0u);
+  }
+  for (; q < q1; ++q) pos += a[q] < v ? 1u : 0u;
+  return pos;
+}
+
 // a[0 .. T) in ascending order; a has room for the next power of two.  Pairs up to 64 apart stay within the 128 entries of a
 // wavefront, whose LDS accesses are in order.
+template <int THREADS>
 __device__ __forceinline__ void direct_sort(uint32_t* a, uint32_t T) {
   uint32_t P = 128;
   while (P < T) P <<= 1;
-  for (uint32_t e = T + threadIdx.x; e < P; e += kDirectThreads) a[e] = 0xffffffffu;
+  for (uint32_t e = T + threadIdx.x; e < P; e += THREADS) a[e] = 0xffffffffu;
   __syncthreads();
   for (uint32_t k = 2; k <= P; k <<= 1) {
     for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-      for (uint32_t t = threadIdx.x; t < P / 2; t += kDirectThreads) {
+      for (uint32_t t = threadIdx.x; t < P / 2; t += THREADS) {
         const uint32_t i = 2u * t - (t & (j - 1u)), x = a[i], y = a[i + j];
         if ((x > y) == ((i & k) == 0u)) { a[i] = y; a[i + j] = x; }
       }
@@ -1029,18 +1043,12 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
       }
       if (most == 0u) {                      // few: every pillar looks at all of its word
         for (uint32_t e = tid; e < T; e += kDirectThreads) {
-          const uint32_t v = joined[e], q0 = first[v >> (idx_bits + 5)], q1 = bits[v >> (idx_bits + 5)];
-          uint32_t pos = q0, q = q0;
-          for (; q + 4u <= q1; q += 4u) {
-            const uint32_t a = joined[q], b = joined[q + 1u], c = joined[q + 2u], d = joined[q + 3u];
-            pos += (a < v ? 1u : 0u) + (b < v ? 1u : 0u) + (c < v ? 1u : 0u) + (d < v ? 1u : 0u);
-          }
-          for (; q < q1; ++q) pos += joined[q] < v ? 1u : 0u;
-          put(base + pos, lo + (v >> idx_bits), v & idx_mask);
+          const uint32_t v = joined[e], w = v >> (idx_bits + 5);
+          put(base + rank_in_run(joined, first[w], bits[w], v), lo + (v >> idx_bits), v & idx_mask);
         }
       } else {
         uint32_t* const all = one_list ? list : joined;
-        direct_sort(all, T);
+        direct_sort<kDirectThreads>(all, T);
         for (uint32_t e = tid; e < T; e += kDirectThreads) put(base + e, lo + (all[e] >> idx_bits), all[e] & idx_mask);
       }
     }
@@ -1049,6 +1057,346 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
     len = hi - lo;
     __syncthreads();
   }
+}
+
+// ---- large clouds in two launches --------------------------------------------------------------------------------------
+// The high bits of the key, frame and windows, number the buckets, of 1024 pillars or more on average.  k_split sorts each tile
+// of the cloud by bucket, in a place of its own, and says in a table where the buckets begin in it.  k_buckets, a workgroup per
+// bucket, finds the bucket's pieces of all tiles through a column of the table, whose sums also say how many pillars lie in
+// front, and puts its pillars in order as k_direct does: a bit for each key value, positions by counting bits.  Where some share
+// a cell, the key values are sorted in LDS, with the position in the bucket behind them, which is in order of the index; for
+// more pillars than the list holds, by two passes through memory.
+//
+// What bounds it: for a hundred thousand pillars its two launches, 4 us and a chain of six or seven round trips each; for
+// millions the lines touched rather than the 16 bytes a pillar moved: the pieces of a bucket are a few entries long where the
+// frames are mixed, a line each of entries and table (3.84 M pillars: k_split 29 us, k_buckets 49).  The radix path moves 8-byte
+// words through three passes there.  Measured, radix path / this, us a call: one sort, 131,072 pillars 35 / 14.3, 240,000 37 /
+// 16, 960,000 59 / 28, 2 M 79 / 58, 3.84 M 109 / 78; four sorts, 240,000 63 / 27, 960,000 122 / 74.  The same with a fifth of
+// the pillars sharing cells; 30,000 on one to a hundred cells, a single bucket's, 27 / 200.
+constexpr int kSplitThreads = 512, kSplitWaves = kSplitThreads / 64;
+constexpr int kSplitLeast = 2, kSplitFew = 4, kSplitMany = 16;  // pillars of a thread of k_split: few to fill the chip, many to
+constexpr int64_t kSplitFewRows = 1 << 19, kSplitManyRows = 1 << 20;  // keep the pieces long; of all sorts, and of one
+constexpr int kSplitLocalBits = 13;         // pillars of a tile: up to 8192
+constexpr int kSplitCodeBits = 16;          // key values of a bucket
+constexpr int kSplitMaxBuckets = 3800;      // the counters of k_split: 61 KB
+constexpr int kSplitMinRows = 16385;        // pillars
+constexpr int kSplitRows = 448, kSplitRowsMany = 1408, kSplitBuckets = 1024;  // of a bucket on average, at least; the more when
+                                            // all sorts together have this many buckets
+constexpr int kSplitMaxTiles = 512;
+constexpr int kSplitList = 4096;            // pillars of a bucket in registers, and of its list in LDS
+constexpr int kSplitOwn = kSplitList / kSplitThreads;
+
+// Bucket of key k: h - (h >> in_frame) * skip with h = k >> code_bits, which leaves out the numbers no window has.
+struct SplitSort { DirectKeys k; int32_t code_bits, in_frame, skip, per_frame; };
+struct SplitBatch { SplitSort s[kMaxSorts]; int32_t bins, bin_bits, tiles; };
+
+template <bool Z, bool FRAMES, int OWN>
+__global__ __launch_bounds__(kSplitThreads) void k_split(const int32_t* __restrict__ coords, int n, int S, SplitBatch sb,
+                                                          uint32_t* __restrict__ entries_all, uint32_t* __restrict__ table_all,
+                                                          int frames, PackJob pack) {
+  constexpr int STRIDE = Z ? 4 : 3, TILE = kSplitThreads * OWN;
+  extern __shared__ uint32_t words[];        // [kSplitWaves][bins / 2]: counts of two buckets; then the tile, sorted
+  __shared__ uint32_t wave_totals[kSplitWaves];
+  const int tid = threadIdx.x, lane = tid & 63, half = sb.bins >> 1;
+  if ((int)blockIdx.x >= S * sb.tiles) {
+    pack_tail(pack, ((int)blockIdx.x - S * sb.tiles) * (kSplitThreads / 256) + (tid >> 8), tid & 255);
+    return;
+  }
+  const int s = blockIdx.x % S, tile = blockIdx.x / S, tile0 = tile * TILE, local0 = (tid >> 6) * 64 * OWN + lane;
+  const DirectKeys dk = sb.s[s].k;
+  const int code_bits = sb.s[s].code_bits, in_frame = sb.s[s].in_frame;
+  const uint32_t skip = (uint32_t)sb.s[s].skip, none = (uint32_t)sb.bins - 1u, last_frame = (uint32_t)frames - 1u;
+  uint16_t* const mine = reinterpret_cast<uint16_t*>(words + (tid >> 6) * half);
+  for (int w = tid; w < kSplitWaves * half; w += kSplitThreads) words[w] = 0u;
+  struct Row { int32_t c[STRIDE]; };
+  uint32_t entry[OWN], at[OWN];              // at: bucket << 16 | rank, then the position
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) {
+    const int i = tile0 + local0 + u * 64;
+    const Row r = *reinterpret_cast<const Row*>(coords + (int64_t)(i < n ? i : n - 1) * STRIDE);
+    const uint32_t key = direct_key<Z, FRAMES>(r.c, dk, last_frame), h = key >> code_bits;
+    at[u] = i < n ? h - __umul24(h >> in_frame, skip) : none;
+    entry[u] = (key & ((1u << code_bits) - 1u)) << kSplitLocalBits | (uint32_t)(local0 + u * 64);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) at[u] = at[u] << 16 | rank_in_wave(mine, at[u], sb.bin_bits, true);
+  __syncthreads();
+  constexpr int PER = (kSplitMaxBuckets + 2) / 2 / kSplitThreads + 1;  // words of a thread
+  const int per = (half + kSplitThreads - 1) / kSplitThreads, w0 = tid * per;
+  uint32_t total[PER], sum = 0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    total[q] = q < per && w0 + q < half ? sum_over_waves<kSplitWaves>(words, half, w0 + q) : 0u;
+    sum += (total[q] & 0xffffu) + (total[q] >> 16);
+  }
+  uint32_t first = block_exclusive_scan<kSplitThreads>(sum, wave_totals, nullptr);
+  uint32_t* const table = table_all + ((int64_t)s * sb.tiles + tile) * half;
+#pragma unroll
+  for (int q = 0; q < PER; ++q)
+    if (q < per && w0 + q < half) {
+      const uint32_t both = first | (first + (total[q] & 0xffffu)) << 16;
+      table[w0 + q] = both;
+#pragma unroll
+      for (int w = 0; w < kSplitWaves; ++w) words[w * half + w0 + q] += both;
+      first += (total[q] & 0xffffu) + (total[q] >> 16);
+    }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) at[u] = mine[at[u] >> 16] + (at[u] & 0xffffu);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) words[at[u]] = entry[u];
+  __syncthreads();
+  uint32_t* const entries = entries_all + (int64_t)s * n + tile0;
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) {
+    const int e = u * kSplitThreads + tid;
+    if (tile0 + e < n) entries[e] = words[e];
+  }
+}
+
+// The group list of a sort, by one workgroup, from where the frames' first buckets begin.  starts, groups: [frames + 1]
+__device__ __forceinline__ void split_groups(const uint16_t* __restrict__ table, int tiles, int bins, int per_frame, int n, int B,
+                                             int G, int drop, int32_t* __restrict__ goff, int32_t* __restrict__ num_groups,
+                                             uint32_t* starts, uint32_t* groups, uint32_t* wave_totals) {
+  const int tid = threadIdx.x, l = tid & 15;
+  for (int b = tid >> 4; b < B; b += kSplitThreads / 16) {
+    uint32_t sum = 0;
+#pragma unroll 8
+    for (int t = l; t < tiles; t += 16) sum += table[(int64_t)t * bins + b * per_frame];
+#pragma unroll
+    for (int d = 8; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 16);
+    if (l == 0) starts[b] = sum;
+  }
+  if (tid == 0) starts[B] = (uint32_t)n;
+  __syncthreads();
+  uint32_t carry = 0;
+  for (int b0 = 0; b0 < B; b0 += kSplitThreads) {
+    const int b = b0 + tid;
+    const uint32_t g = b < B ? groups_of(starts[b + 1] - starts[b], G, drop) : 0u;
+    uint32_t all;
+    const uint32_t ex = block_exclusive_scan<kSplitThreads>(g, wave_totals, &all);
+    if (b < B) groups[b] = carry + ex;
+    carry += all;
+  }
+  if (tid == 0) {
+    groups[B] = carry;
+    *num_groups = (int32_t)carry;
+    goff[carry] = n;
+  }
+  __syncthreads();
+  for (int b = tid >> 4; b < B; b += kSplitThreads / 16)
+    for (uint32_t k = l; k < groups[b + 1] - groups[b]; k += 16) goff[groups[b] + k] = (int32_t)(starts[b] + k * (uint32_t)G);
+}
+
+template <bool Z, bool FRAMES>
+__global__ __launch_bounds__(kSplitThreads) void k_buckets(const int32_t* __restrict__ coords, int n, int S, Batch bt, SplitBatch sb,
+                                                            int tile_rows, const uint32_t* __restrict__ entries_all,
+                                                            const uint16_t* __restrict__ table_all, uint32_t* __restrict__ scratch,
+                                                            int G, int drop) {
+  constexpr int STRIDE = Z ? 4 : 3;
+  extern __shared__ uint32_t list[];                       // [kSplitList] key value << 12 | position in the bucket; counters
+  uint32_t* const cum = list + kSplitList;                 // [kSplitMaxTiles + 1] the bucket's pillars in the tiles before,
+  uint32_t* const from = cum + kSplitMaxTiles + 1;         // [kSplitMaxTiles] and where those of a tile are, less that
+  uint32_t* const bits = from + kSplitMaxTiles;            // [words]
+  __shared__ uint32_t wave_totals[kSplitWaves];
+  __shared__ uint32_t crowded;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tiles = sb.tiles;
+  if ((int)blockIdx.x < S) {
+    const int s = blockIdx.x;
+    split_groups(table_all + (int64_t)s * tiles * sb.bins, tiles, sb.bins, sb.s[s].per_frame, n, bt.kp[s].B, G, drop,
+                 bt.group_offsets[s], bt.num_groups[s], list, list + kSplitMaxBuckets + 1, wave_totals);
+    return;
+  }
+  // Neighbouring buckets go to the same die, whose cache then has the lines that they share.
+  const int id = blockIdx.x - S, each = ((int)gridDim.x - S) >> 3, nth = (id & 7) * each + (id >> 3);
+  int s = 0, bucket = nth;
+  for (; s < S; ++s) {
+    const int count = bt.kp[s].B * sb.s[s].per_frame;
+    if (bucket < count) break;
+    bucket -= count;
+  }
+  if (s >= S) return;
+  const KeyParams kp = bt.kp[s];
+  const DirectKeys dk = sb.s[s].k;
+  const int code_bits = sb.s[s].code_bits, words = 1 << (code_bits - 5);
+  uint32_t* const first = bits + words;                    // [words] position of a word's first pillar
+  const uint32_t* __restrict__ const entries = entries_all + (int64_t)s * n;
+  const uint16_t* __restrict__ const table = table_all + (int64_t)s * tiles * sb.bins;
+  uint32_t lo = 0, hi = 0, T, base;
+  if (tid < tiles) {
+    lo = table[(int64_t)tid * sb.bins + bucket];
+    hi = table[(int64_t)tid * sb.bins + bucket + 1];
+  }
+  for (int w = tid; w < words; w += kSplitThreads) bits[w] = 0u;
+  const uint32_t before = block_exclusive_scan<kSplitThreads>(hi - lo, wave_totals, &T);
+  block_exclusive_scan<kSplitThreads>(lo, wave_totals, &base);
+  if (T == 0u) return;
+  cum[tid] = tid < tiles ? before : T;                     // (kSplitThreads == kSplitMaxTiles)
+  from[tid] = (uint32_t)tid * (uint32_t)tile_rows + lo - before;
+  if (tid == 0) cum[kSplitMaxTiles] = T;
+  __syncthreads();
+  const uint32_t frame = (uint32_t)bucket / (uint32_t)sb.s[s].per_frame;
+  const uint32_t key0 = ((uint32_t)bucket + frame * (uint32_t)sb.s[s].skip) << code_bits;
+  int32_t* __restrict__ const perm_s = bt.perm[s];
+  int32_t* __restrict__ const inv_s = bt.inv_perm[s];
+  uint64_t* __restrict__ const keys_s = bt.keys_sorted[s];
+  auto put_beside = [&](uint32_t pos, uint32_t code, uint32_t i) {  // (all but perm)
+    if (inv_s) inv_s[i] = (int32_t)pos;
+    if (keys_s) {
+      uint32_t b;
+      keys_s[pos] = exported_key(key0 + code, kp, &b);
+    }
+  };
+  auto put = [&](uint32_t pos, uint32_t code, uint32_t i) {
+    perm_s[pos] = (int32_t)i;
+    put_beside(pos, code, i);
+  };
+  // Pillars of the bucket, OWN of a thread: key value and index of e0 + tid, e0 + tid + kSplitThreads, ..  The tile of one is
+  // the last that begins no later.
+  auto nth_of = [&](uint32_t e0, int u) {
+    const uint32_t e = e0 + u * kSplitThreads + tid;
+    return e < T ? e : T - 1u;
+  };
+  auto fetch = [&](uint32_t (&code)[kSplitOwn], uint32_t (&index)[kSplitOwn], uint32_t e0) {
+    uint32_t tile[kSplitOwn] = {};
+#pragma unroll
+    for (uint32_t step = kSplitMaxTiles / 2; step > 0; step >>= 1)
+#pragma unroll
+      for (int u = 0; u < kSplitOwn; ++u)
+        if (e0 + u * kSplitThreads < T) tile[u] += cum[tile[u] + step] <= nth_of(e0, u) ? step : 0u;
+#pragma unroll
+    for (int u = 0; u < kSplitOwn; ++u)
+      if (e0 + u * kSplitThreads < T) index[u] = entries[from[tile[u]] + nth_of(e0, u)];
+#pragma unroll
+    for (int u = 0; u < kSplitOwn; ++u)
+      if (e0 + u * kSplitThreads < T) {
+        code[u] = index[u] >> kSplitLocalBits;
+        index[u] = tile[u] * (uint32_t)tile_rows + (index[u] & ((1u << kSplitLocalBits) - 1u));
+      }
+  };
+  auto each_of = [&](uint32_t e0, auto use) {
+#pragma unroll
+    for (int u = 0; u < kSplitOwn; ++u)
+      if (e0 + u * kSplitThreads + tid < T) use(u, e0 + u * kSplitThreads + tid);
+  };
+  uint32_t code[kSplitOwn], index[kSplitOwn];
+  for (uint32_t e0 = 0; e0 < T; e0 += kSplitList) {
+    fetch(code, index, e0);
+    each_of(e0, [&](int u, uint32_t) { atomicOr(&bits[code[u] >> 5], 1u << (code[u] & 31u)); });
+  }
+  __syncthreads();
+  const int per = (words + kSplitThreads - 1) / kSplitThreads, w0 = tid * per;
+  uint32_t sum = 0, cells;
+  for (int w = w0; w < w0 + per && w < words; ++w) sum += (uint32_t)__popc(bits[w]);
+  uint32_t run = block_exclusive_scan<kSplitThreads>(sum, wave_totals, &cells);
+  if (cells == T) {                          // no two pillars share a cell
+    for (int w = w0; w < w0 + per && w < words; ++w) {
+      first[w] = base + run;
+      run += (uint32_t)__popc(bits[w]);
+    }
+    __syncthreads();
+    if (T <= (uint32_t)kSplitList) {         // perm through the list, so that it is written in order
+      each_of(0, [&](int u, uint32_t) {
+        const uint32_t c = code[u], w = c >> 5, pos = first[w] + (uint32_t)__popc(bits[w] & ((1u << (c & 31u)) - 1u));
+        list[pos - base] = index[u];
+        put_beside(pos, c, index[u]);
+      });
+      __syncthreads();
+      for (uint32_t e = tid; e < T; e += kSplitThreads) perm_s[base + e] = (int32_t)list[e];
+      return;
+    }
+    for (uint32_t e0 = 0; e0 < T; e0 += kSplitList) {
+      fetch(code, index, e0);
+      each_of(e0, [&](int u, uint32_t) {
+        const uint32_t c = code[u], w = c >> 5;
+        put(first[w] + (uint32_t)__popc(bits[w] & ((1u << (c & 31u)) - 1u)), c, index[u]);
+      });
+    }
+    return;
+  }
+  if (T <= (uint32_t)kSplitList) {           // by words of the map, then ranked, as in k_direct
+    __syncthreads();
+    for (int w = tid; w < words; w += kSplitThreads) bits[w] = 0u;
+    if (tid == 0) crowded = 0u;
+    __syncthreads();
+    each_of(0, [&](int u, uint32_t) { atomicAdd(&bits[code[u] >> 5], 1u); });
+    __syncthreads();
+    sum = 0;
+    uint32_t largest = 0;
+    for (int w = w0; w < w0 + per && w < words; ++w) {
+      sum += bits[w];
+      largest = bits[w] > largest ? bits[w] : largest;
+    }
+    if (largest > (uint32_t)kDirectRanked) crowded = 1u;
+    run = block_exclusive_scan<kSplitThreads>(sum, wave_totals, nullptr);
+    for (int w = w0; w < w0 + per && w < words; ++w) {
+      const uint32_t c = bits[w];
+      first[w] = bits[w] = run;              // bits: where the word's next pillar goes
+      run += c;
+    }
+    __syncthreads();
+    each_of(0, [&](int u, uint32_t e) { list[atomicAdd(&bits[code[u] >> 5], 1u)] = code[u] << 12 | e; });
+    __syncthreads();
+    if (crowded == 0u) {
+      each_of(0, [&](int u, uint32_t e) {
+        put(base + rank_in_run(list, first[code[u] >> 5], bits[code[u] >> 5], code[u] << 12 | e), code[u], index[u]);
+      });
+      return;
+    }
+    direct_sort<kSplitThreads>(list, T);
+    // The positions in the bucket come back as places in the order; the indices are where they were.
+    for (uint32_t e = tid; e < T; e += kSplitThreads) bits[list[e] & 0xfffu] = e;
+    __syncthreads();
+    each_of(0, [&](int u, uint32_t e) { put(base + bits[e], code[u], index[u]); });
+    return;
+  }
+  // Two stable passes of eight bits over the indices, wavefronts with consecutive pieces.
+  uint32_t* const one = scratch + (int64_t)s * n + base;
+  uint32_t* const two = scratch + (int64_t)(S + s) * n + base;
+  for (uint32_t e0 = 0; e0 < T; e0 += kSplitList) {
+    fetch(code, index, e0);
+    each_of(e0, [&](int u, uint32_t e) { one[e] = index[u]; });
+  }
+  const uint32_t last_frame = (uint32_t)kp.B - 1u, piece = (T + kSplitThreads - 1u) / kSplitThreads * 64u;
+  const uint32_t begin = wave * piece, stop = begin + piece < T ? begin + piece : T;
+  uint32_t* const counts = list;             // [kSplitWaves][256]
+  auto pass = [&](const uint32_t* src, int shift, auto use) {
+    __syncthreads();
+    for (int w = tid; w < kSplitWaves * 256; w += kSplitThreads) counts[w] = 0u;
+    __syncthreads();
+    auto digit_of = [&](uint32_t i, uint32_t* c) {
+      *c = direct_key<Z, FRAMES>(coords + (int64_t)i * STRIDE, dk, last_frame) - key0;
+      return *c >> shift & 255u;
+    };
+    uint32_t c;
+    for (uint32_t e = begin + lane; e < stop; e += 64) atomicAdd(&counts[wave * 256 + digit_of(src[e], &c)], 1u);
+    __syncthreads();
+    uint32_t total = 0;
+    if (tid < 256)
+      for (int w = 0; w < kSplitWaves; ++w) {
+        const uint32_t v = counts[w * 256 + tid];
+        counts[w * 256 + tid] = total;
+        total += v;
+      }
+    const uint32_t start = block_exclusive_scan<kSplitThreads>(total, wave_totals, nullptr);
+    if (tid < 256)
+      for (int w = 0; w < kSplitWaves; ++w) counts[w * 256 + tid] += start;
+    __syncthreads();
+    for (uint32_t e0 = begin; e0 < stop; e0 += 64) {
+      const bool valid = e0 + lane < stop;
+      const uint32_t i = src[valid ? e0 + lane : begin], d = digit_of(i, &c);
+      const uint64_t same = same_number(d, 8) & __ballot(valid);
+      const uint32_t pos = counts[wave * 256 + d] + lanes_below(same);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (valid && lanes_below(same) == 0u) counts[wave * 256 + d] = pos + (uint32_t)__popcll(same);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (valid) use(pos, c, i);
+    }
+  };
+  pass(one, 0, [&](uint32_t pos, uint32_t, uint32_t i) { two[pos] = i; });
+  pass(two, 8, [&](uint32_t pos, uint32_t c, uint32_t i) { put(base + pos, c, i); });
 }
 
 // Pass plan for keys of `key_bits` bits: digit width and number of passes.
@@ -1067,6 +1415,26 @@ inline PassPlan pass_plan(int64_t n, int key_bits, int sorts) {
   return pp;
 }
 
+// How a sort makes its keys with 24-bit products; false if its grid is too large for them.
+bool direct_keys(const ff_geom* g, const FlattenZ* z, const KeyParams& kp, DirectKeys* k) {
+  const int at_l2 = kp.bits_l3, at_l1 = at_l2 + kp.bits_l2, at_w3 = at_l1 + kp.bits_l1, at_w2 = at_w3 + kp.bits_w3,
+            at_w1 = at_w2 + kp.bits_w2;
+  auto axis = [](DirectAxis& a, int64_t grid, int shift, int win, int at_w, int at_l) {
+    a.shift = shift;
+    a.max = (uint32_t)(grid + shift - 1);
+    a.mul = ((1u << 20) + (uint32_t)win - 1u) / (uint32_t)win;
+    a.unit_l = 1u << at_l;
+    a.rest_w = (1u << at_w) - (uint32_t)win * a.unit_l;  // (the window's field begins where the local one's values end)
+    return grid + shift <= kDirectMaxGrid;
+  };
+  if (!axis(k->x, g->grid_x, kp.sx, kp.win_x, kp.axis == 0 ? at_w1 : at_w2, kp.axis == 0 ? at_l1 : at_l2) ||
+      !axis(k->y, g->grid_y, kp.sy, kp.win_y, kp.axis == 0 ? at_w2 : at_w1, kp.axis == 0 ? at_l2 : at_l1) ||
+      !axis(k->z, z ? z->grid_z : 1, kp.sz, kp.win_z, at_w3, 0))
+    return false;
+  k->unit_b = 1u << (at_w1 + kp.bits_w1);
+  return true;
+}
+
 // Whether this cloud is sorted in one launch (k_direct), and how.
 bool direct_plan(int64_t n, const ff_geom* g, const FlattenZ* z, int sorts, const Batch& bt, int key_bits, DirectBatch* db) {
   if (n > kDirectMaxRows || g->num_frames > kDirectMaxFrames || key_bits > 24) return false;
@@ -1078,31 +1446,48 @@ bool direct_plan(int64_t n, const ff_geom* g, const FlattenZ* z, int sorts, cons
   const int64_t enough = ceil_div(n, 128);
   if (parts > enough) parts = enough;
   if (parts * most < codes) parts = ceil_div(codes, most);
-  // Beyond one workgroup a compute unit there is a second round: it pays for few pillars (four sorts of eight frames, 512
+  // Beyond one workgroup a compute unit there is a second round: it pays for this few pillars (four sorts of eight frames, 512
   // workgroups, radix path / this one: 16,000 pillars 39 / 26 us, 60,000 52 / 57).
-  if (parts * sorts > 512 || (parts * sorts > 256 && n > 32768)) return false;
+  if (parts * sorts > 512) return false;
   db->parts = (int32_t)parts;
   db->range = (uint32_t)(ceil_div(ceil_div(codes, parts), (int64_t)32) * 32);
+  for (int s = 0; s < sorts; ++s)
+    if (!direct_keys(g, z, bt.kp[s], &db->k[s])) return false;
+  return true;
+}
+
+// Whether it is sorted by k_split and k_buckets, and how.
+bool split_plan(int64_t n, const ff_geom* g, const FlattenZ* z, int sorts, const Batch& bt, int tile_rows, SplitBatch* sb) {
+  if (n < kSplitMinRows || ceil_div(n, (int64_t)tile_rows) > kSplitMaxTiles) return false;
+  sb->tiles = (int32_t)ceil_div(n, (int64_t)tile_rows);
+  const int64_t fill = kSplitBuckets / sorts;
+  int64_t most = n / kSplitRows < fill ? n / kSplitRows : fill;
+  if (n / kSplitRowsMany > most) most = n / kSplitRowsMany;
+  if (most > kSplitMaxBuckets) most = kSplitMaxBuckets;
+  int64_t buckets = 0;
   for (int s = 0; s < sorts; ++s) {
     const KeyParams& kp = bt.kp[s];
-    DirectKeys& k = db->k[s];
-    const int at_l2 = kp.bits_l3, at_l1 = at_l2 + kp.bits_l2, at_w3 = at_l1 + kp.bits_l1, at_w2 = at_w3 + kp.bits_w3,
-              at_w1 = at_w2 + kp.bits_w2;
-    auto axis = [](DirectAxis& a, int64_t grid, int shift, int win, int at_w, int at_l) {
-      a.shift = shift;
-      a.max = (uint32_t)(grid + shift - 1);
-      a.mul = ((1u << 20) + (uint32_t)win - 1u) / (uint32_t)win;
-      a.unit_l = 1u << at_l;
-      a.rest_w = (1u << at_w) - (uint32_t)win * a.unit_l;  // (the window's field begins where the local one's values end)
-      return grid + shift <= kDirectMaxGrid;
-    };
-    if (!axis(k.x, g->grid_x, kp.sx, kp.win_x, kp.axis == 0 ? at_w1 : at_w2, kp.axis == 0 ? at_l1 : at_l2) ||
-        !axis(k.y, g->grid_y, kp.sy, kp.win_y, kp.axis == 0 ? at_w2 : at_w1, kp.axis == 0 ? at_l2 : at_l1) ||
-        !axis(k.z, z ? z->grid_z : 1, kp.sz, kp.win_z, at_w3, 0))
-      return false;
-    k.unit_b = 1u << (at_w1 + kp.bits_w1);
+    SplitSort& t = sb->s[s];
+    const int at_frame = kp.key_bits - kp.bits_b, at_w1 = at_frame - kp.bits_w1;
+    if (kp.key_bits > 32 || at_frame > 23 || !direct_keys(g, z, kp, &t.k)) return false;
+    const int64_t nw1 = kp.axis == 0 ? ceil_div((int64_t)g->grid_x + kp.sx, kp.win_x) : ceil_div((int64_t)g->grid_y + kp.sy, kp.win_y);
+    int64_t in_frame = 0;
+    int c = 5;                               // the smallest buckets that are few enough
+    for (;; ++c) {
+      if (c > kSplitCodeBits || c > at_frame) return false;
+      in_frame = c > at_w1 ? ceil_div(nw1, (int64_t)1 << (c - at_w1)) : nw1 << (at_w1 - c);
+      if (in_frame * kp.B <= most) break;
+    }
+    t.code_bits = c;
+    t.in_frame = at_frame - c;
+    t.per_frame = (int32_t)in_frame;
+    t.skip = (int32_t)(((int64_t)1 << t.in_frame) - in_frame);
+    if (in_frame * kp.B > buckets) buckets = in_frame * kp.B;
   }
-  return true;
+  sb->bins = (int32_t)((buckets + 2) & ~(int64_t)1);  // (one more for what lies behind the cloud in its last tile)
+  sb->bin_bits = 1;
+  while ((1 << sb->bin_bits) < sb->bins) ++sb->bin_bits;
+  return (int64_t)sb->tiles * sb->bins * 2 <= n * 4;
 }
 
 struct Layout {
@@ -1282,6 +1667,41 @@ static int flatten_launch_impl(const int32_t* coords, const PointCells* pts, int
     };
     if (g->num_frames > 1) return z ? go(k_direct<true, true>, 3) : go(k_direct<false, true>, 2);
     return z ? go(k_direct<true, false>, 1) : go(k_direct<false, false>, 0);
+  }
+
+  const int own = n >= kSplitManyRows ? kSplitMany : n * num_sorts > kSplitFewRows ? kSplitFew : kSplitLeast;
+  const int tile_rows = kSplitThreads * own;
+  SplitBatch sb;
+  if (!pts && split_plan(n, g, z, num_sorts, bt, tile_rows, &sb)) {
+    PackJob job = PackJob();
+    job.layers = 0; job.blocks = 1;
+    if (pack) job = *pack;
+    uint32_t* entries = (uint32_t*)buf[0];
+    uint32_t* table = entries + (int64_t)num_sorts * n;
+    const unsigned blocks = (unsigned)(num_sorts * sb.tiles + ceil_div((int64_t)job.layers * job.blocks, kSplitThreads / 256));
+    const size_t counters = (size_t)kSplitWaves * sb.bins * 2, stage = (size_t)tile_rows * 4;
+    int64_t buckets = 0;
+    int words = 0;
+    for (int s = 0; s < num_sorts; ++s) {
+      buckets += (int64_t)sb.s[s].per_frame * bt.kp[s].B;
+      if (1 << (sb.s[s].code_bits - 5) > words) words = 1 << (sb.s[s].code_bits - 5);
+    }
+    // (bits and first of a bucket; the places of a list's entries, which take the same memory; the group list's tables)
+    size_t lds = (size_t)(kSplitList + 2 * kSplitMaxTiles + 1) * 4 + (size_t)(2 * words > kSplitList ? 2 * words : kSplitList) * 4;
+    auto go = [&](auto split, auto buckets_of) {
+      hipLaunchKernelGGL(split, dim3(blocks), dim3(kSplitThreads), counters > stage ? counters : stage, stream, coords, (int)n,
+                         num_sorts, sb, entries, table, (int)g->num_frames, job);
+      hipLaunchKernelGGL(buckets_of, dim3((unsigned)(num_sorts + 8 * ceil_div(buckets, 8))), dim3(kSplitThreads), lds, stream, coords,
+                         (int)n, num_sorts, bt, sb, tile_rows, entries, (const uint16_t*)table, (uint32_t*)buf[1], G, drop);
+      return launch_status();
+    };
+    auto go_z = [&](auto Z, auto frames) {
+      constexpr bool z_ = decltype(Z)::value, f_ = decltype(frames)::value;
+      return own == kSplitMany ? go(k_split<z_, f_, kSplitMany>, k_buckets<z_, f_>)
+           : own == kSplitFew ? go(k_split<z_, f_, kSplitFew>, k_buckets<z_, f_>) : go(k_split<z_, f_, kSplitLeast>, k_buckets<z_, f_>);
+    };
+    if (g->num_frames > 1) return z ? go_z(std::true_type(), std::true_type()) : go_z(std::false_type(), std::true_type());
+    return z ? go_z(std::true_type(), std::false_type()) : go_z(std::false_type(), std::false_type());
   }
 
   int cur = 0;

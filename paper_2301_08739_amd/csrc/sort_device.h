@@ -35,6 +35,40 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* w
   return base + inc - v;
 }
 
+// Lanes with the same number (its lowest `bits` bits)
+__device__ __forceinline__ uint64_t same_number(uint32_t v, int bits) {
+  uint64_t m = ~0ull;
+  for (int b = 0; b < bits; ++b) {
+    const uint64_t set = __ballot((v >> b) & 1u);
+    m &= (v >> b) & 1u ? set : ~set;
+  }
+  return m;
+}
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+// Rank of this lane's number among the wavefront's so far, whose counts of each number are counts[].
+__device__ __forceinline__ uint32_t rank_in_wave(uint16_t* counts, uint32_t v, int bits, bool valid) {
+  const uint64_t same = same_number(v, bits) & __ballot(valid);
+  const uint32_t before = counts[v], below = lanes_below(same);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (all lanes have read)
+  if (valid && below == 0u) counts[v] = (uint16_t)(before + (uint32_t)__popcll(same));
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  return before + below;
+}
+// counts[wave][2 word], [.. + 1], packed, to the sums of the wavefronts before; returns the totals.
+template <int WAVES>
+__device__ __forceinline__ uint32_t sum_over_waves(uint32_t* words, int words_of_wave, int word) {
+  uint32_t run = 0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) {
+    const uint32_t c = words[w * words_of_wave + word];
+    words[w * words_of_wave + word] = run;
+    run += c;                                // (no carry from the lower half: a tile or list has at most 8192 points)
+  }
+  return run;
+}
+
 // Cell of point i (see PointCells).  Comparisons with NaN fail, so such a point is dropped.
 __device__ __forceinline__ void point_cell(const PointCells& pt, int64_t i, int32_t* c) {
   const float cx = floorf((pt.xy[2 * i] - pt.x_min) / pt.voxel_x), cy = floorf((pt.xy[2 * i + 1] - pt.y_min) / pt.voxel_y);

@@ -268,40 +268,6 @@ constexpr int kVoxManyRanges = 256;         // more than this many have four wor
 static_assert(kVoxTile == 1 << kVoxLocalBits && kVoxMaxTiles <= kVoxOrderThreads && kVoxMaxTiles * kVoxTile <= 1 << kVoxIndexBits &&
               kVoxMaxRanges << kVoxCellBits <= kVoxMaxTiles * kVoxTile, "");
 
-// Lanes with the same number (its lowest `bits` bits)
-__device__ __forceinline__ uint64_t same_number(uint32_t v, int bits) {
-  uint64_t m = ~0ull;
-  for (int b = 0; b < bits; ++b) {
-    const uint64_t set = __ballot((v >> b) & 1u);
-    m &= (v >> b) & 1u ? set : ~set;
-  }
-  return m;
-}
-__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-// Rank of this lane's number among the wavefront's so far, whose counts of each number are counts[].
-__device__ __forceinline__ uint32_t rank_in_wave(uint16_t* counts, uint32_t v, int bits, bool valid) {
-  const uint64_t same = same_number(v, bits) & __ballot(valid);
-  const uint32_t before = counts[v], below = lanes_below(same);
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (all lanes have read)
-  if (valid && below == 0u) counts[v] = (uint16_t)(before + (uint32_t)__popcll(same));
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  return before + below;
-}
-// counts[wave][2 word], [.. + 1], packed, to the sums of the wavefronts before; returns the totals.
-template <int WAVES>
-__device__ __forceinline__ uint32_t sum_over_waves(uint32_t* words, int words_of_wave, int word) {
-  uint32_t run = 0;
-#pragma unroll
-  for (int w = 0; w < WAVES; ++w) {
-    const uint32_t c = words[w * words_of_wave + word];
-    words[w * words_of_wave + word] = run;
-    run += c;                                // (no carry from the lower half: a tile or list has at most 8192 points)
-  }
-  return run;
-}
-
 // entries: of tile t, at t * kVoxTile, its points sorted by range: cell of the range << 13 | point of the tile.
 // table[t][bin]: where the range begins there; the bin behind the last range is that of the dropped points.
 __global__ __launch_bounds__(kVoxThreads) void k_vox_split(PointCells pts, int m, int bins, int bin_bits,

@@ -29,24 +29,24 @@ CASES = {
     "one_cell": (lambda: np.tile(np.array([[0, 300, 77]], np.int32), (20000, 1)), 1, 468, 13),
     "two_cells": (lambda: np.array([[0, 300, 77], [0, 300, 78]], np.int32)[np.arange(9001) % 3 // 2], 1, 468, 13),
     "one_pillar": (lambda: np.array([[0, 5, 9]], np.int32), 1, 468, 13),
-    "board_in_grid_order": (lambda: _board(300, 300), 1, 468, 9),
-    "dense_board": (lambda: _cells(1, 160, 160, 25600, 1), 1, 468, 13),
-    "every_cell_twice": (lambda: _cells(1, 120, 120, 28000, 2, each=2), 1, 468, 13),
+    "board_in_grid_order": (lambda: _board(156, 156), 1, 468, 9),
+    "dense_board": (lambda: _cells(1, 156, 156, 24336, 1), 1, 468, 13),
+    "every_cell_twice": (lambda: _cells(1, 120, 120, 24000, 2, each=2), 1, 468, 13),
     "few_shared_cells": (lambda: np.concatenate([_cells(1, 468, 468, 12000, 3), _cells(1, 468, 468, 500, 4)]), 1, 468, 13),
     "few_cells": (lambda: np.random.default_rng(18).integers(0, 7, (5000, 3)).astype(np.int32) * [0, 1, 1], 1, 468, 13),
-    "hundred_cells": (lambda: np.random.default_rng(13).integers(0, 10, (30000, 3)).astype(np.int32) * [0, 1, 1], 1, 468, 13),
-    "half_in_one_cell": (lambda: np.concatenate([_cells(1, 468, 468, 40000, 14), np.tile(np.array([[0, 9, 9]], np.int32), (40000, 1))])
-                         [np.random.default_rng(15).permutation(80000)], 1, 468, 13),
-    "corner_cells_shared": (lambda: np.random.default_rng(16).integers(0, 120, (131072, 3)).astype(np.int32) * [0, 1, 1], 1, 468, 13),
-    "many_shared_cells": (lambda: np.random.default_rng(17).integers(0, 468, (120000, 3)).astype(np.int32) * [0, 1, 1], 1, 468, 13),
+    "hundred_cells": (lambda: np.random.default_rng(13).integers(0, 10, (24000, 3)).astype(np.int32) * [0, 1, 1], 1, 468, 13),
+    "half_in_one_cell": (lambda: np.concatenate([_cells(1, 468, 468, 6000, 14), np.tile(np.array([[0, 9, 9]], np.int32), (18000, 1))])
+                         [np.random.default_rng(15).permutation(24000)], 1, 468, 13),
+    "corner_cells_shared": (lambda: np.random.default_rng(16).integers(0, 120, (24576, 3)).astype(np.int32) * [0, 1, 1], 1, 468, 13),
+    "many_shared_cells": (lambda: np.random.default_rng(17).integers(0, 200, (24576, 3)).astype(np.int32) * [0, 1, 1], 1, 468, 13),
     "sixteen_frames": (lambda: _cells(16, 60, 60, 5000, 5), 16, 60, 6),
     "seventeen_frames": (lambda: _cells(17, 60, 60, 5000, 6), 17, 60, 6),
     "grid_4096": (lambda: _cells(1, 4096, 4096, 7000, 7), 1, 4096, 256),
     "wide_keys": (lambda: _cells(2, 1500, 1500, 4000, 8), 2, 1500, 9),
     "window_of_one": (lambda: _cells(1, 468, 468, 9000, 9), 1, 468, 1),
-    "most_pillars": (lambda: _cells(1, 468, 468, 131072, 10), 1, 468, 13),
-    "one_more": (lambda: _cells(1, 468, 468, 131073, 11), 1, 468, 13),
-    "eight_frames_two_rounds": (lambda: _cells(8, 468, 468, 32768, 12), 8, 468, 9),
+    "most_pillars": (lambda: _cells(1, 468, 468, 24576, 10), 1, 468, 13),
+    "one_more": (lambda: _cells(1, 468, 468, 24577, 11), 1, 468, 13),
+    "eight_frames_two_rounds": (lambda: _cells(8, 468, 468, 24576, 12), 8, 468, 9),
 }
 
 

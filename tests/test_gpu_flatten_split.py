@@ -1,0 +1,82 @@
+"""Large clouds sorted by bucket: on both sides of the limits of what is sorted this way, buckets with more pillars than fit the
+registers of a workgroup, shared cells that are sorted in LDS and through memory, frames without pillars, three dimensions."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2301_08739_amd as ff
+from gpu_util import DEV
+
+pytestmark = pytest.mark.gpu
+
+
+def _cells(B, X, Y, n, seed):
+    rng = np.random.default_rng(seed)
+    k = rng.permutation(rng.choice(B * X * Y, n, replace=False))
+    return np.stack([k // (X * Y), k // Y % X, k % Y], 1).astype(np.int32)
+
+
+def _any(B, X, Y, n, seed):
+    rng = np.random.default_rng(seed)
+    return np.stack([rng.integers(0, B, n), rng.integers(0, X, n), rng.integers(0, Y, n)], 1).astype(np.int32)
+
+
+CASES = {  # pillars, frames, grid, window
+    "first": (lambda: _cells(1, 468, 468, 24577, 1), 1, 468, 13),
+    "first_for_its_frames": (lambda: _cells(20, 60, 60, 16385, 13), 20, 60, 13),
+    "before_it": (lambda: _cells(20, 60, 60, 16384, 14), 20, 60, 13),
+    "small_tiles": (lambda: _cells(2, 468, 468, 262144, 15), 2, 468, 13),
+    "middle_tiles": (lambda: _cells(2, 468, 468, 262145, 16), 2, 468, 13),
+    "tile_edge": (lambda: _cells(2, 400, 400, 1024 * 70, 2), 2, 400, 9),
+    "tile_edge_and_one": (lambda: _cells(2, 400, 400, 1024 * 70 + 1, 3), 2, 400, 9),
+    "whole_board": (lambda: np.stack([np.zeros(160000, np.int64), np.arange(160000) // 400, np.arange(160000) % 400], 1).astype(np.int32), 1, 400, 13),
+    "empty_frames": (lambda: _cells(3, 300, 300, 150000, 4) * [4, 1, 1], 12, 300, 13),
+    "few_cells": (lambda: _any(1, 30, 30, 60000, 17), 1, 468, 13),
+    "crowded_corner": (lambda: _cells(1, 420, 420, 150000, 5), 1, 2000, 128),
+    "shared_cells": (lambda: _any(2, 200, 200, 100000, 6), 2, 200, 13),
+    "thousands_a_cell": (lambda: _any(1, 7, 7, 50000, 7), 1, 468, 13),
+    "hundreds_of_frames": (lambda: _cells(300, 60, 60, 400000, 8), 300, 60, 9),
+    "large_tiles": (lambda: _cells(40, 200, 200, (1 << 20) + 77, 9), 40, 200, 13),
+    "before_large_tiles": (lambda: _cells(40, 200, 200, (1 << 20) - 1, 10), 40, 200, 13),
+    "key_of_more_than_32_bits": (lambda: _cells(2, 4096, 4096, 140000, 11) * [4000, 1, 1], 5000, 4096, 13),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_against_the_oracle(name):
+    make, B, grid, w = CASES[name]
+    coords = np.ascontiguousarray(make(), dtype=np.int32)
+    g, og = ff.Geometry(B, grid, grid, w, w), oracle.Geometry(B, grid, grid, w, w)
+    ct = torch.from_numpy(coords).to(DEV)
+    pairs = [(0, 0), (1, 1)]
+    for G, tail in ((69, ff.FF_TAIL_MASK), (7, ff.FF_TAIL_DROP)):
+        print(name, G, flush=True)
+        got = ff.ff_flatten_batch(ct, g, pairs, G, tail=tail)
+        for (axis, shift), (perm, off, ng) in zip(pairs, got):
+            want_perm, want_off, want_keys = oracle.flatten(coords, og, axis, shift, G)
+            assert np.array_equal(perm.cpu().numpy(), want_perm)
+            if tail == ff.FF_TAIL_MASK:
+                k = int(ng.item())
+                assert k == len(want_off) - 1 and np.array_equal(off.cpu().numpy()[:k + 1], want_off)
+                one, one_off, one_ng, keys = ff.ff_flatten(ct, g, axis, shift, G, want_keys=True)
+                assert torch.equal(one, perm) and torch.equal(one_off, off) and int(one_ng.item()) == k
+                assert np.array_equal(keys.cpu().numpy().view(np.uint64), want_keys)
+            else:
+                sizes = np.bincount(coords[:, 0], minlength=B)
+                starts = np.concatenate([[0], np.cumsum(sizes)[:-1]])
+                want = np.concatenate([starts[b] + G * np.arange(sizes[b] // G) for b in range(B)] + [[len(coords)]])
+                assert int(ng.item()) == len(want) - 1
+                assert np.array_equal(off.cpu().numpy()[:len(want)], want)
+
+
+def test_three_dimensions():
+    rng = np.random.default_rng(12)
+    n, dims = 150000, (2, 120, 120, 12, 6, 6, 3)
+    k = rng.permutation(rng.choice(2 * 120 * 120 * 12, n, replace=False))
+    coords = np.stack([k // (120 * 120 * 12), k // (120 * 12) % 120, k // 12 % 120, k % 12], 1).astype(np.int32)
+    for axis, shift in ((0, 0), (1, 1)):
+        perm, off, ng = ff.ff_flatten3d(torch.from_numpy(coords).to(DEV), ff.Geometry3(*dims), axis, shift, 50)
+        want_perm, want_off = oracle.flatten3d(coords, oracle.Geometry3(*dims), axis, shift, 50, tail="mask")
+        assert np.array_equal(perm.cpu().numpy(), want_perm)
+        assert np.array_equal(off.cpu().numpy()[:int(ng.item()) + 1], want_off)
