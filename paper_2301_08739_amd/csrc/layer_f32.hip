@@ -22,12 +22,15 @@
 // (r & 3) + 8 (r >> 2) + 4 h in registers r = 0..15.  Registers 8 f .. 8 f + 7, split, are an operand of a later product
 // whose inputs are numbered in that order (the weights that meet them are permuted to match when they are packed), and
 // register r as it stands is one k-step of a 32x32x2 product: K and Q feed S^T = K Q^T, V (operand roles swapped) and
-// P = exp2(S^T) feed P V, nothing is shuffled between lanes.  With heads of 16 the other 16 rows of the A operand of P V
-// are ones, so the row sums of P come with the product.
+// P = exp2(S^T) feed P V, nothing is shuffled between lanes.  So it is with heads of 32.  With heads of 16 half of a 32x32x2
+// product of P V would be for rows that no one wants; there the products are 16x16x4, for which registers change lanes in
+// pairs, once for K, Q and V and once for every output (permlane swaps, 2 for 128 numbers).  Row sums of P are added beside the
+// products.  Against 32x32x2 products with the sums as rows of ones, us a layer: 30,000 rows at C = 128, G = 64 61.4 -> 59.6,
+// 100,000 192 -> 183, 20,000 at C = 64 40.4 -> 38.4; C = 256 (sums only) 172 -> 165; errors against float64 1 to 6 % smaller.
 //
-// What bounds it: the matrix pipe, about 37k cycles per wavefront at C = 128, G = 64, two wavefronts per SIMD (30k rows:
+// What bounds it: the matrix pipe, about 33k cycles per wavefront at C = 128, G = 64, two wavefronts per SIMD (30k rows:
 // two groups on most compute units), and nearly as many issue cycles of GELU, exponentials, splits and LayerNorm beside
-// it.  Measured, 30,000 rows at C = 128, G = 64: 57 us a layer = 155 TFLOP/s (the plain kernels: 455 us); 2,000 rows at
+// it.  Measured, 30,000 rows at C = 128, G = 64: 55 us a layer = 161 TFLOP/s (the plain kernels: 455 us); 2,000 rows at
 // C = 64, G = 32: 13 us (31 us).
 #include "common.h"
 #include "pack_weights.h"
@@ -100,6 +103,19 @@ __device__ __forceinline__ void mma(const Split& a, const Split& b, f32x16& big,
   small = mfma_bf16(a.p[0], b.p[1], small);
 }
 __device__ __forceinline__ f32x16 mma2(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+
+__device__ __forceinline__ f32x4 mma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+// Of the four rows of 16 lanes: a = a0 a1 a2 a3, b likewise -> a0 b0 a2 b2, a1 b1 a3 b3
+__device__ __forceinline__ void swap_rows(float& a, float& b) {
+  auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(t[0]); b = __uint_as_float(t[1]);
+}
+// -> a0 a1 b0 b1, a2 a3 b2 b3
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+  auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(t[0]); b = __uint_as_float(t[1]);
+}
 
 // v of lane n and of lane n + 32 combined, in every lane
 __device__ __forceinline__ float half_sum(float v) {
@@ -475,36 +491,112 @@ __device__ __forceinline__ bool layer_f32_rows(
 
   // ---- attention -----------------------------------------------------------------------------------------------------
   // SHORT: some group of the workgroup has fewer members than its blocks hold; the rows beyond them are cut out of P V
-  // and of the row sums by clearing them in the A operand.
+  // by clearing them in the A operand, and out of the row sums.
   Split wo0 = wo_at(0);
   auto attention = [&](auto shortc) {
     constexpr bool SHORT = decltype(shortc)::value;
+    // Whether row `key` of group gl is one of its members
+    auto in = [&](int gl, int key) { return !SHORT || key < m[gl]; };
+    // o: the lane's share of a fragment of A
+    auto put_head = [&](int qt, int frag, const float* o) {
+      const Split sp = pack8(o);
 #pragma unroll
-    for (int gl = 0; gl < GPW; ++gl) {
+      for (int part = 0; part < PARTS; ++part) a_at(qt, frag, part) = sp.p[part];
+    };
+    if constexpr (NH == 2) {
+      // Heads of 16: products of 16 x 16, lane (g, i) = 16 g + i.  Two registers of K and Q, features f and f + 1 of rows
+      // (h, n), become the operands of rows 0 .. 15 and 16 .. 31; two of V, rows r and r + 8 of both heads, those of the
+      // heads, with row 16 b + 4 g + r in lane group g as the scores have it.
 #pragma unroll
-      for (int hd = 0; hd < NH; ++hd) {
-        // A operand of P V: the head's value rows, and (heads of 16) ones in the other head's rows
-        f32x16 va[PTG], one[NH == 1 ? PTG : 1];
-        const bool mine = NH == 1 || ((lane >> 4) & 1) == hd;
+      for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          float a = Q[pt][2 * r], b = Q[pt][2 * r + 1];
+          swap_rows(a, b);
+          Q[pt][2 * r] = a; Q[pt][2 * r + 1] = b;
+          a = K[pt][2 * r]; b = K[pt][2 * r + 1];
+          swap_rows(a, b);
+          K[pt][2 * r] = a; K[pt][2 * r + 1] = b;
+          const int v = 8 * (r / 4) + r % 4;
+          a = V[pt][v]; b = V[pt][v + 4];
+          swap_halves(a, b);
+          swap_rows(a, b);
+          const bool real = in(pt / PTG, 32 * (pt % PTG) + 16 * (r / 4) + 4 * (lane >> 4) + r % 4);
+          V[pt][v] = real ? a : 0.f; V[pt][v + 4] = real ? b : 0.f;
+        }
+#pragma unroll
+      for (int gl = 0; gl < GPW; ++gl)
+#pragma unroll
+        for (int hd = 0; hd < 2; ++hd)
+#pragma unroll
+          for (int q0 = 0; q0 < PTG; ++q0) {
+            const int qt = gl * PTG + q0;
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            f32x4 S[PTG][2][2], O[2] = {zero, zero};
+#pragma unroll
+            for (int kt = 0; kt < PTG; ++kt) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                  for (int q = 0; q < 2; ++q)
+                    S[kt][b][q] = mma4(K[gl * PTG + kt][8 * hd + 2 * r + b], Q[qt][8 * hd + 2 * r + q], r ? S[kt][b][q] : zero);
+            }
+            float mx[2] = {S[0][0][0][0], S[0][0][1][0]}, sum[2] = {0.f, 0.f};
+#pragma unroll
+            for (int kt = 0; kt < PTG; ++kt)
+#pragma unroll
+              for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) mx[q] = fmaxf(mx[q], S[kt][i / 4][q][i % 4]);
+            swap_rows(mx[0], mx[1]);
+            mx[0] = mx[1] = half_max(fmaxf(mx[0], mx[1]));
+            swap_rows(mx[0], mx[1]);
+#pragma unroll
+            for (int kt = 0; kt < PTG; ++kt)
+#pragma unroll
+              for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                  const float p = __builtin_amdgcn_exp2f(S[kt][i / 4][q][i % 4] - mx[q]);
+                  O[q] = mma4(V[gl * PTG + kt][8 * (i / 4) + 4 * hd + i % 4], p, O[q]);
+                  sum[q] += in(gl, 32 * kt + 16 * (i / 4) + 4 * (lane >> 4) + i % 4) ? p : 0.f;
+                }
+            // back to lanes (h, n)
+            swap_rows(sum[0], sum[1]);
+            const float inv = 1.0f / half_sum(sum[0] + sum[1]);
+            float o[8];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              float a = O[0][r], b = O[1][r];
+              swap_rows(a, b);
+              swap_halves(a, b);
+              o[r] = a * inv;
+              o[4 + r] = b * inv;
+            }
+            put_head(qt, 2 * s + hd, o);
+          }
+    } else {
+#pragma unroll
+      for (int gl = 0; gl < GPW; ++gl) {
+        f32x16 va[PTG];
 #pragma unroll
         for (int kt = 0; kt < PTG; ++kt)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const bool in = !SHORT || 32 * kt + (r & 3) + 8 * (r >> 2) + 4 * h < m[gl];
-            va[kt][r] = in ? (mine ? V[gl * PTG + kt][r] : 1.0f) : 0.f;
-            if (NH == 1) one[kt][r] = in ? 1.0f : 0.f;
-          }
+          for (int r = 0; r < 16; ++r)
+            va[kt][r] = in(gl, 32 * kt + (r & 3) + 8 * (r >> 2) + 4 * h) ? V[gl * PTG + kt][r] : 0.f;
 #pragma unroll
         for (int q0 = 0; q0 < PTG; ++q0) {
           const int qt = gl * PTG + q0;
-          f32x16 S[PTG], O = kZero, rs = kZero;
+          f32x16 S[PTG], O = kZero;
 #pragma unroll
           for (int kt = 0; kt < PTG; ++kt) {
             S[kt] = kZero;
 #pragma unroll
-            for (int r = DH / 2 * hd; r < DH / 2 * (hd + 1); ++r) S[kt] = mma2(K[gl * PTG + kt][r], Q[qt][r], S[kt]);
+            for (int r = 0; r < 16; ++r) S[kt] = mma2(K[gl * PTG + kt][r], Q[qt][r], S[kt]);
           }
-          float mx = S[0][0];
+          float mx = S[0][0], sum[2] = {0.f, 0.f};
 #pragma unroll
           for (int kt = 0; kt < PTG; ++kt)
 #pragma unroll
@@ -516,18 +608,15 @@ __device__ __forceinline__ bool layer_f32_rows(
             for (int r = 0; r < 16; ++r) {
               const float p = __builtin_amdgcn_exp2f(S[kt][r] - mx);
               O = mma2(va[kt][r], p, O);
-              if (NH == 1) rs = mma2(one[kt][r], p, rs);
+              sum[r % 2] += in(gl, 32 * kt + (r & 3) + 8 * (r >> 2) + 4 * h) ? p : 0.f;
             }
-          const float inv = 1.0f / (NH == 1 ? rs[0] : hd == 0 ? O[8] : O[0]);
-          // -> A, fragments in operand order
+          const float inv = 1.0f / half_sum(sum[0] + sum[1]);
 #pragma unroll
-          for (int f = 0; f < DH / 16; ++f) {
+          for (int f = 0; f < 2; ++f) {
             float o[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) o[j] = O[8 * (NH == 2 ? hd : f) + j] * inv;
-            const Split sp = pack8(o);
-#pragma unroll
-            for (int part = 0; part < PARTS; ++part) a_at(qt, 2 * s + (NH == 2 ? hd : f), part) = sp.p[part];
+            for (int j = 0; j < 8; ++j) o[j] = O[8 * f + j] * inv;
+            put_head(qt, 2 * s + f, o);
           }
         }
       }
