@@ -421,15 +421,21 @@ def _bits(v):
 def flatten_bytes(n, B, grid, window):
     """Bytes of one sort configuration (shifted geometry, the wider key).  algorithmic: what the method is
     credited with, 28 + 24 P per pillar for P = ceil(live key bits / 8) passes that move key and index as two
-    arrays.  moved: what this implementation moves: one 64-bit word per pillar carries key and index, digits are
-    up to 10 bits wide: coordinates in (12) and words out (8), 16 per pass but the last, which reads 8 and writes
-    the 4-byte permutation; above 131,072 pillars every pass after the first also reads its words once more to
-    count its tiles (8)."""
+    arrays.  moved: what this implementation moves.  Up to 24,576 pillars (16 frames, 24 key bits) one launch reads the
+    coordinates (12; all its workgroups do, from cache) and writes the permutation (4); up to 512 tiles of 8192 pillars
+    two launches pass on 4 bytes a pillar in between; beyond, a radix sort: coordinates in (12) and words out (8), 16
+    per pass of up to 10 bits but the last, which reads 8 and writes the permutation (4), and 8 for counting the tiles
+    of every pass after the first."""
     nw = -(-(grid + window // 2) // window)
     live = _bits(B) + 2 * _bits(nw) + 2 * _bits(window)
-    p8, p10 = -(-live // 8), max(1, -(-live // 10))
-    moved = 12 + 8 + 16 * (p10 - 1) + 8 + 4 + (8 * (p10 - 1) if n > 131072 else 0)
-    return {"algorithmic": (28 + 24 * p8) * n, "moved": moved * n, "passes_credited": p8, "passes_run": p10}
+    p8, run = -(-live // 8), max(1, -(-live // 10))
+    if n <= 24576 and B <= 16 and live <= 24:
+        run, moved = 1, 12 + 4
+    elif 16384 < n <= 512 * 8192:
+        run, moved = 2, 12 + 4 + 4 + 4
+    else:
+        moved = 12 + 8 + 16 * (run - 1) + 8 + 4 + (8 * (run - 1) if n > 131072 else 0)
+    return {"algorithmic": (28 + 24 * p8) * n, "moved": moved * n, "passes_credited": p8, "passes_run": run}
 
 
 def saturation_point(ff, torch, c, dt, dev, B, variants):
