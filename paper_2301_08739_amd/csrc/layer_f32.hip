@@ -30,7 +30,7 @@
 //
 // What bounds it: the matrix pipe, about 33k cycles per wavefront at C = 128, G = 64, two wavefronts per SIMD (30k rows:
 // two groups on most compute units), and nearly as many issue cycles of GELU, exponentials, splits and LayerNorm beside
-// it.  Measured, 30,000 rows at C = 128, G = 64: 55 us a layer = 161 TFLOP/s (the plain kernels: 455 us); 2,000 rows at
+// it.  Measured, 30,000 rows at C = 128, G = 64: 60 us a layer = 148 TFLOP/s (the plain kernels: 455 us); 2,000 rows at
 // C = 64, G = 32: 13 us (31 us).
 #include "common.h"
 #include "pack_weights.h"
