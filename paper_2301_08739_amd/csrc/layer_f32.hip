@@ -282,11 +282,16 @@ __device__ __forceinline__ bool layer_f32_rows(
   int pil[PT];                             // pillar of my LN1 / store rows
   int xrow[PT];                            // row of feats of (row block, n): the residual
   f32x4 raw[PT][2][2];                     // features 8 (lc + LPR k) .. + 7 of my rows
+  // Slots without a member, and all of them before the group list is there, meet entries of perm that need not name a row.
+  auto pillar_at = [&](int p) -> int {
+    const uint32_t i = (uint32_t)perm[p], last = (uint32_t)n - 1u;
+    return (int)(i < last ? i : last);
+  };
   auto fetch = [&](auto pos) {
 #pragma unroll
-    for (int t = 0; t < PT; ++t) pil[t] = perm[pos((s * PT + t) * RPS + lr)];
+    for (int t = 0; t < PT; ++t) pil[t] = pillar_at(pos((s * PT + t) * RPS + lr));
 #pragma unroll
-    for (int t = 0; t < PT; ++t) xrow[t] = in_sorted ? pos(32 * t + nrow) : perm[pos(32 * t + nrow)];
+    for (int t = 0; t < PT; ++t) xrow[t] = in_sorted ? pos(32 * t + nrow) : pillar_at(pos(32 * t + nrow));
 #pragma unroll
     for (int t = 0; t < PT; ++t) {
       const int64_t row = in_sorted ? pos((s * PT + t) * RPS + lr) : pil[t];
@@ -364,8 +369,8 @@ __device__ __forceinline__ bool layer_f32_rows(
   };
   put_rows(false);
 
-  // ---- rows of no group ('Drop Residual'): copied ------------------------------------------------------------------
-  if (drop) {
+  // ---- rows of no group ('Drop Residual'): copied, unless there is no list -----------------------------------------
+  if (drop && ngroups >= 0) {
     auto copy_rows = [&](int lo, int hi) {
       constexpr int PR = C / 4;            // 16-byte pieces per row
       hi = hi < n ? hi : n;

@@ -100,7 +100,9 @@ __global__ __launch_bounds__(256) void k_ln_qkv(const T* __restrict__ feats, con
                                                  int64_t n, int C, const T* __restrict__ ln_g,
                                                  const T* __restrict__ ln_b, float eps,
                                                  const T* __restrict__ w_qkv, const T* __restrict__ b_qkv,
-                                                 const T* __restrict__ pos_embed, float* __restrict__ qkv) {
+                                                 const T* __restrict__ pos_embed, const int32_t* __restrict__ num_groups,
+                                                 float* __restrict__ qkv) {
+  if (*num_groups < 0) return;  // no list: perm need not be one either
   extern __shared__ float lds[];
   float* X = lds;              // [RBT][C]
   float* U = X + RBT * C;      // [RBT][C]
@@ -201,7 +203,8 @@ __global__ __launch_bounds__(256) void k_out_ffn(const T* __restrict__ feats, co
                                                   const T* __restrict__ ln_g, const T* __restrict__ ln_b, float eps,
                                                   const T* __restrict__ w1, const T* __restrict__ b1,
                                                   const T* __restrict__ w2, const T* __restrict__ b2,
-                                                  TO* __restrict__ out) {
+                                                  const int32_t* __restrict__ num_groups, TO* __restrict__ out) {
+  if (*num_groups < 0) return;
   extern __shared__ float lds[];
   float* O = lds;               // [RBT][C]
   float* X1 = O + RBT * C;      // [RBT][C]
@@ -270,7 +273,7 @@ int launch_typed(const void* feats, void* out, int64_t n, const int32_t* perm, c
   auto run_qkv = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(n, pa.rb)), dim3(256), pa.lds, stream, (const T*)feats, perm, n, C,
                        (const T*)w->ln1_g, (const T*)w->ln1_b, w->ln_eps, (const T*)w->w_qkv, (const T*)w->b_qkv,
-                       (const T*)w->pos_embed, qkv);
+                       (const T*)w->pos_embed, num_groups, qkv);
   };
   if (pa.tiled) run_qkv(k_ln_qkv<T, kRowsWide, true>);
   else run_qkv(k_ln_qkv<T, RB, false>);
@@ -299,7 +302,7 @@ int launch_typed(const void* feats, void* out, int64_t n, const int32_t* perm, c
     hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(n, rb)), dim3(256),
                        ((size_t)3 * rb * C + (size_t)rb * F + 2 * C) * 4, stream, (const T*)feats, perm, n, C, F, o,
                        (const T*)w->w_o, (const T*)w->b_o, (const T*)w->ln2_g, (const T*)w->ln2_b, w->ln_eps,
-                       (const T*)w->w1, (const T*)w->b1, (const T*)w->w2, (const T*)w->b2, (TO*)out);
+                       (const T*)w->w1, (const T*)w->b1, (const T*)w->w2, (const T*)w->b2, num_groups, (TO*)out);
   };
   if (n >= kRowsWideMin && ffn_wide <= kRowLdsMax) run_ffn(k_out_ffn<T, TO, kRowsWide, false>, kRowsWide);
   else run_ffn(k_out_ffn<T, TO, RB, false>, RB);

@@ -346,10 +346,10 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
         pef[vb][nb / 2].u[(nb & 1) * 2 + 1] = row[vb] >= 0 ? praw[vb][nb].y : 0u;
       }
   }
-  if (drop) {
+  if (drop && ngroups >= 0) {
     // Pillars of no group skip the layer: their rows are copied.  The wavefronts of group g take the
     // sorted positions between its end and the next group's start, those of group index 0 also the
-    // positions before the first start (every position when the list is empty).
+    // positions before the first start (every position when the list is empty).  Without a list none are.
     auto copy_rows = [&](int lo, int hi) {
       constexpr int LPR = C / 8, RPW = 64 / LPR;  // 16 bytes per lane, several rows per wavefront
       const int sub = lane / LPR, col = (lane % LPR) * 8;

@@ -209,10 +209,15 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   static_assert((5 * C + F) / 4 <= PL::NT, "one piece a thread");
   f32x4 par_piece;
   if (tid < (5 * C + F) / 4) par_piece = *reinterpret_cast<const f32x4*>(params + 2 * C + 4 * tid);
-  const bool guessed = (int64_t)g_s * G == start && (m == G || start + m == n || m == 0);  // wave-uniform
+  const bool guessed = (int64_t)g_s * G == start && (m == G || start + m == n);  // wave-uniform, as is m
   if (!guessed) {
     place(start, m > 0 ? m - 1 : 0);
-    fetch_pillars();
+    if (m > 0) {
+      fetch_pillars();
+    } else {                               // no such group: its slots hold row 0, whatever is in perm
+#pragma unroll
+      for (int t = 0; t < NL; ++t) pil[t] = 0;
+    }
   }
   if (in_sorted != 2 || !guessed) fetch_rows();
   u32x4 pe[PE ? NL : 1];
@@ -252,8 +257,8 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     }
   }
   if (tid < (5 * C + F) / 4) reinterpret_cast<f32x4*>(par)[tid] = par_piece;
-  // ---- rows of no group ('Drop Residual'): copied ------------------------------------------------------------------
-  if (drop) {
+  // ---- rows of no group ('Drop Residual'): copied, unless there is no list -----------------------------------------
+  if (drop && ngroups >= 0) {
     auto copy_rows = [&](int lo, int hi, int w0, int nw) {  // by wavefronts w0 .. w0 + nw - 1
       hi = hi < n ? hi : n;
       for (int p = lo + (s - w0) * RPI + lr; p < hi; p += nw * RPI) {

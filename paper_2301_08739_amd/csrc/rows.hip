@@ -35,14 +35,13 @@ __global__ __launch_bounds__(256) void k_copy_ungrouped(const T* __restrict__ fe
     const int64_t p = p0 + threadIdx.x;
     int32_t row = -1;
     if (p < n) {
-      int ng = max_groups > 0 ? *num_groups : 0;
-      ng = ng < 0 ? 0 : (ng > max_groups ? max_groups : ng);
+      const int listed = num_groups ? *num_groups : 0, ng = listed < max_groups ? listed : max_groups;
       int lo = 0, hi = ng;  // first group start beyond p
       while (lo < hi) {
         const int mid = (lo + hi) >> 1;
         if (group_offsets[mid] <= p) lo = mid + 1; else hi = mid;
       }
-      if (lo == 0 || p >= (int64_t)group_offsets[lo - 1] + G) row = perm[p];
+      if (ng >= 0 && (lo == 0 || p >= (int64_t)group_offsets[lo - 1] + G)) row = perm[p];  // (negative: no list)
     }
     row_of[threadIdx.x] = row;
   }
