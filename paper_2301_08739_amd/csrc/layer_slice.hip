@@ -296,9 +296,10 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
                  pack2(v[8 + 4 * k], v[8 + 4 * k + 1]), pack2(v[8 + 4 * k + 2], v[8 + 4 * k + 3])};
   };
 
-  // A bias as the start of a sum: one product, of the bias in the first input and ones (16-bit numbers both, so exact).
+  // A bias as the start of a sum: one product, of the bias in the first input and ones (16-bit numbers both, so exact), and
+  // zeros in all other inputs of both (an infinite bias times zero would be no number).
   const u32x4 first_one = {h == 0 ? kOnePair & 0xffffu : 0u, 0u, 0u, 0u};
-  auto bias = [&](int off) -> u32x4 { return u32x4{pack2(par[off + nrow], 0.f), 0u, 0u, 0u}; };
+  auto bias = [&](int off) -> u32x4 { return u32x4{h == 0 ? pack2(par[off + nrow], 0.f) : 0u, 0u, 0u, 0u}; };
 
   // Steps of a product: N weight operands and RB activation operands (of `rows`) a step.  Weights are requested D - 1 steps
   // ahead, the first of them by `ahead`, before the caller's barrier; step k of this product is step `at` + k of whatever

@@ -12,7 +12,7 @@ from gpu_util import DEV, gpu_flatten, to_dev_feats, to_host
 
 pytestmark = pytest.mark.gpu
 
-HEADS = {128: 8, 256: 8}
+HEADS = {64: 4, 128: 8, 256: 8}
 
 
 @pytest.mark.parametrize("dt", [ff.FF_BF16, ff.FF_F16])
@@ -76,3 +76,25 @@ def test_scores_beyond_the_exponents(C, G, dt, score):
     assert np.isfinite(got).all()
     # one value row reaches the output projection as it is (no averaging over keys): sqrt(2) of the bar, as for groups of one
     assert np.abs(got - want).max() <= (2e-2 if dt == ff.FF_BF16 else 2.5e-3) * 2 ** 0.5
+
+
+@pytest.mark.parametrize("dt", [ff.FF_BF16, ff.FF_F16])
+@pytest.mark.parametrize("C,G", [(64, 64), (128, 32), (128, 64), (128, 100), (256, 64), (256, 90)])
+def test_infinite_output_biases(C, G, dt):
+    """An infinite second FFN bias makes its feature infinite in every row, as in the plain kernels, and leaves the others as
+    they are."""
+    n = 2 * G + 5
+    rng = np.random.default_rng(C)
+    x = to_dev_feats(rng.standard_normal((n, C)), dt)
+    dev = [torch.from_numpy(a).to(DEV) for a in (rng.permutation(n).astype(np.int32), np.array([0, G, 2 * G, n], np.int32),
+                                                 np.array([3], np.int32))]
+    run = lambda p, flags=0: to_host(ff.ff_group_attention(x, *dev, 3, ff.LayerWeights(p, dt, DEV), G, dt, ff.FF_FLAG_OUT_F32 | flags))
+    p = dict(ffsynth.layer_params(C, 2 * C, HEADS[C], seed=41))
+    want = run(p)
+    p["b2"] = np.array(p["b2"], np.float32)
+    p["b2"][[3, C - 7]] = np.inf, -np.inf
+    got = run(p)
+    assert np.isposinf(got[:, 3]).all() and np.isneginf(got[:, C - 7]).all()
+    others = np.delete(np.arange(C), [3, C - 7])
+    assert np.array_equal(got[:, others], want[:, others])
+    assert np.array_equal(np.isposinf(got), np.isposinf(run(p, ff.FF_FLAG_FORCE_GENERIC)))
