@@ -666,10 +666,9 @@ __global__ __launch_bounds__(256) void k_finalize(const uint64_t* __restrict__ s
 // A workgroup owns a range of key values of one sort.  It looks at every pillar of the cloud, works out the key, counts the
 // ones below its range (where its share of the output begins) and takes those inside: into a list, and as bits of a map with
 // one bit per key value.  Prefix counts of the bits are the sorted positions: no digits, no passes, no other workgroup's
-// results.  Fewer bits than pillars say that some share a cell: then the list's entries, which are different numbers in the
-// order wanted, are brought together by words of the map and ranked there, or, where a word has many, sorted as they are.  A
-// range with more pillars than the list holds is cut where counts of its key values say; pillars of a key value that alone has
-// too many leave in the order in which they come.
+// results.  Fewer bits than pillars say that some share a cell: then the pillars are brought together by words of the map and
+// ranked there, or, where there are many to a cell, counted by cell in the order in which they come.  Pillars that do not fit the
+// lists are looked up in the cloud again.
 //
 // What bounds it: the look at all pillars, 12 bytes and some 20 vector instructions each in every workgroup, 0.23 us for
 // every thousand of them, and 6 us for the launch, the scan and the way out; the radix path is three dependent launches of
@@ -677,16 +676,18 @@ __global__ __launch_bounds__(256) void k_finalize(const uint64_t* __restrict__ s
 // 12,345 22.5 / 11.2, 30,000 23 / 15, 131,072 41 / 37.5; four sorts, 30,000 35.5 / 25, 80,000 61.5 / 38.  The line to the two
 // launches of k_split: with one fill a call, one sort and four, 20,000 pillars of two frames 12.4 and 13.0 by this, 24 to 25 by
 // those, 30,000 14.1 and 15.2 by this, 13.4 and 13.9 by those, 60,000 21.0 and 22.5, 14.6 and 16.4.
-// What it is not made for are clouds whose pillars share a window's few cells, tens or hundreds each, which one workgroup then
-// has all to itself.  Pillars are cells that a cloud of points fills, one each.
+// Clouds whose pillars share a window's few cells, hundreds each, are one workgroup's, two more looks at the cloud: 20,000 on one,
+// a hundred or a thousand cells 39, 44 and 50 us, radix path 21 to 25 (bitonic sorts of the lists: 106, 217, 130).
 constexpr int kDirectThreads = 1024;
 constexpr int kDirectWaves = kDirectThreads / 64;
 constexpr int kDirectOwn = 1024;            // pillars of a range that a wavefront finds (4 bytes each),
 constexpr int kDirectList = kDirectWaves * kDirectOwn;  // all together,
 constexpr int kDirectShared = 8192;         // and when some share a cell and the wavefronts' lists have to be joined
-constexpr int kDirectRanked = 256;          // pillars of 32 key values that are ranked by comparing them all (80 each: 28 us a
-                                            // call of 30,000; sorted 45)
+constexpr int kDirectRanked = 256;          // pillars of 32 key values that are ranked by comparing them all
 constexpr int kDirectMaxRows = 24576;       // pillars,
+constexpr int kDirectCrowds = kDirectMaxRows / (kDirectRanked + 1);  // words that can have more
+constexpr int kDirectDigits = 2 * (kDirectShared + kDirectList) / kDirectWaves;  // cells of a range that are counted at a time
+static_assert(kDirectMaxRows <= kDirectShared + kDirectList && 32 * kDirectCrowds <= kDirectDigits && kDirectMaxRows < 1 << 16, "");
 constexpr int kDirectMaxCodes = 131072;     // and key values of a workgroup's range; a list entry of 32 bits holds one of each
 constexpr int kDirectMaxFrames = 16;
 constexpr int kDirectMaxGrid = 4096;        // cells an axis, shift included: windows by a 24-bit multiplication
@@ -795,12 +796,12 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
                                                                DirectBatch db, int G, int drop, PackJob pack) {
   constexpr int STRIDE = Z ? 4 : 3, ROWS = 4;  // rows of a thread in a round; the next round's are on their way meanwhile
   constexpr int ROUND = kDirectThreads * ROWS;
-  __shared__ uint32_t wave_totals[kDirectWaves], found[kDirectWaves], starts[kDirectMaxFrames];
-  __shared__ uint32_t taken, below, full, head, cut;
+  __shared__ uint32_t wave_totals[kDirectWaves], starts[kDirectMaxFrames], crowd_start[kDirectCrowds];
+  __shared__ uint32_t taken, below, full;
   extern __shared__ uint32_t bits[];                            // [range / 32]
   uint32_t* const first = bits + db.range / 32;                 // [range / 32] position of a word's first pillar
-  uint32_t* const joined = first + db.range / 32;               // [kDirectShared] list of all wavefronts, or counts
-  uint32_t* const list = joined + kDirectShared;                // [kDirectList] (key - lo) << idx_bits | index
+  uint32_t* const joined = first + db.range / 32;               // [kDirectShared], or with the next kDirectMaxRows: pillars by word
+  uint32_t* const list = joined + kDirectShared;                // [kDirectList] those of each wavefront: (key - lo) << idx_bits | index
   const int tid = threadIdx.x, lane = tid & 63;
   const int parts = db.parts;
   if ((int)blockIdx.x >= S * (parts + 1)) {
@@ -818,13 +819,15 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
   const int idx_bits = bt.kp[s].idx_bits;
   const uint32_t idx_mask = (1u << idx_bits) - 1u;
   const uint32_t last_frame = (uint32_t)bt.kp[s].B - 1u, end = 1u << bt.kp[s].key_bits;
-  uint32_t lo = (uint32_t)part * db.range;
+  const uint32_t lo = (uint32_t)part * db.range;
   if (lo >= end) return;
   const uint32_t hi = end - lo < db.range ? end : lo + db.range;
   int32_t* __restrict__ const perm_s = bt.perm[s];
   int32_t* __restrict__ const inv_s = bt.inv_perm[s];
   uint64_t* __restrict__ const keys_s = bt.keys_sorted[s];
+  // (The looks at a cloud that changes under the call do not agree: no position is written that is none.)
   auto put = [&](uint32_t pos, uint32_t key, uint32_t i) {
+    if (pos >= (uint32_t)n) return;
     perm_s[pos] = (int32_t)i;
     if (inv_s) inv_s[i] = (int32_t)pos;
     if (keys_s) {
@@ -841,222 +844,229 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
       r[u] = *reinterpret_cast<const Row*>(reinterpret_cast<const char*>(coords) + at);
     }
   };
-  uint32_t* const mine = list + (tid >> 6) * kDirectOwn;
-  // All pillars, one after the other and without haste: use(key, index)
-  auto every_pillar = [&](auto use) {
+  const int wave = tid >> 6;
+  uint32_t* const mine = list + wave * kDirectOwn;
+  const uint32_t len = hi - lo, words = (len + 31u) >> 5;
+  for (uint32_t w = tid; w < words; w += kDirectThreads) bits[w] = 0u;
+  if (tid == 0) { taken = 0u; below = 0u; full = 0u; }
+  __syncthreads();
+  uint32_t less = 0, count = 0;              // count: of the wavefront
+  {
+    Row r[2][ROWS];
+    int begin = 0;
+    asm volatile("" : "+s"(begin));            // (or the addresses of the first round would be kept through everything that follows)
+    fetch(r[0], begin);
+    auto look = [&](Row (&now)[ROWS], int i0, auto whole) {
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) {
+        uint32_t key = direct_key<Z, FRAMES>(now[u].c, dk, last_frame);
+        asm volatile("" : "+v"(key));          // (computed by every lane: under a condition its load would be waited for alone)
+        const uint32_t i = (uint32_t)(i0 + u * kDirectThreads + tid);
+        if (!decltype(whole)::value) key = i < (uint32_t)n ? key : 0xffffffffu;
+        less += key < lo ? 1u : 0u;
+        const uint32_t code = key - lo;
+        const uint64_t in = __ballot(code < len);
+        if (code < len) {
+          const uint32_t at = count + lanes_below(in);
+          if (at < (uint32_t)kDirectOwn) mine[at] = (code << idx_bits) | i;
+          atomicOr(&bits[code >> 5], 1u << (code & 31u));
+        }
+        count += (uint32_t)__popcll(in);
+      }
+    };
+    int i0 = begin;
+    for (; i0 + 2 * ROUND <= n; i0 += 2 * ROUND) {
+      fetch(r[1], i0 + ROUND);
+      look(r[0], i0, std::true_type());
+      fetch(r[0], i0 + 2 * ROUND);
+      look(r[1], i0 + ROUND, std::true_type());
+    }
+    if (i0 + ROUND < n) {
+      fetch(r[1], i0 + ROUND);
+      look(r[0], i0, std::true_type());
+      look(r[1], i0 + ROUND, std::false_type());
+    } else if (i0 < n) {
+      look(r[0], i0, std::false_type());
+    }
+  }
+  less = wave_inclusive_scan(less);
+  if (lane == 63) atomicAdd(&below, less);
+  if (lane == 0) {
+    atomicAdd(&taken, count);
+    if (count > (uint32_t)kDirectOwn) full = 1u;
+  }
+  __syncthreads();
+  const uint32_t T = taken, base = below;
+  const uint32_t per = (words + kDirectThreads - 1u) / kDirectThreads, w0 = tid * per;
+  uint32_t sum = 0, cells;
+  for (uint32_t w = w0; w < w0 + per && w < words; ++w) sum += (uint32_t)__popc(bits[w]);
+  uint32_t run = block_exclusive_scan<kDirectThreads>(sum, wave_totals, &cells);
+  const bool plain = cells == T;             // no two pillars share a cell
+  // The range's pillars once more, in no order: use(key - lo, index).  From the lists where all are in them, and nothing else is
+  // to be written there.
+  const bool listed = !full && (plain || T <= (uint32_t)kDirectShared);
+  auto each = [&](auto use) {
+    if (listed) {
+      for (uint32_t e = lane; e < count; e += 64) use(mine[e] >> idx_bits, mine[e] & idx_mask);
+      return;
+    }
     for (int i0 = 0; i0 < n; i0 += ROUND) {
       Row r[ROWS];
       fetch(r, i0);
 #pragma unroll
       for (int u = 0; u < ROWS; ++u) {
         const int i = i0 + u * kDirectThreads + tid;
-        if (i < n) use(direct_key<Z, FRAMES>(r[u].c, dk, last_frame), (uint32_t)i);
+        const uint32_t code = direct_key<Z, FRAMES>(r[u].c, dk, last_frame) - lo;
+        if (i < n && code < len) use(code, (uint32_t)i);
       }
     }
   };
-  // Pillars of one key value, in order: wavefronts take consecutive pieces of the cloud.  Returns how many there are.
-  auto in_order = [&](uint32_t key, uint32_t base) -> uint32_t {
-    const int wave = tid >> 6, piece = (n + kDirectThreads - 1) / kDirectThreads * 64, from = wave * piece;
-    const int to = from + piece < n ? from + piece : n;
-    auto go = [&](auto use) {
-#pragma unroll 4
-      for (int i0 = from; i0 < to; i0 += 64) {
-        const int i = i0 + lane;
-        const bool in = i < to && direct_key<Z, FRAMES>(coords + (uint32_t)(i < to ? i : 0) * STRIDE, dk, last_frame) == key;
-        use(in, i, __ballot(in));
+  if (plain) {
+    for (uint32_t w = w0; w < w0 + per && w < words; ++w) {
+      first[w] = run;
+      run += (uint32_t)__popc(bits[w]);
+    }
+    __syncthreads();
+    each([&](uint32_t code, uint32_t i) {
+      const uint32_t w = code >> 5;
+      put(base + first[w] + (uint32_t)__popc(bits[w] & ((1u << (code & 31u)) - 1u)), lo + code, i);
+    });
+    return;
+  }
+  // Some share a cell.  Pillars of few cells that do not fit the lists, or of crowded words of the map, are counted by cell, in two
+  // looks at the cloud of which wavefronts take consecutive pieces.
+  int digit_bits = 0;
+  auto in_order = [&](uint16_t* counts, auto digit, auto use) {  // digit: of a key value of the range, -1 if it is not counted
+    const int piece = (n + kDirectThreads - 1) / kDirectThreads * 64, from = wave * piece, to = from + piece < n ? from + piece : n;
+    Row r[2][ROWS];
+    auto bring = [&](Row (&r)[ROWS], int i0) {
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) {
+        const int i = i0 + u * 64 + lane;
+        r[u] = *reinterpret_cast<const Row*>(coords + (uint32_t)(i < n ? i : n - 1) * STRIDE);
       }
     };
-    uint32_t count = 0, total = 0;
-    go([&](bool, int, uint64_t all) { count += (uint32_t)__popcll(all); });
-    if (lane == 0) found[wave] = count;
-    __syncthreads();
-    uint32_t at = base;
-    for (int w = 0; w < kDirectWaves; ++w) {
-      at += w < wave ? found[w] : 0u;
-      total += found[w];
+    auto rank = [&](Row (&r)[ROWS], int i0) {
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) {
+        const int i = i0 + u * 64 + lane;
+        const uint32_t code = direct_key<Z, FRAMES>(r[u].c, dk, last_frame) - lo;
+        const int d = i < to && code < len ? digit(code) : -1;
+        const uint32_t pos = rank_in_wave(counts, d < 0 ? 0u : (uint32_t)d, digit_bits, d >= 0);
+        if (d >= 0) use(pos, code, (uint32_t)i);
+      }
+    };
+    if (from < to) bring(r[0], from);
+    for (int i0 = from; i0 < to; i0 += 2 * 64 * ROWS) {
+      bring(r[1], i0 + 64 * ROWS);
+      rank(r[0], i0);
+      bring(r[0], i0 + 2 * 64 * ROWS);
+      if (i0 + 64 * ROWS < to) rank(r[1], i0 + 64 * ROWS);
     }
-    go([&](bool in, int i, uint64_t all) {
-      if (in) put(at + __builtin_amdgcn_mbcnt_hi((uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u)), key, (uint32_t)i);
-      at += (uint32_t)__popcll(all);
-    });
-    __syncthreads();
-    return total;
   };
-  const uint32_t whole = hi - lo, origin = lo, unit = (whole + kDirectShared - 1u) / kDirectShared;  // key values of a count
-  uint32_t base = 0, len = whole;
-  // one_list: a wavefront's list overflowed, the range is gone through again for a list of all; counted: that did as well
-  bool count_below = true, one_list = false, counted = false;
-  while (lo < hi) {  // (the same for the whole workgroup, as is everything that decides below)
-    if (counted) {   // as many key values as the list holds, from the first that has pillars
-      if (tid == 0) { head = 0xffffffffu; cut = 0u; }
-      constexpr uint32_t PER = kDirectShared / kDirectThreads;
-      const uint32_t at = (lo - origin) / unit;
-      uint32_t c[PER], sum = 0;
-#pragma unroll
-      for (uint32_t q = 0; q < PER; ++q) {
-        const uint32_t p = (uint32_t)tid * PER + q;
-        c[q] = p >= at ? joined[p] : 0u;
-        sum += c[q];
-      }
-      uint32_t before = block_exclusive_scan<kDirectThreads>(sum, wave_totals, nullptr);
-#pragma unroll
-      for (uint32_t q = 0; q < PER; ++q) {
-        const uint32_t p = (uint32_t)tid * PER + q;
-        if (c[q] != 0u && before == 0u) head = p;
-        before += c[q];
-        if (before <= (uint32_t)kDirectList) atomicMax(&cut, p + 1u);
-      }
-      __syncthreads();
-      if (head == 0xffffffffu) break;
-      lo = origin + head * unit;
-      const bool heavy = cut <= head;
-      const uint32_t to = (heavy ? 1u : cut - head) * unit;
-      len = to < hi - lo ? to : hi - lo;
-      __syncthreads();
-      if (heavy) {
-        for (const uint32_t stop = lo + len; lo < stop; ++lo) base += in_order(lo, base);
-        continue;
-      }
-    }
-    const uint32_t words = (len + 31u) >> 5;
-    for (uint32_t w = tid; w < words; w += kDirectThreads) bits[w] = 0u;
-    if (tid == 0) { taken = 0u; below = 0u; full = 0u; }
+  // half: counts of a wavefront, two in a word.  start: where the first of words p's digits go, given how many there are
+  auto count_and_put = [&](uint32_t half, auto digit, auto start) {
+    uint16_t* const counts = reinterpret_cast<uint16_t*>(joined + wave * half);
     __syncthreads();
-    uint32_t less = 0, count = 0;            // count: of the wavefront
-    if (!one_list) {
-      Row r[2][ROWS];
-      int begin = 0;
-      asm volatile("" : "+s"(begin));          // (or the addresses of the first round would be kept through everything that follows)
-      fetch(r[0], begin);
-      auto look = [&](Row (&now)[ROWS], int i0, auto whole) {
+    for (uint32_t w = tid; w < kDirectWaves * half; w += kDirectThreads) joined[w] = 0u;
+    __syncthreads();
+    in_order(counts, digit, [](uint32_t, uint32_t, uint32_t) {});
+    __syncthreads();
+    for (uint32_t p0 = 0; p0 < half; p0 += kDirectThreads) {
+      const uint32_t p = p0 + tid;
+      const uint32_t total = p < half ? sum_over_waves<kDirectWaves>(joined, (int)half, (int)p) : 0u;
+      const uint32_t at = start(p, (total & 0xffffu) + (total >> 16)), both = at | (at + (total & 0xffffu)) << 16;
+      if (p < half)
 #pragma unroll
-        for (int u = 0; u < ROWS; ++u) {
-          uint32_t key = direct_key<Z, FRAMES>(now[u].c, dk, last_frame);
-          asm volatile("" : "+v"(key));        // (computed by every lane: under a condition its load would be waited for alone)
-          const uint32_t i = (uint32_t)(i0 + u * kDirectThreads + tid);
-          if (!decltype(whole)::value) key = i < (uint32_t)n ? key : 0xffffffffu;
-          less += key < lo ? 1u : 0u;
-          const uint32_t code = key - lo;
-          const uint64_t in = __ballot(code < len);
-          if (code < len) {
-            const uint32_t at = count + __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));
-            if (at < (uint32_t)kDirectOwn) mine[at] = (code << idx_bits) | i;
-            atomicOr(&bits[code >> 5], 1u << (code & 31u));
-          }
-          count += (uint32_t)__popcll(in);
-        }
-      };
-      int i0 = begin;
-      for (; i0 + 2 * ROUND <= n; i0 += 2 * ROUND) {
-        fetch(r[1], i0 + ROUND);
-        look(r[0], i0, std::true_type());
-        fetch(r[0], i0 + 2 * ROUND);
-        look(r[1], i0 + ROUND, std::true_type());
-      }
-      if (i0 + ROUND < n) {
-        fetch(r[1], i0 + ROUND);
-        look(r[0], i0, std::true_type());
-        look(r[1], i0 + ROUND, std::false_type());
-      } else if (i0 < n) {
-        look(r[0], i0, std::false_type());
-      }
-    } else {
-      every_pillar([&](uint32_t key, uint32_t i) {
-        const uint32_t code = key - lo;
-        if (code < len) {
-          const uint32_t at = atomicAdd(&taken, 1u), bit = 1u << (code & 31u);
-          if (at < (uint32_t)kDirectList) list[at] = (code << idx_bits) | i;
-          if (!(bits[code >> 5] & bit)) atomicOr(&bits[code >> 5], bit);
-          if (!counted) atomicAdd(&joined[code / unit], 1u);
-        }
-      });
-    }
-    if (count_below) {
-      const uint32_t w = wave_inclusive_scan(less);
-      if (lane == 63) atomicAdd(&below, w);
-    }
-    if (lane == 0 && !one_list) {
-      atomicAdd(&taken, count);
-      found[tid >> 6] = count;
-      if (count > (uint32_t)kDirectOwn) full = 1u;
+        for (int w = 0; w < kDirectWaves; ++w) joined[w * half + p] += both;
     }
     __syncthreads();
-    if (count_below) { base = below; count_below = false; }
-    const uint32_t T = taken;
-    const uint32_t per = (words + kDirectThreads - 1u) / kDirectThreads, w0 = tid * per;
-    uint32_t sum = 0, cells;
-    for (uint32_t w = w0; w < w0 + per && w < words; ++w) sum += (uint32_t)__popc(bits[w]);
-    uint32_t run = block_exclusive_scan<kDirectThreads>(sum, wave_totals, &cells);
-    const bool plain = cells == T;           // no two pillars share a cell
-    if (!one_list && (full || (!plain && T > (uint32_t)kDirectShared))) {
-      one_list = true;
-      for (int p = tid; p < kDirectShared; p += kDirectThreads) joined[p] = 0u;
-      __syncthreads();
-      continue;
+    in_order(counts, digit, [&](uint32_t pos, uint32_t code, uint32_t i) { put(base + pos, lo + code, i); });
+  };
+  auto by_cell = [&] {
+    for (uint32_t w = w0, at = run; w < w0 + per && w < words; ++w) {
+      first[w] = at;
+      at += (uint32_t)__popc(bits[w]);
     }
-    if (T > (uint32_t)kDirectList && one_list) {
-      counted = true;
-      __syncthreads();
-      continue;
-    }
-    if (plain) {
-      for (uint32_t w = w0; w < w0 + per && w < words; ++w) {
-        first[w] = run;
-        run += (uint32_t)__popc(bits[w]);
-      }
-      __syncthreads();
-      const uint32_t* const from = one_list ? list : mine;
-      for (uint32_t e = one_list ? tid : lane; e < (one_list ? T : count); e += one_list ? kDirectThreads : 64) {
-        const uint32_t v = from[e], code = v >> idx_bits, w = code >> 5;
-        put(base + first[w] + (uint32_t)__popc(bits[w] & ((1u << (code & 31u)) - 1u)), lo + code, v & idx_mask);
-      }
-    } else {
-      uint32_t most = 1u;                    // whether a word has too many pillars for ranking them
-      if (!one_list) {                       // counts of the words' pillars instead of bits
-        __syncthreads();
-        for (uint32_t w = tid; w < words; w += kDirectThreads) bits[w] = 0u;
-        if (tid == 0) cut = 0u;
-        __syncthreads();
-        for (uint32_t e = lane; e < count; e += 64) atomicAdd(&bits[mine[e] >> (idx_bits + 5)], 1u);
-        __syncthreads();
-        sum = 0;
-        uint32_t largest = 0;
-        for (uint32_t w = w0; w < w0 + per && w < words; ++w) {
-          const uint32_t c = bits[w];
-          sum += c;
-          largest = c > largest ? c : largest;
-        }
-        if (largest > (uint32_t)kDirectRanked) cut = 1u;
-        run = block_exclusive_scan<kDirectThreads>(sum, wave_totals, nullptr);
-        for (uint32_t w = w0; w < w0 + per && w < words; ++w) {
-          const uint32_t c = bits[w];
-          first[w] = bits[w] = run;          // bits: where the word's next pillar goes
-          run += c;
-        }
-        __syncthreads();
-        most = cut;
-        for (uint32_t e = lane; e < count; e += 64) {
-          const uint32_t v = mine[e];
-          joined[atomicAdd(&bits[v >> (idx_bits + 5)], 1u)] = v;
-        }
-        __syncthreads();
-      }
-      if (most == 0u) {                      // few: every pillar looks at all of its word
-        for (uint32_t e = tid; e < T; e += kDirectThreads) {
-          const uint32_t v = joined[e], w = v >> (idx_bits + 5);
-          put(base + rank_in_run(joined, first[w], bits[w], v), lo + (v >> idx_bits), v & idx_mask);
-        }
-      } else {
-        uint32_t* const all = one_list ? list : joined;
-        direct_sort<kDirectThreads>(all, T);
-        for (uint32_t e = tid; e < T; e += kDirectThreads) put(base + e, lo + (all[e] >> idx_bits), all[e] & idx_mask);
-      }
-    }
-    base += T;
-    lo += len;
-    len = hi - lo;
-    __syncthreads();
+    while (1u << digit_bits < cells) ++digit_bits;
+    uint32_t carry = 0;
+    count_and_put((cells + 1u) / 2u, [&](uint32_t code) { return (int)(first[code >> 5] + __popc(bits[code >> 5] & ((1u << (code & 31u)) - 1u))); },
+                  [&](uint32_t, uint32_t both) {
+      uint32_t all;
+      const uint32_t at = carry + block_exclusive_scan<kDirectThreads>(both, wave_totals, &all);
+      carry += all;
+      return at;
+    });
+  };
+  const bool few = cells <= (uint32_t)kDirectDigits;
+  if (few && !listed) {
+    by_cell();
+    return;
   }
+  // Otherwise they are brought together by words.  first: counts, then where a word's next pillar goes, in the end where the word
+  // ends; of a crowded word its end and number.
+  const uint32_t cells_before = run;
+  for (uint32_t w = tid; w < words; w += kDirectThreads) first[w] = 0u;
+  __syncthreads();
+  each([&](uint32_t code, uint32_t) { atomicAdd(&first[code >> 5], 1u); });
+  __syncthreads();
+  sum = 0;                                   // pillars, and << 16 crowded words
+  for (uint32_t w = w0; w < w0 + per && w < words; ++w) sum += first[w] + (first[w] > (uint32_t)kDirectRanked ? 1u << 16 : 0u);
+  uint32_t crowds;
+  run = block_exclusive_scan<kDirectThreads>(sum, wave_totals, &crowds);
+  crowds >>= 16;
+  if (few && crowds && T > (uint32_t)kDirectThreads) {
+    run = cells_before;
+    by_cell();
+    return;
+  }
+  const bool sorted = T <= (uint32_t)kDirectThreads;  // so few that crowds are no matter: the list's entries are put in order as they are
+  for (uint32_t w = w0; w < w0 + per && w < words; ++w) {
+    const uint32_t c = first[w];
+    if (c > (uint32_t)kDirectRanked && !sorted) {
+      crowd_start[run >> 16] = run & 0xffffu;
+      first[w] = 1u << 31 | (run + c);
+      run += c + (1u << 16);
+    } else {
+      first[w] = run & 0xffffu;
+      run += c;
+    }
+  }
+  __syncthreads();
+  each([&](uint32_t code, uint32_t i) {
+    if (first[code >> 5] >> 31) return;
+    const uint32_t at = atomicAdd(&first[code >> 5], 1u);
+    if (at < T) joined[at] = code << idx_bits | i;
+  });
+  __syncthreads();
+  if (crowds && sorted) {
+    direct_sort<kDirectThreads>(joined, T);
+    for (uint32_t e = tid; e < T; e += kDirectThreads) put(base + e, lo + (joined[e] >> idx_bits), joined[e] & idx_mask);
+    return;
+  }
+  auto rank = [&](uint32_t code, uint32_t i) {  // every pillar looks at all of its word
+    const uint32_t w = code >> 5, end = first[w];
+    if (!(end >> 31)) put(base + rank_in_run(joined, w ? first[w - 1u] & 0xffffu : 0u, end, code << idx_bits | i), lo + code, i);
+  };
+  if (crowds == 0u) {
+    for (uint32_t e = tid; e < T; e += kDirectThreads) rank(joined[e] >> idx_bits, joined[e] & idx_mask);
+    return;
+  }
+  each(rank);
+  digit_bits = 5;                            // 32 key values of each crowded word
+  while ((1u << (digit_bits - 5)) < crowds) ++digit_bits;
+  count_and_put(crowds * 16u, [&](uint32_t code) {
+    const uint32_t v = first[code >> 5];
+    return v >> 31 ? (int)((v >> 16 & 0x7fffu) * 32u + (code & 31u)) : -1;
+  }, [&](uint32_t p, uint32_t both) {        // sixteen threads for a word
+    uint32_t inc = both;
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) {
+      const uint32_t t = __shfl_up(inc, d, 16);
+      if ((tid & 15) >= d) inc += t;
+    }
+    return crowd_start[p < crowds * 16u ? p >> 4 : 0u] + inc - both;
+  });
 }
 
 // ---- large clouds in two launches --------------------------------------------------------------------------------------
@@ -1064,15 +1074,16 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
 // of the cloud by bucket, in a place of its own, and says in a table where the buckets begin in it.  k_buckets, a workgroup per
 // bucket, finds the bucket's pieces of all tiles through a column of the table, whose sums also say how many pillars lie in
 // front, and puts its pillars in order as k_direct does: a bit for each key value, positions by counting bits.  Where some share
-// a cell, the key values are sorted in LDS, with the position in the bucket behind them, which is in order of the index; for
-// more pillars than the list holds, by two passes through memory.
+// a cell, the key values are sorted in LDS, with the position in the bucket behind them, which is in order of the index; more
+// pillars than the list holds are counted by cell, or sorted in two passes through memory where the cells are many.
 //
 // What bounds it: for a hundred thousand pillars its two launches, 4 us and a chain of six or seven round trips each; for
 // millions the lines touched rather than the 16 bytes a pillar moved: the pieces of a bucket are a few entries long where the
 // frames are mixed, a line each of entries and table (3.84 M pillars: k_split 29 us, k_buckets 49).  The radix path moves 8-byte
 // words through three passes there.  Measured, radix path / this, us a call: one sort, 131,072 pillars 35 / 14.3, 240,000 37 /
 // 16, 960,000 59 / 28, 2 M 79 / 58, 3.84 M 109 / 78; four sorts, 240,000 63 / 27, 960,000 122 / 74.  The same with a fifth of
-// the pillars sharing cells; 30,000 on one to a hundred cells, a single bucket's, 27 / 200.
+// the pillars sharing cells; on one, a hundred and ten thousand cells of a corner, 30,000 87, 121 and 34, 131,072 325, 481 and
+// 76, 960,000 2375, 3480 and 1230 (21 to 67 by the radix path).
 constexpr int kSplitThreads = 512, kSplitWaves = kSplitThreads / 64;
 constexpr int kSplitLeast = 2, kSplitFew = 4, kSplitMany = 16;  // pillars of a thread of k_split: few to fill the chip, many to
 constexpr int64_t kSplitFewRows = 1 << 19, kSplitManyRows = 1 << 20;  // keep the pieces long; of all sorts, and of one
@@ -1085,6 +1096,8 @@ constexpr int kSplitRows = 448, kSplitRowsMany = 1408, kSplitBuckets = 1024;  //
 constexpr int kSplitMaxTiles = 512;
 constexpr int kSplitList = 4096;            // pillars of a bucket in registers, and of its list in LDS
 constexpr int kSplitOwn = kSplitList / kSplitThreads;
+constexpr int kSplitDigits = 9;             // cells of a bucket, in bits, that one pass sorts: counters in place of the list
+static_assert(kSplitWaves << kSplitDigits == kSplitList && 1 << kSplitDigits <= kSplitThreads && kSplitCodeBits <= 16, "");
 
 // Bucket of key k: h - (h >> in_frame) * skip with h = k >> code_bits, which leaves out the numbers no window has.
 struct SplitSort { DirectKeys k; int32_t code_bits, in_frame, skip, per_frame; };
@@ -1190,12 +1203,10 @@ __device__ __forceinline__ void split_groups(const uint16_t* __restrict__ table,
     for (uint32_t k = l; k < groups[b + 1] - groups[b]; k += 16) goff[groups[b] + k] = (int32_t)(starts[b] + k * (uint32_t)G);
 }
 
-template <bool Z, bool FRAMES>
-__global__ __launch_bounds__(kSplitThreads) void k_buckets(const int32_t* __restrict__ coords, int n, int S, Batch bt, SplitBatch sb,
-                                                            int tile_rows, const uint32_t* __restrict__ entries_all,
-                                                            const uint16_t* __restrict__ table_all, uint32_t* __restrict__ scratch,
+__global__ __launch_bounds__(kSplitThreads, 6) void k_buckets(int n, int S, Batch bt, SplitBatch sb, int tile_rows,
+                                                            const uint32_t* __restrict__ entries_all,
+                                                            const uint16_t* __restrict__ table_all, uint32_t* scratch,
                                                             int G, int drop) {
-  constexpr int STRIDE = Z ? 4 : 3;
   extern __shared__ uint32_t list[];                       // [kSplitList] key value << 12 | position in the bucket; counters
   uint32_t* const cum = list + kSplitList;                 // [kSplitMaxTiles + 1] the bucket's pillars in the tiles before,
   uint32_t* const from = cum + kSplitMaxTiles + 1;         // [kSplitMaxTiles] and where those of a tile are, less that
@@ -1219,7 +1230,6 @@ __global__ __launch_bounds__(kSplitThreads) void k_buckets(const int32_t* __rest
   }
   if (s >= S) return;
   const KeyParams kp = bt.kp[s];
-  const DirectKeys dk = sb.s[s].k;
   const int code_bits = sb.s[s].code_bits, words = 1 << (code_bits - 5);
   uint32_t* const first = bits + words;                    // [words] position of a word's first pillar
   const uint32_t* __restrict__ const entries = entries_all + (int64_t)s * n;
@@ -1284,7 +1294,9 @@ __global__ __launch_bounds__(kSplitThreads) void k_buckets(const int32_t* __rest
   uint32_t code[kSplitOwn], index[kSplitOwn];
   for (uint32_t e0 = 0; e0 < T; e0 += kSplitList) {
     fetch(code, index, e0);
-    each_of(e0, [&](int u, uint32_t) { atomicOr(&bits[code[u] >> 5], 1u << (code[u] & 31u)); });
+    each_of(e0, [&](int u, uint32_t) {       // (of many on a cell, all but the first would wait for each other in vain)
+      if (e0 == 0u || !(bits[code[u] >> 5] >> (code[u] & 31u) & 1u)) atomicOr(&bits[code[u] >> 5], 1u << (code[u] & 31u));
+    });
   }
   __syncthreads();
   const int per = (words + kSplitThreads - 1) / kSplitThreads, w0 = tid * per;
@@ -1352,51 +1364,101 @@ __global__ __launch_bounds__(kSplitThreads) void k_buckets(const int32_t* __rest
     each_of(0, [&](int u, uint32_t e) { put(base + bits[e], code[u], index[u]); });
     return;
   }
-  // Two stable passes of eight bits over the indices, wavefronts with consecutive pieces.
-  uint32_t* const one = scratch + (int64_t)s * n + base;
-  uint32_t* const two = scratch + (int64_t)(S + s) * n + base;
-  for (uint32_t e0 = 0; e0 < T; e0 += kSplitList) {
-    fetch(code, index, e0);
-    each_of(e0, [&](int u, uint32_t e) { one[e] = index[u]; });
-  }
-  const uint32_t last_frame = (uint32_t)kp.B - 1u, piece = (T + kSplitThreads - 1u) / kSplitThreads * 64u;
-  const uint32_t begin = wave * piece, stop = begin + piece < T ? begin + piece : T;
-  uint32_t* const counts = list;             // [kSplitWaves][256]
-  auto pass = [&](const uint32_t* src, int shift, auto use) {
-    __syncthreads();
-    for (int w = tid; w < kSplitWaves * 256; w += kSplitThreads) counts[w] = 0u;
-    __syncthreads();
-    auto digit_of = [&](uint32_t i, uint32_t* c) {
-      *c = direct_key<Z, FRAMES>(coords + (int64_t)i * STRIDE, dk, last_frame) - key0;
-      return *c >> shift & 255u;
+  // Stable passes, wavefronts with consecutive pieces: one by the cells' numbers where these are few, otherwise two by eight bits
+  // of the key value with the pillars in memory in between.
+  const uint32_t piece = (T + kSplitThreads - 1u) / kSplitThreads * 64u, begin = wave * piece;
+  const uint32_t stop = begin + piece < T ? begin + piece : T;
+  constexpr int STEPS = 6;                   // loads of a lane in flight
+  // The wavefront's pillars as k_split left them, tile after tile: use(valid, key value, index), of up to 64 at a time
+  auto from_tiles = [&](auto use) {
+    int t = 0;
+    for (int skip = kSplitMaxTiles / 2; skip > 0; skip >>= 1)
+      if ((uint32_t)__builtin_amdgcn_readfirstlane((int)cum[t + skip]) <= begin) t += skip;
+    uint32_t e = begin, tile_end = (uint32_t)__builtin_amdgcn_readfirstlane((int)cum[t + 1]);
+    while (e < stop) {
+      uint32_t v[STEPS], left[STEPS], tile_first[STEPS];
+#pragma unroll
+      for (int u = 0; u < STEPS; ++u) {
+        left[u] = 0u;
+        if (e < stop) {
+          while (tile_end <= e) tile_end = (uint32_t)__builtin_amdgcn_readfirstlane((int)cum[++t + 1]);
+          left[u] = (tile_end < stop ? tile_end : stop) - e;
+          tile_first[u] = (uint32_t)t * (uint32_t)tile_rows;
+          v[u] = entries[(uint32_t)__builtin_amdgcn_readfirstlane((int)from[t]) + e + ((uint32_t)lane < left[u] ? (uint32_t)lane : 0u)];
+          e += left[u] < 64u ? left[u] : 64u;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < STEPS; ++u)
+        if (left[u]) use((uint32_t)lane < left[u], v[u] >> kSplitLocalBits, tile_first[u] + (v[u] & ((1u << kSplitLocalBits) - 1u)));
+    }
+  };
+  // read: as from_tiles.  use: where it goes, key value, index
+  auto pass = [&](int bits_of, auto read, auto digit, auto use) {
+    uint32_t* const counts = list + (wave << bits_of);     // [kSplitWaves][1 << bits_of]
+    auto ranked = [&](bool valid, uint32_t c) -> uint32_t {  // place of the pillar, once more counted
+      const uint32_t d = digit(c);
+      const uint64_t same = same_number(d, bits_of) & __ballot(valid);
+      const uint32_t before = counts[d], nth = lanes_below(same);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (valid && nth == 0u) counts[d] = before + (uint32_t)__popcll(same);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      return before + nth;
     };
-    uint32_t c;
-    for (uint32_t e = begin + lane; e < stop; e += 64) atomicAdd(&counts[wave * 256 + digit_of(src[e], &c)], 1u);
+    __syncthreads();
+    for (int w = tid; w < kSplitWaves << bits_of; w += kSplitThreads) list[w] = 0u;
+    __syncthreads();
+    read([&](bool valid, uint32_t c, uint32_t) { ranked(valid, c); });
     __syncthreads();
     uint32_t total = 0;
-    if (tid < 256)
+    if (tid < 1 << bits_of)
       for (int w = 0; w < kSplitWaves; ++w) {
-        const uint32_t v = counts[w * 256 + tid];
-        counts[w * 256 + tid] = total;
+        const uint32_t v = list[(w << bits_of) + tid];
+        list[(w << bits_of) + tid] = total;
         total += v;
       }
     const uint32_t start = block_exclusive_scan<kSplitThreads>(total, wave_totals, nullptr);
-    if (tid < 256)
-      for (int w = 0; w < kSplitWaves; ++w) counts[w * 256 + tid] += start;
+    if (tid < 1 << bits_of)
+      for (int w = 0; w < kSplitWaves; ++w) list[(w << bits_of) + tid] += start;
     __syncthreads();
-    for (uint32_t e0 = begin; e0 < stop; e0 += 64) {
-      const bool valid = e0 + lane < stop;
-      const uint32_t i = src[valid ? e0 + lane : begin], d = digit_of(i, &c);
-      const uint64_t same = same_number(d, 8) & __ballot(valid);
-      const uint32_t pos = counts[wave * 256 + d] + lanes_below(same);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      if (valid && lanes_below(same) == 0u) counts[wave * 256 + d] = pos + (uint32_t)__popcll(same);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    read([&](bool valid, uint32_t c, uint32_t i) {
+      const uint32_t pos = ranked(valid, c);
       if (valid) use(pos, c, i);
+    });
+  };
+  auto put_in = [&](uint32_t pos, uint32_t c, uint32_t i) { put(base + pos, c, i); };
+  if (cells <= 1u << kSplitDigits) {
+    for (int w = w0; w < w0 + per && w < words; ++w) {
+      first[w] = run;
+      run += (uint32_t)__popc(bits[w]);
+    }
+    int bits_of = 0;
+    while (1u << bits_of < cells) ++bits_of;
+    pass(bits_of, from_tiles, [&](uint32_t c) { return first[c >> 5] + (uint32_t)__popc(bits[c >> 5] & ((1u << (c & 31u)) - 1u)); },
+         put_in);
+    return;
+  }
+  uint32_t* const codes = scratch + (int64_t)s * n + base;
+  uint32_t* const indices = scratch + (int64_t)(S + s) * n + base;
+  pass(8, from_tiles, [](uint32_t c) { return c & 255u; }, [&](uint32_t pos, uint32_t c, uint32_t i) {
+    codes[pos] = c;
+    indices[pos] = i;
+  });
+  auto from_memory = [&](auto use) {
+    for (uint32_t e0 = begin; e0 < stop; e0 += 64 * STEPS) {
+      uint32_t c[STEPS], i[STEPS];
+#pragma unroll
+      for (int u = 0; u < STEPS; ++u) {
+        const uint32_t e = e0 + u * 64 + lane, at = e < stop ? e : stop - 1u;
+        c[u] = codes[at];
+        i[u] = indices[at];
+      }
+#pragma unroll
+      for (int u = 0; u < STEPS; ++u)
+        if (e0 + u * 64 < stop) use(e0 + u * 64 + lane < stop, c[u], i[u]);
     }
   };
-  pass(one, 0, [&](uint32_t pos, uint32_t, uint32_t i) { two[pos] = i; });
-  pass(two, 8, [&](uint32_t pos, uint32_t c, uint32_t i) { put(base + pos, c, i); });
+  pass(8, from_memory, [](uint32_t c) { return c >> 8; }, put_in);
 }
 
 // Pass plan for keys of `key_bits` bits: digit width and number of passes.
@@ -1688,17 +1750,17 @@ static int flatten_launch_impl(const int32_t* coords, const PointCells* pts, int
     }
     // (bits and first of a bucket; the places of a list's entries, which take the same memory; the group list's tables)
     size_t lds = (size_t)(kSplitList + 2 * kSplitMaxTiles + 1) * 4 + (size_t)(2 * words > kSplitList ? 2 * words : kSplitList) * 4;
-    auto go = [&](auto split, auto buckets_of) {
+    auto go = [&](auto split) {
       hipLaunchKernelGGL(split, dim3(blocks), dim3(kSplitThreads), counters > stage ? counters : stage, stream, coords, (int)n,
                          num_sorts, sb, entries, table, (int)g->num_frames, job);
-      hipLaunchKernelGGL(buckets_of, dim3((unsigned)(num_sorts + 8 * ceil_div(buckets, 8))), dim3(kSplitThreads), lds, stream, coords,
-                         (int)n, num_sorts, bt, sb, tile_rows, entries, (const uint16_t*)table, (uint32_t*)buf[1], G, drop);
+      hipLaunchKernelGGL(k_buckets, dim3((unsigned)(num_sorts + 8 * ceil_div(buckets, 8))), dim3(kSplitThreads), lds, stream, (int)n,
+                         num_sorts, bt, sb, tile_rows, entries, (const uint16_t*)table, (uint32_t*)buf[1], G, drop);
       return launch_status();
     };
     auto go_z = [&](auto Z, auto frames) {
       constexpr bool z_ = decltype(Z)::value, f_ = decltype(frames)::value;
-      return own == kSplitMany ? go(k_split<z_, f_, kSplitMany>, k_buckets<z_, f_>)
-           : own == kSplitFew ? go(k_split<z_, f_, kSplitFew>, k_buckets<z_, f_>) : go(k_split<z_, f_, kSplitLeast>, k_buckets<z_, f_>);
+      return own == kSplitMany ? go(k_split<z_, f_, kSplitMany>)
+           : own == kSplitFew ? go(k_split<z_, f_, kSplitFew>) : go(k_split<z_, f_, kSplitLeast>);
     };
     if (g->num_frames > 1) return z ? go_z(std::true_type(), std::true_type()) : go_z(std::false_type(), std::true_type());
     return z ? go_z(std::true_type(), std::false_type()) : go_z(std::false_type(), std::false_type());

@@ -64,7 +64,7 @@ __device__ __forceinline__ uint32_t sum_over_waves(uint32_t* words, int words_of
   for (int w = 0; w < WAVES; ++w) {
     const uint32_t c = words[w * words_of_wave + word];
     words[w * words_of_wave + word] = run;
-    run += c;                                // (no carry from the lower half: a tile or list has at most 8192 points)
+    run += c;                                // (no carry from the lower half: at most 24,576 points are counted)
   }
   return run;
 }

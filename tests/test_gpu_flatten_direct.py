@@ -1,6 +1,6 @@
-"""Clouds sorted in one launch: where a workgroup's range of key values holds more pillars than its lists (it is cut, down
-to a single value), where pillars share cells, and on both sides of the limits of what is sorted this way (frames, grid,
-pillars, key values of a range)."""
+"""Clouds sorted in one launch: where a workgroup's range of key values holds more pillars than its lists, where pillars share
+cells, few or many of 32 key values, and on both sides of the limits of what is sorted this way (frames, grid, pillars, key values
+of a range)."""
 import numpy as np
 import pytest
 import torch
@@ -25,7 +25,23 @@ def _board(X, Y):  # every cell, in grid order: neighbours share a window
     return np.stack([0 * k, k // Y, k % Y], 1).astype(np.int32)
 
 
+def _crowds(words, each, single, seed):
+    """`words` runs of 32 cells of one window of 256 x 256 with `each` pillars, and `single` cells with one, shuffled."""
+    rng = np.random.default_rng(seed)
+    crowd = np.repeat(2 * np.arange(words), each) * 32 + rng.integers(0, 32, words * each)
+    k = rng.permutation(np.concatenate([crowd, 65536 - 1 - 5 * np.arange(single)]))
+    return np.stack([0 * k, k // 256, k % 256], 1).astype(np.int32)
+
+
 CASES = {
+    "most_of_one_cell": (lambda: np.tile(np.array([[0, 467, 467]], np.int32), (24576, 1)), 1, 468, 13),
+    "ranked_words": (lambda: _crowds(90, 256, 0, 19), 1, 4096, 256),
+    "crowded_word": (lambda: _crowds(1, 257, 0, 20), 1, 4096, 256),
+    "most_crowded_words": (lambda: _crowds(95, 257, 150, 21), 1, 4096, 256),
+    "crowded_and_single": (lambda: _crowds(3, 5000, 9000, 22), 1, 4096, 256),
+    "a_window_twice": (lambda: _cells(1, 96, 128, 24576, 23, each=2), 1, 4096, 256),
+    "a_window_once": (lambda: _cells(1, 256, 256, 24576, 24), 1, 4096, 256),
+    "a_window_nearly_once": (lambda: np.concatenate([_cells(1, 256, 256, 24570, 25), np.zeros((6, 3), np.int32)]), 1, 4096, 256),
     "one_cell": (lambda: np.tile(np.array([[0, 300, 77]], np.int32), (20000, 1)), 1, 468, 13),
     "two_cells": (lambda: np.array([[0, 300, 77], [0, 300, 78]], np.int32)[np.arange(9001) % 3 // 2], 1, 468, 13),
     "one_pillar": (lambda: np.array([[0, 5, 9]], np.int32), 1, 468, 13),

@@ -1,5 +1,6 @@
 """Large clouds sorted by bucket: on both sides of the limits of what is sorted this way, buckets with more pillars than fit the
-registers of a workgroup, shared cells that are sorted in LDS and through memory, frames without pillars, three dimensions."""
+registers of a workgroup, shared cells that are sorted in LDS, by counting cells and through memory, frames without pillars,
+three dimensions."""
 import numpy as np
 import pytest
 import torch
@@ -22,7 +23,19 @@ def _any(B, X, Y, n, seed):
     return np.stack([rng.integers(0, B, n), rng.integers(0, X, n), rng.integers(0, Y, n)], 1).astype(np.int32)
 
 
+def _on(cells, n, seed):  # n pillars on so many cells of a window, every cell at least once
+    rng = np.random.default_rng(seed)
+    k = rng.permutation(np.concatenate([np.arange(cells), rng.integers(0, cells, n - cells)]))
+    return np.stack([0 * k, k // 128, k % 128], 1).astype(np.int32)
+
+
 CASES = {  # pillars, frames, grid, window
+    "one_cell": (lambda: _on(1, 100003, 18), 1, 2048, 256),
+    "two_cells": (lambda: _on(2, 40000, 19), 1, 2048, 256),
+    "counted_cells": (lambda: _on(512, 70001, 20), 1, 2048, 256),
+    "one_cell_more": (lambda: _on(513, 70001, 21), 1, 2048, 256),
+    "many_cells_shared": (lambda: _on(16000, 90001, 22), 1, 2048, 256),
+    "most_in_the_last_cell": (lambda: np.concatenate([_any(1, 468, 468, 30000, 23), np.full((70000, 3), [0, 467, 467], np.int32)]), 1, 468, 13),
     "first": (lambda: _cells(1, 468, 468, 24577, 1), 1, 468, 13),
     "first_for_its_frames": (lambda: _cells(20, 60, 60, 16385, 13), 20, 60, 13),
     "before_it": (lambda: _cells(20, 60, 60, 16384, 14), 20, 60, 13),
