@@ -1,6 +1,6 @@
 """Large clouds sorted by bucket: on both sides of the limits of what is sorted this way, buckets with more pillars than fit the
-registers of a workgroup, shared cells that are sorted in LDS, by counting cells and through memory, frames without pillars,
-three dimensions."""
+registers of a workgroup, shared cells that are sorted in LDS, by counting cells and through memory,
+frames without pillars, three dimensions."""
 import numpy as np
 import pytest
 import torch
@@ -29,12 +29,27 @@ def _on(cells, n, seed):  # n pillars on so many cells of a window, every cell a
     return np.stack([0 * k, k // 128, k % 128], 1).astype(np.int32)
 
 
+def _mixed(crowds, grid, rest, seed):  # crowds: (pillars, first cell, cells); the rest anywhere; shuffled
+    rng = np.random.default_rng(seed)
+    k = np.concatenate([c + rng.integers(0, m, n) for n, c, m in crowds] + [rng.integers(0, grid * grid, rest)])
+    k = rng.permutation(k)
+    return np.ascontiguousarray(np.stack([0 * k, k // grid, k % grid], 1).astype(np.int32))
+
+
 CASES = {  # pillars, frames, grid, window
     "one_cell": (lambda: _on(1, 100003, 18), 1, 2048, 256),
     "two_cells": (lambda: _on(2, 40000, 19), 1, 2048, 256),
     "counted_cells": (lambda: _on(512, 70001, 20), 1, 2048, 256),
     "one_cell_more": (lambda: _on(513, 70001, 21), 1, 2048, 256),
     "many_cells_shared": (lambda: _on(16000, 90001, 22), 1, 2048, 256),
+    "alone_counting": (lambda: _mixed([(6000, 0, 300)], 468, 30000, 24), 1, 468, 13),
+    "alone_in_memory": (lambda: _mixed([(7000, 0, 4000)], 2048, 30000, 25), 1, 2048, 256),
+    "half_on_a_cell": (lambda: _mixed([(60000, 9, 1)], 468, 60000, 26), 1, 468, 13),
+    "several_crowds": (lambda: _mixed([(20000, 0, 3), (30000, 77, 40), (9000, 300, 1), (50000, 150000, 7)], 468, 40000, 27), 1, 468, 13),
+    "one_digit": (lambda: _mixed([(50000, 0, 60)], 156, 50000, 28), 1, 156, 13),
+    "crowd_in_grid_order": (lambda: np.unique(_mixed([(60000, 5000, 900)], 468, 60000, 29), axis=0, return_index=False).repeat(3, 0), 1, 468, 13),
+    "crowd_runs": (lambda: np.sort(_mixed([(60000, 9, 2)], 468, 60000, 30).view("i4,i4,i4"), order=["f1", "f2"], axis=0).view(np.int32), 1, 468, 13),
+    "million_on_a_cell": (lambda: _mixed([(700000, 9, 1)], 468, 700000, 31), 8, 468, 13),
     "most_in_the_last_cell": (lambda: np.concatenate([_any(1, 468, 468, 30000, 23), np.full((70000, 3), [0, 467, 467], np.int32)]), 1, 468, 13),
     "first": (lambda: _cells(1, 468, 468, 24577, 1), 1, 468, 13),
     "first_for_its_frames": (lambda: _cells(20, 60, 60, 16385, 13), 20, 60, 13),
