@@ -251,8 +251,9 @@ __global__ __launch_bounds__(256) void k_seg_mean(const int32_t* __restrict__ pe
 // through two radix passes.  The call, us, before / this: 2,000 points 31 / 18, 20,000 36 / 22, 60,000 48 / 31, 180,000 of 4
 // features 50.5 / 42.3, of 8 56.3 / 49.1, 262,144 of two frames 55 / 47.  Ranges of 1024 cells, which cover four times the
 // grid: 180,000 47.9 us, and 1.44 M points of eight frames 177, which the general path takes 137 for.  Rows brought into LDS by
-// the whole workgroup before they are added up, or four lanes to a short pillar: k_vox_mean 19 to 40 us instead of 17.  180,000
-// points in a single cell, one workgroup's and one chain of sums: 1.6 ms before, 2.1 now.
+// the whole workgroup before they are added up, or four lanes to a short pillar: k_vox_mean 19 to 40 us instead of 17.
+// Thousands of points in a single cell are one workgroup's, and one chain of sums as ever: 60,000 of 4 features 505 / 620 us, 180,000
+// 1.63 / 1.95 ms, of 5 features 4.8 / 6.5 (the general path's radix passes spread them over the chip).
 constexpr int kVoxThreads = 1024, kVoxWaves = kVoxThreads / 64;              // of k_vox_split
 constexpr int kVoxOrderThreads = 512, kVoxOrderWaves = kVoxOrderThreads / 64;
 constexpr int kVoxCellBits = 8;             // cells of a range: 256
@@ -260,13 +261,14 @@ constexpr int kVoxMaxRanges = 1983;         // with one more bin for the points 
 constexpr int kVoxPoints = 2;               // points of a thread of k_vox_split
 constexpr int kVoxTile = kVoxThreads * kVoxPoints, kVoxLocalBits = 11;
 constexpr int kVoxMaxTiles = 248;           // (as many points as cells)
+constexpr uint32_t kVoxMaxTilesPow = 256;
 constexpr int kVoxIndexBits = 19;           // points: index and cell of the range share a word of 32 bits
 constexpr int kVoxList = 4096;              // points in LDS at a time
 constexpr int kVoxInFlight = 8;            // points of a lane on their way there
 constexpr int kVoxManyRanges = 256;         // more than this many have four workgroups each in k_vox_mean (180,000 points in
                                             // 855 ranges: two 23 us, four 17, six 20), fewer sixteen
 static_assert(kVoxTile == 1 << kVoxLocalBits && kVoxMaxTiles <= kVoxOrderThreads && kVoxMaxTiles * kVoxTile <= 1 << kVoxIndexBits &&
-              kVoxMaxRanges << kVoxCellBits <= kVoxMaxTiles * kVoxTile, "");
+              kVoxMaxRanges << kVoxCellBits <= kVoxMaxTiles * kVoxTile && kVoxMaxTiles <= (int)kVoxMaxTilesPow, "");
 
 // entries: of tile t, at t * kVoxTile, its points sorted by range: cell of the range << 13 | point of the tile.
 // table[t][bin]: where the range begins there; the bin behind the last range is that of the dropped points.
@@ -353,18 +355,39 @@ __global__ __launch_bounds__(kVoxOrderThreads) void k_vox_order(const uint32_t* 
     __syncthreads();
     len = T - list0 < (uint32_t)kVoxList ? T - list0 : (uint32_t)kVoxList;
     for (int w = tid; w < kVoxOrderWaves * CELLS / 2; w += kVoxOrderThreads) words[w] = 0u;
-    for (int t = tid >> lane_bits; t < tiles; t += kVoxOrderThreads >> lane_bits) {
-      const uint32_t c0 = cum[t], c1 = cum[t + 1], src = from[t] - c0;
-      const uint32_t stop = c1 < list0 + len ? c1 : list0 + len;
-      for (uint32_t p = (c0 > list0 ? c0 : list0) + (tid & (lanes - 1u)); p < stop; p += lanes * kVoxInFlight) {
-        uint32_t v[kVoxInFlight];
+    if (T > (uint32_t)kVoxList) {            // a few tiles' pieces, too few for the wavefronts: each point finds its tile, the last that
+      uint32_t tile[ROUNDS] = {}, v[ROUNDS]; // begins no later
 #pragma unroll
-        for (int u = 0; u < kVoxInFlight; ++u) v[u] = entries[src + (p + lanes * u < stop ? p + lanes * u : p)];
+      for (uint32_t step = kVoxMaxTilesPow / 2; step > 0; step >>= 1)
 #pragma unroll
-        for (int u = 0; u < kVoxInFlight; ++u)
-          if (p + lanes * u < stop)
-            list[p + lanes * u - list0] = v[u] >> kVoxLocalBits << kVoxIndexBits |
-                                       ((uint32_t)t * (uint32_t)kVoxTile + (v[u] & ((1u << kVoxLocalBits) - 1u)));
+        for (int u = 0; u < ROUNDS; ++u) {
+          const uint32_t p = (uint32_t)(tid + u * kVoxOrderThreads) < len ? list0 + tid + u * kVoxOrderThreads : list0;
+          tile[u] += tile[u] + step < (uint32_t)tiles && cum[tile[u] + step] <= p ? step : 0u;
+        }
+#pragma unroll
+      for (int u = 0; u < ROUNDS; ++u) {
+        const uint32_t p = (uint32_t)(tid + u * kVoxOrderThreads) < len ? list0 + tid + u * kVoxOrderThreads : list0;
+        v[u] = entries[from[tile[u]] + p - cum[tile[u]]];
+      }
+#pragma unroll
+      for (int u = 0; u < ROUNDS; ++u)
+        if ((uint32_t)(tid + u * kVoxOrderThreads) < len)
+          list[tid + u * kVoxOrderThreads] = v[u] >> kVoxLocalBits << kVoxIndexBits |
+                                             (tile[u] * (uint32_t)kVoxTile + (v[u] & ((1u << kVoxLocalBits) - 1u)));
+    } else {
+      for (int t = tid >> lane_bits; t < tiles; t += kVoxOrderThreads >> lane_bits) {
+        const uint32_t c0 = cum[t], c1 = cum[t + 1], src = from[t] - c0;
+        const uint32_t stop = c1 < list0 + len ? c1 : list0 + len;
+        for (uint32_t p = (c0 > list0 ? c0 : list0) + (tid & (lanes - 1u)); p < stop; p += lanes * kVoxInFlight) {
+          uint32_t v[kVoxInFlight];
+#pragma unroll
+          for (int u = 0; u < kVoxInFlight; ++u) v[u] = entries[src + (p + lanes * u < stop ? p + lanes * u : p)];
+#pragma unroll
+          for (int u = 0; u < kVoxInFlight; ++u)
+            if (p + lanes * u < stop)
+              list[p + lanes * u - list0] = v[u] >> kVoxLocalBits << kVoxIndexBits |
+                                         ((uint32_t)t * (uint32_t)kVoxTile + (v[u] & ((1u << kVoxLocalBits) - 1u)));
+        }
       }
     }
     __syncthreads();
@@ -388,11 +411,38 @@ __global__ __launch_bounds__(kVoxOrderThreads) void k_vox_order(const uint32_t* 
         order[base + place[cell] + mine[cell] + rank[u]] = (int32_t)(v & ((1u << kVoxIndexBits) - 1u));
       }
   };
-  uint32_t total = take(0u), c0 = total & 0xffffu, c1 = total >> 16;
-  for (uint32_t list0 = kVoxList; list0 < T; list0 += kVoxList) {
-    total = take(list0);
-    c0 += total & 0xffffu;
-    c1 += total >> 16;
+  uint32_t total, c0 = 0, c1 = 0;
+  if (T <= (uint32_t)kVoxList) {
+    total = take(0u);
+    c0 = total & 0xffffu;
+    c1 = total >> 16;
+  } else {                                   // several lists: the cells' points are counted in front of them
+    for (int c = tid; c < CELLS; c += kVoxOrderThreads) place[c] = 0u;
+    __syncthreads();
+    for (int t = wave; t < tiles; t += kVoxOrderWaves) {
+      const uint32_t n = cum[t + 1] - cum[t];
+      for (uint32_t p = lane; p < n; p += 64u * kVoxInFlight) {
+        uint32_t v[kVoxInFlight];
+#pragma unroll
+        for (int u = 0; u < kVoxInFlight; ++u) v[u] = entries[from[t] + (p + 64u * u < n ? p + 64u * u : p)];
+#pragma unroll
+        for (int u = 0; u < kVoxInFlight; ++u)
+          if (p + 64u * u < n) {             // (all of one cell: one addition, where they would wait for each other)
+            const uint32_t cell = v[u] >> kVoxLocalBits, of_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)cell);
+            const uint64_t here = __ballot(true);
+            if (__ballot(cell != of_first) == 0ull) {
+              if (lanes_below(here) == 0u) atomicAdd(&place[cell], (uint32_t)__popcll(here));
+            } else {
+              atomicAdd(&place[cell], 1u);
+            }
+          }
+      }
+    }
+    __syncthreads();
+    if (tid < CELLS / 2) {
+      c0 = place[2 * tid];
+      c1 = place[2 * tid + 1];
+    }
   }
   uint32_t np;
   const uint32_t pos = block_exclusive_scan<kVoxOrderThreads>(c0 + c1, wave_totals, nullptr);
