@@ -84,7 +84,7 @@ struct Plan {
   static constexpr int STATS = R * NS * 8;
   static constexpr int PAR = (5 * C + F) * 4;  // query bias, output bias, LN2 scale and shift, FFN biases
   static constexpr int TAB = RB * 64;          // which rows are members, as operand masks
-  static constexpr int SRC = R * 4;            // where the rows came from
+  static constexpr int SRC = R * (RB > 3 ? 8 : 4);  // where the rows came from, and (four blocks) their pillars
   static constexpr int TOTAL = A + B + STATS + PAR + TAB + SRC;
   static_assert(F == 2 * C, "half of the hidden units are one set of operands");
 };
@@ -117,6 +117,13 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   float* const par = reinterpret_cast<float*>(ldsc + PL::STATS);
   uint32_t* const tab = reinterpret_cast<uint32_t*>(ldsc + PL::STATS + PL::PAR);
   int32_t* const src = reinterpret_cast<int32_t*>(ldsc + PL::STATS + PL::PAR + PL::TAB);
+  // Four whole row blocks (of the widest form three and a half) leave no registers beside the attention: the pillars wait in LDS,
+  // the weights that come after it are requested behind it, and what follows from the lane's number is worked out again.  12,000
+  // and 30,000 rows with 6 to 25 registers in scratch memory / so, us: 128 features, G = 128, float32 results 21.8 / 20.9 and 25.7
+  // / 24.4; 256 features, G = 120 33.0 / 32.3 and 46.1 / 44.3.  At 128 features with 16-bit results it is even, G = 120 19.9 / 19.5 and
+  // 21.6 / 21.9, G = 128 19.2 / 19.5 and 21.1 / 21.4; where there are registers it costs 1 to 4 %.
+  constexpr bool FULL = RB > 3 && (!HALF || (C > 128 && PE && OUT_F32));
+  int32_t* const pillar = src + PL::R;
   constexpr int P_BQ = 0, P_BO = C, P_G2 = 2 * C, P_B2N = 3 * C, P_B2 = 4 * C, P_B1 = 5 * C;
 
   const int tid = threadIdx.x, lane = tid & 63, nrow = lane & 31, h = lane >> 5;
@@ -230,7 +237,10 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
 #pragma unroll
   for (int t = 0; t < NL; ++t) {
     const int row = s * RPW + t * RPI + lr;
-    if (lc == 0) src[row] = in_sorted ? first + off[t] : pil[t];
+    if (lc == 0) {
+      src[row] = in_sorted ? first + off[t] : pil[t];
+      if constexpr (FULL) pillar[row] = pil[t];
+    }
     float y[8], su = 0.f, ss = 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j) { y[2 * j] = el_lo(raw[t][j]); y[2 * j + 1] = el_hi(raw[t][j]); }
@@ -514,9 +524,13 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
       }
     }
   };
-  ahead(w, wf);
+  if constexpr (!FULL) ahead(w, wf);
   if (!HALF && whole) attention(std::false_type());
   else attention(std::true_type());
+  if constexpr (FULL) ahead(w, wf);
+  int lane_again = lane;
+  if constexpr (FULL) asm volatile("" : "+v"(lane_again));
+  const int lr_out = lane_again / LPR, lc_out = lane_again % LPR;
 
   // ---- output projection + residual ----------------------------------------------------------------------------------
   // The rows again, 16 bytes a lane: lane h holds features 16 h + 8 u .. + 7 of the slice, the operand of a product whose other
@@ -553,7 +567,10 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     for (int u = 0; u < 2; ++u) x1[b] = mma(unit[u], again[b][u], x1[b]);
   int orow[NL];                            // rows of `out` of my rows
 #pragma unroll
-  for (int t = 0; t < NL; ++t) orow[t] = out_index ? out_index[pil[t]] : pil[t];
+  for (int t = 0; t < NL; ++t) {
+    const int p = FULL ? pillar[s * RPW + t * RPI + lr_out] : pil[t];
+    orow[t] = out_index ? out_index[p] : p;
+  }
 
   // ---- LN2 -> A ------------------------------------------------------------------------------------------------------
   // Sum and sum of squares of a row: every wavefront's 32 features, combined through LDS.
@@ -654,16 +671,16 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     lds_barrier();
 #pragma unroll
     for (int t = 0; t < NL; ++t) {
-      const int row = s * RPW + t * RPI + lr;
-      const u32x4 v = Out[row * LPR + (lc ^ (row & 15))];
-      if (slot0 + t * RPI + lr < m)  // non-temporal: the next reader is another XCD, and the kernel's end has less to write back
-        __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out) + (size_t)orow[t] * C + 8 * lc));
+      const int row = s * RPW + t * RPI + lr_out;
+      const u32x4 v = Out[row * LPR + (lc_out ^ (row & 15))];
+      if (slot0 + t * RPI + lr_out < m)  // non-temporal: the next reader is another XCD, and the kernel's end has less to write back
+        __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out) + (size_t)orow[t] * C + 8 * lc_out));
     }
   } else {                                 // output rows of all row blocks, through LDS; then 16 bytes a lane and piece
     int32_t* const rowof = reinterpret_cast<int32_t*>(Out);
-    if (lc == 0) {
+    if (lc_out == 0) {
 #pragma unroll
-      for (int t = 0; t < NL; ++t) rowof[s * RPW + t * RPI + lr] = slot0 + t * RPI + lr < m ? orow[t] : -1;
+      for (int t = 0; t < NL; ++t) rowof[s * RPW + t * RPI + lr_out] = slot0 + t * RPI + lr_out < m ? orow[t] : -1;
     }
     lds_barrier();
 #pragma unroll
