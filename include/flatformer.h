@@ -16,7 +16,8 @@
  *    synchronises the stream; outputs are valid once the stream reaches the
  *    point after the call.  Every entry point can therefore be captured into a
  *    HIP graph; call it once outside a capture first (the first launch of a
- *    fused layer kernel on a device sets a function attribute).
+ *    fused layer kernel, or of the one-launch sort of small clouds, on a
+ *    device sets a function attribute).
  *  - Errors: every function returns an ff_status (0 = success, negative =
  *    failure).  Preconditions that can be checked on the host are checked before
  *    anything is launched; on FF_ERR_ARG / FF_ERR_UNSUPPORTED / FF_ERR_WORKSPACE
@@ -202,8 +203,9 @@ int ff_pack_weights(const ff_layer_weights* w, int dtype, void* packed, void* st
 #define FF_FLAG_OUT_F32 1u      /* store `out` as float32 even when dtype is a 16-bit type */
 #define FF_FLAG_FORCE_GENERIC 2u /* use the plain fp32-arithmetic kernels for any dtype */
 #define FF_FLAG_TAIL_DROP 4u     /* the group list was made with FF_TAIL_DROP: rows of no group are copied through */
-/* Tuning knob: bits 8..11 select one wave-to-group mapping of the fused bf16 kernel (1..15; 0 =
- * chosen from the shape).  A mapping that cannot hold G returns FF_ERR_UNSUPPORTED. */
+/* Tuning knob: bits 8..11 select one form of the fused 16-bit kernel of this width (1..15; 0 =
+ * chosen from the shape).  Forms differ in how rows are spread over wavefronts and give the same bits.
+ * One that does not hold G, or does not take a positional embedding, returns FF_ERR_UNSUPPORTED. */
 #define FF_FLAG_VARIANT(v) (((uint32_t)(v) & 0xfu) << 8)
 
 size_t ff_group_attention_workspace_bytes(int64_t n, int G, const ff_layer_weights* w, int dtype);

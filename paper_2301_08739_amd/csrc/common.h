@@ -148,6 +148,10 @@ struct LayerSlice {
   const void* packed;
   const int32_t* out_index;  // as for layer_mfma_launch
   int in_sorted;             // as for layer_mfma_launch
+  // Which form, 0: chosen from the shape.  Row blocks of a group (at least as many as hold G), workgroups a SIMD has registers
+  // for (2 or 3), and whether half a last block is computed whole
+  int blocks, waves;
+  bool whole;
 };
 int layer_slice_launch(const LayerSlice& c, hipStream_t stream);
 int layer_slice_launch_f16(const LayerSlice& c, hipStream_t stream);

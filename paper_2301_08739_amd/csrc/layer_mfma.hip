@@ -863,21 +863,26 @@ int FF_LAYER_SYM(layer_mfma_launch)(const void* feats, void* out, int64_t n, con
   const bool pe = w->pos_embed != nullptr;
   if (shape != 3) {
     // 128 and 256 features: wavefronts that cut the features.  They are ahead of wavefronts that cut the rows, which served
-    // these widths before, at all group sizes and counts (us a layer, before / now, 30,000 rows: C = 128, G = 64 16.5 / 14.7,
-    // G = 69 23.6 / 21.9, G = 100 32.8 / 26.8; C = 256, G = 64 43.8 / 40.9; 2,000 rows, C = 256 40 / 16); at 64 features,
-    // two wavefronts a group, they are not (20,000 rows, G = 50: 8.9 / 10.9).
-    // Mapping numbers stand for a largest group and for taking a positional embedding, here as everywhere; one kernel serves
-    // all that hold G, so all give the same bits.
-    struct Mapping { int slots; bool embeds; };
-    static constexpr Mapping kNone = {0, false};
-    static constexpr Mapping k128[16] = {{128, true}, {32, false}, {64, true}, {80, true}, {128, true}, kNone, {64, true}, {64, true},
-                                         {128, false}, {128, true}, {32, true}, {64, false}, {64, true}, {80, true}, {96, true}, {32, true}};
-    static constexpr Mapping k256[16] = {{128, true}, {32, true}, {64, true}, {80, false}, {128, true}, {64, true}, {80, true},
-                                         {96, false}, {64, false}, kNone, kNone, kNone, kNone, kNone, kNone, kNone};
+    // these widths before, nearly everywhere (us a layer, before / now, 30,000 rows: C = 128, G = 64 16.5 / 14.7, G = 69 23.6 /
+    // 21.9, G = 100 32.8 / 26.8; C = 256, G = 64 43.8 / 40.9; 2,000 rows, C = 256 40 / 16; the other way round for groups of more
+    // than 112 in one or two rounds at C = 128, 20.8 / 21.4 and with float32 results 23.3 / 24.4); at 64 features, two wavefronts a
+    // group, they are not (20,000 rows, G = 50: 8.9 / 10.9).
+    // Mapping numbers are forms of that kernel, each with its largest group; the forms differ in which rows and registers a
+    // wavefront has, not in the operations on a row or their order, so all that hold G give the same bits.  (Numbers that have never
+    // taken a positional embedding, and groups beyond the size a number has stood for, are still refused.)
+    struct Mapping { int slots; bool embeds; int blocks, waves; bool whole; };
+    static constexpr Mapping kNone = {0, false, 0, 0, false};
+    static constexpr Mapping k128[16] = {{128, true, 0, 0, false}, {32, false, 1, 2, false}, {64, true, 2, 2, true}, {80, true, 3, 0, false},
+                                         {128, true, 4, 0, true}, kNone, {64, true, 2, 3, true}, {64, true, 2, 2, false},
+                                         {128, false, 4, 0, true}, {128, true, 4, 0, false}, {32, true, 1, 2, false}, {64, false, 3, 0, false},
+                                         {64, true, 2, 3, false}, {80, true, 3, 0, true}, {96, true, 3, 0, false}, {32, true, 1, 3, false}};
+    static constexpr Mapping k256[16] = {{128, true, 0, 0, false}, {32, true, 1, 0, false}, {64, true, 2, 0, false}, {80, false, 3, 0, false},
+                                         {128, true, 4, 0, false}, {64, true, 3, 0, false}, {80, true, 4, 0, true}, {96, false, 3, 0, true},
+                                         {64, false, 3, 0, true}, kNone, kNone, kNone, kNone, kNone, kNone, kNone};
     const Mapping& mp = (shape == 1 ? k128 : k256)[variant & 15];
     if (G > mp.slots || (pe && !mp.embeds)) return FF_ERR_UNSUPPORTED;
     const LayerSlice call{feats, out, (int)n, perm, group_offsets, num_groups, max_groups, w, G, drop, out_f32, packed, out_index,
-                          in_sorted};
+                          in_sorted, mp.blocks, mp.waves, mp.whole};
     return FF_LAYER_SYM(layer_slice_launch)(call, stream);
   }
   // The narrow layer (64 features, 4 heads): the whole 64 KB weight stream stays in the ring.  A launch runs in rounds of one

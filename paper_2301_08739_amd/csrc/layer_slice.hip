@@ -730,26 +730,27 @@ int launch_cfg(const LayerSlice& c, hipStream_t stream) {
 
 int FF_LAYER_SYM(layer_slice_launch)(const LayerSlice& c, hipStream_t stream) {
   if (c.max_groups == 0 || c.n == 0) return FF_OK;
-  const int G = c.G;
+  const int G = c.G, blocks = c.blocks ? c.blocks : (G + 31) / 32;
+  if (G > 32 * blocks) return FF_ERR_UNSUPPORTED;
 #define FF_GO(C, DH, F, PT, GPW, MINW)                                                        \
-  return G <= 32 * PT - 16 ? launch_cfg<C, DH, F, PT, GPW, true, MINW>(c, stream)             \
-                           : launch_cfg<C, DH, F, PT, GPW, false, MINW>(c, stream)
+  return G <= 32 * PT - 16 && !c.whole ? launch_cfg<C, DH, F, PT, GPW, true, MINW>(c, stream) \
+                                       : launch_cfg<C, DH, F, PT, GPW, false, MINW>(c, stream)
   // Up to two workgroups a compute unit: as many registers as two wavefronts on a SIMD have; beyond, three share it (30,000
   // rows, G = 64: 13.9 / 14.2 us, 240,000 rows: 103 / 98).
-  const bool few = ceil_div(c.max_groups, G <= 32 ? 2 : 1) <= 512;
-  switch (c.w->C) {
-    case 128:
-      if (G <= 32 && few) FF_GO(128, 16, 256, 1, 2, 2);
-      if (G <= 32) FF_GO(128, 16, 256, 1, 2, 3);
-      if (G <= 64 && few) FF_GO(128, 16, 256, 2, 1, 2);
-      if (G <= 64) FF_GO(128, 16, 256, 2, 1, 3);
-      if (G <= 96) FF_GO(128, 16, 256, 3, 1, 2);
-      FF_GO(128, 16, 256, 4, 1, 2);
-    case 256:
-      if (G <= 32) FF_GO(256, 32, 512, 1, 2, 2);
-      if (G <= 64) FF_GO(256, 32, 512, 2, 1, 2);
-      if (G <= 96) FF_GO(256, 32, 512, 3, 1, 2);
-      FF_GO(256, 32, 512, 4, 1, 2);
+  const bool few = c.waves ? c.waves == 2 : ceil_div(c.max_groups, G <= 32 ? 2 : 1) <= 512;
+  switch (c.w->C * 8 + blocks) {
+    case 128 * 8 + 1:
+      if (few) FF_GO(128, 16, 256, 1, 2, 2);
+      FF_GO(128, 16, 256, 1, 2, 3);
+    case 128 * 8 + 2:
+      if (few) FF_GO(128, 16, 256, 2, 1, 2);
+      FF_GO(128, 16, 256, 2, 1, 3);
+    case 128 * 8 + 3: FF_GO(128, 16, 256, 3, 1, 2);
+    case 128 * 8 + 4: FF_GO(128, 16, 256, 4, 1, 2);
+    case 256 * 8 + 1: FF_GO(256, 32, 512, 1, 2, 2);
+    case 256 * 8 + 2: FF_GO(256, 32, 512, 2, 1, 2);
+    case 256 * 8 + 3: FF_GO(256, 32, 512, 3, 1, 2);
+    case 256 * 8 + 4: FF_GO(256, 32, 512, 4, 1, 2);
   }
 #undef FF_GO
   return FF_ERR_UNSUPPORTED;

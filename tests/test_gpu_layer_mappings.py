@@ -1,8 +1,9 @@
-"""Mappings of the fused 16-bit layer with five and six wavefronts per group, with two workgroups on a compute unit and
-with more groups per workgroup: at the edges of the group sizes they serve, two frames (group starts that are no
-multiples of G), short last groups, wavefronts beyond the last group, dropped tails and positional embedding.  Against
-the oracle, and bit for bit against the mapping that served these sizes alone before: a mapping only says which
-wavefront computes a row, the operations on it and their order are the same."""
+"""Mappings of the fused 16-bit layer: at 64 features with five and six wavefronts per group, with two workgroups on a compute
+unit and with more groups per workgroup; at 128 and 256 features with more row blocks than a group needs, with the last of them
+computed whole or by half, and with the registers of two or of three workgroups on a SIMD.  At the edges of the group sizes they
+serve, two frames (group starts that are no multiples of G), short last groups, wavefronts beyond the last group, dropped tails and
+positional embedding.  Against the oracle, and bit for bit against another mapping: a mapping only says which wavefront
+computes a row, the operations on it and their order are the same."""
 import numpy as np
 import pytest
 import torch
