@@ -6,7 +6,7 @@
 //
 // Scores, probabilities, Q/K/V and the FFN hidden activations never leave the chip.
 //
-// Mapping.  A wavefront owns NVB blocks of 16 pillars of one group ("its" pillars); WPG wavefronts
+// Mapping.  A wavefront owns 16 pillars of one group ("its" pillars); WPG wavefronts
 // share a group, NW wavefronts form a workgroup.  Everything is computed transposed, features x
 // pillars, with v_mfma_f32_16x16x32_bf16: the weight tile is the A operand (16 output features x
 // 32 inputs), the activations of 16 pillars are the B operand, and the accumulator holds
@@ -81,8 +81,8 @@ __global__ __launch_bounds__(256) void k_pack_weights(PackBatch pb, int C, int F
 }
 
 // ---- the fused layer ------------------------------------------------------------------------------
+constexpr int C = 64, F = 128, DH = 16;  // features, hidden units, head dimension
 // LDS map (bytes): [weight ring RING x 16 KB][small parameters as fp32: (7C + F) x 4][K/V exchange, 2 buffers].
-template <int C, int F>
 struct ParamOff {  // float offsets inside the small-parameter area
   static constexpr int LN1G = 0, LN1B = C, BQ = 2 * C, BO = 3 * C, LN2G = 4 * C, LN2B = 5 * C, B2 = 6 * C,
                        B1 = 7 * C, TOTAL = 7 * C + F;
@@ -94,13 +94,13 @@ constexpr int kLdsBytes = 160 * 1024;  // LDS of one compute unit
 constexpr int kComputeUnits = 256;      // of an MI355X
 constexpr int kWindow = 8;             // weight fragments a wavefront keeps in flight (LDS -> registers)
 
-template <int C, int F, int NVB, int WPG, int NW, int MINW>
+template <int WPG, int NW, int MINW>
 struct LdsPlan {
-  static constexpr int NKB = NVB * WPG, GPW = NW / WPG;
+  static constexpr int GPW = NW / WPG;
   static constexpr int WGS = (MINW * 4 / NW) > 1 ? (MINW * 4 / NW) : 1;  // workgroups meant to share a compute unit
   static constexpr int PARAMS = pack_param_bytes(C, F);   // padded to whole 1 KB pieces
-  static constexpr int KVX_ONE = 2 * 2 * NKB * 64 * 8;                     // K and V of one group, one unit
-  static constexpr int KVX = WPG > 1 ? 2 * GPW * KVX_ONE : 0;              // double buffered
+  static constexpr int KVX_ONE = 2 * 2 * WPG * 64 * 8;    // K and V of one group, one unit
+  static constexpr int KVX = 2 * GPW * KVX_ONE;           // double buffered
   static constexpr int NCHUNK = ((C / 32) * (6 * (C / 32) + C / 16) + (F / 32) * (2 * (C / 32) + C / 16)) / kChunkFrags;
   static constexpr int FIT = (kLdsBytes / WGS - PARAMS - KVX) / (kChunkFrags * 1024);
   static constexpr int RING = FIT < NCHUNK ? FIT : NCHUNK;
@@ -108,7 +108,7 @@ struct LdsPlan {
   static_assert(RING >= 2, "weight ring");
 };
 
-template <int C, int DH, int F, int NVB, int WPG, int NW, int MINW, bool OUT_F32, bool PE>
+template <int WPG, int NW, int MINW, bool OUT_F32, bool PE>
 __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __restrict__ feats, void* __restrict__ out,
                                                                const uint16_t* __restrict__ pos_embed,
                                                                const int32_t* __restrict__ perm,
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   constexpr int NB = C / 16;          // 16-wide blocks of the output features
   constexpr int HP = C / 32;          // 32-wide head-dim units
   constexpr int FC = F / 32;          // 32-wide hidden units
-  constexpr int NKB = NVB * WPG;      // key blocks of a group
+  constexpr int NKB = WPG;            // key blocks of a group
   constexpr int NT = NW * 64;
   constexpr int GPW = NW / WPG;       // groups per workgroup
   constexpr int CF = kChunkFrags;
@@ -134,10 +134,9 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   constexpr int ATT_UNROLL = NKB > 4 && MINW >= 4 ? 1 : 2;
   constexpr bool LEAN = MINW >= 4;    // four wavefronts on a SIMD: 128 registers each
   constexpr int PF = LEAN ? 4 : kWindow;
-  using LP = LdsPlan<C, F, NVB, WPG, NW, MINW>;
+  using LP = LdsPlan<WPG, NW, MINW>;
   constexpr int NCHUNK = LP::NCHUNK, RING = LP::RING;
-  using PO = ParamOff<C, F>;
-  static_assert(DH == 16 || DH == 32, "head dim");
+  using PO = ParamOff;
   static_assert(FH % CF == 0 && FF % CF == 0 && CF % PF == 0, "units are whole chunks");
 
   extern __shared__ u32x4 lds[];
@@ -147,7 +146,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   uint32_t par_units = RING * CF * 64;
   asm volatile("" : "+v"(par_units));
   float* par = reinterpret_cast<float*>(lds + par_units);       // [PO::TOTAL]
-  u32x2* kvx = reinterpret_cast<u32x2*>(reinterpret_cast<char*>(par) + LP::PARAMS);  // K/V exchange, only when WPG > 1
+  u32x2* kvx = reinterpret_cast<u32x2*>(reinterpret_cast<char*>(par) + LP::PARAMS);  // K/V exchange
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, q = lane >> 4;
   const int wu = __builtin_amdgcn_readfirstlane(w);
@@ -160,25 +159,17 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   const int ngroups = *num_groups;
   // Groups of the first (or only) frame start at g * G: fetch the pillar indices from there
   // without waiting for the offsets, and use them if the guess turns out right.
-  int32_t guess[NVB];
-#pragma unroll
-  for (int vb = 0; vb < NVB; ++vb) {
-    // (unsigned 32-bit: g * G stays below n + num_frames * G, and one minimum clamps it)
-    const uint32_t at = (uint32_t)g * (uint32_t)G + (uint32_t)((part * NVB + vb) * 16 + i);
-    guess[vb] = perm[at < (uint32_t)n ? at : (uint32_t)n - 1u];
-  }
+  // (unsigned 32-bit: g * G stays below n + num_frames * G, and one minimum clamps it)
+  const uint32_t at = (uint32_t)g * (uint32_t)G + (uint32_t)(part * 16 + i);
+  const int32_t guess = perm[at < (uint32_t)n ? at : (uint32_t)n - 1u];
   // in_sorted: row p of feats is the pillar at sorted position p (the previous layer of a block wrote
   // its result in this layer's order), so the rows of a group are contiguous and need no index.
   // in_sorted == 2 (one frame): they are fetched from the guessed start without waiting for anything.
-  uint2 early[NVB][NB];
+  uint2 early[NB];
   if (in_sorted == 2) {
 #pragma unroll
-    for (int vb = 0; vb < NVB; ++vb) {
-      const uint32_t at = (uint32_t)g * (uint32_t)G + (uint32_t)((part * NVB + vb) * 16 + i);
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        early[vb][nb] = *reinterpret_cast<const uint2*>(feats + (size_t)(at < (uint32_t)n ? at : (uint32_t)n - 1u) * C + 16 * nb + 4 * q);
-    }
+    for (int nb = 0; nb < NB; ++nb)
+      early[nb] = *reinterpret_cast<const uint2*>(feats + (size_t)(at < (uint32_t)n ? at : (uint32_t)n - 1u) * C + 16 * nb + 4 * q);
   }
   int start = 0, m = 0;
   // A list of full groups only ('Drop Residual') has the next start beyond this group's end.
@@ -281,70 +272,50 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   }
 
   // ---- gather + LN1 ---------------------------------------------------------------------------------
-  f32x4 x1[NVB][NB];  // residual stream of my pillars, accumulator layout
-  int32_t row[NVB];   // pillar index, -1 for padding slots
-  int32_t orow[NVB];  // row of `out` the result goes to
+  f32x4 x1[NB];  // residual stream of my pillars, accumulator layout
   const bool guessed = (int64_t)g * G == start;  // wave-uniform
-#pragma unroll
-  for (int vb = 0; vb < NVB; ++vb) {
-    const int s = (part * NVB + vb) * 16 + i;
-    if (guessed) row[vb] = s < m ? guess[vb] : -1;
-    else row[vb] = s < m ? perm[start + s] : -1;
-  }
+  const int s = part * 16 + i;
+  int32_t row;        // pillar index, -1 for padding slots
+  if (guessed) row = s < m ? guess : -1;
+  else row = s < m ? perm[start + s] : -1;
   if (in_sorted == 2 && guessed) {  // the early fetch hit
+    const bool live = s < m;
 #pragma unroll
-    for (int vb = 0; vb < NVB; ++vb) {
-      const bool live = (part * NVB + vb) * 16 + i < m;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const uint2 u = early[vb][nb];
-        // (padding slots: the bits are cleared before the conversion, two instructions per block instead of a
-        // branch around each block)
-        const uint32_t keep = live ? 0xffffffffu : 0u;
-        x1[vb][nb] = f32x4{el_lo(u.x & keep), el_hi(u.x & keep), el_lo(u.y & keep), el_hi(u.y & keep)};
-      }
+    for (int nb = 0; nb < NB; ++nb) {
+      const uint2 u = early[nb];
+      // (padding slots: the bits are cleared before the conversion, two instructions per block instead of a
+      // branch around each block)
+      const uint32_t keep = live ? 0xffffffffu : 0u;
+      x1[nb] = f32x4{el_lo(u.x & keep), el_hi(u.x & keep), el_lo(u.y & keep), el_hi(u.y & keep)};
     }
   } else {
     // every lane loads (padding slots read a valid row and drop it): loads under a condition of their
     // own are waited for one by one
-    uint2 raw[NVB][NB];
-    int32_t srcv[NVB];  // row of feats for my pillar of block vb
+    uint2 raw[NB];
+    const int32_t src = row >= 0 ? (in_sorted ? start + s : row) : 0;  // row of feats for my pillar
 #pragma unroll
-    for (int vb = 0; vb < NVB; ++vb) {
-      const int s = (part * NVB + vb) * 16 + i;
-      srcv[vb] = row[vb] >= 0 ? (in_sorted ? start + s : row[vb]) : 0;
+    for (int nb = 0; nb < NB; ++nb)
+      raw[nb] = *reinterpret_cast<const uint2*>(feats + (int64_t)src * C + 16 * nb + 4 * q);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const uint2 u = raw[nb];
+      const uint32_t keep = row >= 0 ? 0xffffffffu : 0u;
+      x1[nb] = f32x4{el_lo(u.x & keep), el_hi(u.x & keep), el_lo(u.y & keep), el_hi(u.y & keep)};
     }
-#pragma unroll
-    for (int vb = 0; vb < NVB; ++vb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        raw[vb][nb] = *reinterpret_cast<const uint2*>(feats + (int64_t)srcv[vb] * C + 16 * nb + 4 * q);
-#pragma unroll
-    for (int vb = 0; vb < NVB; ++vb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const uint2 u = raw[vb][nb];
-        const uint32_t keep = row[vb] >= 0 ? 0xffffffffu : 0u;
-        x1[vb][nb] = f32x4{el_lo(u.x & keep), el_hi(u.x & keep), el_lo(u.y & keep), el_hi(u.y & keep)};
-      }
   }
   // Positional embedding of my pillars, still bf16, in the layout of `act` (Eq. (2), second argument
   // of the attention): it is added to the LayerNorm output on the way to the query and key products.
-  Frag8 pef[PE ? NVB : 1][PE ? KB : 1];
+  Frag8 pef[PE ? KB : 1];
   if constexpr (PE) {
-    uint2 praw[NVB][NB];
+    uint2 praw[NB];
 #pragma unroll
-    for (int vb = 0; vb < NVB; ++vb)
+    for (int nb = 0; nb < NB; ++nb)
+      praw[nb] = *reinterpret_cast<const uint2*>(pos_embed + (int64_t)(row >= 0 ? row : 0) * C + 16 * nb + 4 * q);
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        praw[vb][nb] = *reinterpret_cast<const uint2*>(pos_embed + (int64_t)(row[vb] >= 0 ? row[vb] : 0) * C + 16 * nb + 4 * q);
-#pragma unroll
-    for (int vb = 0; vb < NVB; ++vb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        pef[vb][nb / 2].u[(nb & 1) * 2 + 0] = row[vb] >= 0 ? praw[vb][nb].x : 0u;
-        pef[vb][nb / 2].u[(nb & 1) * 2 + 1] = row[vb] >= 0 ? praw[vb][nb].y : 0u;
-      }
+    for (int nb = 0; nb < NB; ++nb) {
+      pef[nb / 2].u[(nb & 1) * 2 + 0] = row >= 0 ? praw[nb].x : 0u;
+      pef[nb / 2].u[(nb & 1) * 2 + 1] = row >= 0 ? praw[nb].y : 0u;
+    }
   }
   if (drop && ngroups >= 0) {
     // Pillars of no group skip the layer: their rows are copied.  The wavefronts of group g take the
@@ -376,8 +347,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   sync(0);  // chunks 0 and 1 and the small parameters are in LDS; the rest of the ring is requested
   // out_index: the next layer of a block wants its input in its own sorted order.  Fetched only now:
   // the barrier above waits for every load in flight, and this one hangs on the pillar index.
-#pragma unroll
-  for (int vb = 0; vb < NVB; ++vb) orow[vb] = out_index && row[vb] >= 0 ? out_index[row[vb]] : row[vb];
+  const int32_t orow = out_index && row >= 0 ? out_index[row] : row;  // row of `out` the result goes to
 
   // The window: fragments j .. j + PF - 1 of the stream are in registers (or on their way) while
   // fragment j is being used.
@@ -390,23 +360,18 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   if (!LEAN) fill_window();  // early, so that the reads overlap the LayerNorm arithmetic
   __builtin_amdgcn_sched_barrier(0);
 
-  Frag8 act[NVB][KB];  // normalised activations as B operands (LN1 output, later LN2 output)
-  Frag8 actqk[PE ? NVB : 1][PE ? KB : 1];  // LN1 output plus the positional embedding: input of Q and K
+  Frag8 act[KB];  // normalised activations as B operands (LN1 output, later LN2 output)
+  Frag8 actqk[PE ? KB : 1];  // LN1 output plus the positional embedding: input of Q and K
   auto layer_norm = [&](int goff_f, int boff_f, bool first) {
-    float sc[NVB], sh[NVB];  // y = x * sc + sh  with sc = rstd, sh = -mean * rstd
+    float s = 0.f, ss = 0.f;
 #pragma unroll
-    for (int vb = 0; vb < NVB; ++vb) {
-      float s = 0.f, ss = 0.f;
+    for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { s += x1[vb][nb][j]; ss = fmaf(x1[vb][nb][j], x1[vb][nb][j], ss); }
-      }
-      const float mu = quad_sum(s) * (1.0f / C);
-      const float var = fmaxf(quad_sum(ss) * (1.0f / C) - mu * mu, 0.f);
-      sc[vb] = rsqrtf(var + eps);
-      sh[vb] = -mu * sc[vb];
+      for (int j = 0; j < 4; ++j) { s += x1[nb][j]; ss = fmaf(x1[nb][j], x1[nb][j], ss); }
     }
+    const float mu = quad_sum(s) * (1.0f / C);
+    const float var = fmaxf(quad_sum(ss) * (1.0f / C) - mu * mu, 0.f);
+    const float sc = rsqrtf(var + eps), sh = -mu * sc;  // y = x * sc + sh
     // the affine parameters come from LDS four feature blocks at a time, all eight reads of a batch
     // issued before the first is used (read, wait, use per block exposed the LDS latency every time)
     constexpr int NBG = LEAN ? 1 : 4;  // the lean mapping has no registers for a batch
@@ -422,25 +387,20 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < NBG; ++u) {
-      const int nb = nb0 + u;
-      const f32x4 gm = gmv[u], bt = btv[u];
-#pragma unroll
-      for (int vb = 0; vb < NVB; ++vb) {
+        const int nb = nb0 + u;
+        const f32x4 gm = gmv[u], bt = btv[u];
         float y[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) y[j] = fmaf(fmaf(x1[vb][nb][j], sc[vb], sh[vb]), gm[j], bt[j]);
-        act[vb][nb / 2].u[(nb & 1) * 2 + 0] = pack2(y[0], y[1]);
-        act[vb][nb / 2].u[(nb & 1) * 2 + 1] = pack2(y[2], y[3]);
+        for (int j = 0; j < 4; ++j) y[j] = fmaf(fmaf(x1[nb][j], sc, sh), gm[j], bt[j]);
+        act[nb / 2].u[(nb & 1) * 2 + 0] = pack2(y[0], y[1]);
+        act[nb / 2].u[(nb & 1) * 2 + 1] = pack2(y[2], y[3]);
         if constexpr (PE) {
           if (first) {
-            const uint32_t p01 = pef[vb][nb / 2].u[(nb & 1) * 2 + 0], p23 = pef[vb][nb / 2].u[(nb & 1) * 2 + 1];
-            actqk[vb][nb / 2].u[(nb & 1) * 2 + 0] =
-                pack2(y[0] + el_lo(p01), y[1] + el_hi(p01));
-            actqk[vb][nb / 2].u[(nb & 1) * 2 + 1] =
-                pack2(y[2] + el_lo(p23), y[3] + el_hi(p23));
+            const uint32_t p01 = pef[nb / 2].u[(nb & 1) * 2 + 0], p23 = pef[nb / 2].u[(nb & 1) * 2 + 1];
+            actqk[nb / 2].u[(nb & 1) * 2 + 0] = pack2(y[0] + el_lo(p01), y[1] + el_hi(p01));
+            actqk[nb / 2].u[(nb & 1) * 2 + 1] = pack2(y[2] + el_lo(p23), y[3] + el_hi(p23));
           }
         }
-      }
       }
     }
   };
@@ -452,9 +412,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
 #pragma unroll
       for (int u = 0; u < NBG; ++u) b[u] = *reinterpret_cast<const f32x4*>(par + off_f + 16 * (nb0 + u) + 4 * q);
 #pragma unroll
-      for (int u = 0; u < NBG; ++u)
-#pragma unroll
-        for (int vb = 0; vb < NVB; ++vb) x1[vb][nb0 + u] += b[u];
+      for (int u = 0; u < NBG; ++u) x1[nb0 + u] += b[u];
     }
   };
   // Bias of the Q rows of a unit (accumulator layout).  K and V start from zero: the key bias has no
@@ -473,7 +431,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
   // (zero) keys instead, so that it computes finite numbers it never stores rather than -inf - -inf.
   const bool short_group = m > 0 && m < NKB * 16;
 
-  // ---- attention: one 32-wide head-dim unit per iteration (two heads of 16 or one head of 32) --------
+  // ---- attention: one 32-wide head-dim unit per iteration (two heads of 16) --------
 #pragma unroll ATT_UNROLL
   for (int hp = 0; hp < HP; ++hp) {
     const int c0 = hp * CPH;
@@ -484,29 +442,26 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
     auto refill = [&](int j) {
       const int jj = j + PF, k = jj / CF;
       __builtin_amdgcn_sched_barrier(0);
-      if (jj % CF == 0) boundary(c0 + k, c0 + (j + 1) / CF, WPG == 1);
+      if (jj % CF == 0) boundary(c0 + k, c0 + (j + 1) / CF, false);
       win[j % PF].q = pb[k][(jj % CF) * 64];  // a hidden unit always follows: the chunk exists
       __builtin_amdgcn_sched_barrier(0);
     };
     if (LEAN) load_unit_bias(hp);
-    Frag4 Qf[2][NVB], Kf[2][NVB], Vf[2][NVB];  // bf16 fragments of my pillars, index [16-block a][vb]
+    Frag4 Qf[2], Kf[2], Vf[2];  // bf16 fragments of my pillars, index [16-block a]
     u32x2* kv = kvx + (size_t)((hp & 1) * GPW + gl) * (2 * 2 * NKB * 64) + lane;  // this unit's exchange buffer
 
     // Six accumulation chains: Q a=0,1 and K a=0,1 as D[feature][pillar], V a=0,1 with the operand
     // roles swapped as D[pillar][feature].  The conversion of a finished chain is issued after the
     // first product of the next one.
     {
-      f32x4 acc[2][NVB];
+      f32x4 acc[2];
       auto finish = [&](int ch) {
         const int a = ch & 1;
-#pragma unroll
-        for (int vb = 0; vb < NVB; ++vb) {
-          Frag4& dst = ch < 2 ? Qf[a][vb] : ch < 4 ? Kf[a][vb] : Vf[a][vb];
-          dst.u[0] = pack2(acc[ch & 1][vb][0], acc[ch & 1][vb][1]);
-          dst.u[1] = pack2(acc[ch & 1][vb][2], acc[ch & 1][vb][3]);
-          // K/V of the whole group go through LDS: [K|V][16-block a][key block][lane]
-          if (WPG > 1 && ch >= 2) kv[(((ch >= 4 ? 1 : 0) * 2 + a) * NKB + part * NVB + vb) * 64] = dst.d;
-        }
+        Frag4& dst = ch < 2 ? Qf[a] : ch < 4 ? Kf[a] : Vf[a];
+        dst.u[0] = pack2(acc[ch & 1][0], acc[ch & 1][1]);
+        dst.u[1] = pack2(acc[ch & 1][2], acc[ch & 1][3]);
+        // K/V of the whole group go through LDS: [K|V][16-block a][key block][lane]
+        if (ch >= 2) kv[(((ch >= 4 ? 1 : 0) * 2 + a) * NKB + part) * 64] = dst.d;
       };
       // Stream order (kQkvOrder): K and V first, so that their way to LDS overlaps the Q products
       // instead of standing between the last product and the barrier.
@@ -518,171 +473,105 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
           const int j = p * KB + kb;
           const Frag8 wf = win[j % PF];
           if (kb == 0) {  // the accumulator starts from the bias
-#pragma unroll
-            for (int vb = 0; vb < NVB; ++vb)
-              acc[ch & 1][vb] = ch < 2 ? bqk[ch] : f32x4{0.f, 0.f, 0.f, 0.f};
+              acc[ch & 1] = ch < 2 ? bqk[ch] : f32x4{0.f, 0.f, 0.f, 0.f};
           }
-#pragma unroll
-          for (int vb = 0; vb < NVB; ++vb)
-            acc[ch & 1][vb] = ch < 4 ? mfma32(wf, PE ? actqk[PE ? vb : 0][PE ? kb : 0] : act[vb][kb], acc[ch & 1][vb])
-                                     : mfma32(act[vb][kb], wf, acc[ch & 1][vb]);
+            acc[ch & 1] = ch < 4 ? mfma32(wf, PE ? actqk[PE ? kb : 0] : act[kb], acc[ch & 1])
+                                     : mfma32(act[kb], wf, acc[ch & 1]);
           if (kb == 0 && p > 0) finish(kQkvOrder[p - 1]);
           refill(j);
         }
       }
       finish(kQkvOrder[5]);
     }
-    if (WPG > 1) sync(c0 + (6 * KB) / CF);  // K/V of the group are in LDS
+    sync(c0 + (6 * KB) / CF);         // K/V of the group are in LDS
     if (!LEAN) load_unit_bias(hp + 1 < HP ? hp + 1 : hp);
-    auto Kget = [&](int a, int jb) -> Frag4 {
-      if (WPG == 1) return Kf[a][jb];
-      Frag4 f; f.d = kv[((0 * 2 + a) * NKB + jb) * 64]; return f;
-    };
-    auto Vget = [&](int a, int jb) -> Frag4 {
-      if (WPG == 1) return Vf[a][jb];
-      Frag4 f; f.d = kv[((1 * 2 + a) * NKB + jb) * 64]; return f;
-    };
-    Frag8 Of[NVB];  // attention output of this unit as B operand of the output projection
-    constexpr int NH = 32 / DH;   // heads in this unit
-    constexpr int NA = DH / 16;   // 16-blocks of head dims per head
-    // The (head, pillar-block) instances are independent; they go through the softmax in
-    // lockstep stages so that the long per-instance dependency chains interleave.  HJ heads are
-    // staged jointly, limited by the registers the score tiles take (168 of them with three wavefronts on a SIMD).
-    constexpr int VJ = NVB * NKB <= 16 ? NVB : (16 / NKB >= 1 ? 16 / NKB : 1);
-    constexpr int HJ = (NH * VJ * NKB <= (MINW == 3 ? 8 : 16) && MINW < 4) ? NH : 1;
-    static_assert(NVB % VJ == 0, "pillar blocks per stage");
+    auto Kget = [&](int a, int jb) -> Frag4 { Frag4 f; f.d = kv[((0 * 2 + a) * NKB + jb) * 64]; return f; };
+    auto Vget = [&](int a, int jb) -> Frag4 { Frag4 f; f.d = kv[((1 * 2 + a) * NKB + jb) * 64]; return f; };
+    Frag8 Of;                         // attention output of this unit as B operand of the output projection
+    // The unit's two heads are independent; they go through the softmax in lockstep stages so that the long
+    // dependency chains interleave, if there are registers for both heads' score tiles (168 of them with three
+    // wavefronts on a SIMD).
+    constexpr int HJ = 2 * NKB <= (MINW == 3 ? 8 : 16) && MINW < 4 ? 2 : 1;
 #pragma unroll
-    for (int v0 = 0; v0 < NVB; v0 += VJ)
+    for (int h0 = 0; h0 < 2; h0 += HJ) {
+      f32x4 S[HJ][NKB];               // scores, transposed: S[key 16*jb + 4q + j][query i]
 #pragma unroll
-    for (int h0 = 0; h0 < NH; h0 += HJ) {
-      f32x4 S[HJ][VJ][NKB];  // scores, transposed: S[key 16*jb + 4q + j][query i]
+      for (int hh = 0; hh < HJ; ++hh)
 #pragma unroll
-      for (int hh = 0; hh < HJ; ++hh) {
-        const int h = h0 + hh;
-#pragma unroll
-        for (int vb = 0; vb < VJ; ++vb) {
-#pragma unroll
-          for (int jb = 0; jb < NKB; ++jb) {
-            const f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (DH == 16) {
-              // the only k=16 products left: their accumulator input is zero, so they depend on no
-              // earlier product (see the note at the odd key block below)
-              S[hh][vb][jb] = mfma16_from_zero(Kget(h, jb), Qf[h][v0 + vb]);
-            } else {
-              Frag8 k8, q8;
-              const Frag4 k0 = Kget(0, jb), k1 = Kget(1, jb);
-              k8.u[0] = k0.u[0]; k8.u[1] = k0.u[1]; k8.u[2] = k1.u[0]; k8.u[3] = k1.u[1];
-              q8.u[0] = Qf[0][v0 + vb].u[0]; q8.u[1] = Qf[0][v0 + vb].u[1]; q8.u[2] = Qf[1][v0 + vb].u[0]; q8.u[3] = Qf[1][v0 + vb].u[1];
-              S[hh][vb][jb] = mfma32(k8, q8, z);
-            }
-          }
-        }
-      }
+        for (int jb = 0; jb < NKB; ++jb)
+          // the only k=16 products left: their accumulator input is zero, so they depend on no
+          // earlier product (see the note at the odd key block below)
+          S[hh][jb] = mfma16_from_zero(Kget(h0 + hh, jb), Qf[h0 + hh]);
       if (short_group) {  // keys beyond the group's real members
 #pragma unroll
         for (int hh = 0; hh < HJ; ++hh)
 #pragma unroll
-          for (int vb = 0; vb < VJ; ++vb)
-#pragma unroll
-            for (int jb = 0; jb < NKB; ++jb)
-#pragma unroll
-              for (int j = 0; j < 4; ++j)
-                if (16 * jb + 4 * q + j >= m) S[hh][vb][jb][j] = -INFINITY;
-      }
-      float mxs[HJ][VJ];
-#pragma unroll
-      for (int hh = 0; hh < HJ; ++hh) {
-#pragma unroll
-        for (int vb = 0; vb < VJ; ++vb) {
-          float mx = S[hh][vb][0][0];
-#pragma unroll
           for (int jb = 0; jb < NKB; ++jb)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) mx = fmaxf(mx, S[hh][vb][jb][j]);
-          mxs[hh][vb] = mx;
-        }
+            for (int j = 0; j < 4; ++j)
+              if (16 * jb + 4 * q + j >= m) S[hh][jb][j] = -INFINITY;
+      }
+      float mxs[HJ];
+#pragma unroll
+      for (int hh = 0; hh < HJ; ++hh) {
+        float mx = S[hh][0][0];
+#pragma unroll
+        for (int jb = 0; jb < NKB; ++jb)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) mx = fmaxf(mx, S[hh][jb][j]);
+        mxs[hh] = mx;
       }
 #pragma unroll
-      for (int hh = 0; hh < HJ; ++hh)
-#pragma unroll
-        for (int vb = 0; vb < VJ; ++vb) mxs[hh][vb] = -quad_max(mxs[hh][vb]) * qscale;
+      for (int hh = 0; hh < HJ; ++hh) mxs[hh] = -quad_max(mxs[hh]) * qscale;
       // p = 2^((s - max) * log2(e) / sqrt(d)): the score scale lives in the exponent argument
 #pragma unroll
       for (int hh = 0; hh < HJ; ++hh)
 #pragma unroll
-        for (int vb = 0; vb < VJ; ++vb)
+        for (int jb = 0; jb < NKB; ++jb)
 #pragma unroll
-          for (int jb = 0; jb < NKB; ++jb)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              S[hh][vb][jb][j] = __builtin_amdgcn_exp2f(fmaf(S[hh][vb][jb][j], qscale, mxs[hh][vb]));
-            }
+          for (int j = 0; j < 4; ++j) S[hh][jb][j] = __builtin_amdgcn_exp2f(fmaf(S[hh][jb][j], qscale, mxs[hh]));
       // O^T[d][query] = sum over keys V^T[d][key] P^T[key][query], two key blocks per product.
       // The row sums of P come from the matrix cores as well: an all-ones A operand makes every
-      // accumulator row the sum over keys of the (bf16-rounded) probabilities.
-      f32x4 O[HJ][VJ][NA], rowsum[HJ][VJ];
+      // accumulator row the sum over keys of the (16-bit rounded) probabilities.
+      f32x4 O[HJ], rowsum[HJ];
 #pragma unroll
       for (int hh = 0; hh < HJ; ++hh) {
         const int h = h0 + hh;
+        Frag8 ones;
+        ones.u[0] = ones.u[1] = ones.u[2] = ones.u[3] = kOnePair;
+        rowsum[hh] = f32x4{0.f, 0.f, 0.f, 0.f};
+        O[hh] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int vb = 0; vb < VJ; ++vb) {
-          rowsum[hh][vb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int a = 0; a < NA; ++a) O[hh][vb][a] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int jb = 0; jb + 1 < NKB; jb += 2) {
-            Frag8 p8;
-            p8.u[0] = pack2(S[hh][vb][jb][0], S[hh][vb][jb][1]); p8.u[1] = pack2(S[hh][vb][jb][2], S[hh][vb][jb][3]);
-            p8.u[2] = pack2(S[hh][vb][jb + 1][0], S[hh][vb][jb + 1][1]);
-            p8.u[3] = pack2(S[hh][vb][jb + 1][2], S[hh][vb][jb + 1][3]);
-#pragma unroll
-            for (int a = 0; a < NA; ++a) {
-              const int ab = DH == 16 ? h : a;
-              const Frag4 v0 = Vget(ab, jb), v1 = Vget(ab, jb + 1);
-              Frag8 v8;
-              v8.u[0] = v0.u[0]; v8.u[1] = v0.u[1]; v8.u[2] = v1.u[0]; v8.u[3] = v1.u[1];
-              O[hh][vb][a] = mfma32(v8, p8, O[hh][vb][a]);
-            }
-            Frag8 ones;
-            ones.u[0] = ones.u[1] = ones.u[2] = ones.u[3] = kOnePair;
-            rowsum[hh][vb] = mfma32(ones, p8, rowsum[hh][vb]);
-          }
-          if (NKB & 1) {
-            // The odd last key block: a k=32 product whose upper half multiplies zeros.  A k=16
-            // product here was wrong on this chip: issued right behind a k=32 product into the same
-            // accumulator it read the accumulator before that product had written it (row sums of 48
-            // instead of 80, whenever the scheduler put the two back to back), so every product of an
-            // accumulation chain is of one kind.  The k=16 product takes the same 16 cycles anyway.
-            constexpr int jb = NKB - 1;
-            Frag8 p8;
-            p8.u[0] = pack2(S[hh][vb][jb][0], S[hh][vb][jb][1]); p8.u[1] = pack2(S[hh][vb][jb][2], S[hh][vb][jb][3]);
-            p8.u[2] = p8.u[3] = 0u;
-#pragma unroll
-            for (int a = 0; a < NA; ++a) {
-              const Frag4 v0 = Vget(DH == 16 ? h : a, jb);
-              Frag8 v8;
-              v8.u[0] = v0.u[0]; v8.u[1] = v0.u[1]; v8.u[2] = v8.u[3] = 0u;
-              O[hh][vb][a] = mfma32(v8, p8, O[hh][vb][a]);
-            }
-            Frag8 ones;
-            ones.u[0] = ones.u[1] = ones.u[2] = ones.u[3] = kOnePair;
-            rowsum[hh][vb] = mfma32(ones, p8, rowsum[hh][vb]);
-          }
+        for (int jb = 0; jb + 1 < NKB; jb += 2) {
+          Frag8 p8, v8;
+          p8.u[0] = pack2(S[hh][jb][0], S[hh][jb][1]); p8.u[1] = pack2(S[hh][jb][2], S[hh][jb][3]);
+          p8.u[2] = pack2(S[hh][jb + 1][0], S[hh][jb + 1][1]); p8.u[3] = pack2(S[hh][jb + 1][2], S[hh][jb + 1][3]);
+          const Frag4 v0 = Vget(h, jb), v1 = Vget(h, jb + 1);
+          v8.u[0] = v0.u[0]; v8.u[1] = v0.u[1]; v8.u[2] = v1.u[0]; v8.u[3] = v1.u[1];
+          O[hh] = mfma32(v8, p8, O[hh]);
+          rowsum[hh] = mfma32(ones, p8, rowsum[hh]);
+        }
+        if (NKB & 1) {
+          // The odd last key block: a k=32 product whose upper half multiplies zeros.  A k=16
+          // product here was wrong on this chip: issued right behind a k=32 product into the same
+          // accumulator it read the accumulator before that product had written it (row sums of 48
+          // instead of 80, whenever the scheduler put the two back to back), so every product of an
+          // accumulation chain is of one kind.  The k=16 product takes the same 16 cycles anyway.
+          constexpr int jb = NKB - 1;
+          Frag8 p8, v8;
+          p8.u[0] = pack2(S[hh][jb][0], S[hh][jb][1]); p8.u[1] = pack2(S[hh][jb][2], S[hh][jb][3]);
+          p8.u[2] = p8.u[3] = 0u;
+          const Frag4 v0 = Vget(h, jb);
+          v8.u[0] = v0.u[0]; v8.u[1] = v0.u[1]; v8.u[2] = v8.u[3] = 0u;
+          O[hh] = mfma32(v8, p8, O[hh]);
+          rowsum[hh] = mfma32(ones, p8, rowsum[hh]);
         }
       }
 #pragma unroll
       for (int hh = 0; hh < HJ; ++hh) {
-        const int h = h0 + hh;
-#pragma unroll
-        for (int vb = 0; vb < VJ; ++vb) {
-          const float inv = __builtin_amdgcn_rcpf(rowsum[hh][vb][0]);
-#pragma unroll
-          for (int a = 0; a < NA; ++a) {
-            const int slot = DH == 16 ? h : a;
-            Of[v0 + vb].u[slot * 2 + 0] = pack2(O[hh][vb][a][0] * inv, O[hh][vb][a][1] * inv);
-            Of[v0 + vb].u[slot * 2 + 1] = pack2(O[hh][vb][a][2] * inv, O[hh][vb][a][3] * inv);
-          }
-        }
+        const float inv = __builtin_amdgcn_rcpf(rowsum[hh][0]);
+        Of.u[(h0 + hh) * 2 + 0] = pack2(O[hh][0] * inv, O[hh][1] * inv);
+        Of.u[(h0 + hh) * 2 + 1] = pack2(O[hh][2] * inv, O[hh][3] * inv);
       }
     }
     // output projection of this unit, accumulated into the residual stream
@@ -690,8 +579,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
     for (int nb = 0; nb < NB; ++nb) {
       const int j = 6 * KB + nb;
       const Frag8 wf = win[j % PF];
-#pragma unroll
-      for (int vb = 0; vb < NVB; ++vb) x1[vb][nb] = mfma32(wf, Of[vb], x1[vb][nb]);
+      x1[nb] = mfma32(wf, Of, x1[nb]);
       refill(j);
     }
   }
@@ -718,16 +606,13 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
       if (k < CPF || fc + 1 < FC) win[j % PF].q = pb[k][(jj % CF) * 64];
       __builtin_amdgcn_sched_barrier(0);
     };
-    Frag8 Hf[NVB];
+    Frag8 Hf;
     if (LEAN) load_b1(fc);
     {
-      f32x4 acc[2][NVB];
+      f32x4 acc[2];
       auto finish = [&](int a) {
-#pragma unroll
-        for (int vb = 0; vb < NVB; ++vb) {
-          Hf[vb].u[a * 2 + 0] = pack2(gelu2_fast(acc[a][vb][0]), gelu2_fast(acc[a][vb][1]));
-          Hf[vb].u[a * 2 + 1] = pack2(gelu2_fast(acc[a][vb][2]), gelu2_fast(acc[a][vb][3]));
-        }
+        Hf.u[a * 2 + 0] = pack2(gelu2_fast(acc[a][0]), gelu2_fast(acc[a][1]));
+        Hf.u[a * 2 + 1] = pack2(gelu2_fast(acc[a][2]), gelu2_fast(acc[a][3]));
       };
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
@@ -735,12 +620,8 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
         for (int kb = 0; kb < KB; ++kb) {
           const int j = a * KB + kb;
           const Frag8 wf = win[j % PF];
-          if (kb == 0) {
-#pragma unroll
-            for (int vb = 0; vb < NVB; ++vb) acc[a][vb] = b1r[a];
-          }
-#pragma unroll
-          for (int vb = 0; vb < NVB; ++vb) acc[a][vb] = mfma32(wf, act[vb][kb], acc[a][vb]);
+          if (kb == 0) acc[a] = b1r[a];
+          acc[a] = mfma32(wf, act[kb], acc[a]);
           if (kb == 0 && a == 1) finish(0);
           refill(j);
         }
@@ -752,37 +633,33 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
     for (int nb = 0; nb < NB; ++nb) {
       const int j = 2 * KB + nb;
       const Frag8 wf = win[j % PF];
-#pragma unroll
-      for (int vb = 0; vb < NVB; ++vb) x1[vb][nb] = mfma32(wf, Hf[vb], x1[vb][nb]);
+      x1[nb] = mfma32(wf, Hf, x1[nb]);
       refill(j);
     }
   }
 
   // ---- scatter -------------------------------------------------------------------------------------
+  if (row < 0) return;
 #pragma unroll
-  for (int vb = 0; vb < NVB; ++vb) {
-    if (row[vb] < 0) continue;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const size_t o = (size_t)orow[vb] * C + 16 * nb + 4 * q;
-      if (OUT_F32) {
-        *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + o) =
-            make_float4(x1[vb][nb][0], x1[vb][nb][1], x1[vb][nb][2], x1[vb][nb][3]);
-      } else {
-        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + o) =
-            make_uint2(pack2(x1[vb][nb][0], x1[vb][nb][1]), pack2(x1[vb][nb][2], x1[vb][nb][3]));
-      }
+  for (int nb = 0; nb < NB; ++nb) {
+    const size_t o = (size_t)orow * C + 16 * nb + 4 * q;
+    if (OUT_F32) {
+      *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + o) =
+          make_float4(x1[nb][0], x1[nb][1], x1[nb][2], x1[nb][3]);
+    } else {
+      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + o) =
+          make_uint2(pack2(x1[nb][0], x1[nb][1]), pack2(x1[nb][2], x1[nb][3]));
     }
   }
 }
 
-template <int C, int DH, int F, int NVB, int WPG, int NW, int MINW>
+template <int WPG, int NW, int MINW>
 int launch_cfg(const void* feats, void* out, const void* pos_embed, const int32_t* perm, const int32_t* goff,
                const int32_t* num_groups,
                int32_t max_groups, const u32x4* packed, float eps, bool out_f32, int n, int G,
                int drop, const int32_t* out_index, int in_sorted, hipStream_t stream) {
   constexpr int GPW = NW / WPG;
-  const size_t lds_bytes = LdsPlan<C, F, NVB, WPG, NW, MINW>::TOTAL;
+  const size_t lds_bytes = LdsPlan<WPG, NW, MINW>::TOTAL;
   const unsigned blocks = (unsigned)((max_groups + GPW - 1) / GPW);
   // The dynamic LDS size has to be allowed once per kernel and device (output type and positional
   // embedding make four kernels of a mapping).
@@ -803,11 +680,11 @@ int launch_cfg(const void* feats, void* out, const void* pos_embed, const int32_
     return launch_status();
   };
   if (pos_embed) {
-    if (out_f32) return go(k_layer_mfma<C, DH, F, NVB, WPG, NW, MINW, true, true>, 3);
-    return go(k_layer_mfma<C, DH, F, NVB, WPG, NW, MINW, false, true>, 2);
+    if (out_f32) return go(k_layer_mfma<WPG, NW, MINW, true, true>, 3);
+    return go(k_layer_mfma<WPG, NW, MINW, false, true>, 2);
   }
-  if (out_f32) return go(k_layer_mfma<C, DH, F, NVB, WPG, NW, MINW, true, false>, 1);
-  return go(k_layer_mfma<C, DH, F, NVB, WPG, NW, MINW, false, false>, 0);
+  if (out_f32) return go(k_layer_mfma<WPG, NW, MINW, true, false>, 1);
+  return go(k_layer_mfma<WPG, NW, MINW, false, false>, 0);
 }
 
 }  // namespace
@@ -856,8 +733,8 @@ int FF_LAYER_SYM(layer_mfma_launch)(const void* feats, void* out, int64_t n, con
                       int in_sorted, hipStream_t stream) {
   if (max_groups == 0 || n == 0) return FF_OK;
   const u32x4* pk = (const u32x4*)packed;
-#define FF_GO(C, DH, F, NVB, WPG, NW, MINW) \
-  return launch_cfg<C, DH, F, NVB, WPG, NW, MINW>(feats, out, w->pos_embed, perm, group_offsets, num_groups, max_groups, pk, \
+#define FF_GO(WPG, NW, MINW) \
+  return launch_cfg<WPG, NW, MINW>(feats, out, w->pos_embed, perm, group_offsets, num_groups, max_groups, pk, \
                                                   w->ln_eps, out_f32, (int)n, G, drop ? 1 : 0, out_index, in_sorted, stream)
   const int shape = shape_id(w);
   const bool pe = w->pos_embed != nullptr;
@@ -901,16 +778,16 @@ int FF_LAYER_SYM(layer_mfma_launch)(const void* feats, void* out, int64_t n, con
     else if (G <= 96) variant = rounds(1) == 1 ? 4 : G <= 80 ? 5 : 6;
     else variant = rounds(1) * 90 <= rounds(2) * 151 ? 4 : 7;
   }
-  // (pillar blocks per wave, waves per group, waves per workgroup, min waves per SIMD)
+  // (waves per group, waves per workgroup, min waves per SIMD)
   switch (variant) {
-    case 1: if (G <= 32) FF_GO(64, 16, 128, 1, 2, 8, 2); break;
-    case 2: if (G <= 64) FF_GO(64, 16, 128, 1, 4, 8, 2); break;
-    case 3: if (G <= 32) FF_GO(64, 16, 128, 1, 2, 16, 4); break;   // eight groups
-    case 4: if (G <= 128) FF_GO(64, 16, 128, 1, 8, 8, 2); break;
-    case 5: if (G <= 80) FF_GO(64, 16, 128, 1, 5, 10, 3); break;   // two groups
-    case 6: if (G <= 96) FF_GO(64, 16, 128, 1, 6, 12, 3); break;   // two groups
-    case 7: if (G <= 128) FF_GO(64, 16, 128, 1, 8, 16, 4); break;  // two groups
-    case 8: if (G <= 64) FF_GO(64, 16, 128, 1, 4, 16, 4); break;   // four groups
+    case 1: if (G <= 32) FF_GO(2, 8, 2); break;
+    case 2: if (G <= 64) FF_GO(4, 8, 2); break;
+    case 3: if (G <= 32) FF_GO(2, 16, 4); break;   // eight groups
+    case 4: if (G <= 128) FF_GO(8, 8, 2); break;
+    case 5: if (G <= 80) FF_GO(5, 10, 3); break;   // two groups
+    case 6: if (G <= 96) FF_GO(6, 12, 3); break;   // two groups
+    case 7: if (G <= 128) FF_GO(8, 16, 4); break;  // two groups
+    case 8: if (G <= 64) FF_GO(4, 16, 4); break;   // four groups
     default: break;
   }
 #undef FF_GO
