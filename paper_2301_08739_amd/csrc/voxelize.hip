@@ -355,7 +355,7 @@ __global__ __launch_bounds__(kVoxOrderThreads) void k_vox_order(const uint32_t* 
     __syncthreads();
     len = T - list0 < (uint32_t)kVoxList ? T - list0 : (uint32_t)kVoxList;
     for (int w = tid; w < kVoxOrderWaves * CELLS / 2; w += kVoxOrderThreads) words[w] = 0u;
-    if (T > (uint32_t)kVoxList) {            // a few tiles' pieces, too few for the wavefronts: each point finds its tile, the last that
+    if (lane_bits == 6 && T > (uint32_t)kVoxList) {  // a few tiles' pieces, too few for the wavefronts: each point finds its tile, the last that
       uint32_t tile[ROUNDS] = {}, v[ROUNDS]; // begins no later
 #pragma unroll
       for (uint32_t step = kVoxMaxTilesPow / 2; step > 0; step >>= 1)
@@ -419,15 +419,15 @@ __global__ __launch_bounds__(kVoxOrderThreads) void k_vox_order(const uint32_t* 
   } else {                                   // several lists: the cells' points are counted in front of them
     for (int c = tid; c < CELLS; c += kVoxOrderThreads) place[c] = 0u;
     __syncthreads();
-    for (int t = wave; t < tiles; t += kVoxOrderWaves) {
+    for (int t = tid >> lane_bits; t < tiles; t += kVoxOrderThreads >> lane_bits) {
       const uint32_t n = cum[t + 1] - cum[t];
-      for (uint32_t p = lane; p < n; p += 64u * kVoxInFlight) {
+      for (uint32_t p = tid & (lanes - 1u); p < n; p += lanes * kVoxInFlight) {
         uint32_t v[kVoxInFlight];
 #pragma unroll
-        for (int u = 0; u < kVoxInFlight; ++u) v[u] = entries[from[t] + (p + 64u * u < n ? p + 64u * u : p)];
+        for (int u = 0; u < kVoxInFlight; ++u) v[u] = entries[from[t] + (p + lanes * u < n ? p + lanes * u : p)];
 #pragma unroll
         for (int u = 0; u < kVoxInFlight; ++u)
-          if (p + 64u * u < n) {             // (all of one cell: one addition, where they would wait for each other)
+          if (p + lanes * u < n) {           // (all of one cell: one addition, where they would wait for each other)
             const uint32_t cell = v[u] >> kVoxLocalBits, of_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)cell);
             const uint64_t here = __ballot(true);
             if (__ballot(cell != of_first) == 0ull) {
