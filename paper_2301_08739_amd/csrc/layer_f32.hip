@@ -26,7 +26,11 @@
 // product of P V would be for rows that no one wants; there the products are 16x16x4, for which registers change lanes in
 // pairs, once for K, Q and V and once for every output (permlane swaps, 2 for 128 numbers).  Row sums of P are added beside the
 // products.  Against 32x32x2 products with the sums as rows of ones, us a layer: 30,000 rows at C = 128, G = 64 61.4 -> 59.6,
-// 100,000 192 -> 183, 20,000 at C = 64 40.4 -> 38.4; C = 256 (sums only) 172 -> 165; errors against float64 1 to 6 % smaller.
+// 100,000 192 -> 183, 20,000 at C = 64, G = 64 40.4 -> 38.4; C = 256 (sums only) 172 -> 165; errors against float64 1 to 6 %
+// smaller.  Four row blocks keep 144 to 340 bytes a lane in scratch with them and are the faster for it all the same: 30,000
+// rows at C = 64, G = 128 76 -> 73, C = 128, G = 128 110 -> 109, with an embedding 133 -> 118, 120,000 rows 430 -> 421 and
+// 489 -> 459; only C = 128, G = 120 without an embedding is behind, 112 -> 116 and 439 -> 448.  32x32x2 products with zeros
+// for the other head's rows and the sums beside them need no scratch there and were slower (78, 111, 124, 434, 478, 115, 448).
 //
 // What bounds it: the matrix pipe, about 33k cycles per wavefront at C = 128, G = 64, two wavefronts per SIMD (30k rows:
 // two groups on most compute units), and nearly as many issue cycles of GELU, exponentials, splits and LayerNorm beside

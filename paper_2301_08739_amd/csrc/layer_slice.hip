@@ -18,9 +18,9 @@
 //
 // What bounds it.  One group on a compute unit (C = 128, G = 64): the chain of one wavefront, 9 us, of which 2 are the trip to
 // its rows; a lone wavefront issues an instruction every five to seven cycles.  Two groups: 14 us.  Many: instruction issue
-// (1,690 vector instructions a wavefront, a fifth of them exponentials and their 16-bit roundings, for 152 products of 32
+// (1,657 vector instructions a wavefront, a fifth of them exponentials and their 16-bit roundings, beside 161 products of 32
 // cycles) and weight delivery (256 KB a group from L2, a quarter of the time in a build without it); the matrix pipe is
-// busy 45 % of the time.  Before (wavefronts that cut the rows, every one reading all weights from LDS) / now, us a
+// busy 43 % of the time.  Before (wavefronts that cut the rows, every one reading all weights from LDS) / now, us a
 // launch: C = 128, G = 64, 12,345 rows 14.5 / 10.3, 480,000 rows 208 / 190; G = 100, 30,000 rows 32.8 / 27; G = 128,
 // 80,000 rows 46.5 / 42.5; C = 256, G = 64, 2,000 rows 40 / 16, 60,000 rows 85 / 79; G = 96, 240,000 rows 364 / 311.
 #include "elem16.h"

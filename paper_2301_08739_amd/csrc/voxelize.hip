@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void k_seg_mean(const int32_t* __restrict__ pe
 // sorts keep the order of the points (ranks of equal numbers in a wavefront, counters of its own for each wavefront), so a
 // pillar's points come in the order of their indices.
 //
-// What bounds it: three dependent launches, each a chain of four to six round trips to memory (8.5 + 17 + 17 us for 180,000
+// What bounds it: three dependent launches, each a chain of four to six round trips to memory (9.3 + 10.8 + 19.4 us for 180,000
 // points of one frame, 4 of each the launch itself), not the 7 MB moved.  In front of them were nine launches, keys of 64 bits
 // through two radix passes.  The call, us, before / this: 2,000 points 31 / 18, 20,000 36 / 22, 60,000 48 / 31, 180,000 of 4
 // features 50.5 / 42.3, of 8 56.3 / 49.1, 262,144 of two frames 55 / 47.  Ranges of 1024 cells, which cover four times the
