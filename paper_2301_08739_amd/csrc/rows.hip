@@ -1,23 +1,63 @@
 // Row gather / scatter between pillar order and the flattened (sorted) order: the explicit form
 // of the reshape [N, C] -> [N/G, G, C] of paper Sec. 4.2.1.  Pure data movement, HBM-bound:
-// every thread moves one 16-byte piece, consecutive threads move consecutive pieces of a row.
+// every thread moves 16-byte pieces, consecutive threads move consecutive pieces of a row.
 #include "common.h"
 
 namespace ff {
 namespace {
 
-template <bool SCATTER>
-__global__ __launch_bounds__(256) void k_rows(const uint4* __restrict__ src, uint4* __restrict__ dst,
-                                               const int32_t* __restrict__ perm, int64_t n, int vec_per_row) {
-  const int64_t total = n * vec_per_row;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t p = i / vec_per_row;
-    const int v = (int)(i - p * vec_per_row);
-    const int64_t r = perm[p];
-    if (SCATTER) dst[r * vec_per_row + v] = src[i];
-    else         dst[i] = src[r * vec_per_row + v];
+typedef uint32_t piece_t __attribute__((ext_vector_type(4)));
+
+// Pieces of 16 bytes that lie side by side in the order of the rows of one side: which row a piece is of.
+struct RowPieces { int64_t total; int32_t per_row, log; };  // log: of per_row if that is a power of two, else -1
+RowPieces row_pieces(int64_t n, int per_row) {
+  int log = 0;
+  while ((1 << log) < per_row) ++log;
+  return {n * per_row, per_row, 1 << log == per_row ? log : -1};
+}
+__device__ __forceinline__ int64_t row_of(const RowPieces& rp, int64_t i) {
+  return rp.log >= 0 ? i >> rp.log : i / rp.per_row;  // the same way for every thread
+}
+
+// What bounds it: memory.  A 64-bit division for every piece was most of the instructions; rows of 2^k pieces (all feature
+// counts of the layers) take shifts.  What is read once and what is not read again soon passes the 256 MB memory-side cache
+// by, so that it still holds what a gather has written when the next launch reads it: 240,000 rows of 256 bfloat16, gather
+// and scatter on buffers that no cache holds, us: plain accesses 96-99, the scatter's non-temporal 76, with the gather's
+// loads 76 too (120,000 rows 47 / 38 / 41; 480,000 rows 195 / 169 / 144: kRowsStreamed).  Each piece one thread's, two or
+// four: within 1 us.
+constexpr int kRowsInFlight = 2;
+constexpr int64_t kRowsStreamed = (int64_t)128 << 20;  // bytes: larger sources of a gather would push out what it writes
+
+template <bool SCATTER, bool STREAM>
+__global__ __launch_bounds__(256) void k_rows(const piece_t* __restrict__ src, piece_t* __restrict__ dst,
+                                               const int32_t* __restrict__ perm, RowPieces rp) {
+  constexpr int U = kRowsInFlight;
+  for (int64_t i0 = (int64_t)blockIdx.x * (256 * U) + threadIdx.x; i0 < rp.total; i0 += (int64_t)gridDim.x * (256 * U)) {
+    int64_t here[U], there[U];               // of the side in sorted order, and of the other
+    piece_t v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + u * 256;
+      here[u] = i < rp.total ? i : i0;
+      const int64_t p = row_of(rp, here[u]);
+      there[u] = here[u] + ((int64_t)perm[p] - p) * rp.per_row;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const piece_t* const from = src + (SCATTER ? here[u] : there[u]);
+      v[u] = STREAM ? __builtin_nontemporal_load(from) : *from;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + u * 256 >= rp.total) continue;
+      if (SCATTER) __builtin_nontemporal_store(v[u], dst + there[u]);
+      else         dst[here[u]] = v[u];
+    }
   }
+}
+unsigned row_blocks(int64_t pieces) {
+  const int64_t b = ceil_div(pieces, (int64_t)256 * kRowsInFlight);
+  return (unsigned)(b < (1 << 20) ? b : 1 << 20);
 }
 
 // Rows of sorted positions outside every group skip the layer ('Drop Residual', Sec. 4.3): for a
@@ -57,23 +97,29 @@ __global__ __launch_bounds__(256) void k_copy_ungrouped(const T* __restrict__ fe
 // ---- sparse pillars -> dense bird's-eye-view map (the step after the FWA blocks, Sec. 5.1 'Model') -----
 // bev[b][y][x][:] = feats[i][:] for pillar i = (b, x, y), zero elsewhere; channels last, so that a
 // pillar's features stay one contiguous row.  Two launches: zero fill (the map is mostly empty:
-// 30k of 219k cells at the paper's resolution), then one 16-byte piece per thread.
-__global__ __launch_bounds__(256) void k_fill_zero(uint4* __restrict__ dst, int64_t pieces) {
-  const uint4 z = make_uint4(0u, 0u, 0u, 0u);
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < pieces; i += (int64_t)gridDim.x * blockDim.x)
-    dst[i] = z;
+// 30k of 219k cells at the paper's resolution), then the rows, a 16-byte piece per thread.
+// What bounds it: memory, 37 of 48 us for four 468 x 468 maps of 128 bfloat16 (224 MB) the fill's writes.  Non-temporal ones
+// leave the memory-side cache to the rows that come after it: 51.5 -> 47.9 us; maps that the cache holds are better filled
+// through it (56 MB 12.9 / 14.0, 84 MB 17.2 / 18.2, 112 MB 26.5 / 24.8: kFillStreamed).  Writing each cell once, with the pillars' numbers left in the map's last rows by a launch of their own and
+// checked against the coordinates, was slower (52.9 to 74 us: the rows' addresses hang on two trips to memory).
+constexpr int64_t kFillStreamed = (int64_t)96 << 20;  // bytes of a map
+
+template <bool STREAM>
+__global__ __launch_bounds__(256) void k_fill_zero(piece_t* __restrict__ dst, int64_t pieces) {
+  const piece_t z = {0u, 0u, 0u, 0u};
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < pieces; i += (int64_t)gridDim.x * blockDim.x) {
+    if (STREAM) __builtin_nontemporal_store(z, dst + i);
+    else        dst[i] = z;
+  }
 }
 
-__global__ __launch_bounds__(256) void k_bev_scatter(const uint4* __restrict__ feats, const int32_t* __restrict__ coords,
-                                                      int64_t n, int vec_per_row, int B, int gx, int gy,
-                                                      uint4* __restrict__ bev) {
-  const int64_t total = n * vec_per_row;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t p = i / vec_per_row;
-    const int v = (int)(i - p * vec_per_row);
+__global__ __launch_bounds__(256) void k_bev_scatter(const piece_t* __restrict__ feats, const int32_t* __restrict__ coords,
+                                                      RowPieces rp, int B, int gx, int gy, piece_t* __restrict__ bev) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < rp.total; i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t p = row_of(rp, i);
     const int32_t b = coords[3 * p], x = coords[3 * p + 1], y = coords[3 * p + 2];
     if ((uint32_t)b >= (uint32_t)B || (uint32_t)x >= (uint32_t)gx || (uint32_t)y >= (uint32_t)gy) continue;  // outside the map
-    bev[(((int64_t)b * gy + y) * gx + x) * vec_per_row + v] = feats[i];
+    bev[(((int64_t)b * gy + y) * gx + x - p) * rp.per_row + i] = feats[i];
   }
 }
 
@@ -87,16 +133,16 @@ int bev_scatter_launch(const void* feats, const int32_t* coords, int64_t n, cons
   if (row_bytes % 16) return FF_ERR_UNSUPPORTED;
   if (((uintptr_t)bev & 15) || ((uintptr_t)feats & 15)) return FF_ERR_ARG;
   if (n > 0 && (!feats || !coords)) return FF_ERR_ARG;
-  const int vec = (int)(row_bytes / 16);
-  const int64_t pieces = (int64_t)g->num_frames * g->grid_x * g->grid_y * vec;
+  const RowPieces rp = row_pieces(n, (int)(row_bytes / 16));
+  const int64_t pieces = (int64_t)g->num_frames * g->grid_x * g->grid_y * rp.per_row;
   int64_t fb = ceil_div(pieces, 256 * 8);
   if (fb > 256 * 64) fb = 256 * 64;
-  hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)fb), dim3(256), 0, stream, (uint4*)bev, pieces);
+  if (pieces * 16 > kFillStreamed) hipLaunchKernelGGL(k_fill_zero<true>, dim3((unsigned)fb), dim3(256), 0, stream, (piece_t*)bev, pieces);
+  else hipLaunchKernelGGL(k_fill_zero<false>, dim3((unsigned)fb), dim3(256), 0, stream, (piece_t*)bev, pieces);
   if (n > 0) {
-    int64_t blocks = ceil_div(n * vec, 256);
-    if (blocks > 256 * 32) blocks = 256 * 32;
-    hipLaunchKernelGGL(k_bev_scatter, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint4*)feats, coords, n, vec,
-                       g->num_frames, g->grid_x, g->grid_y, (uint4*)bev);
+    const int64_t blocks = ceil_div(rp.total, 256);
+    hipLaunchKernelGGL(k_bev_scatter, dim3((unsigned)(blocks < (1 << 20) ? blocks : 1 << 20)), dim3(256), 0, stream,
+                       (const piece_t*)feats, coords, rp, g->num_frames, g->grid_x, g->grid_y, (piece_t*)bev);
   }
   return launch_status();
 }
@@ -170,15 +216,13 @@ int rows_launch(bool scatter, const void* src, void* dst, const int32_t* perm, i
   if (n == 0) return FF_OK;
   if (!src || !dst || !perm || src == dst) return FF_ERR_ARG;
   if (((uintptr_t)src | (uintptr_t)dst) & 15) return FF_ERR_ARG;
-  const int vec = (int)(row_bytes / 16);
-  int64_t blocks = ceil_div(n * vec, 256);
-  if (blocks > 256 * 32) blocks = 256 * 32;
-  if (scatter)
-    hipLaunchKernelGGL(k_rows<true>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                       (const uint4*)src, (uint4*)dst, perm, n, vec);
-  else
-    hipLaunchKernelGGL(k_rows<false>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                       (const uint4*)src, (uint4*)dst, perm, n, vec);
+  const RowPieces rp = row_pieces(n, (int)(row_bytes / 16));
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(row_blocks(rp.total)), dim3(256), 0, stream, (const piece_t*)src, (piece_t*)dst, perm, rp);
+  };
+  if (scatter) go(k_rows<true, true>);
+  else if (rp.total * 16 > kRowsStreamed) go(k_rows<false, true>);
+  else go(k_rows<false, false>);
   return launch_status();
 }
 
