@@ -25,6 +25,26 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
   return (uint16_t)(u >> 16);
 }
 
+// ---- weights of a layer into the L2s ---------------------------------------------------------------
+// A launch begins with weights that its XCDs' L2s have not seen: the launch before wrote them, or another layer's were
+// there.  Met one by one at the products, each first use is a trip to memory.  So the first workgroups of an XCD (at most
+// 32) ask for all lines at once, beside their rows, N lines a thread at most, and give what they got to `touch_done` once
+// the rows are there.  16-bit layer, C = 128, G = 64, 30,000 rows: 5,900 -> 3,450 clocks from LayerNorm 1 to the end of Q, K, V.
+template <int NT, int BYTES, int N>
+__device__ __forceinline__ void touch_lines(const void* base, int workgroups, int tid, uint32_t (&got)[N]) {
+  const int on_xcd = (workgroups + 7) / 8, share = blockIdx.x / 8, of = on_xcd < 32 ? on_xcd : 32;
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const int line = (u * NT + tid) * of + share;
+    got[u] = 0;
+    if (share < of && line < BYTES / 128) got[u] = reinterpret_cast<const uint32_t*>(base)[line * 32];
+  }
+}
+template <int N> __device__ __forceinline__ void touch_done(const uint32_t (&got)[N]) {
+#pragma unroll
+  for (int u = 0; u < N; ++u) asm volatile("" :: "v"(got[u]));
+}
+
 // Storage-type traits: T is float, bf16_t or f16_t (16-bit wrappers).
 struct bf16_t { uint16_t bits; };
 struct f16_t { uint16_t bits; };

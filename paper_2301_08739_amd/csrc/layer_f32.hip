@@ -248,20 +248,6 @@ __device__ __forceinline__ bool layer_f32_rows(
 
   // ---- which rows ----------------------------------------------------------------------------------------------------
   int start[GPW], m[GPW], end1[GPW];
-  const int ngroups = *num_groups;
-  bool all_guessed = true;
-#pragma unroll
-  for (int gl = 0; gl < GPW; ++gl) {
-    const int g = blockIdx.x * GPW + gl;
-    const int gc = g < max_groups ? g : max_groups - 1;
-    const int o0 = goff[gc], o1 = goff[gc + 1];
-    const bool valid = g < ngroups;
-    start[gl] = valid ? o0 : 0;
-    end1[gl] = o1;
-    // A list of full groups only ('Drop Residual') has the next start beyond this group's end.
-    m[gl] = valid ? (o1 - o0 < G ? o1 - o0 : G) : 0;
-    all_guessed = all_guessed && (!valid || ((int64_t)g * G == o0 && (m[gl] == G || o0 + m[gl] == n)));
-  }
   // Row `r` of the workgroup -> sorted position.  Rows beyond the group's members repeat its last member: their scores
   // then never exceed the real ones, and they are cut out of the sums below.
   auto position = [&](int r) -> int {
@@ -306,7 +292,26 @@ __device__ __forceinline__ bool layer_f32_rows(
           raw[t][k][e] = *reinterpret_cast<const f32x4*>(feats + row * C + 8 * (lc + LPR * k) + 4 * e);
     }
   };
-  fetch(guess);
+  fetch(guess);                            // before anything that waits
+  // (Up to a workgroup a compute unit: two layers of 2,000 rows, C = 64, 31.0 -> 29.3 us.  Beyond, 768 KB of weights beside
+  // the rows of all workgroups only delay these: four layers of 30,000 rows, C = 128, 235 us without and 239 with it.)
+  uint32_t touched[2] = {0, 0};
+  const int workgroups = (max_groups + GPW - 1) / GPW;
+  if (workgroups <= 256) touch_lines<NT, NS * SLICE_FR * 3072>(wt.packed, workgroups, tid, touched);
+  const int ngroups = *num_groups;
+  bool all_guessed = true;
+#pragma unroll
+  for (int gl = 0; gl < GPW; ++gl) {
+    const int g = blockIdx.x * GPW + gl;
+    const int gc = g < max_groups ? g : max_groups - 1;
+    const int o0 = goff[gc], o1 = goff[gc + 1];
+    const bool valid = g < ngroups;
+    start[gl] = valid ? o0 : 0;
+    end1[gl] = o1;
+    // A list of full groups only ('Drop Residual') has the next start beyond this group's end.
+    m[gl] = valid ? (o1 - o0 < G ? o1 - o0 : G) : 0;
+    all_guessed = all_guessed && (!valid || ((int64_t)g * G == o0 && (m[gl] == G || o0 + m[gl] == n)));
+  }
   f32x4 gam[2][2], bet[2][2];              // LayerNorm 1 scale and shift of my features
 #pragma unroll
   for (int k = 0; k < 2; ++k)
@@ -315,13 +320,11 @@ __device__ __forceinline__ bool layer_f32_rows(
       gam[k][e] = *reinterpret_cast<const f32x4*>(wt.ln1_g + 8 * (lc + LPR * k) + 4 * e);
       bet[k][e] = *reinterpret_cast<const f32x4*>(wt.ln1_b + 8 * (lc + LPR * k) + 4 * e);
     }
-  {
-    auto put = [&](int off, const float* src, int len) {
-      for (int i = tid; i < len; i += NT) par[off + i] = src[i];
-    };
-    put(P_BQ, wt.b_qkv, C); put(P_BO, wt.b_o, C); put(P_G2, wt.ln2_g, C); put(P_B2N, wt.ln2_b, C);
-    put(P_B2, wt.b2, C); put(P_B1, wt.b1, F);
-  }
+  // The other vectors in the order of `par`, a column of it each thread (asked for together, written when the rows are there).
+  static_assert(NT == 2 * C && F == NT && P_BO == C && P_G2 == NT && P_B2N == 3 * C && P_B2 == 2 * NT, "columns of 2 C");
+  const bool low = tid < C;
+  const int col = low ? tid : tid - C;
+  const float par_at[4] = {(low ? wt.b_qkv : wt.b_o)[col], (low ? wt.ln2_g : wt.ln2_b)[col], wt.b2[col], wt.b1[tid]};
   const float bv = wt.b_qkv[2 * C + 32 * s + nrow];
   // The key bias shifts all scores of a query alike and drops out of the softmax, unless it is no finite number.
   const float bk = wt.b_qkv[C + 32 * s + nrow] * 0.f;
@@ -372,6 +375,11 @@ __device__ __forceinline__ bool layer_f32_rows(
     }
   };
   put_rows(false);
+  par[tid] = par_at[0];
+  par[P_G2 + tid] = par_at[1];
+  if (low) par[P_B2 + tid] = par_at[2];
+  par[P_B1 + tid] = par_at[3];
+  touch_done(touched);
 
   // ---- rows of no group ('Drop Residual'): copied, unless there is no list -----------------------------------------
   if (drop && ngroups >= 0) {
@@ -819,9 +827,9 @@ template <typename T> __device__ __forceinline__ T* again(T* p) {
 
 template <int C, int DH, int F, int PT, int GPW, int MINW, bool PE>
 __global__ __launch_bounds__(2 * C, MINW) void k_layer_f32(
-    const float* __restrict__ feats, float* __restrict__ out, const float* __restrict__ pos_embed,
-    const int32_t* __restrict__ perm, const int32_t* __restrict__ goff, const int32_t* __restrict__ num_groups,
-    int max_groups, int n, int G, const int32_t* __restrict__ out_index, int in_sorted, int drop, float eps, Weights wt) {
+    const float* __restrict__ feats, const int32_t* __restrict__ perm, int n, int G, int in_sorted, int max_groups,
+    const int32_t* __restrict__ goff, const int32_t* __restrict__ num_groups, const int32_t* __restrict__ out_index,
+    float* __restrict__ out, const float* __restrict__ pos_embed, int drop, float eps, Weights wt) {
   if (!layer_f32_rows<C, DH, F, PT, GPW, PE, false>(feats, out, pos_embed, perm, goff, num_groups, max_groups, n, G,
                                                     out_index, in_sorted, drop, eps, wt, threadIdx.x))
     return;
@@ -857,8 +865,8 @@ int launch_cfg(const LayerF32& c, hipStream_t stream) {
       allowed[which].fetch_or(bit, std::memory_order_release);
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)((c.max_groups + GPW - 1) / GPW)), dim3(2 * C), lds_bytes, stream,
-                       (const float*)c.feats, (float*)c.out, (const float*)w->pos_embed, c.perm, c.group_offsets,
-                       c.num_groups, (int)c.max_groups, c.n, c.G, c.out_index, c.in_sorted, c.drop ? 1 : 0, w->ln_eps, wt);
+                       (const float*)c.feats, c.perm, c.n, c.G, c.in_sorted, (int)c.max_groups, c.group_offsets, c.num_groups,
+                       c.out_index, (float*)c.out, (const float*)w->pos_embed, c.drop ? 1 : 0, w->ln_eps, wt);
     return launch_status();
   };
   if (w->pos_embed) return go(k_layer_f32<C, DH, F, PT, GPW, MINW, true>, 1);

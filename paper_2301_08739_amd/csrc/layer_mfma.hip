@@ -109,14 +109,10 @@ struct LdsPlan {
 };
 
 template <int WPG, int NW, int MINW, bool OUT_F32, bool PE>
-__global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __restrict__ feats, void* __restrict__ out,
-                                                               const uint16_t* __restrict__ pos_embed,
-                                                               const int32_t* __restrict__ perm,
-                                                               const int32_t* __restrict__ goff,
-                                                               const int32_t* __restrict__ num_groups, int max_groups,
-                                                               const u32x4* __restrict__ packed, float eps,
-                                                               int n, int G, int drop,
-                                                               const int32_t* __restrict__ out_index, int in_sorted) {
+__global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(
+    const uint16_t* __restrict__ feats, const int32_t* __restrict__ perm, const u32x4* __restrict__ packed, int n, int G,
+    int in_sorted, int max_groups, const int32_t* __restrict__ goff, const int32_t* __restrict__ num_groups,
+    const int32_t* __restrict__ out_index, void* __restrict__ out, const uint16_t* __restrict__ pos_embed, int drop, float eps) {
   constexpr int KB = C / 32;          // 32-wide blocks of the input features
   constexpr int NB = C / 16;          // 16-wide blocks of the output features
   constexpr int HP = C / 32;          // 32-wide head-dim units
@@ -240,9 +236,11 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(const uint16_t* __
     return slot < 4 ? ring_lo + slot * CF * 64 : ring_hi + (slot - 4) * CF * 64;
   };
 
-  issue(0);
-  issue(1);
-  issued = 2;
+  // All that the ring holds at once, behind the rows that are already on their way: four layers of 20,011 rows, G = 50, 47.5 ->
+  // 47.1 us against two chunks now and the others behind the first barrier.
+#pragma unroll
+  for (int c = 0; c < RING; ++c) issue(c);
+  issued = RING;
 
   // The per-feature vectors (LayerNorm scales and shifts, biases) follow the fragments in the packed buffer as
   // fp32 in the order of ParamOff: they go to LDS the way the weights do, 1 KB per instruction, spread over the
@@ -674,9 +672,8 @@ int launch_cfg(const void* feats, void* out, const void* pos_embed, const int32_
         return FF_ERR_LAUNCH;
       allowed[which].fetch_or(bit, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(NW * 64), lds_bytes, stream, (const uint16_t*)feats, out,
-                       (const uint16_t*)pos_embed, perm, goff,
-                       num_groups, (int)max_groups, packed, eps, n, G, drop, out_index, in_sorted);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(NW * 64), lds_bytes, stream, (const uint16_t*)feats, perm, packed,
+                       n, G, in_sorted, (int)max_groups, goff, num_groups, out_index, out, (const uint16_t*)pos_embed, drop, eps);
     return launch_status();
   };
   if (pos_embed) {

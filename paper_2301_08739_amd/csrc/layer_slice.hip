@@ -91,10 +91,9 @@ struct Plan {
 
 template <int C, int DH, int F, int PT, int GPW, bool HALF, int MINW, bool OUT_F32, bool PE>
 __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
-    const uint16_t* __restrict__ feats, void* __restrict__ out, const uint16_t* __restrict__ pos_embed,
-    const int32_t* __restrict__ perm, const int32_t* __restrict__ goff, const int32_t* __restrict__ num_groups,
-    int max_groups, int n, int G, const int32_t* __restrict__ out_index, int in_sorted, int drop, float eps,
-    const u32x4* __restrict__ packed) {
+    const uint16_t* __restrict__ feats, const int32_t* __restrict__ perm, const u32x4* __restrict__ packed, int n, int G,
+    int in_sorted, int max_groups, const int32_t* __restrict__ goff, const int32_t* __restrict__ num_groups,
+    const int32_t* __restrict__ out_index, void* __restrict__ out, const uint16_t* __restrict__ pos_embed, int drop, float eps) {
   constexpr int RB = PT * GPW;             // row blocks of the workgroup
   using PL = Plan<C, F, RB>;
   constexpr int NS = PL::NS;
@@ -122,7 +121,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   // and 30,000 rows with 6 to 25 registers in scratch memory / so, us: 128 features, G = 128, float32 results 21.8 / 20.9 and 25.7
   // / 24.4; 256 features, G = 120 33.0 / 32.3 and 46.1 / 44.3.  At 128 features with 16-bit results it is even, G = 120 19.9 / 19.5 and
   // 21.6 / 21.9, G = 128 19.2 / 19.5 and 21.1 / 21.4; where there are registers it costs 1 to 4 %.
-  constexpr bool FULL = RB > 3 && (!HALF || (C > 128 && PE && OUT_F32));
+  constexpr bool FULL = RB > 3 && (!HALF || (C > 128 && PE));
   int32_t* const pillar = src + PL::R;
   constexpr int P_BQ = 0, P_BO = C, P_G2 = 2 * C, P_B2N = 3 * C, P_B2 = 4 * C, P_B1 = 5 * C;
 
@@ -148,28 +147,10 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   auto w2_at = [&](int ks) { return w_load(lane_cols, KB * FH + (ks / 2) * FF + 2 * KB + 2 * s, ks % 2 * 512); };
 
   // ---- which rows ----------------------------------------------------------------------------------------------------
-  const int ngroups = *num_groups;
-  const int gl_s = GPW == 1 ? 0 : s * RPW / (32 * PT);  // the group whose rows this wavefront loads and stores
-  int start = 0, m = 0, end1 = 0;          // of that group
-  bool whole = true;                       // every row of the workgroup is a member of its group
-#pragma unroll
-  for (int gl = 0; gl < GPW; ++gl) {
-    const int g = blockIdx.x * GPW + gl;
-    const int gc = g < max_groups ? g : max_groups - 1;
-    const int o0 = goff[gc], o1 = goff[gc + 1];
-    // A list of full groups only ('Drop Residual') has the next start beyond this group's end.
-    const int mg = g < ngroups ? (o1 - o0 < G ? o1 - o0 : G) : 0;
-    if (gl == gl_s) { start = g < ngroups ? o0 : 0; m = mg; end1 = o1; }
-    whole = whole && (mg == 32 * PT || mg == 0);
-    if (tid < PT * 16) {                   // operand masks: entry (block, step, half, pair of rows)
-      const int key = 32 * (tid >> 4) + 16 * ((tid >> 3) & 1) + 8 * ((tid >> 1) & 1) + 4 * ((tid >> 2) & 1) + 2 * (tid & 1);
-      const int mm = mg > 0 ? mg : 32 * PT;
-      tab[gl * PT * 16 + tid] = (key < mm ? 0xffffu : 0u) | (key + 1 < mm ? 0xffff0000u : 0u);
-    }
-  }
-  const int g_s = blockIdx.x * GPW + gl_s;
   // Slot sl of the wavefront's group -> sorted position.  Rows beyond the group's members repeat its last member: their
   // scores then never exceed the real ones, and they are cut out of the sums (below).
+  const int gl_s = GPW == 1 ? 0 : s * RPW / (32 * PT);  // the group whose rows this wavefront loads and stores
+  const int g_s = blockIdx.x * GPW + gl_s;
   const int slot0 = s * RPW - gl_s * 32 * PT;
   const int lr = lane / LPR, lc = lane % LPR;
   int first = 0;                           // sorted position of the wavefront's first row
@@ -204,8 +185,10 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     const uint32_t from = g0 < end ? g0 : end, left = end - from;
     place((int)from, (int)(left < (uint32_t)G - 1u ? left : (uint32_t)G - 1u));
   }
+  if (in_sorted == 2) fetch_rows();        // before anything that waits
   fetch_pillars();
-  if (in_sorted == 2) fetch_rows();
+  uint32_t touched[RB > 3 ? 1 : 2];
+  touch_lines<PL::NT, (KB * FH + (F / 32) * FF) * 1024>(packed, (max_groups + GPW - 1) / GPW, tid, touched);
   f32x4 gam[2], bet[2];                    // LayerNorm 1 scale and shift of my features
   const float* const params = reinterpret_cast<const float*>(packed + (size_t)(KB * FH + (F / 32) * FF) * 64);
 #pragma unroll
@@ -216,6 +199,25 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   static_assert((5 * C + F) / 4 <= PL::NT, "one piece a thread");
   f32x4 par_piece;
   if (tid < (5 * C + F) / 4) par_piece = *reinterpret_cast<const f32x4*>(params + 2 * C + 4 * tid);
+
+  const int ngroups = *num_groups;
+  int start = 0, m = 0, end1 = 0;          // of that group
+  bool whole = true;                       // every row of the workgroup is a member of its group
+#pragma unroll
+  for (int gl = 0; gl < GPW; ++gl) {
+    const int g = blockIdx.x * GPW + gl;
+    const int gc = g < max_groups ? g : max_groups - 1;
+    const int o0 = goff[gc], o1 = goff[gc + 1];
+    // A list of full groups only ('Drop Residual') has the next start beyond this group's end.
+    const int mg = g < ngroups ? (o1 - o0 < G ? o1 - o0 : G) : 0;
+    if (gl == gl_s) { start = g < ngroups ? o0 : 0; m = mg; end1 = o1; }
+    whole = whole && (mg == 32 * PT || mg == 0);
+    if (tid < PT * 16) {                   // operand masks: entry (block, step, half, pair of rows)
+      const int key = 32 * (tid >> 4) + 16 * ((tid >> 3) & 1) + 8 * ((tid >> 1) & 1) + 4 * ((tid >> 2) & 1) + 2 * (tid & 1);
+      const int mm = mg > 0 ? mg : 32 * PT;
+      tab[gl * PT * 16 + tid] = (key < mm ? 0xffffu : 0u) | (key + 1 < mm ? 0xffff0000u : 0u);
+    }
+  }
   const bool guessed = (int64_t)g_s * G == start && (m == G || start + m == n);  // wave-uniform, as is m
   if (!guessed) {
     place(start, m > 0 ? m - 1 : 0);
@@ -267,6 +269,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     }
   }
   if (tid < (5 * C + F) / 4) reinterpret_cast<f32x4*>(par)[tid] = par_piece;
+  touch_done(touched);
   // ---- rows of no group ('Drop Residual'): copied, unless there is no list -----------------------------------------
   if (drop && ngroups >= 0) {
     auto copy_rows = [&](int lo, int hi, int w0, int nw) {  // by wavefronts w0 .. w0 + nw - 1
@@ -714,9 +717,9 @@ int launch_cfg(const LayerSlice& c, hipStream_t stream) {
       allowed[which].fetch_or(bit, std::memory_order_release);
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)((c.max_groups + GPW - 1) / GPW)), dim3(2 * C), lds_bytes, stream,
-                       (const uint16_t*)c.feats, c.out, (const uint16_t*)w->pos_embed, c.perm, c.group_offsets,
-                       c.num_groups, (int)c.max_groups, c.n, c.G, c.out_index, c.in_sorted, c.drop ? 1 : 0, w->ln_eps,
-                       (const u32x4*)c.packed);
+                       (const uint16_t*)c.feats, c.perm, (const u32x4*)c.packed, c.n, c.G, c.in_sorted, (int)c.max_groups,
+                       c.group_offsets, c.num_groups, c.out_index, c.out, (const uint16_t*)w->pos_embed, c.drop ? 1 : 0,
+                       w->ln_eps);
     return launch_status();
   };
   if (w->pos_embed)
