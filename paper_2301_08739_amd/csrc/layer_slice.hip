@@ -40,6 +40,25 @@ __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(el8, a), __builtin_bit_cast(el8, b), c, 0, 0, 0);
 #endif
 }
+// Products of the last sixteen rows: the sums come out the same bit for bit as from two products of 32 rows and half the inputs
+// (measured on 51,200 sums of 128 terms, bfloat16 and half; with the inputs in another order 20 to 45 % of them differ).
+__device__ __forceinline__ f32x4 mma16(u32x4 a, u32x4 b, f32x4 c) {
+#ifdef FF_LAYER_F16
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(el8, a), __builtin_bit_cast(el8, b), c, 0, 0, 0);
+#else
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(el8, a), __builtin_bit_cast(el8, b), c, 0, 0, 0);
+#endif
+}
+// Of the four rows of 16 lanes: a = a0 a1 a2 a3, b likewise -> a0 b0 a2 b2, a1 b1 a3 b3
+__device__ __forceinline__ void swap_rows(uint32_t& a, uint32_t& b) {
+  auto t = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = t[0]; b = t[1];
+}
+// -> a0 a1 b0 b1, a2 a3 b2 b3
+__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
+  auto t = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = t[0]; b = t[1];
+}
 // v of lane n and of lane n + 32 combined, in every lane
 __device__ __forceinline__ float half_sum(float v) {
   auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -74,11 +93,17 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// Groups of 65 to 80: the last sixteen rows run through the linear layers, LayerNorm 2 and GELU as such, on 16 x 16 x 32 products
+// (a sixth less of all that than as half of a block of 32), and in the layout of a block only through the attention.  The weights
+// of two steps become two tiles of 16 features by eight lane swaps, which ride beside the products of the other rows.  240,000
+// rows, C = 256, G = 69, us a layer: 408 -> 386; 32,117 rows, C = 128, embedding: 24, the same; registers 256 -> 204.  (Groups of
+// 33 to 48 and 97 to 112 stay with half a block: at C = 128 four blocks so, and two with 16-bit results, need scratch memory.)
+constexpr bool tail_of_16(int PT, bool HALF) { return HALF && PT == 3; }
 constexpr int kLdsBytes = 160 * 1024;  // LDS of one compute unit
 
-template <int C, int F, int RB>
+template <int C, int F, int RB, bool TAIL>
 struct Plan {
-  static constexpr int NS = C / 32, NT = 64 * NS, R = 32 * RB;
+  static constexpr int NS = C / 32, NT = 64 * NS, R = 32 * RB - (TAIL ? 16 : 0);
   static constexpr int A = R * C * 2;          // one set of operands: LN1 output, LN2 output, second half of the hidden units;
   static constexpr int B = A;                  // another: attention output, first half of the hidden units, rows on their way out
   static constexpr int STATS = R * NS * 8;
@@ -95,7 +120,9 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     int in_sorted, int max_groups, const int32_t* __restrict__ goff, const int32_t* __restrict__ num_groups,
     const int32_t* __restrict__ out_index, void* __restrict__ out, const uint16_t* __restrict__ pos_embed, int drop, float eps) {
   constexpr int RB = PT * GPW;             // row blocks of the workgroup
-  using PL = Plan<C, F, RB>;
+  constexpr bool TAIL = tail_of_16(PT, HALF);
+  constexpr int NF = TAIL ? RB - 1 : RB;   // row blocks of 32
+  using PL = Plan<C, F, RB, TAIL>;
   constexpr int NS = PL::NS;
   constexpr int KB = C / 32, NB = C / 16;  // 32-wide input blocks, 16-wide output blocks
   constexpr int KS = C / 16;               // steps along C
@@ -103,10 +130,10 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   constexpr int WD = RB <= 3 && MINW <= 2 ? 4 : 3;  // weight operands in flight
   constexpr int NH = 32 / DH;              // heads of a wavefront
   constexpr int LPR = C / 8, RPI = 64 / LPR;  // lanes per row (16 bytes each), rows per load instruction
-  constexpr int NL = 2 * RB;               // load instructions of a wavefront
+  constexpr int NL = PL::R / 16;           // load instructions of a wavefront
   static_assert(DH == 16 || DH == 32, "head dim");
   constexpr int RPW = NL * RPI;            // rows a wavefront loads, normalises and stores: of one group
-  static_assert(RPW * NS == 32 * RB && 32 * PT % RPW == 0, "of one group");
+  static_assert(RPW * NS == PL::R && (GPW == 1 || 32 * PT % RPW == 0), "of one group");
 
   extern __shared__ u32x4 lds[];
   u32x4* const Ab = lds;
@@ -126,6 +153,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   constexpr int P_BQ = 0, P_BO = C, P_G2 = 2 * C, P_B2N = 3 * C, P_B2 = 4 * C, P_B1 = 5 * C;
 
   const int tid = threadIdx.x, lane = tid & 63, nrow = lane & 31, h = lane >> 5;
+  const int trow = lane & 15, tq = lane >> 4;    // of the last sixteen rows: the row, and features 4 tq .. + 3 of each tile of 16
   const int s = __builtin_amdgcn_readfirstlane(tid >> 6);  // slice
 
   // ---- weights: a 32 x 16 operand is one 16-byte piece per lane of two 16 x 32 fragments -----------------------------
@@ -257,6 +285,12 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     for (int j = 0; j < 8; ++j) y[j] = fmaf(fmaf(y[j], sc, sh), gam[j / 4][j % 4], bet[j / 4][j % 4]);
     // features 8 lc .. + 7: eight bytes for each half of step lc & 1 of input block lc / 4
     auto put = [&](u32x4* dst) {
+      if (TAIL && row >= 32 * NF) {        // of the last sixteen: eight bytes each of two runs of four features
+        char* const p = reinterpret_cast<char*>(dst + (NF * KS + (lc >> 2)) * 64 + 32 * (lc & 1) + (row & 15)) + 8 * ((lc >> 1) & 1);
+        *reinterpret_cast<u32x2*>(p) = u32x2{pack2(y[0], y[1]), pack2(y[2], y[3])};
+        *reinterpret_cast<u32x2*>(p + 256) = u32x2{pack2(y[4], y[5]), pack2(y[6], y[7])};
+        return;
+      }
       char* const p = reinterpret_cast<char*>(dst + ((row >> 5) * KS + 2 * (lc >> 2) + (lc & 1)) * 64 + (row & 31)) + 8 * ((lc >> 1) & 1);
       *reinterpret_cast<u32x2*>(p) = u32x2{pack2(y[0], y[1]), pack2(y[2], y[3])};
       *reinterpret_cast<u32x2*>(p + 512) = u32x2{pack2(y[4], y[5]), pack2(y[6], y[7])};
@@ -303,6 +337,14 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     }
     return v;
   };
+  auto vec4 = [&](f32x4 (&v)[2], int off) {  // the same for the last sixteen rows
+#pragma unroll
+    for (int t = 0; t < 2; ++t) v[t] = *reinterpret_cast<const f32x4*>(par + off + 16 * t + 4 * tq);
+  };
+  // Operand of a product over the 32 features of a slice, of the last sixteen rows
+  auto operand16 = [&](const f32x4 (&v)[2]) -> u32x4 {
+    return u32x4{pack2(v[0][0], v[0][1]), pack2(v[0][2], v[0][3]), pack2(v[1][0], v[1][1]), pack2(v[1][2], v[1][3])};
+  };
   // Operand of step k of a product over the 32 features of an accumulator
   auto operand = [&](const f32x16& v, int k) -> u32x4 {
     return u32x4{pack2(v[4 * k], v[4 * k + 1]), pack2(v[4 * k + 2], v[4 * k + 3]),
@@ -314,7 +356,8 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   const u32x4 first_one = {h == 0 ? kOnePair & 0xffffu : 0u, 0u, 0u, 0u};
   auto bias = [&](int off) -> u32x4 { return u32x4{h == 0 ? pack2(par[off + nrow], 0.f) : 0u, 0u, 0u, 0u}; };
 
-  // Steps of a product: N weight operands and RB activation operands (of `rows`) a step.  Weights are requested D - 1 steps
+  // Steps of a product: N weight operands and NF activation operands (of `rows`) a step, handed to `mm`; every second step the
+  // weights of two as tiles of sixteen features, with the operand of the last sixteen rows, to `mt`.  Weights are requested D - 1 steps
   // ahead, the first of them by `ahead`, before the caller's barrier; step k of this product is step `at` + k of whatever
   // `w` and `wf` stand for.  `beside`: work of the vector units for each step.
   auto ahead = [&](auto& w, auto wf) {
@@ -323,24 +366,52 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     for (int d = 0; d < D - 1; ++d) wf(w[d], d);
   };
   auto nothing = [](int) {};
-  auto product = [&](auto& w, auto wf, int at, const u32x4* rows, auto mm, auto beside) {
-    constexpr int D = sizeof(w) / sizeof(w[0]);
+  auto product = [&](auto& w, auto wf, int at, const u32x4* rows, auto mm, auto mt, auto beside) {
+    constexpr int D = sizeof(w) / sizeof(w[0]), N = sizeof(w[0]) / 16;
     const u32x4* const p = rows + lane;
-    constexpr int DA = sizeof(w[0]) == 16 && RB <= 3 ? 3 : 2;
-    u32x4 a[DA][RB];
+    const u32x4* const tail = p + NF * KS * 64;
+    constexpr int DA = N == 1 && RB <= 3 ? 3 : 2;
+    u32x4 a[DA][NF], a16[2];
 #pragma unroll
     for (int d = 0; d < DA - 1; ++d)
 #pragma unroll
-      for (int b = 0; b < RB; ++b) a[d][b] = p[(b * KS + d) * 64];
+      for (int b = 0; b < NF; ++b) a[d][b] = p[(b * KS + d) * 64];
+    if constexpr (TAIL) a16[0] = tail[0];
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
       fence();
+      u32x4 before[N];
+      if constexpr (TAIL) {
+        if (k % 2) {
+#pragma unroll
+          for (int i = 0; i < N; ++i) before[i] = w[(at + k - 1) % D][i];
+          if (k + 1 < KS) a16[(k + 1) / 2 % 2] = tail[(k + 1) / 2 * 64];
+        }
+      }
       wf(w[(at + k + D - 1) % D], at + k + D - 1);
       if (k + DA - 1 < KS) {
 #pragma unroll
-        for (int b = 0; b < RB; ++b) a[(k + DA - 1) % DA][b] = p[(b * KS + k + DA - 1) * 64];
+        for (int b = 0; b < NF; ++b) a[(k + DA - 1) % DA][b] = p[(b * KS + k + DA - 1) * 64];
       }
       mm(w[(at + k) % D], a[k % DA]);
+      if constexpr (TAIL) {
+        if (k % 2) {                       // two steps' weights as two tiles of 16 features x 32 inputs
+          u32x4 t[N][2];
+#pragma unroll
+          for (int i = 0; i < N; ++i) {
+            t[i][0] = before[i];
+            t[i][1] = w[(at + k) % D][i];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              uint32_t lo = t[i][0][j], hi = t[i][1][j];
+              swap_halves(lo, hi);
+              swap_rows(lo, hi);
+              t[i][0][j] = lo; t[i][1][j] = hi;
+            }
+          }
+          mt(t, a16[k / 2 % 2]);
+        }
+      }
       beside(k);
     }
     fence();
@@ -367,64 +438,123 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     if constexpr (JOINT) ahead(w3, kqvf);
     else ahead(w1, vf);
     lds_barrier();
-    f32x16 aq[RB], ak[RB], av[RB];
-    auto start_at = [&](f32x16 (&v)[RB], const f32x16& from) {
+    f32x16 aq[NF], ak[NF], av[NF];
+    f32x4 tq4[2], tk4[2], tv4[2];          // of the last sixteen rows: two tiles of 16 features
+    auto start_at = [&](f32x16 (&v)[NF], f32x4 (&t)[2]) {
 #pragma unroll
-      for (int b = 0; b < RB; ++b) v[b] = from;
+      for (int b = 0; b < NF; ++b) v[b] = kZero;
+      t[0] = t[1] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
-    auto done = [&](u32x4 (&d)[RB][2], f32x16 (&v)[RB]) {
+    auto done = [&](u32x4 (&d)[RB][2], f32x16 (&v)[NF]) {
 #pragma unroll
-      for (int b = 0; b < RB; ++b) halves(d[b], v[b]);
+      for (int b = 0; b < NF; ++b) halves(d[b], v[b]);
+    };
+    // Sixteen rows in the layout of 32: rows 16 .. 31 repeat them (queries, keys) or stay unused (values)
+    auto done16 = [&](u32x4 (&d)[RB][2], const f32x4 (&t)[2], bool values) {
+      if constexpr (TAIL) {
+        uint32_t lo[4], hi[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) lo[j] = pack2(t[j / 2][2 * (j % 2)], t[j / 2][2 * (j % 2) + 1]);
+        if (values) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            hi[j] = lo[2 + j];
+            swap_rows(lo[j], hi[j]);
+            swap_halves(lo[j], hi[j]);
+          }
+          d[RB - 1][0] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+          d[RB - 1][1] = u32x4{0u, 0u, 0u, 0u};
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            hi[j] = lo[j];
+            swap_rows(lo[j], hi[j]);
+            swap_halves(lo[j], hi[j]);
+          }
+#pragma unroll
+          for (int a = 0; a < 2; ++a) d[RB - 1][a] = u32x4{lo[2 * a], lo[2 * a + 1], hi[2 * a], hi[2 * a + 1]};
+        }
+      }
     };
     const u32x4* const qk = PE ? Bb : Ab;
-    start_at(av, kZero);
+    start_at(av, tv4);
     if constexpr (!JOINT) {
-      product(w1, vf, 0, Ab, [&](const u32x4 (&w)[1], const u32x4 (&a)[RB]) {
+      product(w1, vf, 0, Ab, [&](const u32x4 (&w)[1], const u32x4 (&a)[NF]) {
 #pragma unroll
-        for (int b = 0; b < RB; ++b) av[b] = mma(a[b], w[0], av[b]);
+        for (int b = 0; b < NF; ++b) av[b] = mma(a[b], w[0], av[b]);
+      }, [&](const u32x4 (&w)[1][2], u32x4 a) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) tv4[t] = mma16(a, w[0][t], tv4[t]);
       }, nothing);
       if constexpr (PAIR) ahead(w2, kqf);
       else ahead(w1, kf);
       done(V, av);
+      done16(V, tv4, true);
     }
-    start_at(ak, kZero);
+    start_at(ak, tk4);
     {
       const u32x4 bq = bias(P_BQ + 32 * s);
 #pragma unroll
-      for (int b = 0; b < RB; ++b) aq[b] = mma(bq, first_one, kZero);
+      for (int b = 0; b < NF; ++b) aq[b] = mma(bq, first_one, kZero);
+      if constexpr (TAIL) vec4(tq4, P_BQ + 32 * s);
     }
     if constexpr (JOINT) {
-      product(w3, kqvf, 0, Ab, [&](const u32x4 (&w)[3], const u32x4 (&a)[RB]) {
+      product(w3, kqvf, 0, Ab, [&](const u32x4 (&w)[3], const u32x4 (&a)[NF]) {
 #pragma unroll
-        for (int b = 0; b < RB; ++b) {
+        for (int b = 0; b < NF; ++b) {
           ak[b] = mma(w[0], a[b], ak[b]);
           aq[b] = mma(w[1], a[b], aq[b]);
           av[b] = mma(a[b], w[2], av[b]);
         }
+      }, [&](const u32x4 (&w)[3][2], u32x4 a) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          tk4[t] = mma16(w[0][t], a, tk4[t]);
+          tq4[t] = mma16(w[1][t], a, tq4[t]);
+          tv4[t] = mma16(a, w[2][t], tv4[t]);
+        }
       }, nothing);
       done(V, av);
+      done16(V, tv4, true);
     } else if constexpr (PAIR) {
-      product(w2, kqf, 0, qk, [&](const u32x4 (&w)[2], const u32x4 (&a)[RB]) {
+      product(w2, kqf, 0, qk, [&](const u32x4 (&w)[2], const u32x4 (&a)[NF]) {
 #pragma unroll
-        for (int b = 0; b < RB; ++b) {
+        for (int b = 0; b < NF; ++b) {
           ak[b] = mma(w[0], a[b], ak[b]);
           aq[b] = mma(w[1], a[b], aq[b]);
         }
+      }, [&](const u32x4 (&w)[2][2], u32x4 a) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          tk4[t] = mma16(w[0][t], a, tk4[t]);
+          tq4[t] = mma16(w[1][t], a, tq4[t]);
+        }
       }, nothing);
     } else {
-      product(w1, kf, 0, qk, [&](const u32x4 (&w)[1], const u32x4 (&a)[RB]) {
+      auto onto = [&](f32x4 (&v)[2]) {
+        return [&](const u32x4 (&w)[1][2], u32x4 a) {
 #pragma unroll
-        for (int b = 0; b < RB; ++b) ak[b] = mma(w[0], a[b], ak[b]);
-      }, nothing);
+          for (int t = 0; t < 2; ++t) v[t] = mma16(w[0][t], a, v[t]);
+        };
+      };
+      product(w1, kf, 0, qk, [&](const u32x4 (&w)[1], const u32x4 (&a)[NF]) {
+#pragma unroll
+        for (int b = 0; b < NF; ++b) ak[b] = mma(w[0], a[b], ak[b]);
+      }, onto(tk4), nothing);
       ahead(w1, qf);
       done(K, ak);
-      product(w1, qf, 0, qk, [&](const u32x4 (&w)[1], const u32x4 (&a)[RB]) {
+      done16(K, tk4, false);
+      product(w1, qf, 0, qk, [&](const u32x4 (&w)[1], const u32x4 (&a)[NF]) {
 #pragma unroll
-        for (int b = 0; b < RB; ++b) aq[b] = mma(w[0], a[b], aq[b]);
-      }, nothing);
+        for (int b = 0; b < NF; ++b) aq[b] = mma(w[0], a[b], aq[b]);
+      }, onto(tq4), nothing);
     }
     done(Q, aq);
-    if constexpr (JOINT || PAIR) done(K, ak);
+    done16(Q, tq4, false);
+    if constexpr (JOINT || PAIR) {
+      done(K, ak);
+      done16(K, tk4, false);
+    }
     if constexpr (PE) lds_barrier();       // the attention output goes where the embedded rows were
   }
 
@@ -509,19 +639,22 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
             accumulate(kt, S[kt]);
           }
           const float inv = __builtin_amdgcn_rcpf(sum());
-          u32x4* const dst = Bb + (qt * KS + 2 * s) * 64 + lane;
+          const bool last16 = TAIL && qt == NF;
+          u32x4* const dst = Bb + (last16 ? (NF * KS + s) * 64 + 16 * h + trow : (qt * KS + 2 * s) * 64 + lane);
+          const int step = last16 ? 32 : 64;
+          if (last16 && nrow > 15) continue;  // (they repeat the other sixteen)
           if constexpr (DH == 16) {        // the head's eight features: half of the operands of both steps
             float o[8];
 #pragma unroll
             for (int r = 0; r < 8; ++r) o[r] = O[8 * hd + r] * inv;
 #pragma unroll
             for (int k = 0; k < 2; ++k)
-              *reinterpret_cast<u32x2*>(reinterpret_cast<char*>(dst + k * 64) + 8 * hd) =
+              *reinterpret_cast<u32x2*>(reinterpret_cast<char*>(dst + k * step) + 8 * hd) =
                   u32x2{pack2(o[4 * k], o[4 * k + 1]), pack2(o[4 * k + 2], o[4 * k + 3])};
           } else {
             O *= inv;
 #pragma unroll
-            for (int k = 0; k < 2; ++k) dst[k * 64] = operand(O, k);
+            for (int k = 0; k < 2; ++k) dst[k * step] = operand(O, k);
           }
         }
       }
@@ -539,9 +672,9 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   // The rows again, 16 bytes a lane: lane h holds features 16 h + 8 u .. + 7 of the slice, the operand of a product whose other
   // operand is one where the feature is the output's own.  It adds the numbers as they are (1 x), and leaves the vector units
   // out of it.
-  u32x4 again[RB][2], unit[2];
+  u32x4 again[NF][2], unit[2], again16, unit16[2];
 #pragma unroll
-  for (int b = 0; b < RB; ++b)
+  for (int b = 0; b < NF; ++b)
 #pragma unroll
     for (int u = 0; u < 2; ++u)
       again[b][u] = *reinterpret_cast<const u32x4*>(feats + (int64_t)src[32 * b + nrow] * C + 32 * s + 16 * h + 8 * u);
@@ -553,21 +686,40 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
 #pragma unroll
       for (int j = 0; j < 4; ++j) unit[u][j] = (mine >> 1) == 4 * u + j ? one : 0u;
   }
-  f32x16 x1[RB];                           // residual stream of (my 32 features, all rows)
+  if constexpr (TAIL) {                    // (all 32 features of the slice are one step: lane tq holds 8 tq .. + 7)
+    again16 = *reinterpret_cast<const u32x4*>(feats + (int64_t)src[32 * NF + trow] * C + 32 * s + 8 * tq);
+    const uint32_t one = (kOnePair & 0xffffu) << (16 * (trow & 1));
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) unit16[t][j] = 2 * t + (trow >> 3) == tq && ((trow & 7) >> 1) == j ? one : 0u;
+  }
+  f32x16 x1[NF];                           // residual stream of (my 32 features, all rows)
+  f32x4 x16[2];
   {
     const f32x16 bo = vec16(P_BO + 32 * s);
 #pragma unroll
-    for (int b = 0; b < RB; ++b) x1[b] = bo;
+    for (int b = 0; b < NF; ++b) x1[b] = bo;
+    if constexpr (TAIL) vec4(x16, P_BO + 32 * s);
   }
+  auto onto_x1 = [&](const u32x4 (&w)[1], const u32x4 (&a)[NF]) {
+#pragma unroll
+    for (int b = 0; b < NF; ++b) x1[b] = mma(w[0], a[b], x1[b]);
+  };
+  auto onto_x16 = [&](const u32x4 (&w)[1][2], u32x4 a) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) x16[t] = mma16(w[0][t], a, x16[t]);
+  };
   lds_barrier();
-  product(w, wf, 0, Bb, [&](const u32x4 (&w)[1], const u32x4 (&a)[RB]) {
+  product(w, wf, 0, Bb, onto_x1, onto_x16, nothing);
 #pragma unroll
-    for (int b = 0; b < RB; ++b) x1[b] = mma(w[0], a[b], x1[b]);
-  }, nothing);
-#pragma unroll
-  for (int b = 0; b < RB; ++b)
+  for (int b = 0; b < NF; ++b)
 #pragma unroll
     for (int u = 0; u < 2; ++u) x1[b] = mma(unit[u], again[b][u], x1[b]);
+  if constexpr (TAIL) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) x16[t] = mma16(unit16[t], again16, x16[t]);
+  }
   int orow[NL];                            // rows of `out` of my rows
 #pragma unroll
   for (int t = 0; t < NL; ++t) {
@@ -577,35 +729,72 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
 
   // ---- LN2 -> A ------------------------------------------------------------------------------------------------------
   // Sum and sum of squares of a row: every wavefront's 32 features, combined through LDS.
-#pragma unroll
-  for (int b = 0; b < RB; ++b) {
+  auto sums = [&](const f32x16& x) -> f32x2 {  // of this lane's features
     float su4[4], ss4[4];                  // (short chains)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      su4[j] = x1[b][j];
-      ss4[j] = x1[b][j] * x1[b][j];
+      su4[j] = x[j];
+      ss4[j] = x[j] * x[j];
 #pragma unroll
-      for (int e = 1; e < 4; ++e) { su4[j] += x1[b][4 * e + j]; ss4[j] = fmaf(x1[b][4 * e + j], x1[b][4 * e + j], ss4[j]); }
+      for (int e = 1; e < 4; ++e) { su4[j] += x[4 * e + j]; ss4[j] = fmaf(x[4 * e + j], x[4 * e + j], ss4[j]); }
     }
-    const float su = half_sum((su4[0] + su4[1]) + (su4[2] + su4[3]));
-    const float ss = half_sum((ss4[0] + ss4[1]) + (ss4[2] + ss4[3]));
+    return f32x2{(su4[0] + su4[1]) + (su4[2] + su4[3]), (ss4[0] + ss4[1]) + (ss4[2] + ss4[3])};
+  };
+#pragma unroll
+  for (int b = 0; b < NF; ++b) {
+    const f32x2 v = sums(x1[b]);
+    const float su = half_sum(v[0]), ss = half_sum(v[1]);
     if (h == 0) stats[(b * 32 + nrow) * NS + s] = f32x2{su, ss};
+  }
+  if constexpr (TAIL) {                    // (lanes n and n + 32 hold what one lane holds of a whole block: the same sums)
+    f32x16 x;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      uint32_t lo = __float_as_uint(x16[r / 4][r % 4]), hi = lo;
+      swap_halves(lo, hi);
+      x[8 * (r / 4) + r % 4] = __uint_as_float(lo);
+      x[8 * (r / 4) + 4 + r % 4] = __uint_as_float(hi);
+    }
+    const f32x2 v = sums(x);
+    uint32_t s0 = __float_as_uint(v[0]), s1 = s0, q0 = __float_as_uint(v[1]), q1 = q0;
+    swap_rows(s0, s1);
+    swap_rows(q0, q1);
+    if (tq == 0)
+      stats[(NF * 32 + trow) * NS + s] = f32x2{__uint_as_float(s0) + __uint_as_float(s1), __uint_as_float(q0) + __uint_as_float(q1)};
   }
   lds_barrier();
   {
     const f32x16 gm = vec16(P_G2 + 32 * s), bt = vec16(P_B2N + 32 * s);
     const u32x4 b2 = bias(P_B2 + 32 * s);
-#pragma unroll
-    for (int b = 0; b < RB; ++b) {
+    auto scale_shift = [&](int row) -> f32x2 {
       float su = 0.f, ss = 0.f;
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
-        const f32x2 st = stats[(b * 32 + nrow) * NS + k];
+        const f32x2 st = stats[row * NS + k];
         su += st[0];
         ss += st[1];
       }
       const float mu = su * (1.0f / C), var = fmaxf(ss * (1.0f / C) - mu * mu, 0.f);
-      const float sc = rsqrtf(var + eps), sh = -mu * sc;
+      const float sc = rsqrtf(var + eps);
+      return f32x2{sc, -mu * sc};
+    };
+    if constexpr (TAIL) {
+      const f32x2 ssh = scale_shift(NF * 32 + trow);
+      f32x4 z[2], g4[2], b4[2];
+      vec4(g4, P_G2 + 32 * s);
+      vec4(b4, P_B2N + 32 * s);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) z[r / 4][r % 4] = fmaf(fmaf(x16[r / 4][r % 4], ssh[0], ssh[1]), g4[r / 4][r % 4], b4[r / 4][r % 4]);
+      Ab[(NF * KS + s) * 64 + lane] = operand16(z);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        x16[t] = mma16(u32x4{tq == 0 ? pack2(par[P_B2 + 32 * s + 16 * t + trow], 0.f) : 0u, 0u, 0u, 0u},
+                       u32x4{tq == 0 ? kOnePair & 0xffffu : 0u, 0u, 0u, 0u}, x16[t]);
+    }
+#pragma unroll
+    for (int b = 0; b < NF; ++b) {
+      const f32x2 ssh = scale_shift(b * 32 + nrow);
+      const float sc = ssh[0], sh = ssh[1];
       f32x16 z;
 #pragma unroll
       for (int r = 0; r < 16; ++r) z[r] = fmaf(fmaf(x1[b][r], sc, sh), gm[r], bt[r]);
@@ -620,53 +809,67 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   // Two hidden tiles a wavefront: tile t of slice s is unit t NS + s.  GELU of a tile runs beside the products that come
   // after it: those of the second tile, and the first half of the second FFN product.
   {
-    f32x16 acc[2][RB];
-    auto gelu_part = [&](f32x16 (&v)[RB], int k) {  // of step k
-      constexpr int PER = 16 * RB / KS;
+    f32x16 acc[2][NF];
+    f32x4 acc16[2][2];
+    auto gelu_part = [&](int t, int k) {   // of step k
+      constexpr int ALL = 16 * NF + (TAIL ? 8 : 0);
 #pragma unroll
-      for (int i = k * PER; i < (k + 1) * PER; ++i) v[i / 16][i % 16] = gelu2_fast(v[i / 16][i % 16]);
+      for (int i = k * ALL / KS; i < (k + 1) * ALL / KS; ++i) {
+        if (i < 16 * NF) acc[t][i / 16][i % 16] = gelu2_fast(acc[t][i / 16][i % 16]);
+        else acc16[t][(i - 16 * NF) / 4][i % 4] = gelu2_fast(acc16[t][(i - 16 * NF) / 4][i % 4]);
+      }
     };
-    auto put_hidden = [&](f32x16 (&v)[RB], u32x4* to) {
+    auto put_hidden = [&](int t, u32x4* to) {
 #pragma unroll
-      for (int b = 0; b < RB; ++b)
+      for (int b = 0; b < NF; ++b)
 #pragma unroll
-        for (int k = 0; k < 2; ++k) to[(b * KS + 2 * s + k) * 64 + lane] = operand(v[b], k);
+        for (int k = 0; k < 2; ++k) to[(b * KS + 2 * s + k) * 64 + lane] = operand(acc[t][b], k);
+      if constexpr (TAIL) to[(NF * KS + s) * 64 + lane] = operand16(acc16[t]);
     };
     auto first = [&](int t) {
       const u32x4 b1 = bias(P_B1 + 32 * (t * NS + s));
 #pragma unroll
-      for (int b = 0; b < RB; ++b) acc[t][b] = mma(b1, first_one, kZero);
-      return [&, t](const u32x4 (&w)[1], const u32x4 (&a)[RB]) {
+      for (int b = 0; b < NF; ++b) acc[t][b] = mma(b1, first_one, kZero);
+      if constexpr (TAIL) vec4(acc16[t], P_B1 + 32 * (t * NS + s));
+      return [&, t](const u32x4 (&w)[1], const u32x4 (&a)[NF]) {
 #pragma unroll
-        for (int b = 0; b < RB; ++b) acc[t][b] = mma(w[0], a[b], acc[t][b]);
+        for (int b = 0; b < NF; ++b) acc[t][b] = mma(w[0], a[b], acc[t][b]);
       };
     };
-    auto second_product = [&](const u32x4 (&w)[1], const u32x4 (&a)[RB]) {
+    auto first16 = [&](int t) {
+      return [&, t](const u32x4 (&w)[1][2], u32x4 a) {
 #pragma unroll
-      for (int b = 0; b < RB; ++b) x1[b] = mma(w[0], a[b], x1[b]);
+        for (int e = 0; e < 2; ++e) acc16[t][e] = mma16(w[0][e], a, acc16[t][e]);
+      };
     };
-    product(w, wf, KS, Ab, first(0), nothing);
+    product(w, wf, KS, Ab, first(0), first16(0), nothing);
     if constexpr (RB <= 3) {
-      product(w, wf, 2 * KS, Ab, first(1), [&](int k) { gelu_part(acc[0], k); });
-      put_hidden(acc[0], Bb);
+      product(w, wf, 2 * KS, Ab, first(1), first16(1), [&](int k) { gelu_part(0, k); });
+      put_hidden(0, Bb);
     } else {                               // (no registers for two tiles)
 #pragma unroll
-      for (int k = 0; k < KS; ++k) gelu_part(acc[0], k);
-      put_hidden(acc[0], Bb);
-      product(w, wf, 2 * KS, Ab, first(1), nothing);
+      for (int k = 0; k < KS; ++k) gelu_part(0, k);
+      put_hidden(0, Bb);
+      product(w, wf, 2 * KS, Ab, first(1), first16(1), nothing);
     }
     lds_barrier();
-    product(w, wf, 3 * KS, Bb, second_product, [&](int k) { gelu_part(acc[1], k); });
-    put_hidden(acc[1], Ab);
+    product(w, wf, 3 * KS, Bb, onto_x1, onto_x16, [&](int k) { gelu_part(1, k); });
+    put_hidden(1, Ab);
     lds_barrier();
-    product(w, wf, 4 * KS, Ab, second_product, nothing);
+    product(w, wf, 4 * KS, Ab, onto_x1, onto_x16, nothing);
   }
 
   // ---- scatter -------------------------------------------------------------------------------------------------------
   u32x4* const Out = Bb;
   if constexpr (!OUT_F32) {                // whole rows through LDS
+    if constexpr (TAIL) {
 #pragma unroll
-    for (int b = 0; b < RB; ++b)
+      for (int t = 0; t < 2; ++t)
+        *reinterpret_cast<u32x2*>(reinterpret_cast<char*>(Out + (32 * NF + trow) * LPR + ((4 * s + 2 * t + (tq >> 1)) ^ trow)) + 8 * (tq & 1)) =
+            u32x2{pack2(x16[t][0], x16[t][1]), pack2(x16[t][2], x16[t][3])};
+    }
+#pragma unroll
+    for (int b = 0; b < NF; ++b)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         *reinterpret_cast<u32x2*>(reinterpret_cast<char*>(Out + (32 * b + nrow) * LPR + ((4 * s + e) ^ (nrow & 15))) + 8 * h) =
@@ -686,8 +889,14 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
       for (int t = 0; t < NL; ++t) rowof[s * RPW + t * RPI + lr_out] = slot0 + t * RPI + lr_out < m ? orow[t] : -1;
     }
     lds_barrier();
+    if constexpr (TAIL) {
+      const int o = rowof[32 * NF + trow];
 #pragma unroll
-    for (int b = 0; b < RB; ++b) {
+      for (int t = 0; t < 2; ++t)
+        if (o >= 0) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out) + (size_t)o * C + 32 * s + 16 * t + 4 * tq) = x16[t];
+    }
+#pragma unroll
+    for (int b = 0; b < NF; ++b) {
       const int o = rowof[32 * b + nrow];
       if (o >= 0) {
 #pragma unroll
@@ -701,7 +910,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
 
 template <int C, int DH, int F, int PT, int GPW, bool HALF, int MINW>
 int launch_cfg(const LayerSlice& c, hipStream_t stream) {
-  constexpr int lds_bytes = Plan<C, F, PT * GPW>::TOTAL;
+  constexpr int lds_bytes = Plan<C, F, PT * GPW, tail_of_16(PT, HALF)>::TOTAL;
   static_assert(lds_bytes <= kLdsBytes, "LDS");
   const ff_layer_weights* w = c.w;
   // The dynamic LDS size has to be allowed once per kernel and device.

@@ -98,3 +98,27 @@ def test_infinite_output_biases(C, G, dt):
     others = np.delete(np.arange(C), [3, C - 7])
     assert np.array_equal(got[:, others], want[:, others])
     assert np.array_equal(np.isposinf(got), np.isposinf(run(p, ff.FF_FLAG_FORCE_GENERIC)))
+
+
+@pytest.mark.parametrize("dt", [ff.FF_BF16, ff.FF_F16])
+@pytest.mark.parametrize("C,whole", [(128, 4), (256, 6)])
+@pytest.mark.parametrize("G", [65, 66, 72, 79, 80])
+def test_last_sixteen_rows(C, whole, G, dt):
+    """Groups of 65 to 80: the last sixteen rows on products of their own give the bits of whole blocks of 32, in full groups, a
+    last group of any length (rows below, across and in the last sixteen), with infinite biases and with an embedding."""
+    rng = np.random.default_rng(C + G)
+    p = dict(ffsynth.layer_params(C, 2 * C, HEADS[C], seed=43))
+    q = {k: np.array(p[k], np.float32) for k in ("b1", "b2")}
+    q["b1"][[1, C + 17]], q["b2"][[2, C - 9]] = np.inf, (np.inf, -np.inf)
+    for last in (1, 63, 64, 65, G):
+        n = 3 * G + last
+        x, e = (to_dev_feats(rng.standard_normal((n, C)), dt) for _ in range(2))
+        dev = [torch.from_numpy(a).to(DEV) for a in (rng.permutation(n).astype(np.int32),
+                                                     np.array([0, G, 2 * G, 3 * G, n], np.int32), np.array([4], np.int32))]
+        for params in (p, dict(p, **q)):
+            lw = ff.LayerWeights(params, dt, DEV)
+            for embed in (None, e):
+                for fl in (0, ff.FF_FLAG_OUT_F32):
+                    got, want = (ff.ff_group_attention(x, *dev, 4, lw, G, dt, fl | ff.FF_FLAG_VARIANT(v), pos_embed=embed)
+                                 for v in (0, whole))
+                    assert torch.equal(got.view(torch.int32 if fl else torch.int16), want.view(torch.int32 if fl else torch.int16))
