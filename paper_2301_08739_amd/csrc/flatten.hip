@@ -792,18 +792,18 @@ __device__ __forceinline__ void direct_sort(uint32_t* a, uint32_t T) {
 }
 
 template <bool Z, bool FRAMES>
-__global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __restrict__ coords, int n, int S, Batch bt,
-                                                               DirectBatch db, int G, int drop, PackJob pack) {
+__global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __restrict__ coords, int n, int S, int parts,
+                                                               uint32_t range, int G, int drop, Batch bt, DirectBatch db,
+                                                               PackJob pack) {
   constexpr int STRIDE = Z ? 4 : 3, ROWS = 4;  // rows of a thread in a round; the next round's are on their way meanwhile
   constexpr int ROUND = kDirectThreads * ROWS;
   __shared__ uint32_t wave_totals[kDirectWaves], starts[kDirectMaxFrames], crowd_start[kDirectCrowds];
   __shared__ uint32_t taken, below, full;
   extern __shared__ uint32_t bits[];                            // [range / 32]
-  uint32_t* const first = bits + db.range / 32;                 // [range / 32] position of a word's first pillar
-  uint32_t* const joined = first + db.range / 32;               // [kDirectShared], or with the next kDirectMaxRows: pillars by word
+  uint32_t* const first = bits + range / 32;                    // [range / 32] position of a word's first pillar
+  uint32_t* const joined = first + range / 32;                  // [kDirectShared], or with the next kDirectMaxRows: pillars by word
   uint32_t* const list = joined + kDirectShared;                // [kDirectList] those of each wavefront: (key - lo) << idx_bits | index
   const int tid = threadIdx.x, lane = tid & 63;
-  const int parts = db.parts;
   if ((int)blockIdx.x >= S * (parts + 1)) {
     pack_tail(pack, ((int)blockIdx.x - S * (parts + 1)) * (kDirectThreads / 256) + (tid >> 8), tid & 255);
     return;
@@ -819,9 +819,9 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
   const int idx_bits = bt.kp[s].idx_bits;
   const uint32_t idx_mask = (1u << idx_bits) - 1u;
   const uint32_t last_frame = (uint32_t)bt.kp[s].B - 1u, end = 1u << bt.kp[s].key_bits;
-  const uint32_t lo = (uint32_t)part * db.range;
+  const uint32_t lo = (uint32_t)part * range;
   if (lo >= end) return;
-  const uint32_t hi = end - lo < db.range ? end : lo + db.range;
+  const uint32_t hi = end - lo < range ? end : lo + range;
   int32_t* __restrict__ const perm_s = bt.perm[s];
   int32_t* __restrict__ const inv_s = bt.inv_perm[s];
   uint64_t* __restrict__ const keys_s = bt.keys_sorted[s];
@@ -847,15 +847,15 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
   const int wave = tid >> 6;
   uint32_t* const mine = list + wave * kDirectOwn;
   const uint32_t len = hi - lo, words = (len + 31u) >> 5;
-  for (uint32_t w = tid; w < words; w += kDirectThreads) bits[w] = 0u;
-  if (tid == 0) { taken = 0u; below = 0u; full = 0u; }
-  __syncthreads();
   uint32_t less = 0, count = 0;              // count: of the wavefront
   {
     Row r[2][ROWS];
     int begin = 0;
     asm volatile("" : "+s"(begin));            // (or the addresses of the first round would be kept through everything that follows)
     fetch(r[0], begin);
+    for (uint32_t w = tid; w < words; w += kDirectThreads) bits[w] = 0u;
+    if (tid == 0) { taken = 0u; below = 0u; full = 0u; }
+    __syncthreads();
     auto look = [&](Row (&now)[ROWS], int i0, auto whole) {
 #pragma unroll
       for (int u = 0; u < ROWS; ++u) {
@@ -1103,37 +1103,43 @@ static_assert(kSplitWaves << kSplitDigits == kSplitList && 1 << kSplitDigits <= 
 struct SplitSort { DirectKeys k; int32_t code_bits, in_frame, skip, per_frame; };
 struct SplitBatch { SplitSort s[kMaxSorts]; int32_t bins, bin_bits, tiles; };
 
+// (What the first loads need comes first: it is in registers when a wavefront starts.)
 template <bool Z, bool FRAMES, int OWN>
-__global__ __launch_bounds__(kSplitThreads) void k_split(const int32_t* __restrict__ coords, int n, int S, SplitBatch sb,
-                                                          uint32_t* __restrict__ entries_all, uint32_t* __restrict__ table_all,
-                                                          int frames, PackJob pack) {
+__global__ __launch_bounds__(kSplitThreads) void k_split(const int32_t* __restrict__ coords, int n, int S, int tiles, int bins,
+                                                          int bin_bits, int frames, uint32_t* __restrict__ entries_all,
+                                                          uint32_t* __restrict__ table_all, SplitBatch sb, PackJob pack) {
   constexpr int STRIDE = Z ? 4 : 3, TILE = kSplitThreads * OWN;
   extern __shared__ uint32_t words[];        // [kSplitWaves][bins / 2]: counts of two buckets; then the tile, sorted
   __shared__ uint32_t wave_totals[kSplitWaves];
-  const int tid = threadIdx.x, lane = tid & 63, half = sb.bins >> 1;
-  if ((int)blockIdx.x >= S * sb.tiles) {
-    pack_tail(pack, ((int)blockIdx.x - S * sb.tiles) * (kSplitThreads / 256) + (tid >> 8), tid & 255);
+  const int tid = threadIdx.x, lane = tid & 63, half = bins >> 1;
+  if ((int)blockIdx.x >= S * tiles) {
+    pack_tail(pack, ((int)blockIdx.x - S * tiles) * (kSplitThreads / 256) + (tid >> 8), tid & 255);
     return;
   }
   const int s = blockIdx.x % S, tile = blockIdx.x / S, tile0 = tile * TILE, local0 = (tid >> 6) * 64 * OWN + lane;
+  struct Row { int32_t c[STRIDE]; };
+  Row r[OWN];
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) {
+    const int i = tile0 + local0 + u * 64;
+    r[u] = *reinterpret_cast<const Row*>(coords + (int64_t)(i < n ? i : n - 1) * STRIDE);
+  }
   const DirectKeys dk = sb.s[s].k;
   const int code_bits = sb.s[s].code_bits, in_frame = sb.s[s].in_frame;
-  const uint32_t skip = (uint32_t)sb.s[s].skip, none = (uint32_t)sb.bins - 1u, last_frame = (uint32_t)frames - 1u;
+  const uint32_t skip = (uint32_t)sb.s[s].skip, none = (uint32_t)bins - 1u, last_frame = (uint32_t)frames - 1u;
   uint16_t* const mine = reinterpret_cast<uint16_t*>(words + (tid >> 6) * half);
   for (int w = tid; w < kSplitWaves * half; w += kSplitThreads) words[w] = 0u;
-  struct Row { int32_t c[STRIDE]; };
   uint32_t entry[OWN], at[OWN];              // at: bucket << 16 | rank, then the position
 #pragma unroll
   for (int u = 0; u < OWN; ++u) {
     const int i = tile0 + local0 + u * 64;
-    const Row r = *reinterpret_cast<const Row*>(coords + (int64_t)(i < n ? i : n - 1) * STRIDE);
-    const uint32_t key = direct_key<Z, FRAMES>(r.c, dk, last_frame), h = key >> code_bits;
+    const uint32_t key = direct_key<Z, FRAMES>(r[u].c, dk, last_frame), h = key >> code_bits;
     at[u] = i < n ? h - __umul24(h >> in_frame, skip) : none;
     entry[u] = (key & ((1u << code_bits) - 1u)) << kSplitLocalBits | (uint32_t)(local0 + u * 64);
   }
   __syncthreads();
 #pragma unroll
-  for (int u = 0; u < OWN; ++u) at[u] = at[u] << 16 | rank_in_wave(mine, at[u], sb.bin_bits, true);
+  for (int u = 0; u < OWN; ++u) at[u] = at[u] << 16 | rank_in_wave(mine, at[u], bin_bits, true);
   __syncthreads();
   constexpr int PER = (kSplitMaxBuckets + 2) / 2 / kSplitThreads + 1;  // words of a thread
   const int per = (half + kSplitThreads - 1) / kSplitThreads, w0 = tid * per;
@@ -1144,7 +1150,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_split(const int32_t* __restri
     sum += (total[q] & 0xffffu) + (total[q] >> 16);
   }
   uint32_t first = block_exclusive_scan<kSplitThreads>(sum, wave_totals, nullptr);
-  uint32_t* const table = table_all + ((int64_t)s * sb.tiles + tile) * half;
+  uint32_t* const table = table_all + ((int64_t)s * tiles + tile) * half;
 #pragma unroll
   for (int q = 0; q < PER; ++q)
     if (q < per && w0 + q < half) {
@@ -1203,45 +1209,41 @@ __device__ __forceinline__ void split_groups(const uint16_t* __restrict__ table,
     for (uint32_t k = l; k < groups[b + 1] - groups[b]; k += 16) goff[groups[b] + k] = (int32_t)(starts[b] + k * (uint32_t)G);
 }
 
-__global__ __launch_bounds__(kSplitThreads, 6) void k_buckets(int n, int S, Batch bt, SplitBatch sb, int tile_rows,
-                                                            const uint32_t* __restrict__ entries_all,
-                                                            const uint16_t* __restrict__ table_all, uint32_t* scratch,
-                                                            int G, int drop) {
+// end0 .. end3: buckets of the first sort, of the first two, ..
+__global__ __launch_bounds__(kSplitThreads, 6) void k_buckets(const uint16_t* __restrict__ table_all, int n, int S, int tiles, int bins,
+                                                            int tile_rows, int end0, int end1, int end2, int end3,
+                                                            const uint32_t* __restrict__ entries_all, uint32_t* scratch, int G,
+                                                            int drop, Batch bt, SplitBatch sb) {
   extern __shared__ uint32_t list[];                       // [kSplitList] key value << 12 | position in the bucket; counters
   uint32_t* const cum = list + kSplitList;                 // [kSplitMaxTiles + 1] the bucket's pillars in the tiles before,
   uint32_t* const from = cum + kSplitMaxTiles + 1;         // [kSplitMaxTiles] and where those of a tile are, less that
   uint32_t* const bits = from + kSplitMaxTiles;            // [words]
-  __shared__ uint32_t wave_totals[kSplitWaves];
+  __shared__ uint32_t wave_totals[2 * kSplitWaves];
   __shared__ uint32_t crowded;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tiles = sb.tiles;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if ((int)blockIdx.x < S) {
     const int s = blockIdx.x;
-    split_groups(table_all + (int64_t)s * tiles * sb.bins, tiles, sb.bins, sb.s[s].per_frame, n, bt.kp[s].B, G, drop,
+    split_groups(table_all + (int64_t)s * tiles * bins, tiles, bins, sb.s[s].per_frame, n, bt.kp[s].B, G, drop,
                  bt.group_offsets[s], bt.num_groups[s], list, list + kSplitMaxBuckets + 1, wave_totals);
     return;
   }
   // Neighbouring buckets go to the same die, whose cache then has the lines that they share.
-  const int id = blockIdx.x - S, each = ((int)gridDim.x - S) >> 3, nth = (id & 7) * each + (id >> 3);
-  int s = 0, bucket = nth;
-  for (; s < S; ++s) {
-    const int count = bt.kp[s].B * sb.s[s].per_frame;
-    if (bucket < count) break;
-    bucket -= count;
+  const int id = blockIdx.x - S, each = (end3 + 7) >> 3, nth = (id & 7) * each + (id >> 3);
+  if (nth >= end3) return;
+  const int s = (nth >= end0 ? 1 : 0) + (nth >= end1 ? 1 : 0) + (nth >= end2 ? 1 : 0);
+  const int bucket = nth - (s == 0 ? 0 : s == 1 ? end0 : s == 2 ? end1 : end2);
+  const uint16_t* __restrict__ const table = table_all + (int64_t)s * tiles * bins;
+  uint32_t lo = 0, hi = 0, T, base;
+  if (tid < tiles) {
+    lo = table[(int64_t)tid * bins + bucket];
+    hi = table[(int64_t)tid * bins + bucket + 1];
   }
-  if (s >= S) return;
   const KeyParams kp = bt.kp[s];
   const int code_bits = sb.s[s].code_bits, words = 1 << (code_bits - 5);
   uint32_t* const first = bits + words;                    // [words] position of a word's first pillar
   const uint32_t* __restrict__ const entries = entries_all + (int64_t)s * n;
-  const uint16_t* __restrict__ const table = table_all + (int64_t)s * tiles * sb.bins;
-  uint32_t lo = 0, hi = 0, T, base;
-  if (tid < tiles) {
-    lo = table[(int64_t)tid * sb.bins + bucket];
-    hi = table[(int64_t)tid * sb.bins + bucket + 1];
-  }
   for (int w = tid; w < words; w += kSplitThreads) bits[w] = 0u;
-  const uint32_t before = block_exclusive_scan<kSplitThreads>(hi - lo, wave_totals, &T);
-  block_exclusive_scan<kSplitThreads>(lo, wave_totals, &base);
+  const uint32_t before = block_exclusive_scan_and_sum<kSplitThreads>(hi - lo, lo, wave_totals, &T, &base);
   if (T == 0u) return;
   cum[tid] = tid < tiles ? before : T;                     // (kSplitThreads == kSplitMaxTiles)
   from[tid] = (uint32_t)tid * (uint32_t)tile_rows + lo - before;
@@ -1275,7 +1277,7 @@ __global__ __launch_bounds__(kSplitThreads, 6) void k_buckets(int n, int S, Batc
     for (uint32_t step = kSplitMaxTiles / 2; step > 0; step >>= 1)
 #pragma unroll
       for (int u = 0; u < kSplitOwn; ++u)
-        if (e0 + u * kSplitThreads < T) tile[u] += cum[tile[u] + step] <= nth_of(e0, u) ? step : 0u;
+        if ((int)step < tiles && e0 + u * kSplitThreads < T) tile[u] += cum[tile[u] + step] <= nth_of(e0, u) ? step : 0u;
 #pragma unroll
     for (int u = 0; u < kSplitOwn; ++u)
       if (e0 + u * kSplitThreads < T) index[u] = entries[from[tile[u]] + nth_of(e0, u)];
@@ -1724,7 +1726,8 @@ static int flatten_launch_impl(const int32_t* coords, const PointCells* pts, int
           return FF_ERR_LAUNCH;
         allowed[which].fetch_or(bit, std::memory_order_release);
       }
-      hipLaunchKernelGGL(kern, dim3(blocks), dim3(kDirectThreads), lds, stream, coords, (int)n, num_sorts, bt, db, G, drop, job);
+      hipLaunchKernelGGL(kern, dim3(blocks), dim3(kDirectThreads), lds, stream, coords, (int)n, num_sorts, db.parts, db.range, G,
+                         drop, bt, db, job);
       return launch_status();
     };
     if (g->num_frames > 1) return z ? go(k_direct<true, true>, 3) : go(k_direct<false, true>, 2);
@@ -1742,19 +1745,23 @@ static int flatten_launch_impl(const int32_t* coords, const PointCells* pts, int
     uint32_t* table = entries + (int64_t)num_sorts * n;
     const unsigned blocks = (unsigned)(num_sorts * sb.tiles + ceil_div((int64_t)job.layers * job.blocks, kSplitThreads / 256));
     const size_t counters = (size_t)kSplitWaves * sb.bins * 2, stage = (size_t)tile_rows * 4;
-    int64_t buckets = 0;
+    int64_t buckets = 0, ends[kMaxSorts];
     int words = 0;
+    for (int s = 0; s < kMaxSorts; ++s) {
+      if (s < num_sorts) buckets += (int64_t)sb.s[s].per_frame * bt.kp[s].B;
+      ends[s] = buckets;
+    }
     for (int s = 0; s < num_sorts; ++s) {
-      buckets += (int64_t)sb.s[s].per_frame * bt.kp[s].B;
       if (1 << (sb.s[s].code_bits - 5) > words) words = 1 << (sb.s[s].code_bits - 5);
     }
     // (bits and first of a bucket; the places of a list's entries, which take the same memory; the group list's tables)
     size_t lds = (size_t)(kSplitList + 2 * kSplitMaxTiles + 1) * 4 + (size_t)(2 * words > kSplitList ? 2 * words : kSplitList) * 4;
     auto go = [&](auto split) {
       hipLaunchKernelGGL(split, dim3(blocks), dim3(kSplitThreads), counters > stage ? counters : stage, stream, coords, (int)n,
-                         num_sorts, sb, entries, table, (int)g->num_frames, job);
-      hipLaunchKernelGGL(k_buckets, dim3((unsigned)(num_sorts + 8 * ceil_div(buckets, 8))), dim3(kSplitThreads), lds, stream, (int)n,
-                         num_sorts, bt, sb, tile_rows, entries, (const uint16_t*)table, (uint32_t*)buf[1], G, drop);
+                         num_sorts, sb.tiles, sb.bins, sb.bin_bits, (int)g->num_frames, entries, table, sb, job);
+      hipLaunchKernelGGL(k_buckets, dim3((unsigned)(num_sorts + 8 * ceil_div(buckets, 8))), dim3(kSplitThreads), lds, stream,
+                         (const uint16_t*)table, (int)n, num_sorts, sb.tiles, sb.bins, tile_rows, (int)ends[0], (int)ends[1],
+                         (int)ends[2], (int)ends[3], entries, (uint32_t*)buf[1], G, drop, bt, sb);
       return launch_status();
     };
     auto go_z = [&](auto Z, auto frames) {

@@ -163,6 +163,11 @@ __global__ __launch_bounds__(256) void k_seg_starts(const uint64_t* __restrict__
   }
 }
 
+// v of the lane D further in its row of sixteen
+template <int D> __device__ __forceinline__ float row_turned(float v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x120 + D, 0xf, 0xf, false));
+}
+
 // Sixteen lanes per pillar: lane l adds the points l, l + 16, ... of the pillar's run lo .. hi of perm in float32, the
 // sixteen partial sums are combined in a fixed tree, so the result does not depend on timing.  vec4: rows of four features
 // in one 16-byte load.
@@ -173,11 +178,13 @@ __device__ __forceinline__ void pillar_mean(int64_t pid, int lo, int hi, const i
   const float inv = 1.0f / (float)(hi - lo);
   for (int c0 = 0; c0 < Cp; c0 += 4) {  // four features at a time
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    auto add = [&](int q, auto in_flight) {  // points q, q + 16, .. of the pillar, their loads in flight together
+    auto points = [&](int q, auto in_flight, int32_t (&src)[kPointsInFlight]) {  // q, q + 16, .. of the pillar, -1: none
       constexpr int U = decltype(in_flight)::value;
-      int32_t src[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) src[u] = q + 16 * u < hi ? perm[q + 16 * u] : -1;
+    };
+    auto add = [&](const int32_t (&src)[kPointsInFlight], auto in_flight) {  // their loads in flight together
+      constexpr int U = decltype(in_flight)::value;
       if (point_to_pillar && c0 == 0) {  // the point indices are at hand here (Cp >= 1: this round always runs)
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -210,15 +217,28 @@ __device__ __forceinline__ void pillar_mean(int64_t pid, int lo, int hi, const i
     // eight rounds for all / each pillar its own way / this: 180,000 points of 3, 4, 5 and 8 features 62 / 63 / 57, 60 /
     // 53 / 53, 71 / 74 / 67, 67 / 60 / 60; 1.44 M of 3 and 5 155 / 157 / 148 and 191 / 187 / 177; 60,000 of 5 50 / 52 / 51.
     // The same bits.
+    constexpr auto one = std::integral_constant<int, 1>();
+    constexpr auto many = std::integral_constant<int, kPointsInFlight>();
+    int32_t src[kPointsInFlight];
     if (!__builtin_amdgcn_ballot_w64(hi - lo > 16)) {
-      if (lo + sub < hi) add(lo + sub, std::integral_constant<int, 1>());
-    } else {
-      for (int q = lo + sub; q < hi; q += 16 * kPointsInFlight) add(q, std::integral_constant<int, kPointsInFlight>());
+      if (lo + sub < hi) {
+        points(lo + sub, one, src);
+        add(src, one);
+      }
+    } else {                             // (the next round's points are fetched beside this one's features)
+      points(lo + sub, many, src);
+      for (int q = lo + sub; q < hi; q += 16 * kPointsInFlight) {
+        int32_t next[kPointsInFlight];
+        points(q + 16 * kPointsInFlight, many, next);
+        add(src, many);
+#pragma unroll
+        for (int u = 0; u < kPointsInFlight; ++u) src[u] = next[u];
+      }
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
 #pragma unroll
-      for (int d = 8; d >= 1; d >>= 1) acc[j] += __shfl_xor(acc[j], d, 16);
+      for (int d = 0; d < 4; ++d) acc[j] += d == 0 ? row_turned<8>(acc[j]) : d == 1 ? row_turned<4>(acc[j]) : d == 2 ? row_turned<2>(acc[j]) : row_turned<1>(acc[j]);
       if (sub == 0 && c0 + j < Cp) feats[pid * Cp + c0 + j] = acc[j] * inv;
     }
   }
@@ -324,15 +344,14 @@ __global__ __launch_bounds__(kVoxOrderThreads) void k_vox_order(const uint32_t* 
   uint32_t* const place = words + kVoxOrderWaves * CELLS / 2;   // [CELLS] where the cell's next point goes
   uint32_t* const cum = place + CELLS;                     // [kVoxMaxTiles + 1] the range's points in the tiles before,
   uint32_t* const from = cum + kVoxMaxTiles + 1;           // [kVoxMaxTiles] and where those of a tile are
-  __shared__ uint32_t wave_totals[kVoxOrderWaves];
+  __shared__ uint32_t wave_totals[2 * kVoxOrderWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, range = blockIdx.x;
   uint32_t s = 0, e = 0, T, base;
   if (tid < tiles) {
     s = table[(size_t)tid * bins + range];
     e = table[(size_t)tid * bins + range + 1];
   }
-  const uint32_t before = block_exclusive_scan<kVoxOrderThreads>(e - s, wave_totals, &T);
-  block_exclusive_scan<kVoxOrderThreads>(s, wave_totals, &base);
+  const uint32_t before = block_exclusive_scan_and_sum<kVoxOrderThreads>(e - s, s, wave_totals, &T, &base);
   if (tid == 0) {
     range_end[range] = base + T;
     if (T == 0u) range_pillars[range] = 0u;
@@ -444,9 +463,11 @@ __global__ __launch_bounds__(kVoxOrderThreads) void k_vox_order(const uint32_t* 
       c1 = place[2 * tid + 1];
     }
   }
-  uint32_t np;
-  const uint32_t pos = block_exclusive_scan<kVoxOrderThreads>(c0 + c1, wave_totals, nullptr);
-  uint32_t pillar = block_exclusive_scan<kVoxOrderThreads>((c0 ? 1u : 0u) + (c1 ? 1u : 0u), wave_totals, &np);
+  uint32_t np;                               // points and pillars in one scan
+  const uint32_t both = block_exclusive_scan<kVoxOrderThreads>((c0 + c1) | ((c0 ? 1u : 0u) + (c1 ? 1u : 0u)) << kVoxIndexBits, wave_totals, &np);
+  const uint32_t pos = both & ((1u << kVoxIndexBits) - 1u);
+  uint32_t pillar = both >> kVoxIndexBits;
+  np >>= kVoxIndexBits;
   if (tid < CELLS / 2) {
     place[2 * tid] = pos;
     place[2 * tid + 1] = pos + c0;
@@ -493,8 +514,7 @@ __global__ __launch_bounds__(256) void k_vox_mean(const int32_t* __restrict__ or
   if (part * 16 >= np && (range != ranges - 1 || part > 0)) return;
 #pragma unroll
   for (int u = 0; u < LOOKS; ++u) front += look[u];
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) front += __shfl_xor(front, d, 64);
+  front = wave_sum(front);
   if ((tid & 63) == 0) sums[tid >> 6] = front;
   __syncthreads();
   front = sums[0] + sums[1] + sums[2] + sums[3];
