@@ -67,7 +67,7 @@ class LayerWeights:
             return self
         buf = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.tensors["w_o"].device)
         ptr = (buf.data_ptr() + 255) // 256 * 256
-        _check(lib.ff_pack_weights(C.byref(s), self.dtype, C.c_void_p(ptr), _stream()), "ff_pack_weights")
+        _check(lib.ff_pack_weights(C.byref(s), self.dtype, ptr, _stream()), "ff_pack_weights")
         self._packed_buf, self.packed = buf, ptr
         return self
 
@@ -160,11 +160,12 @@ def _check(st, what):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device as a number (0.3 us; a Stream object on the way to it 3.3)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return C.c_void_p(0 if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _workspace(nbytes, device):
@@ -184,6 +185,8 @@ def _group_lists(count, cap, device):
     """`count` pairs (group_offsets of capacity cap, num_groups), -1 throughout.  One fill for all of them: it is a launch,
     1.3 us in a graph and more in an eager call (a captured call of four sorts of 30,000 pillars: a fill for each tensor
     25.7 us, one fill 15.2; one sort 15.7 and 14.2)."""
+    if count == 1:  # (num_groups is always written; a view would cost more than a tensor of its own)
+        return [(torch.full((cap,), -1, dtype=torch.int32, device=device), torch.empty(1, dtype=torch.int32, device=device))]
     width = -(-cap // 64) * 64 + 64  # (each tensor on a 256-byte boundary)
     both = torch.full((count, width), -1, dtype=torch.int32, device=device)
     return [(row[:cap], row[width - 64:width - 63]) for row in both.unbind(0)]
@@ -203,7 +206,7 @@ def ff_flatten(coords, geom, axis, shift, G, tail=FF_TAIL_MASK, want_keys=False,
     need = lib.ff_flatten_workspace_bytes(n, C.byref(geom))
     ws = workspace if workspace is not None else _workspace(need, dev)
     st = lib.ff_flatten(_ptr(coords), n, C.byref(geom), axis, shift, G, tail, _ptr(perm), _ptr(goff), _ptr(ng),
-                        _ptr(keys), C.c_void_p(_aligned_ptr(ws)), ws.numel() - 256, _stream())
+                        _ptr(keys), _aligned_ptr(ws), ws.numel() - 256, _stream())
     _check(st, "ff_flatten")
     return perm, goff, ng, keys
 
@@ -235,7 +238,7 @@ def ff_flatten_batch(coords, geom, sorts, G, tail=FF_TAIL_MASK, workspace=None, 
     ptrs = [(C.c_void_p * S)(*[t[k].data_ptr() for t in out]) for k in range(3)]
     ws = workspace if workspace is not None else _workspace(lib.ff_flatten_batch_workspace_bytes(n, C.byref(geom), S), dev)
     st = lib.ff_flatten_batch(_ptr(coords), n, C.byref(geom), S, axis, shift, G, tail, ptrs[0], ptrs[1], ptrs[2],
-                              C.c_void_p(_aligned_ptr(ws)), ws.numel() - 256, _stream())
+                              _aligned_ptr(ws), ws.numel() - 256, _stream())
     _check(st, "ff_flatten_batch")
     return out
 
@@ -279,7 +282,7 @@ def ff_flatten3d(coords, geom, axis, shift, G, tail=FF_TAIL_MASK, workspace=None
     need = lib.ff_flatten3d_workspace_bytes(n, C.byref(geom))
     ws = workspace if workspace is not None else _workspace(need, dev)
     st = lib.ff_flatten3d(_ptr(coords), n, C.byref(geom), axis, shift, G, tail, _ptr(perm), _ptr(goff), _ptr(ng),
-                          C.c_void_p(_aligned_ptr(ws)), ws.numel() - 256, _stream())
+                          _aligned_ptr(ws), ws.numel() - 256, _stream())
     _check(st, "ff_flatten3d")
     return perm, goff, ng
 
@@ -306,7 +309,7 @@ def ff_group_attention(feats, perm, group_offsets, num_groups, max_groups, weigh
     ws = workspace if workspace is not None else _workspace(need, feats.device)
     st = lib.ff_group_attention(_ptr(feats), _ptr(out), n, _ptr(perm), _ptr(group_offsets), _ptr(num_groups),
                                 int(max_groups), C.byref(s), G, dtype, flags,
-                                C.c_void_p(_aligned_ptr(ws)), ws.numel() - 256, _stream())
+                                _aligned_ptr(ws), ws.numel() - 256, _stream())
     _check(st, "ff_group_attention")
     return out
 
@@ -344,7 +347,7 @@ def ff_voxelize(xy, frame, point_feats, geom, grid, want_map=True, workspace=Non
     need = lib.ff_voxelize_workspace_bytes(m, C.byref(geom))
     ws = workspace if workspace is not None else _workspace(need, dev)
     st = lib.ff_voxelize(_ptr(xy), _ptr(frame), _ptr(point_feats), m, Cp, C.byref(geom), C.byref(grid), _ptr(coords),
-                         _ptr(feats), _ptr(npil), _ptr(p2p), C.c_void_p(_aligned_ptr(ws)), ws.numel() - 256, _stream())
+                         _ptr(feats), _ptr(npil), _ptr(p2p), _aligned_ptr(ws), ws.numel() - 256, _stream())
     _check(st, "ff_voxelize")
     return coords, feats, npil, p2p
 
@@ -412,6 +415,6 @@ def ff_fwa_block(coords, geom, G, layers, dtype, feats_in, out=None, workspace=N
     ws = workspace if workspace is not None else _workspace(query(n, C.byref(geom), G, arr, len(layers), dtype),
                                                               coords.device)   # (the call itself checks the size)
     st = run(_ptr(coords), n, C.byref(geom), G, tail, arr, len(layers), dtype, _ptr(feats_in), _ptr(out),
-             C.c_void_p(_aligned_ptr(ws)), ws.numel() - 256, _stream())
+             _aligned_ptr(ws), ws.numel() - 256, _stream())
     _check(st, name)
     return out
