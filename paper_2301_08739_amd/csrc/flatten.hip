@@ -1079,9 +1079,9 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
 //
 // What bounds it: for a hundred thousand pillars its two launches, 4 us and a chain of six or seven round trips each; for
 // millions the lines touched rather than the 16 bytes a pillar moved: the pieces of a bucket are a few entries long where the
-// frames are mixed, a line each of entries and table (3.84 M pillars: k_split 29 us, k_buckets 49).  The radix path moves 8-byte
-// words through three passes there.  Measured, radix path / this, us a call: one sort, 131,072 pillars 35 / 14.3, 240,000 37 /
-// 16, 960,000 59 / 28, 2 M 79 / 58, 3.84 M 109 / 78; four sorts, 240,000 63 / 27, 960,000 122 / 74.  The same with a fifth of
+// frames are mixed, a line each of entries and table (3.84 M pillars: k_split 28 us, k_buckets 30).  The radix path moves 8-byte
+// words through three passes there.  Measured, radix path / this, us a call: one sort, 131,072 pillars 35 / 11.9, 240,000 37 /
+// 12.1, 960,000 59 / 24, 2 M 79 / 40, 3.84 M 109 / 61; four sorts, 240,000 63 / 21, 960,000 122 / 54.  The same with a fifth of
 // the pillars sharing cells; on one, a hundred and ten thousand cells of a corner, 30,000 87, 121 and 34, 131,072 325, 481 and
 // 76, 960,000 2375, 3480 and 1230 (21 to 67 by the radix path).
 constexpr int kSplitThreads = 512, kSplitWaves = kSplitThreads / 64;
@@ -1107,7 +1107,8 @@ struct SplitBatch { SplitSort s[kMaxSorts]; int32_t bins, bin_bits, tiles; };
 template <bool Z, bool FRAMES, int OWN>
 __global__ __launch_bounds__(kSplitThreads) void k_split(const int32_t* __restrict__ coords, int n, int S, int tiles, int bins,
                                                           int bin_bits, int frames, uint32_t* __restrict__ entries_all,
-                                                          uint32_t* __restrict__ table_all, SplitBatch sb, PackJob pack) {
+                                                          uint32_t* __restrict__ table_all, uint16_t* __restrict__ frame_table,
+                                                          SplitBatch sb, PackJob pack) {
   constexpr int STRIDE = Z ? 4 : 3, TILE = kSplitThreads * OWN;
   extern __shared__ uint32_t words[];        // [kSplitWaves][bins / 2]: counts of two buckets; then the tile, sorted
   __shared__ uint32_t wave_totals[kSplitWaves];
@@ -1161,6 +1162,11 @@ __global__ __launch_bounds__(kSplitThreads) void k_split(const int32_t* __restri
       first += (total[q] & 0xffffu) + (total[q] >> 16);
     }
   __syncthreads();
+  if (FRAMES && frame_table) {               // where the frames begin, once more: a frame's tiles side by side
+    const int tiles8 = (tiles + 7) & ~7, per_frame = sb.s[s].per_frame;
+    for (int b = tid; b < frames; b += kSplitThreads)
+      frame_table[((int64_t)s * frames + b) * tiles8 + tile] = reinterpret_cast<const uint16_t*>(words)[b * per_frame];
+  }
 #pragma unroll
   for (int u = 0; u < OWN; ++u) at[u] = mine[at[u] >> 16] + (at[u] & 0xffffu);
   __syncthreads();
@@ -1175,15 +1181,33 @@ __global__ __launch_bounds__(kSplitThreads) void k_split(const int32_t* __restri
   }
 }
 
-// The group list of a sort, by one workgroup, from where the frames' first buckets begin.  starts, groups: [frames + 1]
-__device__ __forceinline__ void split_groups(const uint16_t* __restrict__ table, int tiles, int bins, int per_frame, int n, int B,
-                                             int G, int drop, int32_t* __restrict__ goff, int32_t* __restrict__ num_groups,
-                                             uint32_t* starts, uint32_t* groups, uint32_t* wave_totals) {
-  const int tid = threadIdx.x, l = tid & 15;
+// The group list of a sort, by one workgroup, from where the frames' first buckets begin in the tiles: in a table of their own if
+// there is room for it (frame_table, a frame's tiles side by side).  From the columns of the large one it was what k_buckets
+// ended with: 128 frames in 469 tiles are 60,000 lines, 49 us where the buckets took 30.  starts, groups: [frames + 1]
+__device__ __forceinline__ void split_groups(const uint16_t* __restrict__ table, const uint16_t* __restrict__ frame_table, int tiles,
+                                             int bins, int per_frame, int n, int B, int G, int drop, int32_t* __restrict__ goff,
+                                             int32_t* __restrict__ num_groups, uint32_t* starts, uint32_t* groups,
+                                             uint32_t* wave_totals) {
+  const int tid = threadIdx.x, l = tid & 15, tiles8 = (tiles + 7) & ~7;
   for (int b = tid >> 4; b < B; b += kSplitThreads / 16) {
     uint32_t sum = 0;
+    if (b == 0) {                            // (the first frame begins with the cloud)
+    } else if (frame_table) {
+      typedef uint16_t eight __attribute__((ext_vector_type(8)));
+      static_assert(kSplitMaxTiles <= 4 * 16 * 8, "four a lane");
+      eight v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (8 * (l + 16 * k) < tiles) v[k] = *reinterpret_cast<const eight*>(frame_table + (int64_t)b * tiles8 + 8 * (l + 16 * k));
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (8 * (l + 16 * k) + j < tiles) sum += v[k][j];
+    } else {
 #pragma unroll 8
-    for (int t = l; t < tiles; t += 16) sum += table[(int64_t)t * bins + b * per_frame];
+      for (int t = l; t < tiles; t += 16) sum += table[(int64_t)t * bins + b * per_frame];
+    }
 #pragma unroll
     for (int d = 8; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 16);
     if (l == 0) starts[b] = sum;
@@ -1205,15 +1229,17 @@ __device__ __forceinline__ void split_groups(const uint16_t* __restrict__ table,
     goff[carry] = n;
   }
   __syncthreads();
-  for (int b = tid >> 4; b < B; b += kSplitThreads / 16)
-    for (uint32_t k = l; k < groups[b + 1] - groups[b]; k += 16) goff[groups[b] + k] = (int32_t)(starts[b] + k * (uint32_t)G);
+  const int lanes = B >= 32 ? 16 : B >= 8 ? 64 : kSplitThreads;  // of a frame
+  for (int b = tid / lanes; b < B; b += kSplitThreads / lanes)
+    for (uint32_t k = tid % lanes; k < groups[b + 1] - groups[b]; k += lanes) goff[groups[b] + k] = (int32_t)(starts[b] + k * (uint32_t)G);
 }
 
 // end0 .. end3: buckets of the first sort, of the first two, ..
 __global__ __launch_bounds__(kSplitThreads, 6) void k_buckets(const uint16_t* __restrict__ table_all, int n, int S, int tiles, int bins,
                                                             int tile_rows, int end0, int end1, int end2, int end3,
-                                                            const uint32_t* __restrict__ entries_all, uint32_t* scratch, int G,
-                                                            int drop, Batch bt, SplitBatch sb) {
+                                                            const uint32_t* __restrict__ entries_all, uint32_t* scratch,
+                                                            const uint16_t* __restrict__ frame_table, int G, int drop, Batch bt,
+                                                            SplitBatch sb) {
   extern __shared__ uint32_t list[];                       // [kSplitList] key value << 12 | position in the bucket; counters
   uint32_t* const cum = list + kSplitList;                 // [kSplitMaxTiles + 1] the bucket's pillars in the tiles before,
   uint32_t* const from = cum + kSplitMaxTiles + 1;         // [kSplitMaxTiles] and where those of a tile are, less that
@@ -1223,7 +1249,8 @@ __global__ __launch_bounds__(kSplitThreads, 6) void k_buckets(const uint16_t* __
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if ((int)blockIdx.x < S) {
     const int s = blockIdx.x;
-    split_groups(table_all + (int64_t)s * tiles * bins, tiles, bins, sb.s[s].per_frame, n, bt.kp[s].B, G, drop,
+    split_groups(table_all + (int64_t)s * tiles * bins,
+                 frame_table ? frame_table + (int64_t)s * bt.kp[s].B * ((tiles + 7) & ~7) : nullptr, tiles, bins, sb.s[s].per_frame, n, bt.kp[s].B, G, drop,
                  bt.group_offsets[s], bt.num_groups[s], list, list + kSplitMaxBuckets + 1, wave_totals);
     return;
   }
@@ -1271,27 +1298,45 @@ __global__ __launch_bounds__(kSplitThreads, 6) void k_buckets(const uint16_t* __
     const uint32_t e = e0 + u * kSplitThreads + tid;
     return e < T ? e : T - 1u;
   };
+  // (N a thread of the workgroup at most: with a branch around each of eight the reads of the search waited for each other, clocks
+  // of a workgroup's fetch, 30,000 pillars 5,500 -> 2,000, 3.84 M 8,600 -> 4,000; k_buckets for four sorts of 30,000, 80,000 and
+  // 240,000 9.2 -> 6.4, 13.2 -> 10.2 and 17.9 -> 13.8 us)
+  uint32_t top = 1;                          // the largest power of two below the number of tiles
+  while (2u * top < (uint32_t)tiles) top *= 2u;
+  auto fetch_n = [&](uint32_t (&code)[kSplitOwn], uint32_t (&index)[kSplitOwn], uint32_t e0, auto n_of) {
+    constexpr int N = decltype(n_of)::value;
+    uint32_t tile[N] = {};
+#pragma unroll 1
+    for (uint32_t step = top; step > 0; step >>= 1) {
+      uint32_t begins[N];
+#pragma unroll
+      for (int u = 0; u < N; ++u) begins[u] = cum[tile[u] + step];
+#pragma unroll
+      for (int u = 0; u < N; ++u) tile[u] += begins[u] <= nth_of(e0, u) ? step : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) index[u] = from[tile[u]];
+#pragma unroll
+    for (int u = 0; u < N; ++u) index[u] = entries[index[u] + nth_of(e0, u)];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      code[u] = index[u] >> kSplitLocalBits;
+      index[u] = __umul24(tile[u], (uint32_t)tile_rows) + (index[u] & ((1u << kSplitLocalBits) - 1u));
+    }
+  };
   auto fetch = [&](uint32_t (&code)[kSplitOwn], uint32_t (&index)[kSplitOwn], uint32_t e0) {
-    uint32_t tile[kSplitOwn] = {};
-#pragma unroll
-    for (uint32_t step = kSplitMaxTiles / 2; step > 0; step >>= 1)
-#pragma unroll
-      for (int u = 0; u < kSplitOwn; ++u)
-        if ((int)step < tiles && e0 + u * kSplitThreads < T) tile[u] += cum[tile[u] + step] <= nth_of(e0, u) ? step : 0u;
-#pragma unroll
-    for (int u = 0; u < kSplitOwn; ++u)
-      if (e0 + u * kSplitThreads < T) index[u] = entries[from[tile[u]] + nth_of(e0, u)];
-#pragma unroll
-    for (int u = 0; u < kSplitOwn; ++u)
-      if (e0 + u * kSplitThreads < T) {
-        code[u] = index[u] >> kSplitLocalBits;
-        index[u] = tile[u] * (uint32_t)tile_rows + (index[u] & ((1u << kSplitLocalBits) - 1u));
-      }
+    const uint32_t left = T - e0;
+    if (left <= (uint32_t)kSplitThreads) fetch_n(code, index, e0, std::integral_constant<int, 1>());
+    else if (left <= 2u * kSplitThreads) fetch_n(code, index, e0, std::integral_constant<int, 2>());
+    else if (left <= 4u * kSplitThreads) fetch_n(code, index, e0, std::integral_constant<int, 4>());
+    else                                 fetch_n(code, index, e0, std::integral_constant<int, kSplitOwn>());
   };
   auto each_of = [&](uint32_t e0, auto use) {
 #pragma unroll
-    for (int u = 0; u < kSplitOwn; ++u)
+    for (int u = 0; u < kSplitOwn; ++u) {
+      if (e0 + u * kSplitThreads >= T) break;  // (all of the workgroup)
       if (e0 + u * kSplitThreads + tid < T) use(u, e0 + u * kSplitThreads + tid);
+    }
   };
   uint32_t code[kSplitOwn], index[kSplitOwn];
   for (uint32_t e0 = 0; e0 < T; e0 += kSplitList) {
@@ -1301,14 +1346,20 @@ __global__ __launch_bounds__(kSplitThreads, 6) void k_buckets(const uint16_t* __
     });
   }
   __syncthreads();
+  constexpr int PER = (1 << (kSplitCodeBits - 5)) / kSplitThreads;  // words of a thread
   const int per = (words + kSplitThreads - 1) / kSplitThreads, w0 = tid * per;
-  uint32_t sum = 0, cells;
-  for (int w = w0; w < w0 + per && w < words; ++w) sum += (uint32_t)__popc(bits[w]);
+  uint32_t pop[PER], sum = 0, cells;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) pop[q] = q < per && w0 + q < words ? bits[w0 + q] : 0u;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) sum += pop[q] = (uint32_t)__popc(pop[q]);
   uint32_t run = block_exclusive_scan<kSplitThreads>(sum, wave_totals, &cells);
   if (cells == T) {                          // no two pillars share a cell
-    for (int w = w0; w < w0 + per && w < words; ++w) {
-      first[w] = base + run;
-      run += (uint32_t)__popc(bits[w]);
+    uint32_t at = base + run;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      if (q < per && w0 + q < words) first[w0 + q] = at;
+      at += pop[q];
     }
     __syncthreads();
     if (T <= (uint32_t)kSplitList) {         // perm through the list, so that it is written in order
@@ -1743,6 +1794,11 @@ static int flatten_launch_impl(const int32_t* coords, const PointCells* pts, int
     if (pack) job = *pack;
     uint32_t* entries = (uint32_t*)buf[0];
     uint32_t* table = entries + (int64_t)num_sorts * n;
+    // (what is left of the first buffer of words; a 16-byte boundary)
+    const size_t table_end = align_up((size_t)num_sorts * (n * 4 + (int64_t)sb.tiles * sb.bins * 2), 16);
+    const size_t frame_bytes = (size_t)num_sorts * g->num_frames * ((sb.tiles + 7) & ~7) * 2;
+    uint16_t* frame_table = g->num_frames > 1 && table_end + frame_bytes <= (size_t)num_sorts * n * 8
+                                ? (uint16_t*)((char*)buf[0] + table_end) : nullptr;
     const unsigned blocks = (unsigned)(num_sorts * sb.tiles + ceil_div((int64_t)job.layers * job.blocks, kSplitThreads / 256));
     const size_t counters = (size_t)kSplitWaves * sb.bins * 2, stage = (size_t)tile_rows * 4;
     int64_t buckets = 0, ends[kMaxSorts];
@@ -1758,10 +1814,11 @@ static int flatten_launch_impl(const int32_t* coords, const PointCells* pts, int
     size_t lds = (size_t)(kSplitList + 2 * kSplitMaxTiles + 1) * 4 + (size_t)(2 * words > kSplitList ? 2 * words : kSplitList) * 4;
     auto go = [&](auto split) {
       hipLaunchKernelGGL(split, dim3(blocks), dim3(kSplitThreads), counters > stage ? counters : stage, stream, coords, (int)n,
-                         num_sorts, sb.tiles, sb.bins, sb.bin_bits, (int)g->num_frames, entries, table, sb, job);
+                         num_sorts, sb.tiles, sb.bins, sb.bin_bits, (int)g->num_frames, entries, table, frame_table,
+                         sb, job);
       hipLaunchKernelGGL(k_buckets, dim3((unsigned)(num_sorts + 8 * ceil_div(buckets, 8))), dim3(kSplitThreads), lds, stream,
                          (const uint16_t*)table, (int)n, num_sorts, sb.tiles, sb.bins, tile_rows, (int)ends[0], (int)ends[1],
-                         (int)ends[2], (int)ends[3], entries, (uint32_t*)buf[1], G, drop, bt, sb);
+                         (int)ends[2], (int)ends[3], entries, (uint32_t*)buf[1], frame_table, G, drop, bt, sb);
       return launch_status();
     };
     auto go_z = [&](auto Z, auto frames) {

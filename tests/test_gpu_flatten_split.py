@@ -65,6 +65,7 @@ CASES = {  # pillars, frames, grid, window
     "shared_cells": (lambda: _any(2, 200, 200, 100000, 6), 2, 200, 13),
     "thousands_a_cell": (lambda: _any(1, 7, 7, 50000, 7), 1, 468, 13),
     "hundreds_of_frames": (lambda: _cells(300, 60, 60, 400000, 8), 300, 60, 9),
+    "no_room_for_the_frames_table": (lambda: _cells(1022, 60, 60, 523270, 32), 1022, 60, 9),  # one sort: a few KB short of it
     "large_tiles": (lambda: _cells(40, 200, 200, (1 << 20) + 77, 9), 40, 200, 13),
     "before_large_tiles": (lambda: _cells(40, 200, 200, (1 << 20) - 1, 10), 40, 200, 13),
     "key_of_more_than_32_bits": (lambda: _cells(2, 4096, 4096, 140000, 11) * [4000, 1, 1], 5000, 4096, 13),
