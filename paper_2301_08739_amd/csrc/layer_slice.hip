@@ -109,19 +109,24 @@ struct Plan {
   static constexpr int STATS = R * NS * 8;
   static constexpr int PAR = (5 * C + F) * 4;  // query bias, output bias, LN2 scale and shift, FFN biases
   static constexpr int TAB = RB * 64;          // which rows are members, as operand masks
-  static constexpr int SRC = R * (RB > 3 ? 8 : 4);  // where the rows came from, and (four blocks) their pillars
+  static constexpr int SRC = R * (RB % 2 == 0 ? 8 : 4);  // where the rows came from, and (four blocks) their pillars
   static constexpr int TOTAL = A + B + STATS + PAR + TAB + SRC;
   static_assert(F == 2 * C, "half of the hidden units are one set of operands");
 };
 
-template <int C, int DH, int F, int PT, int GPW, bool HALF, int MINW, bool OUT_F32, bool PE>
-__global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
+// SPLIT: the workgroup takes half of a group's queries (half_of: which), and the keys and values of all of it.
+template <int C, int DH, int F, int PT, int GPW, bool HALF, int MINW, bool OUT_F32, bool PE, bool SPLIT>
+__device__ __forceinline__ void slice_layer(
     const uint16_t* __restrict__ feats, const int32_t* __restrict__ perm, const u32x4* __restrict__ packed, int n, int G,
     int in_sorted, int max_groups, const int32_t* __restrict__ goff, const int32_t* __restrict__ num_groups,
-    const int32_t* __restrict__ out_index, void* __restrict__ out, const uint16_t* __restrict__ pos_embed, int drop, float eps) {
+    const int32_t* __restrict__ out_index, void* __restrict__ out, const uint16_t* __restrict__ pos_embed, int drop, float eps,
+    const int workgroup, const int half_of) {
   constexpr int RB = PT * GPW;             // row blocks of the workgroup
   constexpr bool TAIL = tail_of_16(PT, HALF);
   constexpr int NF = TAIL ? RB - 1 : RB;   // row blocks of 32
+  constexpr int NQ = SPLIT ? NF / 2 : NF;  // of them, those of its queries,
+  const int qb = half_of * NQ;             // from this one on
+  static_assert(!SPLIT || (!TAIL && GPW == 1 && RB % 2 == 0), "half of the blocks");
   using PL = Plan<C, F, RB, TAIL>;
   constexpr int NS = PL::NS;
   constexpr int KB = C / 32, NB = C / 16;  // 32-wide input blocks, 16-wide output blocks
@@ -132,7 +137,8 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   constexpr int LPR = C / 8, RPI = 64 / LPR;  // lanes per row (16 bytes each), rows per load instruction
   constexpr int NL = PL::R / 16;           // load instructions of a wavefront
   static_assert(DH == 16 || DH == 32, "head dim");
-  constexpr int RPW = NL * RPI;            // rows a wavefront loads, normalises and stores: of one group
+  constexpr int RPW = NL * RPI;            // rows a wavefront loads and normalises: of one group
+  constexpr int NLQ = SPLIT ? NL / 2 : NL, RPWQ = NLQ * RPI;  // and stores
   static_assert(RPW * NS == PL::R && (GPW == 1 || 32 * PT % RPW == 0), "of one group");
 
   extern __shared__ u32x4 lds[];
@@ -148,7 +154,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   // and 30,000 rows with 6 to 25 registers in scratch memory / so, us: 128 features, G = 128, float32 results 21.8 / 20.9 and 25.7
   // / 24.4; 256 features, G = 120 33.0 / 32.3 and 46.1 / 44.3.  At 128 features with 16-bit results it is even, G = 120 19.9 / 19.5 and
   // 21.6 / 21.9, G = 128 19.2 / 19.5 and 21.1 / 21.4; where there are registers it costs 1 to 4 %.
-  constexpr bool FULL = RB > 3 && (!HALF || (C > 128 && PE));
+  constexpr bool FULL = SPLIT || RB > 3 && (!HALF || (C > 128 && PE));
   int32_t* const pillar = src + PL::R;
   constexpr int P_BQ = 0, P_BO = C, P_G2 = 2 * C, P_B2N = 3 * C, P_B2 = 4 * C, P_B1 = 5 * C;
 
@@ -178,7 +184,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   // Slot sl of the wavefront's group -> sorted position.  Rows beyond the group's members repeat its last member: their
   // scores then never exceed the real ones, and they are cut out of the sums (below).
   const int gl_s = GPW == 1 ? 0 : s * RPW / (32 * PT);  // the group whose rows this wavefront loads and stores
-  const int g_s = blockIdx.x * GPW + gl_s;
+  const int g_s = workgroup * GPW + gl_s;
   const int slot0 = s * RPW - gl_s * 32 * PT;
   const int lr = lane / LPR, lc = lane % LPR;
   int first = 0;                           // sorted position of the wavefront's first row
@@ -233,7 +239,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   bool whole = true;                       // every row of the workgroup is a member of its group
 #pragma unroll
   for (int gl = 0; gl < GPW; ++gl) {
-    const int g = blockIdx.x * GPW + gl;
+    const int g = workgroup * GPW + gl;
     const int gc = g < max_groups ? g : max_groups - 1;
     const int o0 = goff[gc], o1 = goff[gc + 1];
     // A list of full groups only ('Drop Residual') has the next start beyond this group's end.
@@ -305,7 +311,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   if (tid < (5 * C + F) / 4) reinterpret_cast<f32x4*>(par)[tid] = par_piece;
   touch_done(touched);
   // ---- rows of no group ('Drop Residual'): copied, unless there is no list -----------------------------------------
-  if (drop && ngroups >= 0) {
+  if (drop && ngroups >= 0 && half_of == 0) {
     auto copy_rows = [&](int lo, int hi, int w0, int nw) {  // by wavefronts w0 .. w0 + nw - 1
       hi = hi < n ? hi : n;
       for (int p = lo + (s - w0) * RPI + lr; p < hi; p += nw * RPI) {
@@ -366,16 +372,16 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     for (int d = 0; d < D - 1; ++d) wf(w[d], d);
   };
   auto nothing = [](int) {};
-  auto product = [&](auto& w, auto wf, int at, const u32x4* rows, auto mm, auto mt, auto beside) {
-    constexpr int D = sizeof(w) / sizeof(w[0]), N = sizeof(w[0]) / 16;
+  auto product_of = [&](auto blocks, auto& w, auto wf, int at, const u32x4* rows, auto mm, auto mt, auto beside) {
+    constexpr int D = sizeof(w) / sizeof(w[0]), N = sizeof(w[0]) / 16, MINE = decltype(blocks)::value;
     const u32x4* const p = rows + lane;
     const u32x4* const tail = p + NF * KS * 64;
-    constexpr int DA = N == 1 && RB <= 3 ? 3 : 2;
-    u32x4 a[DA][NF], a16[2];
+    constexpr int DA = N == 1 && MINE <= 3 ? 3 : 2;
+    u32x4 a[DA][MINE], a16[2];
 #pragma unroll
     for (int d = 0; d < DA - 1; ++d)
 #pragma unroll
-      for (int b = 0; b < NF; ++b) a[d][b] = p[(b * KS + d) * 64];
+      for (int b = 0; b < MINE; ++b) a[d][b] = p[(b * KS + d) * 64];
     if constexpr (TAIL) a16[0] = tail[0];
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
@@ -391,7 +397,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
       wf(w[(at + k + D - 1) % D], at + k + D - 1);
       if (k + DA - 1 < KS) {
 #pragma unroll
-        for (int b = 0; b < NF; ++b) a[(k + DA - 1) % DA][b] = p[(b * KS + k + DA - 1) * 64];
+        for (int b = 0; b < MINE; ++b) a[(k + DA - 1) % DA][b] = p[(b * KS + k + DA - 1) * 64];
       }
       mm(w[(at + k) % D], a[k % DA]);
       if constexpr (TAIL) {
@@ -417,6 +423,13 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     fence();
   };
 
+  auto product = [&](auto& w, auto wf, int at, const u32x4* rows, auto mm, auto mt, auto beside) {  // of the queries' rows
+    product_of(std::integral_constant<int, NQ>(), w, wf, at, rows, mm, mt, beside);
+  };
+  auto product_all = [&](auto& w, auto wf, int at, const u32x4* rows, auto mm, auto mt, auto beside) {
+    product_of(std::integral_constant<int, NF>(), w, wf, at, rows, mm, mt, beside);
+  };
+
   // ---- Q, K, V of this slice -----------------------------------------------------------------------------------------
   u32x4 Q[RB][2], K[RB][2], V[RB][2];      // rounded: registers 8 a .. 8 a + 7 of the accumulators
   auto halves = [&](u32x4 (&d)[2], const f32x16& v) {
@@ -427,8 +440,8 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   };
   constexpr float qscale = (DH == 16 ? 0.25f : 0.17677669529663687f) * 1.44269504088896340736f;  // log2(e) / sqrt(d)
   {
-    constexpr bool JOINT = RB <= 2 && !PE;  // all three at once; otherwise the values first,
-    constexpr bool PAIR = RB <= 3;          // and then keys and queries together (four row blocks: one after the other)
+    constexpr bool JOINT = RB <= 2 && !PE && !SPLIT;  // all three at once; otherwise the values first,
+    constexpr bool PAIR = RB <= 3 && !SPLIT;  // and then keys and queries together (four row blocks: one after the other)
     u32x4 w1[WD][1], w2[4][2], w3[2][3];
     auto vf = [&](u32x4 (&d)[1], int k) { if (k < KS) d[0] = wv_at(k); };
     auto kf = [&](u32x4 (&d)[1], int k) { if (k < KS) d[0] = wk_at(k); };
@@ -438,16 +451,16 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     if constexpr (JOINT) ahead(w3, kqvf);
     else ahead(w1, vf);
     lds_barrier();
-    f32x16 aq[NF], ak[NF], av[NF];
+    f32x16 aq[NQ], ak[NF], av[NF];
     f32x4 tq4[2], tk4[2], tv4[2];          // of the last sixteen rows: two tiles of 16 features
     auto start_at = [&](f32x16 (&v)[NF], f32x4 (&t)[2]) {
 #pragma unroll
       for (int b = 0; b < NF; ++b) v[b] = kZero;
       t[0] = t[1] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
-    auto done = [&](u32x4 (&d)[RB][2], f32x16 (&v)[NF]) {
+    auto done = [&](u32x4 (&d)[RB][2], auto& v) {
 #pragma unroll
-      for (int b = 0; b < NF; ++b) halves(d[b], v[b]);
+      for (int b = 0; b < (int)(sizeof(v) / sizeof(v[0])); ++b) halves(d[b], v[b]);
     };
     // Sixteen rows in the layout of 32: rows 16 .. 31 repeat them (queries, keys) or stay unused (values)
     auto done16 = [&](u32x4 (&d)[RB][2], const f32x4 (&t)[2], bool values) {
@@ -479,7 +492,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     const u32x4* const qk = PE ? Bb : Ab;
     start_at(av, tv4);
     if constexpr (!JOINT) {
-      product(w1, vf, 0, Ab, [&](const u32x4 (&w)[1], const u32x4 (&a)[NF]) {
+      product_all(w1, vf, 0, Ab, [&](const u32x4 (&w)[1], const u32x4 (&a)[NF]) {
 #pragma unroll
         for (int b = 0; b < NF; ++b) av[b] = mma(a[b], w[0], av[b]);
       }, [&](const u32x4 (&w)[1][2], u32x4 a) {
@@ -495,11 +508,11 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     {
       const u32x4 bq = bias(P_BQ + 32 * s);
 #pragma unroll
-      for (int b = 0; b < NF; ++b) aq[b] = mma(bq, first_one, kZero);
+      for (int b = 0; b < NQ; ++b) aq[b] = mma(bq, first_one, kZero);
       if constexpr (TAIL) vec4(tq4, P_BQ + 32 * s);
     }
     if constexpr (JOINT) {
-      product(w3, kqvf, 0, Ab, [&](const u32x4 (&w)[3], const u32x4 (&a)[NF]) {
+      product_all(w3, kqvf, 0, Ab, [&](const u32x4 (&w)[3], const u32x4 (&a)[NF]) {
 #pragma unroll
         for (int b = 0; b < NF; ++b) {
           ak[b] = mma(w[0], a[b], ak[b]);
@@ -517,7 +530,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
       done(V, av);
       done16(V, tv4, true);
     } else if constexpr (PAIR) {
-      product(w2, kqf, 0, qk, [&](const u32x4 (&w)[2], const u32x4 (&a)[NF]) {
+      product_all(w2, kqf, 0, qk, [&](const u32x4 (&w)[2], const u32x4 (&a)[NF]) {
 #pragma unroll
         for (int b = 0; b < NF; ++b) {
           ak[b] = mma(w[0], a[b], ak[b]);
@@ -537,16 +550,16 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
           for (int t = 0; t < 2; ++t) v[t] = mma16(w[0][t], a, v[t]);
         };
       };
-      product(w1, kf, 0, qk, [&](const u32x4 (&w)[1], const u32x4 (&a)[NF]) {
+      product_all(w1, kf, 0, qk, [&](const u32x4 (&w)[1], const u32x4 (&a)[NF]) {
 #pragma unroll
         for (int b = 0; b < NF; ++b) ak[b] = mma(w[0], a[b], ak[b]);
       }, onto(tk4), nothing);
       ahead(w1, qf);
       done(K, ak);
       done16(K, tk4, false);
-      product(w1, qf, 0, qk, [&](const u32x4 (&w)[1], const u32x4 (&a)[NF]) {
+      product(w1, qf, 0, qk + qb * KS * 64, [&](const u32x4 (&w)[1], const u32x4 (&a)[NQ]) {
 #pragma unroll
-        for (int b = 0; b < NF; ++b) aq[b] = mma(w[0], a[b], aq[b]);
+        for (int b = 0; b < NQ; ++b) aq[b] = mma(w[0], a[b], aq[b]);
       }, onto(tq4), nothing);
     }
     done(Q, aq);
@@ -603,7 +616,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
             }
           }
 #pragma unroll
-        for (int q0 = 0; q0 < PT; ++q0) {
+        for (int q0 = 0; q0 < (SPLIT ? NQ : PT); ++q0) {
           const int qt = gl * PT + q0;
           f32x16 O, rs;
           auto used = [](int kt) { return HALF && kt == PT - 1 ? 8 : 16; };  // registers of a block that stand for members
@@ -672,12 +685,12 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   // The rows again, 16 bytes a lane: lane h holds features 16 h + 8 u .. + 7 of the slice, the operand of a product whose other
   // operand is one where the feature is the output's own.  It adds the numbers as they are (1 x), and leaves the vector units
   // out of it.
-  u32x4 again[NF][2], unit[2], again16, unit16[2];
+  u32x4 again[NQ][2], unit[2], again16, unit16[2];
 #pragma unroll
-  for (int b = 0; b < NF; ++b)
+  for (int b = 0; b < NQ; ++b)
 #pragma unroll
     for (int u = 0; u < 2; ++u)
-      again[b][u] = *reinterpret_cast<const u32x4*>(feats + (int64_t)src[32 * b + nrow] * C + 32 * s + 16 * h + 8 * u);
+      again[b][u] = *reinterpret_cast<const u32x4*>(feats + (int64_t)src[32 * (qb + b) + nrow] * C + 32 * s + 16 * h + 8 * u);
   {
     const int mine = nrow - 16 * h;
     const uint32_t one = (kOnePair & 0xffffu) << (16 * (mine & 1));
@@ -694,17 +707,17 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
 #pragma unroll
       for (int j = 0; j < 4; ++j) unit16[t][j] = 2 * t + (trow >> 3) == tq && ((trow & 7) >> 1) == j ? one : 0u;
   }
-  f32x16 x1[NF];                           // residual stream of (my 32 features, all rows)
+  f32x16 x1[NQ];                           // residual stream of (my 32 features, all rows)
   f32x4 x16[2];
   {
     const f32x16 bo = vec16(P_BO + 32 * s);
 #pragma unroll
-    for (int b = 0; b < NF; ++b) x1[b] = bo;
+    for (int b = 0; b < NQ; ++b) x1[b] = bo;
     if constexpr (TAIL) vec4(x16, P_BO + 32 * s);
   }
-  auto onto_x1 = [&](const u32x4 (&w)[1], const u32x4 (&a)[NF]) {
+  auto onto_x1 = [&](const u32x4 (&w)[1], const u32x4 (&a)[NQ]) {
 #pragma unroll
-    for (int b = 0; b < NF; ++b) x1[b] = mma(w[0], a[b], x1[b]);
+    for (int b = 0; b < NQ; ++b) x1[b] = mma(w[0], a[b], x1[b]);
   };
   auto onto_x16 = [&](const u32x4 (&w)[1][2], u32x4 a) {
 #pragma unroll
@@ -713,17 +726,17 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   lds_barrier();
   product(w, wf, 0, Bb, onto_x1, onto_x16, nothing);
 #pragma unroll
-  for (int b = 0; b < NF; ++b)
+  for (int b = 0; b < NQ; ++b)
 #pragma unroll
     for (int u = 0; u < 2; ++u) x1[b] = mma(unit[u], again[b][u], x1[b]);
   if constexpr (TAIL) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) x16[t] = mma16(unit16[t], again16, x16[t]);
   }
-  int orow[NL];                            // rows of `out` of my rows
+  int orow[NLQ];                           // rows of `out` of my rows
 #pragma unroll
-  for (int t = 0; t < NL; ++t) {
-    const int p = FULL ? pillar[s * RPW + t * RPI + lr_out] : pil[t];
+  for (int t = 0; t < NLQ; ++t) {
+    const int p = FULL ? pillar[32 * qb + s * RPWQ + t * RPI + lr_out] : pil[t];
     orow[t] = out_index ? out_index[p] : p;
   }
 
@@ -741,7 +754,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     return f32x2{(su4[0] + su4[1]) + (su4[2] + su4[3]), (ss4[0] + ss4[1]) + (ss4[2] + ss4[3])};
   };
 #pragma unroll
-  for (int b = 0; b < NF; ++b) {
+  for (int b = 0; b < NQ; ++b) {
     const f32x2 v = sums(x1[b]);
     const float su = half_sum(v[0]), ss = half_sum(v[1]);
     if (h == 0) stats[(b * 32 + nrow) * NS + s] = f32x2{su, ss};
@@ -792,7 +805,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
                        u32x4{tq == 0 ? kOnePair & 0xffffu : 0u, 0u, 0u, 0u}, x16[t]);
     }
 #pragma unroll
-    for (int b = 0; b < NF; ++b) {
+    for (int b = 0; b < NQ; ++b) {
       const f32x2 ssh = scale_shift(b * 32 + nrow);
       const float sc = ssh[0], sh = ssh[1];
       f32x16 z;
@@ -809,19 +822,19 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   // Two hidden tiles a wavefront: tile t of slice s is unit t NS + s.  GELU of a tile runs beside the products that come
   // after it: those of the second tile, and the first half of the second FFN product.
   {
-    f32x16 acc[2][NF];
+    f32x16 acc[2][NQ];
     f32x4 acc16[2][2];
     auto gelu_part = [&](int t, int k) {   // of step k
-      constexpr int ALL = 16 * NF + (TAIL ? 8 : 0);
+      constexpr int ALL = 16 * NQ + (TAIL ? 8 : 0);
 #pragma unroll
       for (int i = k * ALL / KS; i < (k + 1) * ALL / KS; ++i) {
-        if (i < 16 * NF) acc[t][i / 16][i % 16] = gelu2_fast(acc[t][i / 16][i % 16]);
-        else acc16[t][(i - 16 * NF) / 4][i % 4] = gelu2_fast(acc16[t][(i - 16 * NF) / 4][i % 4]);
+        if (i < 16 * NQ) acc[t][i / 16][i % 16] = gelu2_fast(acc[t][i / 16][i % 16]);
+        else acc16[t][(i - 16 * NQ) / 4][i % 4] = gelu2_fast(acc16[t][(i - 16 * NQ) / 4][i % 4]);
       }
     };
     auto put_hidden = [&](int t, u32x4* to) {
 #pragma unroll
-      for (int b = 0; b < NF; ++b)
+      for (int b = 0; b < NQ; ++b)
 #pragma unroll
         for (int k = 0; k < 2; ++k) to[(b * KS + 2 * s + k) * 64 + lane] = operand(acc[t][b], k);
       if constexpr (TAIL) to[(NF * KS + s) * 64 + lane] = operand16(acc16[t]);
@@ -829,11 +842,11 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     auto first = [&](int t) {
       const u32x4 b1 = bias(P_B1 + 32 * (t * NS + s));
 #pragma unroll
-      for (int b = 0; b < NF; ++b) acc[t][b] = mma(b1, first_one, kZero);
+      for (int b = 0; b < NQ; ++b) acc[t][b] = mma(b1, first_one, kZero);
       if constexpr (TAIL) vec4(acc16[t], P_B1 + 32 * (t * NS + s));
-      return [&, t](const u32x4 (&w)[1], const u32x4 (&a)[NF]) {
+      return [&, t](const u32x4 (&w)[1], const u32x4 (&a)[NQ]) {
 #pragma unroll
-        for (int b = 0; b < NF; ++b) acc[t][b] = mma(w[0], a[b], acc[t][b]);
+        for (int b = 0; b < NQ; ++b) acc[t][b] = mma(w[0], a[b], acc[t][b]);
       };
     };
     auto first16 = [&](int t) {
@@ -843,7 +856,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
       };
     };
     product(w, wf, KS, Ab, first(0), first16(0), nothing);
-    if constexpr (RB <= 3) {
+    if constexpr (NQ <= 3) {
       product(w, wf, 2 * KS, Ab, first(1), first16(1), [&](int k) { gelu_part(0, k); });
       put_hidden(0, Bb);
     } else {                               // (no registers for two tiles)
@@ -861,6 +874,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
 
   // ---- scatter -------------------------------------------------------------------------------------------------------
   u32x4* const Out = Bb;
+  const int mine = SPLIT ? 32 * qb + s * RPWQ : slot0;  // slot of the first row I store
   if constexpr (!OUT_F32) {                // whole rows through LDS
     if constexpr (TAIL) {
 #pragma unroll
@@ -869,24 +883,24 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
             u32x2{pack2(x16[t][0], x16[t][1]), pack2(x16[t][2], x16[t][3])};
     }
 #pragma unroll
-    for (int b = 0; b < NF; ++b)
+    for (int b = 0; b < NQ; ++b)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         *reinterpret_cast<u32x2*>(reinterpret_cast<char*>(Out + (32 * b + nrow) * LPR + ((4 * s + e) ^ (nrow & 15))) + 8 * h) =
             u32x2{pack2(x1[b][4 * e], x1[b][4 * e + 1]), pack2(x1[b][4 * e + 2], x1[b][4 * e + 3])};
     lds_barrier();
 #pragma unroll
-    for (int t = 0; t < NL; ++t) {
-      const int row = s * RPW + t * RPI + lr_out;
+    for (int t = 0; t < NLQ; ++t) {
+      const int row = s * RPWQ + t * RPI + lr_out;
       const u32x4 v = Out[row * LPR + (lc_out ^ (row & 15))];
-      if (slot0 + t * RPI + lr_out < m)  // non-temporal: the next reader is another XCD, and the kernel's end has less to write back
+      if (mine + t * RPI + lr_out < m)  // non-temporal: the next reader is another XCD, and the kernel's end has less to write back
         __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out) + (size_t)orow[t] * C + 8 * lc_out));
     }
   } else {                                 // output rows of all row blocks, through LDS; then 16 bytes a lane and piece
     int32_t* const rowof = reinterpret_cast<int32_t*>(Out);
     if (lc_out == 0) {
 #pragma unroll
-      for (int t = 0; t < NL; ++t) rowof[s * RPW + t * RPI + lr_out] = slot0 + t * RPI + lr_out < m ? orow[t] : -1;
+      for (int t = 0; t < NLQ; ++t) rowof[s * RPWQ + t * RPI + lr_out] = mine + t * RPI + lr_out < m ? orow[t] : -1;
     }
     lds_barrier();
     if constexpr (TAIL) {
@@ -896,7 +910,7 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
         if (o >= 0) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out) + (size_t)o * C + 32 * s + 16 * t + 4 * tq) = x16[t];
     }
 #pragma unroll
-    for (int b = 0; b < NF; ++b) {
+    for (int b = 0; b < NQ; ++b) {
       const int o = rowof[32 * b + nrow];
       if (o >= 0) {
 #pragma unroll
@@ -908,13 +922,42 @@ __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
   }
 }
 
+// Two and four row blocks, 128 features: two workgroups share a compute unit, 512 the chip, and a few groups more than that, or
+// a few groups in all, have a compute unit each and leave the others idle.  Up to 128 of them are therefore taken by two workgroups
+// each, half of the queries to each, which both make the keys and values of all: the same operations on every row.  Whole / so, us: G =
+// 128, 64 groups 19.1 / 13.8, 128 19.6 / 14.7, 520 45 / 39, 626 46 / 41, 1100 73 / 70; G = 64, 64 groups 10.0 / 8.3, 128 10.5 / 9.2.  (160 groups by
+// halves 20.1 and, G = 64, 11.3, whole 19.8 and 11.0; 188 beyond a round 51 and 46: more than fit beside each other.)
+constexpr bool can_split(int C, int PT, int MINW) { return C == 128 && (PT == 4 || (PT == 2 && MINW == 2)); }
+constexpr int kSplitGroups = 128, kGroupsAtOnce = 512;
+
+// SPLITS: of the launches in which some groups are split (the others are 0.5 us a launch faster without the code).
+template <int C, int DH, int F, int PT, int GPW, bool HALF, int MINW, bool OUT_F32, bool PE, bool SPLITS>
+__global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
+    const uint16_t* __restrict__ feats, const int32_t* __restrict__ perm, const u32x4* __restrict__ packed, int n, int G,
+    int in_sorted, int max_groups, const int32_t* __restrict__ goff, const int32_t* __restrict__ num_groups,
+    const int32_t* __restrict__ out_index, void* __restrict__ out, const uint16_t* __restrict__ pos_embed, int drop, float eps,
+    int unsplit) {
+  if constexpr (SPLITS) {
+    const int beyond = (int)blockIdx.x - unsplit;
+    if (beyond >= 0) {
+      slice_layer<C, DH, F, PT, GPW, HALF, MINW, OUT_F32, PE, true>(feats, perm, packed, n, G, in_sorted, max_groups, goff, num_groups,
+                                                                    out_index, out, pos_embed, drop, eps, unsplit + beyond / 2, beyond & 1);
+      return;
+    }
+  }
+  slice_layer<C, DH, F, PT, GPW, HALF, MINW, OUT_F32, PE, false>(feats, perm, packed, n, G, in_sorted, max_groups, goff, num_groups,
+                                                                 out_index, out, pos_embed, drop, eps, blockIdx.x, 0);
+}
+
 template <int C, int DH, int F, int PT, int GPW, bool HALF, int MINW>
 int launch_cfg(const LayerSlice& c, hipStream_t stream) {
   constexpr int lds_bytes = Plan<C, F, PT * GPW, tail_of_16(PT, HALF)>::TOTAL;
   static_assert(lds_bytes <= kLdsBytes, "LDS");
   const ff_layer_weights* w = c.w;
+  const int workgroups = (c.max_groups + GPW - 1) / GPW, left = workgroups % kGroupsAtOnce;
+  const int split = can_split(C, PT, MINW) && left <= kSplitGroups ? left : 0;
   // The dynamic LDS size has to be allowed once per kernel and device.
-  static std::atomic<uint64_t> allowed[4] = {{0}, {0}, {0}, {0}};  // bit d: done on device d
+  static std::atomic<uint64_t> allowed[8] = {};  // bit d: done on device d
   auto go = [&](auto kern, int which) -> int {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return FF_ERR_LAUNCH;
@@ -925,17 +968,23 @@ int launch_cfg(const LayerSlice& c, hipStream_t stream) {
         return FF_ERR_LAUNCH;
       allowed[which].fetch_or(bit, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)((c.max_groups + GPW - 1) / GPW)), dim3(2 * C), lds_bytes, stream,
+    hipLaunchKernelGGL(kern, dim3((unsigned)(workgroups + split)), dim3(2 * C), lds_bytes, stream,
                        (const uint16_t*)c.feats, c.perm, (const u32x4*)c.packed, c.n, c.G, c.in_sorted, (int)c.max_groups,
                        c.group_offsets, c.num_groups, c.out_index, c.out, (const uint16_t*)w->pos_embed, c.drop ? 1 : 0,
-                       w->ln_eps);
+                       w->ln_eps, workgroups - split);
     return launch_status();
   };
-  if (w->pos_embed)
-    return c.out_f32 ? go(k_layer_slice<C, DH, F, PT, GPW, HALF, MINW, true, true>, 3)
-                     : go(k_layer_slice<C, DH, F, PT, GPW, HALF, MINW, false, true>, 2);
-  return c.out_f32 ? go(k_layer_slice<C, DH, F, PT, GPW, HALF, MINW, true, false>, 1)
-                   : go(k_layer_slice<C, DH, F, PT, GPW, HALF, MINW, false, false>, 0);
+  auto form = [&](auto splits) -> int {
+    constexpr bool S = decltype(splits)::value;
+    if (w->pos_embed)
+      return c.out_f32 ? go(k_layer_slice<C, DH, F, PT, GPW, HALF, MINW, true, true, S>, 3 + 4 * S)
+                       : go(k_layer_slice<C, DH, F, PT, GPW, HALF, MINW, false, true, S>, 2 + 4 * S);
+    return c.out_f32 ? go(k_layer_slice<C, DH, F, PT, GPW, HALF, MINW, true, false, S>, 1 + 4 * S)
+                     : go(k_layer_slice<C, DH, F, PT, GPW, HALF, MINW, false, false, S>, 0 + 4 * S);
+  };
+  if constexpr (can_split(C, PT, MINW))
+    if (split > 0) return form(std::true_type());
+  return form(std::false_type());
 }
 
 }  // namespace

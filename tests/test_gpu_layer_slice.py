@@ -122,3 +122,27 @@ def test_last_sixteen_rows(C, whole, G, dt):
                     got, want = (ff.ff_group_attention(x, *dev, 4, lw, G, dt, fl | ff.FF_FLAG_VARIANT(v), pos_embed=embed)
                                  for v in (0, whole))
                     assert torch.equal(got.view(torch.int32 if fl else torch.int16), want.view(torch.int32 if fl else torch.int16))
+
+
+@pytest.mark.parametrize("dt", [ff.FF_BF16, ff.FF_F16])
+@pytest.mark.parametrize("G", [33, 48, 64, 97, 112, 128])
+@pytest.mark.parametrize("groups", [1, 2, 128, 129, 513, 640, 641])
+def test_groups_split_between_two_workgroups(G, groups, dt):
+    """Up to 128 groups beyond whole rounds of 512 go to two workgroups each, 128 features: the same bits as with a bound on the number
+    of groups (empty ones behind the list) at which none does; a short last group with members in one half only and in both, dropped
+    tails, float32 results, an embedding."""
+    C = 128
+    gen = torch.Generator(device=DEV).manual_seed(G + groups)
+    lw = ff.LayerWeights(ffsynth.layer_params(C, 2 * C, HEADS[C], seed=47), dt, DEV).pack()
+    bits = lambda t: t.view(torch.int32 if t.dtype == torch.float32 else torch.int16)
+    bound = groups + (300 - groups) % 512
+    for last in (G // 2 - 1, G - 1):
+        n = (groups - 1) * G + last
+        x, e = (torch.randn(n, C, device=DEV, generator=gen).to(torch.bfloat16 if dt == ff.FF_BF16 else torch.float16) for _ in range(2))
+        perm = torch.randperm(n, device=DEV, generator=gen).to(torch.int32)
+        for fl, embed, k in ((0, None, groups), (ff.FF_FLAG_OUT_F32, e, groups), (ff.FF_FLAG_TAIL_DROP, None, groups - 1)):
+            off = torch.arange(0, bound + 1, device=DEV, dtype=torch.int32).mul_(G).clamp_(max=n)
+            off[k:] = n
+            num = torch.full((1,), k, device=DEV, dtype=torch.int32)
+            got, want = (ff.ff_group_attention(x, perm, off, num, most, lw, G, dt, fl, pos_embed=embed) for most in (groups, bound))
+            assert torch.equal(bits(got), bits(want)), (last, fl)
