@@ -266,10 +266,10 @@ __global__ __launch_bounds__(256) void k_seg_mean(const int32_t* __restrict__ pe
 // sorts keep the order of the points (ranks of equal numbers in a wavefront, counters of its own for each wavefront), so a
 // pillar's points come in the order of their indices.
 //
-// What bounds it: three dependent launches, each a chain of four to six round trips to memory (9.3 + 10.8 + 19.4 us for 180,000
+// What bounds it: three dependent launches, each a chain of four to six round trips to memory (8.4 + 10.2 + 19 us for 180,000
 // points of one frame, 4 of each the launch itself), not the 7 MB moved.  In front of them were nine launches, keys of 64 bits
-// through two radix passes.  The call, us, before / this: 2,000 points 31 / 18, 20,000 36 / 22, 60,000 48 / 31, 180,000 of 4
-// features 50.5 / 42.3, of 8 56.3 / 49.1, 262,144 of two frames 55 / 47.  Ranges of 1024 cells, which cover four times the
+// through two radix passes.  The call, us, before / this: 2,000 points 31 / 17, 20,000 36 / 20, 60,000 of 5 features 48 / 28,
+// 180,000 of 4 50.5 / 34.7, of 8 56.3 / 41, 262,144 of two frames 55 / 50.  Ranges of 1024 cells, which cover four times the
 // grid: 180,000 47.9 us, and 1.44 M points of eight frames 177, which the general path takes 137 for.  Rows brought into LDS by
 // the whole workgroup before they are added up, or four lanes to a short pillar: k_vox_mean 19 to 40 us instead of 17.
 // Thousands of points in a single cell are one workgroup's, and one chain of sums as ever: 60,000 of 4 features 505 / 620 us, 180,000
