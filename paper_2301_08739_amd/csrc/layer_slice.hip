@@ -955,7 +955,8 @@ int launch_cfg(const LayerSlice& c, hipStream_t stream) {
   static_assert(lds_bytes <= kLdsBytes, "LDS");
   const ff_layer_weights* w = c.w;
   const int workgroups = (c.max_groups + GPW - 1) / GPW, left = workgroups % kGroupsAtOnce;
-  const int split = can_split(C, PT, MINW) && left <= kSplitGroups ? left : 0;
+  // (An embedding that the results overwrite is read and written group by group, each by one workgroup.)
+  const int split = can_split(C, PT, MINW) && left <= kSplitGroups && w->pos_embed != c.out ? left : 0;
   // The dynamic LDS size has to be allowed once per kernel and device.
   static std::atomic<uint64_t> allowed[8] = {};  // bit d: done on device d
   auto go = [&](auto kern, int which) -> int {

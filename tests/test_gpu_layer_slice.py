@@ -146,3 +146,23 @@ def test_groups_split_between_two_workgroups(G, groups, dt):
             num = torch.full((1,), k, device=DEV, dtype=torch.int32)
             got, want = (ff.ff_group_attention(x, perm, off, num, most, lw, G, dt, fl, pos_embed=embed) for most in (groups, bound))
             assert torch.equal(bits(got), bits(want)), (last, fl)
+
+
+@pytest.mark.parametrize("dt", [ff.FF_BF16, ff.FF_F16])
+@pytest.mark.parametrize("C,G", [(128, 20), (128, 40), (128, 64), (128, 69), (128, 100), (128, 128), (256, 64), (256, 100)])
+@pytest.mark.parametrize("groups", [3, 100, 640])
+def test_results_over_the_embedding(C, G, groups, dt):
+    """A caller may let the results overwrite the embedding: a group's rows of both belong to one workgroup, which reads before it
+    writes.  Groups that two workgroups share would not have that, so none are shared then."""
+    gen = torch.Generator(device=DEV).manual_seed(G + groups)
+    tdt = torch.bfloat16 if dt == ff.FF_BF16 else torch.float16
+    n = groups * G - G // 3
+    lw = ff.LayerWeights(ffsynth.layer_params(C, 2 * C, HEADS[C], seed=53), dt, DEV).pack()
+    x, e = (torch.randn(n, C, device=DEV, generator=gen).to(tdt) for _ in range(2))
+    perm = torch.randperm(n, device=DEV, generator=gen).to(torch.int32)
+    off = torch.arange(groups + 1, device=DEV, dtype=torch.int32).mul_(G).clamp_(max=n)
+    num = torch.full((1,), groups, device=DEV, dtype=torch.int32)
+    want = ff.ff_group_attention(x, perm, off, num, groups, lw, G, dt, pos_embed=e)
+    both = e.clone()
+    got = ff.ff_group_attention(x, perm, off, num, groups, lw, G, dt, pos_embed=both, out=both)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
