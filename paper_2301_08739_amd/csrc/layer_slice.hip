@@ -935,10 +935,10 @@ template <int C, int DH, int F, int PT, int GPW, bool HALF, int MINW, bool OUT_F
 __global__ __launch_bounds__(2 * C, MINW) void k_layer_slice(
     const uint16_t* __restrict__ feats, const int32_t* __restrict__ perm, const u32x4* __restrict__ packed, int n, int G,
     int in_sorted, int max_groups, const int32_t* __restrict__ goff, const int32_t* __restrict__ num_groups,
-    const int32_t* __restrict__ out_index, void* __restrict__ out, const uint16_t* __restrict__ pos_embed, int drop, float eps,
-    int unsplit) {
-  if constexpr (SPLITS) {
-    const int beyond = (int)blockIdx.x - unsplit;
+    const int32_t* __restrict__ out_index, void* __restrict__ out, const uint16_t* __restrict__ pos_embed, int drop, float eps) {
+  if constexpr (SPLITS) {                  // (a group a workgroup: from the number of groups, which is in a register from the start)
+    static_assert((kGroupsAtOnce & (kGroupsAtOnce - 1)) == 0, "whole rounds");
+    const int unsplit = max_groups & ~(kGroupsAtOnce - 1), beyond = (int)blockIdx.x - unsplit;
     if (beyond >= 0) {
       slice_layer<C, DH, F, PT, GPW, HALF, MINW, OUT_F32, PE, true>(feats, perm, packed, n, G, in_sorted, max_groups, goff, num_groups,
                                                                     out_index, out, pos_embed, drop, eps, unsplit + beyond / 2, beyond & 1);
@@ -972,7 +972,7 @@ int launch_cfg(const LayerSlice& c, hipStream_t stream) {
     hipLaunchKernelGGL(kern, dim3((unsigned)(workgroups + split)), dim3(2 * C), lds_bytes, stream,
                        (const uint16_t*)c.feats, c.perm, (const u32x4*)c.packed, c.n, c.G, c.in_sorted, (int)c.max_groups,
                        c.group_offsets, c.num_groups, c.out_index, c.out, (const uint16_t*)w->pos_embed, c.drop ? 1 : 0,
-                       w->ln_eps, workgroups - split);
+                       w->ln_eps);
     return launch_status();
   };
   auto form = [&](auto splits) -> int {

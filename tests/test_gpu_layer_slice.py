@@ -130,8 +130,9 @@ def test_last_sixteen_rows(C, whole, G, dt):
 def test_groups_split_between_two_workgroups(G, groups, dt):
     """Up to 128 groups beyond whole rounds of 512 go to two workgroups each, 128 features: the same bits as with a bound on the number
     of groups (empty ones behind the list) at which none does; a short last group with members in one half only and in both, dropped
-    tails, float32 results, an embedding."""
+    tails, float32 results, an embedding.  (Beyond 512 groups of up to 64 the form that splits is asked for.)"""
     C = 128
+    form = ff.FF_FLAG_VARIANT(7) if G <= 64 and groups > 512 else 0
     gen = torch.Generator(device=DEV).manual_seed(G + groups)
     lw = ff.LayerWeights(ffsynth.layer_params(C, 2 * C, HEADS[C], seed=47), dt, DEV).pack()
     bits = lambda t: t.view(torch.int32 if t.dtype == torch.float32 else torch.int16)
@@ -144,7 +145,7 @@ def test_groups_split_between_two_workgroups(G, groups, dt):
             off = torch.arange(0, bound + 1, device=DEV, dtype=torch.int32).mul_(G).clamp_(max=n)
             off[k:] = n
             num = torch.full((1,), k, device=DEV, dtype=torch.int32)
-            got, want = (ff.ff_group_attention(x, perm, off, num, most, lw, G, dt, fl, pos_embed=embed) for most in (groups, bound))
+            got, want = (ff.ff_group_attention(x, perm, off, num, most, lw, G, dt, fl | form, pos_embed=embed) for most in (groups, bound))
             assert torch.equal(bits(got), bits(want)), (last, fl)
 
 
