@@ -150,7 +150,8 @@ __device__ __forceinline__ void slice_layer(
   uint32_t* const tab = reinterpret_cast<uint32_t*>(ldsc + PL::STATS + PL::PAR);
   int32_t* const src = reinterpret_cast<int32_t*>(ldsc + PL::STATS + PL::PAR + PL::TAB);
   // Four whole row blocks (of the widest form three and a half) leave no registers beside the attention: the pillars wait in LDS,
-  // the weights that come after it are requested behind it, and what follows from the lane's number is worked out again.  12,000
+  // the weights that come after it are requested behind it, and all that follows from the lane's number is worked out again (beside
+  // the split groups' form it took two or three registers more than there are: 128 groups of 128 rows 13.09 / 12.98 us).  12,000
   // and 30,000 rows with 6 to 25 registers in scratch memory / so, us: 128 features, G = 128, float32 results 21.8 / 20.9 and 25.7
   // / 24.4; 256 features, G = 120 33.0 / 32.3 and 46.1 / 44.3.  At 128 features with 16-bit results it is even, G = 120 19.9 / 19.5 and
   // 21.6 / 21.9, G = 128 19.2 / 19.5 and 21.1 / 21.4; where there are registers it costs 1 to 4 %.
@@ -158,7 +159,8 @@ __device__ __forceinline__ void slice_layer(
   int32_t* const pillar = src + PL::R;
   constexpr int P_BQ = 0, P_BO = C, P_G2 = 2 * C, P_B2N = 3 * C, P_B2 = 4 * C, P_B1 = 5 * C;
 
-  const int tid = threadIdx.x, lane = tid & 63, nrow = lane & 31, h = lane >> 5;
+  const int tid = threadIdx.x;
+  int lane = tid & 63, nrow = lane & 31, h = lane >> 5;
   const int trow = lane & 15, tq = lane >> 4;    // of the last sixteen rows: the row, and features 4 tq .. + 3 of each tile of 16
   const int s = __builtin_amdgcn_readfirstlane(tid >> 6);  // slice
 
@@ -168,10 +170,14 @@ __device__ __forceinline__ void slice_layer(
   auto w_load = [&](uint32_t lane_off, int frag, int bytes) -> u32x4 {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, (int)lane_off + bytes, frag * 1024, 0));
   };
-  const uint32_t piece = (uint32_t)((16 * h + (lane & 15)) * 16);
   const uint32_t second = (lane >> 4) & 1;       // row of the tile: 0..15 or 16..31
-  const uint32_t lane_rows = piece + second * (KB * 1024u);  // Q, K, V, W1: the second 16 rows come KB fragments later
-  const uint32_t lane_cols = piece + second * 1024u;         // W_o, W2: next to each other
+  uint32_t lane_rows, lane_cols;
+  auto offsets = [&]() {
+    const uint32_t piece = (uint32_t)((16 * (lane >> 5) + (lane & 15)) * 16), row16 = (lane >> 4) & 1;
+    lane_rows = piece + row16 * (KB * 1024u);    // Q, K, V, W1: the second 16 rows come KB fragments later
+    lane_cols = piece + row16 * 1024u;           // W_o, W2: next to each other
+  };
+  offsets();
   auto rows_at = [&](int frag, int ks) { return w_load(lane_rows, frag + ks / 8 * 4, ks % 8 * 512); };  // of a row tile
   auto wk_at = [&](int ks) { return rows_at(s * FH, ks); };
   auto wv_at = [&](int ks) { return rows_at(s * FH + 2 * KB, ks); };
@@ -359,7 +365,7 @@ __device__ __forceinline__ void slice_layer(
 
   // A bias as the start of a sum: one product, of the bias in the first input and ones (16-bit numbers both, so exact), and
   // zeros in all other inputs of both (an infinite bias times zero would be no number).
-  const u32x4 first_one = {h == 0 ? kOnePair & 0xffffu : 0u, 0u, 0u, 0u};
+  u32x4 first_one = {h == 0 ? kOnePair & 0xffffu : 0u, 0u, 0u, 0u};
   auto bias = [&](int off) -> u32x4 { return u32x4{h == 0 ? pack2(par[off + nrow], 0.f) : 0u, 0u, 0u, 0u}; };
 
   // Steps of a product: N weight operands and NF activation operands (of `rows`) a step, handed to `mm`; every second step the
@@ -676,10 +682,15 @@ __device__ __forceinline__ void slice_layer(
   if constexpr (!FULL) ahead(w, wf);
   if (!HALF && whole) attention(std::false_type());
   else attention(std::true_type());
-  if constexpr (FULL) ahead(w, wf);
-  int lane_again = lane;
-  if constexpr (FULL) asm volatile("" : "+v"(lane_again));
-  const int lr_out = lane_again / LPR, lc_out = lane_again % LPR;
+  if constexpr (FULL) {
+    asm volatile("" : "+v"(lane));
+    nrow = lane & 31;
+    h = lane >> 5;
+    first_one[0] = h == 0 ? kOnePair & 0xffffu : 0u;
+    offsets();
+    ahead(w, wf);
+  }
+  const int lr_out = lane / LPR, lc_out = lane % LPR;
 
   // ---- output projection + residual ----------------------------------------------------------------------------------
   // The rows again, 16 bytes a lane: lane h holds features 16 h + 8 u .. + 7 of the slice, the operand of a product whose other
