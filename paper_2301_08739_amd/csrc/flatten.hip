@@ -1354,6 +1354,7 @@ __global__ __launch_bounds__(kSplitThreads, 6) void k_buckets(const uint16_t* __
 #pragma unroll
   for (int q = 0; q < PER; ++q) sum += pop[q] = (uint32_t)__popc(pop[q]);
   uint32_t run = block_exclusive_scan<kSplitThreads>(sum, wave_totals, &cells);
+  cells = (uint32_t)__builtin_amdgcn_readfirstlane((int)cells);  // (one path or another, never both: without scratch memory)
   if (cells == T) {                          // no two pillars share a cell
     uint32_t at = base + run;
 #pragma unroll

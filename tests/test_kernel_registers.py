@@ -7,7 +7,7 @@ import subprocess
 import pytest
 
 READELF = "/opt/rocm/llvm/bin/llvm-readelf"
-MAIN_PATH = ("k_layer_slice", "k_layer_mfma")
+MAIN_PATH = ("k_layer_slice", "k_layer_mfma", "k_direct", "k_split", "k_buckets", "k_vox_", "k_rows")
 
 
 def _kernels(tmp_path):
