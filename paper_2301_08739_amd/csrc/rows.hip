@@ -19,19 +19,26 @@ __device__ __forceinline__ int64_t row_of(const RowPieces& rp, int64_t i) {
   return rp.log >= 0 ? i >> rp.log : i / rp.per_row;  // the same way for every thread
 }
 
-// What bounds it: memory.  A 64-bit division for every piece was most of the instructions; rows of 2^k pieces (all feature
-// counts of the layers) take shifts.  What is read once and what is not read again soon passes the 256 MB memory-side cache
-// by, so that it still holds what a gather has written when the next launch reads it: 240,000 rows of 256 bfloat16, gather
-// and scatter on buffers that no cache holds, us: plain accesses 96-99, the scatter's non-temporal 76, with the gather's
-// loads 76 too (120,000 rows 47 / 38 / 41; 480,000 rows 195 / 169 / 144: kRowsStreamed).  Each piece one thread's, two or
-// four: within 1 us.
-constexpr int kRowsInFlight = 2;
-constexpr int64_t kRowsStreamed = (int64_t)128 << 20;  // bytes: larger sources of a gather would push out what it writes
+// What bounds it: memory, and with few rows the launch.  Rows of 2^k pieces (all feature counts of the layers) take shifts: a 64-bit
+// division for every piece was most of the instructions.  Up to kRowsShort a thread takes one piece: the pieces of a workgroup then
+// lie as in the launches on either side, whose lines its L2 has.  Beyond, two are in flight.  What is read once passes the 256 MB
+// memory-side cache by; what is written does so only where the next launch would hardly find it there.  Measured from graphs, 128 or
+// 256 bfloat16, buffers that no cache holds / that the launches before left there, us:
+//   a launch that writes the rows, scatter, a launch that reads them: two pieces and non-temporal stores 3.7 MiB 12.1 / 11.5, 7 MiB 12.4
+//   / 14.8, 15 MiB 20.6 / 18.7, 29 MiB 34.4 / 32.0, 59 MiB 64.3 / 57.8, 88 MiB 93.9 / 83.0, 117 MiB 121 / 111; two pieces, plain stores
+//   11.2 / 10.9, 12.5 / 15.5, 20.1 / 17.7, 34.3 / 30.6, 63.7 / 55.9, 93.3 / 81.7, 123 / 113; one 11.0 / 9.9, 12.5 / 12.5, 20.4 / 17.5.
+//   The same around gather, two pieces / one: 3.7 MiB 11.7, 11.4 / 11.5, 9.5, 7 MiB 13.1, 15.9 / 13.0, 12.8, 11 MiB 17.2, 18.6 / 17.5, 16.4.
+//   Plain loads in scatter: 29 MiB 36.1 / 30.7 instead of 34.2 / 30.6.
+// Without a reader the stores of 15 to 88 MiB look 4 to 10 % faster non-temporal (gather and scatter alone, 59 MiB 42.4 / 45.1): the
+// reader pays for it.  A gather's loads are non-temporal where its source would push out what it writes (gather and scatter, 117 MiB
+// 76 us so and plain, 234 MiB 144 / 169).
+constexpr int64_t kRowsShort = (int64_t)14 << 20, kScatterStreamed = (int64_t)64 << 20;  // bytes of the rows of one side
+constexpr int64_t kGatherStreamed = (int64_t)128 << 20;
 
-template <bool SCATTER, bool STREAM>
+// U: pieces of a thread.  LOADS, STORES: those that are non-temporal
+template <bool SCATTER, int U, bool LOADS, bool STORES>
 __global__ __launch_bounds__(256) void k_rows(const piece_t* __restrict__ src, piece_t* __restrict__ dst,
                                                const int32_t* __restrict__ perm, RowPieces rp) {
-  constexpr int U = kRowsInFlight;
   for (int64_t i0 = (int64_t)blockIdx.x * (256 * U) + threadIdx.x; i0 < rp.total; i0 += (int64_t)gridDim.x * (256 * U)) {
     int64_t here[U], there[U];               // of the side in sorted order, and of the other
     piece_t v[U];
@@ -45,19 +52,16 @@ __global__ __launch_bounds__(256) void k_rows(const piece_t* __restrict__ src, p
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const piece_t* const from = src + (SCATTER ? here[u] : there[u]);
-      v[u] = STREAM ? __builtin_nontemporal_load(from) : *from;
+      v[u] = LOADS ? __builtin_nontemporal_load(from) : *from;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (i0 + u * 256 >= rp.total) continue;
-      if (SCATTER) __builtin_nontemporal_store(v[u], dst + there[u]);
-      else         dst[here[u]] = v[u];
+      piece_t* const to = dst + (SCATTER ? there[u] : here[u]);
+      if (STORES) __builtin_nontemporal_store(v[u], to);
+      else        *to = v[u];
     }
   }
-}
-unsigned row_blocks(int64_t pieces) {
-  const int64_t b = ceil_div(pieces, (int64_t)256 * kRowsInFlight);
-  return (unsigned)(b < (1 << 20) ? b : 1 << 20);
 }
 
 // Rows of sorted positions outside every group skip the layer ('Drop Residual', Sec. 4.3): for a
@@ -217,12 +221,21 @@ int rows_launch(bool scatter, const void* src, void* dst, const int32_t* perm, i
   if (!src || !dst || !perm || src == dst) return FF_ERR_ARG;
   if (((uintptr_t)src | (uintptr_t)dst) & 15) return FF_ERR_ARG;
   const RowPieces rp = row_pieces(n, (int)(row_bytes / 16));
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(row_blocks(rp.total)), dim3(256), 0, stream, (const piece_t*)src, (piece_t*)dst, perm, rp);
+  auto go = [&](auto kern, int pieces) {
+    const int64_t blocks = ceil_div(rp.total, (int64_t)256 * pieces);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(blocks < (1 << 20) ? blocks : 1 << 20)), dim3(256), 0, stream, (const piece_t*)src,
+                       (piece_t*)dst, perm, rp);
   };
-  if (scatter) go(k_rows<true, true>);
-  else if (rp.total * 16 > kRowsStreamed) go(k_rows<false, true>);
-  else go(k_rows<false, false>);
+  const int64_t bytes = rp.total * 16;
+  if (scatter) {
+    if (bytes <= kRowsShort) go(k_rows<true, 1, true, false>, 1);
+    else if (bytes <= kScatterStreamed) go(k_rows<true, 2, true, false>, 2);
+    else go(k_rows<true, 2, true, true>, 2);
+  } else {
+    if (bytes <= kRowsShort) go(k_rows<false, 1, false, false>, 1);
+    else if (bytes <= kGatherStreamed) go(k_rows<false, 2, false, false>, 2);
+    else go(k_rows<false, 2, true, false>, 2);
+  }
   return launch_status();
 }
 

@@ -14,7 +14,9 @@ TORCH = {ff.FF_BF16: torch.bfloat16, ff.FF_F16: torch.float16, ff.FF_F32: torch.
     (1, 8, ff.FF_BF16), (511, 8, ff.FF_F16), (513, 8, ff.FF_BF16),                    # one piece a row
     (257, 24, ff.FF_BF16), (1000, 96, ff.FF_F16), (171, 12, ff.FF_F32),               # 3 and 12
     (63, 64, ff.FF_BF16), (4097, 128, ff.FF_F16), (3001, 256, ff.FF_F32),             # 8, 16, 64
-    ((128 << 20) // 512, 256, ff.FF_BF16), ((128 << 20) // 512 + 1, 256, ff.FF_BF16)])  # either side of kRowsStreamed
+    ((14 << 20) // 256, 128, ff.FF_F16), ((14 << 20) // 256 + 1, 128, ff.FF_BF16), (50000, 72, ff.FF_F32),  # either side of kRowsShort,
+    ((64 << 20) // 512, 256, ff.FF_BF16), ((64 << 20) // 512 + 1, 256, ff.FF_BF16),    # kScatterStreamed
+    ((128 << 20) // 512, 256, ff.FF_BF16), ((128 << 20) // 512 + 1, 256, ff.FF_BF16)])  # and kGatherStreamed
 def test_rows_there_and_back(n, C, dt):
     gen = torch.Generator(device=DEV).manual_seed(n + C)
     x = torch.randint(-2**31, 2**31 - 1, (n, C * (2 if dt == ff.FF_F32 else 1) // 2), device=DEV, generator=gen,
