@@ -102,11 +102,14 @@ __global__ __launch_bounds__(256) void k_copy_ungrouped(const T* __restrict__ fe
 // bev[b][y][x][:] = feats[i][:] for pillar i = (b, x, y), zero elsewhere; channels last, so that a
 // pillar's features stay one contiguous row.  Two launches: zero fill (the map is mostly empty:
 // 30k of 219k cells at the paper's resolution), then the rows, a 16-byte piece per thread.
-// What bounds it: memory, 37 of 48 us for four 468 x 468 maps of 128 bfloat16 (224 MB) the fill's writes.  Non-temporal ones
-// leave the memory-side cache to the rows that come after it: 51.5 -> 47.9 us; maps that the cache holds are better filled
-// through it (56 MB 12.9 / 14.0, 84 MB 17.2 / 18.2, 112 MB 26.5 / 24.8: kFillStreamed).  Writing each cell once, with the pillars' numbers left in the map's last rows by a launch of their own and
-// checked against the coordinates, was slower (52.9 to 74 us: the rows' addresses hang on two trips to memory).
-constexpr int64_t kFillStreamed = (int64_t)96 << 20;  // bytes of a map
+// What bounds it: memory, 37 of 48 us for four 468 x 468 maps of 128 bfloat16 (214 MiB) the fill's writes.  Non-temporal ones leave the
+// memory-side cache to the rows that come after it, and the map to whoever reads it next in memory.  30,000 pillars a frame, from
+// graphs, buffers that no cache holds, plain / non-temporal, us: the map alone 107 MiB 28.4 / 26.6, 160 MiB 40.9 / 38.4, 214 MiB 52.8 /
+// 51.3, 428 MiB 105.4 / 96.9; with a launch behind it that reads the map 54 MiB 32.8 / 36.2, 107 MiB 62.7 / 66.7, 160 MiB 92.6 / 97.8, 187 MiB
+// 111.1 / 114.1, 214 MiB 128.4 / 129.7, 267 MiB 160.1 / 159.5, 428 MiB 252.9 / 247.3.  Writing each cell once, with the pillars' numbers
+// left in the map's last rows by a launch of their own and checked against the coordinates, was slower (52.9 to 74 us: the rows'
+// addresses hang on two trips to memory).
+constexpr int64_t kFillStreamed = (int64_t)200 << 20;  // bytes of a map
 
 template <bool STREAM>
 __global__ __launch_bounds__(256) void k_fill_zero(piece_t* __restrict__ dst, int64_t pieces) {

@@ -28,9 +28,10 @@ def test_rows_there_and_back(n, C, dt):
     assert torch.equal(ff.ff_scatter(g, perm, dt).view(bits), x.view(bits))
 
 
-@pytest.mark.parametrize("frames, grid, C, n", [(1, 443, 128, 5000), (1, 444, 128, 5000), (2, 31, 12, 700)])
+@pytest.mark.parametrize("frames, grid, C, n", [(1, 443, 128, 5000), (1, 444, 128, 5000), (1, 640, 128, 5000), (1, 641, 128, 5000),
+                                              (2, 31, 12, 700)])
 def test_dense_map_either_side_of_the_streamed_fill(frames, grid, C, n):
-    """443 x 443 x 128 floats are below 96 MiB, 444 x 444 above; 12 floats are three pieces a row."""
+    """640 x 640 x 128 floats are 200 MiB, 641 x 641 more; 12 floats are three pieces a row."""
     gen = torch.Generator(device=DEV).manual_seed(grid)
     cells = torch.randperm(frames * grid * grid, device=DEV, generator=gen)[:n]
     coords = torch.stack([cells // (grid * grid), cells // grid % grid, cells % grid], 1).to(torch.int32).contiguous()
