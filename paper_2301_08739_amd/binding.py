@@ -160,8 +160,10 @@ def _check(st, what):
 
 
 def _stream():
-    """The current stream of the current device as a number (0.3 us; a Stream object on the way to it 3.3)."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    """The current stream of the current device as a number (0.3 us; a Stream object on the way to it, where a torch has no shorter
+    one, 3.3)."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
