@@ -179,6 +179,11 @@ def _aligned_ptr(ws):
     return (p + 255) // 256 * 256
 
 
+def _room(ws):
+    """Bytes of ws that are there from _aligned_ptr on, whatever its alignment; a smaller tensor has none."""
+    return max(ws.numel() - 256, 0)
+
+
 def ff_flatten_workspace_bytes(n, geom):
     return load_library().ff_flatten_workspace_bytes(int(n), C.byref(geom))
 
@@ -208,7 +213,7 @@ def ff_flatten(coords, geom, axis, shift, G, tail=FF_TAIL_MASK, want_keys=False,
     need = lib.ff_flatten_workspace_bytes(n, C.byref(geom))
     ws = workspace if workspace is not None else _workspace(need, dev)
     st = lib.ff_flatten(_ptr(coords), n, C.byref(geom), axis, shift, G, tail, _ptr(perm), _ptr(goff), _ptr(ng),
-                        _ptr(keys), _aligned_ptr(ws), ws.numel() - 256, _stream())
+                        _ptr(keys), _aligned_ptr(ws), _room(ws), _stream())
     _check(st, "ff_flatten")
     return perm, goff, ng, keys
 
@@ -240,7 +245,7 @@ def ff_flatten_batch(coords, geom, sorts, G, tail=FF_TAIL_MASK, workspace=None, 
     ptrs = [(C.c_void_p * S)(*[t[k].data_ptr() for t in out]) for k in range(3)]
     ws = workspace if workspace is not None else _workspace(lib.ff_flatten_batch_workspace_bytes(n, C.byref(geom), S), dev)
     st = lib.ff_flatten_batch(_ptr(coords), n, C.byref(geom), S, axis, shift, G, tail, ptrs[0], ptrs[1], ptrs[2],
-                              _aligned_ptr(ws), ws.numel() - 256, _stream())
+                              _aligned_ptr(ws), _room(ws), _stream())
     _check(st, "ff_flatten_batch")
     return out
 
@@ -284,7 +289,7 @@ def ff_flatten3d(coords, geom, axis, shift, G, tail=FF_TAIL_MASK, workspace=None
     need = lib.ff_flatten3d_workspace_bytes(n, C.byref(geom))
     ws = workspace if workspace is not None else _workspace(need, dev)
     st = lib.ff_flatten3d(_ptr(coords), n, C.byref(geom), axis, shift, G, tail, _ptr(perm), _ptr(goff), _ptr(ng),
-                          _aligned_ptr(ws), ws.numel() - 256, _stream())
+                          _aligned_ptr(ws), _room(ws), _stream())
     _check(st, "ff_flatten3d")
     return perm, goff, ng
 
@@ -311,7 +316,7 @@ def ff_group_attention(feats, perm, group_offsets, num_groups, max_groups, weigh
     ws = workspace if workspace is not None else _workspace(need, feats.device)
     st = lib.ff_group_attention(_ptr(feats), _ptr(out), n, _ptr(perm), _ptr(group_offsets), _ptr(num_groups),
                                 int(max_groups), C.byref(s), G, dtype, flags,
-                                _aligned_ptr(ws), ws.numel() - 256, _stream())
+                                _aligned_ptr(ws), _room(ws), _stream())
     _check(st, "ff_group_attention")
     return out
 
@@ -349,7 +354,7 @@ def ff_voxelize(xy, frame, point_feats, geom, grid, want_map=True, workspace=Non
     need = lib.ff_voxelize_workspace_bytes(m, C.byref(geom))
     ws = workspace if workspace is not None else _workspace(need, dev)
     st = lib.ff_voxelize(_ptr(xy), _ptr(frame), _ptr(point_feats), m, Cp, C.byref(geom), C.byref(grid), _ptr(coords),
-                         _ptr(feats), _ptr(npil), _ptr(p2p), _aligned_ptr(ws), ws.numel() - 256, _stream())
+                         _ptr(feats), _ptr(npil), _ptr(p2p), _aligned_ptr(ws), _room(ws), _stream())
     _check(st, "ff_voxelize")
     return coords, feats, npil, p2p
 
@@ -417,6 +422,6 @@ def ff_fwa_block(coords, geom, G, layers, dtype, feats_in, out=None, workspace=N
     ws = workspace if workspace is not None else _workspace(query(n, C.byref(geom), G, arr, len(layers), dtype),
                                                               coords.device)   # (the call itself checks the size)
     st = run(_ptr(coords), n, C.byref(geom), G, tail, arr, len(layers), dtype, _ptr(feats_in), _ptr(out),
-             _aligned_ptr(ws), ws.numel() - 256, _stream())
+             _aligned_ptr(ws), _room(ws), _stream())
     _check(st, name)
     return out

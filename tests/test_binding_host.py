@@ -1,8 +1,12 @@
 """CPU-only: what the binding itself does between torch and the library."""
+import os
 import types
 
+import pytest
 import torch
 
+import ffsynth
+import paper_2301_08739_amd as ff
 from paper_2301_08739_amd import binding
 
 
@@ -14,3 +18,18 @@ def test_stream_without_the_short_way(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
     monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
     assert binding._stream() == 103
+
+
+@pytest.mark.parametrize("size", [0, 1, 100, 255, 256])
+def test_tiny_workspaces_are_refused(monkeypatch, size):
+    """A workspace that is smaller than what its alignment may cost has no room: the library must not be told of 2^64 bytes less some."""
+    if not os.path.exists(ff.library_path()):
+        pytest.skip("library not built (run __graft_entry__.build())")
+    monkeypatch.setattr(binding, "_stream", lambda: None)
+    ws, n = torch.empty(size, dtype=torch.uint8), 8
+    layers = [ff.LayerWeights(ffsynth.layer_params(64, 128, 4, seed=1), ff.FF_F32, "cpu")]
+    with pytest.raises(ff.FlatformerError, match="workspace"):
+        ff.ff_fwa_block(torch.zeros(n, 3, dtype=torch.int32), ff.Geometry(1, 64, 64, 8, 8), 4, layers, ff.FF_F32, torch.zeros(n, 64),
+                        workspace=ws)
+    with pytest.raises(ff.FlatformerError, match="workspace"):
+        ff.ff_voxelize(torch.zeros(n, 2), None, torch.zeros(n, 4), ff.Geometry(1, 64, 64, 8, 8), ff.VoxelGrid(0., 0., 1., 1.), workspace=ws)
