@@ -159,11 +159,13 @@ def _check(st, what):
         raise FlatformerError(f"{what}: {ff_status_string(st)} ({st})")
 
 
+# The number of a device's current stream, 0.3 us; a Stream object on the way to it, where a torch has no shorter one, 3.3
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream():
-    """The current stream of the current device as a number (0.3 us; a Stream object on the way to it, where a torch has no shorter
-    one, 3.3)."""
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
+    """The current stream of the current device as a number."""
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t):

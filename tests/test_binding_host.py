@@ -1,4 +1,5 @@
 """CPU-only: what the binding itself does between torch and the library."""
+import importlib.util
 import os
 import types
 
@@ -12,12 +13,16 @@ from paper_2301_08739_amd import binding
 
 def test_stream_without_the_short_way(monkeypatch):
     """The number of the current stream comes from a Stream object where this torch has no function for it."""
-    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
-    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=4711))
-    assert binding._stream() == 4711
+    def number():
+        spec = importlib.util.spec_from_file_location("binding_of_its_own", binding.__file__)
+        spec.loader.exec_module(module := importlib.util.module_from_spec(spec))
+        return module._stream()
     monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: types.SimpleNamespace(cuda_stream=4711))
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert number() == 4711
     monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
-    assert binding._stream() == 103
+    assert number() == 103
 
 
 @pytest.mark.parametrize("size", [0, 1, 100, 255, 256])
