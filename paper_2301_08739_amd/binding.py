@@ -191,10 +191,10 @@ def ff_flatten_workspace_bytes(n, geom):
 
 
 def _group_lists(count, cap, device):
-    """`count` pairs (group_offsets of capacity cap, num_groups), -1 throughout.  One fill for all of them: it is a launch,
-    1.3 us in a graph and more in an eager call (a captured call of four sorts of 30,000 pillars: a fill for each tensor
-    25.7 us, one fill 15.2; one sort 15.7 and 14.2)."""
-    if count == 1:  # (num_groups is always written; a view would cost more than a tensor of its own)
+    """`count` pairs (group_offsets of capacity cap, -1 throughout, num_groups, which every sort writes).  One fill for all of
+    them: it is a launch, 1.3 us in a graph and more in an eager call (a captured call of four sorts of 30,000 pillars: a fill
+    for each tensor 25.7 us, one fill 15.2; one sort 15.7 and 14.2)."""
+    if count == 1:  # (a view of a filled tensor would cost more than a tensor of its own)
         return [(torch.full((cap,), -1, dtype=torch.int32, device=device), torch.empty(1, dtype=torch.int32, device=device))]
     width = -(-cap // 64) * 64 + 64  # (each tensor on a 256-byte boundary)
     both = torch.full((count, width), -1, dtype=torch.int32, device=device)

@@ -28,8 +28,11 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
 // ---- weights of a layer into the L2s ---------------------------------------------------------------
 // A launch begins with weights that its XCDs' L2s have not seen: the launch before wrote them, or another layer's were
 // there.  Met one by one at the products, each first use is a trip to memory.  So the first workgroups of an XCD (at most
-// 32) ask for all lines at once, beside their rows, N lines a thread at most, and give what they got to `touch_done` once
-// the rows are there.  16-bit layer, C = 128, G = 64, 30,000 rows: 5,900 -> 3,450 clocks from LayerNorm 1 to the end of Q, K, V.
+// 32) ask for lines of theirs at once, beside their rows, N a thread, and give what they got to `touch_done` once the rows are
+// there.  N * NT lines times the workgroups of an XCD are asked for: all of them from some 57 workgroups of four row blocks on
+// (2,048 lines, 256 threads, N = 1), 57 of 256 features (8,192, 512, 2), 89 of the float32 layer (6,144, 256, 2), part of them in
+// smaller launches; and where the workgroups are no multiple of eight, the XCDs without a last one lack its share.  16-bit layer,
+// C = 128, G = 64, 30,000 rows: 5,900 -> 3,450 clocks from LayerNorm 1 to the end of Q, K, V.
 template <int NT, int BYTES, int N>
 __device__ __forceinline__ void touch_lines(const void* base, int workgroups, int tid, uint32_t (&got)[N]) {
   const int on_xcd = (workgroups + 7) / 8, share = blockIdx.x / 8, of = on_xcd < 32 ? on_xcd : 32;

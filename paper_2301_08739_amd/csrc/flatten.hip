@@ -671,13 +671,14 @@ __global__ __launch_bounds__(256) void k_finalize(const uint64_t* __restrict__ s
 // lists are looked up in the cloud again.
 //
 // What bounds it: the look at all pillars, 12 bytes and some 20 vector instructions each in every workgroup, 0.23 us for
-// every thousand of them, and 6 us for the launch, the scan and the way out; the radix path is three dependent launches of
-// 5 to 12 us.  Measured, radix path / this one, us a call (two small fills a sort with it): one sort, 2,000 pillars 21 / 8.6,
-// 12,345 22.5 / 11.2, 30,000 23 / 15, 131,072 41 / 37.5; four sorts, 30,000 35.5 / 25, 80,000 61.5 / 38.  The line to the two
-// launches of k_split: with one fill a call, one sort and four, 20,000 pillars of two frames 12.4 and 13.0 by this, 24 to 25 by
-// those, 30,000 14.1 and 15.2 by this, 13.4 and 13.9 by those, 60,000 21.0 and 22.5, 14.6 and 16.4.
+// every thousand of them, and 4 us for the launch, the scan and the way out; the radix path is three dependent launches of
+// 5 to 12 us.  From a graph, without fills, radix path / this one, us: one sort, 2,000 pillars 17.6 / 4.8, 12,345 18.7 / 7.3, 24,576
+// 18.9 / 9.6; four sorts, 2,000 18.9 / 4.9, 12,345 20.0 / 7.7, 24,576 21.9 / 10.2.  The line to the two launches of k_split was drawn
+// when these took 2 to 3 us more (one sort and four as plain calls, 20,000 pillars of two frames 12.4 and 13.0 by this, 24 to 25 by
+// those, 30,000 14.1 and 15.2 by this, 13.4 and 13.9 by those, 60,000 21.0 and 22.5, 14.6 and 16.4); from 18,000 on they are now
+// up to 1 us ahead for clouds without crowds, and behind for crowds of few cells.
 // Clouds whose pillars share a window's few cells, hundreds each, are one workgroup's, two more looks at the cloud: 20,000 on one,
-// a hundred or a thousand cells 39, 44 and 50 us, radix path 21 to 25 (bitonic sorts of the lists: 106, 217, 130).
+// a hundred or a thousand cells 38, 44 and 49 us, radix path 20 to 26 (bitonic sorts of the lists: 106, 217, 130).
 constexpr int kDirectThreads = 1024;
 constexpr int kDirectWaves = kDirectThreads / 64;
 constexpr int kDirectOwn = 1024;            // pillars of a range that a wavefront finds (4 bytes each),
@@ -1080,10 +1081,10 @@ __global__ __launch_bounds__(kDirectThreads, 4) void k_direct(const int32_t* __r
 // What bounds it: for a hundred thousand pillars its two launches, 4 us and a chain of six or seven round trips each; for
 // millions the lines touched rather than the 16 bytes a pillar moved: the pieces of a bucket are a few entries long where the
 // frames are mixed, a line each of entries and table (3.84 M pillars: k_split 28 us, k_buckets 30).  The radix path moves 8-byte
-// words through three passes there.  Measured, radix path / this, us a call: one sort, 131,072 pillars 35 / 11.9, 240,000 37 /
-// 12.1, 960,000 59 / 24, 2 M 79 / 40, 3.84 M 109 / 61; four sorts, 240,000 63 / 21, 960,000 122 / 54.  The same with a fifth of
-// the pillars sharing cells; on one, a hundred and ten thousand cells of a corner, 30,000 87, 121 and 34, 131,072 325, 481 and
-// 76, 960,000 2375, 3480 and 1230 (21 to 67 by the radix path).
+// words through three passes there.  From a graph, without fills, radix path / this, us: one sort, 30,000 pillars 19.4 / 8.9,
+// 131,073 29.3 / 10.1, 240,000 31.7 / 11.4, 960,000 53 / 23, 2 M 72 / 38, 3.84 M 102 / 57.7; four sorts, 30,000 22.8 / 9.5, 240,000
+// 45.7 / 19.8, 960,000 107 / 50.6.  With a fifth of the pillars sharing cells 240,000 31.7 / 16.1; on one, a hundred and ten thousand
+// cells of a corner, 30,000 64, 100 and 31, 131,072 239, 406 and 128, 960,000 1909, 3100 and 652 (20 to 47 by the radix path).
 constexpr int kSplitThreads = 512, kSplitWaves = kSplitThreads / 64;
 constexpr int kSplitLeast = 2, kSplitFew = 4, kSplitMany = 16;  // pillars of a thread of k_split: few to fill the chip, many to
 constexpr int64_t kSplitFewRows = 1 << 19, kSplitManyRows = 1 << 20;  // keep the pieces long; of all sorts, and of one

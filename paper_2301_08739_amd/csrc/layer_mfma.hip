@@ -342,7 +342,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void k_layer_mfma(
     if (g == 0) copy_rows(0, ngroups > 0 ? off0 : n);
     if (g < ngroups) copy_rows(start + m, off1);
   }
-  sync(0);  // chunks 0 and 1 and the small parameters are in LDS; the rest of the ring is requested
+  sync(0);  // the ring's first filling and the small parameters are in LDS
   // out_index: the next layer of a block wants its input in its own sorted order.  Fetched only now:
   // the barrier above waits for every load in flight, and this one hangs on the pillar index.
   const int32_t orow = out_index && row >= 0 ? out_index[row] : row;  // row of `out` the result goes to

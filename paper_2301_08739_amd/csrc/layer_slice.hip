@@ -97,7 +97,9 @@ __device__ __forceinline__ void lds_barrier() {
 // (a sixth less of all that than as half of a block of 32), and in the layout of a block only through the attention.  The weights
 // of two steps become two tiles of 16 features by eight lane swaps, which ride beside the products of the other rows.  240,000
 // rows, C = 256, G = 69, us a layer: 408 -> 386; 32,117 rows, C = 128, embedding: 24, the same; registers 256 -> 204.  (Groups of
-// 33 to 48 and 97 to 112 stay with half a block: at C = 128 four blocks so, and two with 16-bit results, need scratch memory.)
+// 33 to 48 and 97 to 112 stay with half a block: four blocks so, and two with 16-bit results, need scratch memory, at C = 128 and, 36 to
+// 232 bytes, at 256.  There, 500 groups with 16-bit and float32 results, us: G = 48 39.1 and 41.8, so 58.1 and 39.4; G = 112 76.2
+// and 83.5, so 82.3 and 82.7.)
 constexpr bool tail_of_16(int PT, bool HALF) { return HALF && PT == 3; }
 constexpr int kLdsBytes = 160 * 1024;  // LDS of one compute unit
 
@@ -935,9 +937,11 @@ __device__ __forceinline__ void slice_layer(
 
 // Two and four row blocks, 128 features: two workgroups share a compute unit, 512 the chip, and a few groups more than that, or
 // a few groups in all, have a compute unit each and leave the others idle.  Up to 128 of them are therefore taken by two workgroups
-// each, half of the queries to each, which both make the keys and values of all: the same operations on every row.  Whole / so, us: G =
-// 128, 64 groups 19.1 / 13.8, 128 19.6 / 14.7, 520 45 / 39, 626 46 / 41, 1100 73 / 70; G = 64, 64 groups 10.0 / 8.3, 128 10.5 / 9.2.  (160 groups by
-// halves 20.1 and, G = 64, 11.3, whole 19.8 and 11.0; 188 beyond a round 51 and 46: more than fit beside each other.)
+// each, half of the queries to each, which both make the keys and values of all: the same operations on every row.  Whole / so, us from
+// a graph: G = 128, 64 groups 17.9 / 12.6, 128 18.0 / 13.0, 520 42.2 / 36.5, 626 43.0 / 38.2, 1100 68.6 / 64.1; G = 100 128 groups 17.9 / 13.0,
+// 626 40.8 / 36.2; G = 64, 64 groups 9.6 / 7.7, 128 9.6 / 8.0; G = 40 9.3 / 7.7 and 9.4 / 8.2; with an embedding G = 128, 128 groups 19.0 /
+// 14.3, G = 64 10.0 / 8.4; with float32 results 20.0 / 14.6 and 10.7 / 8.9.  (160 groups by halves 20.1 and, G = 64, 11.3, whole 19.8 and
+// 11.0; 188 beyond a round 51 and 46: more than fit beside each other.)
 constexpr bool can_split(int C, int PT, int MINW) { return C == 128 && (PT == 4 || (PT == 2 && MINW == 2)); }
 constexpr int kSplitGroups = 128, kGroupsAtOnce = 512;
 
