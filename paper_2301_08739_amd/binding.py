@@ -176,14 +176,10 @@ def _workspace(nbytes, device):
     return torch.empty(max(int(nbytes), 256) + 256, dtype=torch.uint8, device=device)
 
 
-def _aligned_ptr(ws):
-    p = ws.data_ptr()
-    return (p + 255) // 256 * 256
-
-
-def _room(ws):
-    """Bytes of ws that are there from _aligned_ptr on, whatever its alignment; a smaller tensor has none."""
-    return max(ws.numel() - 256, 0)
+def _aligned(ws):
+    """The first 256-byte boundary of ws, and the bytes that are there from it on, whatever it is; a smaller tensor has none."""
+    p, n = ws.data_ptr(), ws.numel()
+    return (p + 255) // 256 * 256, n - 256 if n > 256 else 0
 
 
 def ff_flatten_workspace_bytes(n, geom):
@@ -215,7 +211,7 @@ def ff_flatten(coords, geom, axis, shift, G, tail=FF_TAIL_MASK, want_keys=False,
     need = lib.ff_flatten_workspace_bytes(n, C.byref(geom))
     ws = workspace if workspace is not None else _workspace(need, dev)
     st = lib.ff_flatten(_ptr(coords), n, C.byref(geom), axis, shift, G, tail, _ptr(perm), _ptr(goff), _ptr(ng),
-                        _ptr(keys), _aligned_ptr(ws), _room(ws), _stream())
+                        _ptr(keys), *_aligned(ws), _stream())
     _check(st, "ff_flatten")
     return perm, goff, ng, keys
 
@@ -247,7 +243,7 @@ def ff_flatten_batch(coords, geom, sorts, G, tail=FF_TAIL_MASK, workspace=None, 
     ptrs = [(C.c_void_p * S)(*[t[k].data_ptr() for t in out]) for k in range(3)]
     ws = workspace if workspace is not None else _workspace(lib.ff_flatten_batch_workspace_bytes(n, C.byref(geom), S), dev)
     st = lib.ff_flatten_batch(_ptr(coords), n, C.byref(geom), S, axis, shift, G, tail, ptrs[0], ptrs[1], ptrs[2],
-                              _aligned_ptr(ws), _room(ws), _stream())
+                              *_aligned(ws), _stream())
     _check(st, "ff_flatten_batch")
     return out
 
@@ -291,7 +287,7 @@ def ff_flatten3d(coords, geom, axis, shift, G, tail=FF_TAIL_MASK, workspace=None
     need = lib.ff_flatten3d_workspace_bytes(n, C.byref(geom))
     ws = workspace if workspace is not None else _workspace(need, dev)
     st = lib.ff_flatten3d(_ptr(coords), n, C.byref(geom), axis, shift, G, tail, _ptr(perm), _ptr(goff), _ptr(ng),
-                          _aligned_ptr(ws), _room(ws), _stream())
+                          *_aligned(ws), _stream())
     _check(st, "ff_flatten3d")
     return perm, goff, ng
 
@@ -318,7 +314,7 @@ def ff_group_attention(feats, perm, group_offsets, num_groups, max_groups, weigh
     ws = workspace if workspace is not None else _workspace(need, feats.device)
     st = lib.ff_group_attention(_ptr(feats), _ptr(out), n, _ptr(perm), _ptr(group_offsets), _ptr(num_groups),
                                 int(max_groups), C.byref(s), G, dtype, flags,
-                                _aligned_ptr(ws), _room(ws), _stream())
+                                *_aligned(ws), _stream())
     _check(st, "ff_group_attention")
     return out
 
@@ -356,7 +352,7 @@ def ff_voxelize(xy, frame, point_feats, geom, grid, want_map=True, workspace=Non
     need = lib.ff_voxelize_workspace_bytes(m, C.byref(geom))
     ws = workspace if workspace is not None else _workspace(need, dev)
     st = lib.ff_voxelize(_ptr(xy), _ptr(frame), _ptr(point_feats), m, Cp, C.byref(geom), C.byref(grid), _ptr(coords),
-                         _ptr(feats), _ptr(npil), _ptr(p2p), _aligned_ptr(ws), _room(ws), _stream())
+                         _ptr(feats), _ptr(npil), _ptr(p2p), *_aligned(ws), _stream())
     _check(st, "ff_voxelize")
     return coords, feats, npil, p2p
 
@@ -424,6 +420,6 @@ def ff_fwa_block(coords, geom, G, layers, dtype, feats_in, out=None, workspace=N
     ws = workspace if workspace is not None else _workspace(query(n, C.byref(geom), G, arr, len(layers), dtype),
                                                               coords.device)   # (the call itself checks the size)
     st = run(_ptr(coords), n, C.byref(geom), G, tail, arr, len(layers), dtype, _ptr(feats_in), _ptr(out),
-             _aligned_ptr(ws), _room(ws), _stream())
+             *_aligned(ws), _stream())
     _check(st, name)
     return out
