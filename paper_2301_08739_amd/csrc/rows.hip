@@ -29,7 +29,9 @@ __device__ __forceinline__ int64_t row_of(const RowPieces& rp, int64_t i) {
 //   11.2 / 10.9, 12.5 / 15.5, 20.1 / 17.7, 34.3 / 30.6, 63.7 / 55.9, 93.3 / 81.7, 123 / 113; one 11.0 / 9.9, 12.5 / 12.5, 20.4 / 17.5.
 //   The same around gather, two pieces / one: 3.7 MiB 11.7, 11.4 / 11.5, 9.5, 7 MiB 13.1, 15.9 / 13.0, 12.8, 11 MiB 17.2, 18.6 / 17.5, 16.4.
 //   Plain loads in scatter: 29 MiB 36.1 / 30.7 instead of 34.2 / 30.6.
-// Without a reader the stores of 15 to 88 MiB look 4 to 10 % faster non-temporal (gather and scatter alone, 59 MiB 42.4 / 45.1): the
+//   Scatter of rows that were written long before, and a launch that reads the result, non-temporal stores / plain ones: 3.7 MiB 8.3, 7.9
+//   / 6.7, 7.0, 15 MiB 15.6, 16.0 / 13.3, 15.4, 59 MiB 48.4, 44.0 / 43.8, 40.6.
+// Without a reader the stores of 7 to 64 MiB look 4 to 12 % faster non-temporal (gather and scatter alone, 59 MiB 42.4 / 45.1): the
 // reader pays for it.  A gather's loads are non-temporal where its source would push out what it writes (gather and scatter, 117 MiB
 // 76 us so and plain, 234 MiB 144 / 169).
 constexpr int64_t kRowsShort = (int64_t)14 << 20, kScatterStreamed = (int64_t)64 << 20;  // bytes of the rows of one side
